@@ -43,6 +43,7 @@
 #include "br_sort.h"
 #include "br_assign_common.h"
 #include "br_subset_dp.h"
+#include "br_subset_list.h"
 #include "br_score_wave.h"
 
 template <int E>
@@ -50,14 +51,24 @@ struct Log2E {
   static constexpr int v = E == 4 ? 2 : E == 8 ? 3 : E == 16 ? 4 : 5;
 };
 
-// Subset scan of a window of up to 16 requests (Stage 2, BIGR), this wave's share of it: lane l keeps the lower
-// six mask bits, the upper bits c run as passes over the table `hitab` of their partial sums, four passes per
+// Subset search of a window of up to 16 requests (Stage 2, BIGR), this wave's share of it.  With at most half of the
+// window per subset the admissible masks are taken from a list (br_subset_list.h; `hitab`: its byte tables).
+// Otherwise a scan over all masks: lane l keeps the lower six mask bits, the upper bits c run as passes over the table `hitab` of their partial sums, four passes per
 // trip; the wave takes the trips wv, wv + nwv, ... (trips whose upper bits alone exceed the cardinality limit are
 // skipped).  A lane sees its masks in ascending order and keeps the first best: returns the lane's best key and
 // its lowest mask.
 template <bool BRH>
 __device__ __forceinline__ void br_bigr_scan(const BrParams &p, const int (&mg)[BR_HP + 1], const int *win, const int *hitab,
                                              int w, int kmax, int room, int lane, int wv, int nwv, int &bk, int &bm) {
+  if (br_list_serves(w, kmax)) {
+    br_list_walk<4>(hitab, w, kmax, room, lane, wv, nwv,
+                    [&](const int(&delta)[4], int(&key)[4]) {
+#pragma unroll
+                      for (int u = 0; u < 4; ++u) key[u] = br_score_key<BRH>(p, mg, delta[u]);
+                    },
+                    bk, bm);
+    return;
+  }
   const int nhi = w > 6 ? 1 << (w - 6) : 1;
   const int nmask = 1 << w;
   int base = 0;
@@ -811,29 +822,49 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
         // score wins.
 #pragma unroll
         for (int b = 0; b < 8; ++b) wv[b] = 0, ws[b] = 0;
+        int kmax = min(min(capmax, p.R_max), w);
+        if (!guard_sure) {
+          br_wave_sync();
+          const int sum = br_min_sums(win, w, lane);
+          float F, slack;
+          if constexpr (BRH) {
+            float Dsum = 0.0f;
+#pragma unroll
+            for (int h = 0; h <= BR_HP; ++h) Dsum += p.d[h];
+            F = br_scoreh(p, mg, sum);
+            slack = 3.2e-6f * (p.aD + p.beta * Dsum) * (float)(kmax * (br_uniform(win[0]) >> BR_IDX_BITS));
+          } else {  // (scores of sums below 2^20 times G <= 64 stay below 2^26: rounded to float they keep their order up
+            F = (float)br_score0(G, mg[0], min(sum, 1 << 20)), slack = 32.0f;  // to units of 8, and the slack covers those)
+          }
+          kmax = br_useful_count(sum, F, slack, w > 16 ? min(room, BR_DP_MAX_SUM) : room, kmax, lane);
+        }
         if (!guard_sure && w > 16) {
           // windows of 17..32 requests: reachable sums instead of masks (br_subset_dp.h)
-          br_wave_sync();
           unsigned dm = 0u;
           int *share = nullptr;
           if constexpr (!COOP) share = shared ? svc : nullptr;
-          br_subset_dp<BRH>(p, mg, win, w, min(capmax, p.R_max), room, lane, dprows,
+          br_subset_dp<BRH>(p, mg, win, w, kmax, room, lane, dprows,
                             p.dp + (size_t)inst * br_dp_cluster_words(min(p.B, p.R_max)), dm, bestkey, share);
           bestmask = (int)dm;
         } else if (!guard_sure) {
-          br_wave_sync();
-          const int nhi = w > 6 ? 1 << (w - 6) : 1;
-          for (int c0 = 0; c0 < nhi; c0 += BR_WAVE) {
-            const int c = c0 + lane;
-            int sum = 0;
-            for (int b = 6; b < w; ++b) sum += ((c >> (b - 6)) & 1) * (win[b] >> BR_IDX_BITS);
-            if (c < nhi) hitab[c] = sum;
+          int trips;  // of 256 masks each
+          if (br_list_serves(w, kmax)) {
+            br_list_tables(win, w, hitab, lane);
+            trips = (br_list_size(w, kmax) + 255) >> 8;
+          } else {
+            const int nhi = w > 6 ? 1 << (w - 6) : 1;
+            for (int c0 = 0; c0 < nhi; c0 += BR_WAVE) {
+              const int c = c0 + lane;
+              int sum = 0;
+              for (int b = 6; b < w; ++b) sum += ((c >> (b - 6)) & 1) * (win[b] >> BR_IDX_BITS);
+              if (c < nhi) hitab[c] = sum;
+            }
+            trips = nhi >> 2;
           }
           br_wave_sync();
-          const int kmax = min(capmax, p.R_max);
           int bk, bm;
           bool shared_scan = false;
-          if constexpr (!COOP) shared_scan = shared && nhi >= 16;  // (a few trips are not worth two barriers)
+          if constexpr (!COOP) shared_scan = shared && trips >= 4;  // (a few trips are not worth two barriers)
           if (shared_scan) {
 #pragma unroll
             for (int h = 0; h <= BR_HP; ++h) svc[1 + h] = mg[h];

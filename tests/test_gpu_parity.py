@@ -616,6 +616,21 @@ def test_wide_window_bench_configuration(R_max, S_greedy):
                   sub, "wide window")
 
 
+@pytest.mark.parametrize("H,pred_mode", [(0, 0), (3, 0), (40, 1)])
+@pytest.mark.parametrize("R_max", [9, 10, 15, 16])
+def test_wide_window_by_free_slots(R_max, H, pred_mode):
+    """Windows of 9..16 requests with 1..9 free slots per worker: subsets of at most half of the window come from the
+    list of masks, larger ones from the scan over all masks; windows that shrink as the queue runs out; equal lengths."""
+    for free, tie in [(1, False), (R_max // 2, False), (R_max // 2, True), (R_max // 2 + 1, True), (9, False)]:
+        kw = dict(pred_mode=pred_mode, gate_pfin=0.0) if H else {}
+        cfg, init, arr = wl.random_case(900 + free, N=3, G=3, B=12, max_wait=40, H=H, s_hi=4096, tie_heavy=tie, n_wait=30,
+                                        R_max=R_max, S_greedy=10 ** 6, fill=1.0, **kw)
+        init.n[:] = cfg.B - free
+        _say(f"free slots {free} of {cfg.B}, window {R_max}, H={H}, ties {tie}")
+        oc, r = run_pair(cfg, init, arr, tag=f"window {R_max} free {free}")
+        r.close()
+
+
 def test_wide_window_long_requests_reach_the_row_bound():
     """Windows of 32 requests with lengths up to 32768 and room for many per pop: subset sums beyond the length of
     the bit rows (131071) exist and are not candidates on either side; rows too long for LDS go to the workspace."""
