@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import threading
 from typing import Dict, Optional
 
 import numpy as np
@@ -127,20 +128,26 @@ def _check(rc: int, what: str, ctx=None):
         raise BrError(f"{what} failed: rc={rc} hip_error={hip}")
 
 
+def _check_arrivals(arr, P: int):
+    """(clusters, row length) of a batch of arrivals in host memory; the C ABI takes bare pointers, so sizes are
+    checked here, before anything reaches a kernel."""
+    n_inst, cap = np.shape(arr.s)
+    for name in ("o", "id"):
+        if np.shape(getattr(arr, name)) != (n_inst, cap):
+            raise BrError(f"arrivals.{name} must have shape {(n_inst, cap)}")
+    if np.shape(arr.count) != (n_inst,):
+        raise BrError(f"arrivals.count must have shape {(n_inst,)}")
+    if P and (arr.pred is None or np.shape(arr.pred) != (n_inst, cap, P)):
+        raise BrError(f"arrivals.pred must have shape {(n_inst, cap, P)}")
+    return n_inst, cap
+
+
 class DeviceArrivals:
     """One batch of arrivals resident on the device."""
 
     def __init__(self, arr, device, P: int):
         import torch
-        # the C ABI takes bare pointers: sizes are checked here, before anything reaches a kernel
-        n_inst, cap = np.shape(arr.s)
-        for name in ("o", "id"):
-            if np.shape(getattr(arr, name)) != (n_inst, cap):
-                raise BrError(f"arrivals.{name} must have shape {(n_inst, cap)}")
-        if np.shape(arr.count) != (n_inst,):
-            raise BrError(f"arrivals.count must have shape {(n_inst,)}")
-        if P and (arr.pred is None or np.shape(arr.pred) != (n_inst, cap, P)):
-            raise BrError(f"arrivals.pred must have shape {(n_inst, cap, P)}")
+        _check_arrivals(arr, P)
         self.count = torch.as_tensor(np.ascontiguousarray(arr.count, np.int32), device=device)
         self.s = torch.as_tensor(np.ascontiguousarray(arr.s, np.int32), device=device)
         self.o = torch.as_tensor(np.ascontiguousarray(arr.o, np.int32), device=device)
@@ -152,6 +159,54 @@ class DeviceArrivals:
         return Arrivals(count=self.count.data_ptr(), s=self.s.data_ptr(), o=self.o.data_ptr(),
                         id=self.id.data_ptr(), pred=self.pred.data_ptr() if self.pred is not None else None,
                         arr_cap=self.arr_cap, pad=0)
+
+
+# Host calls (Router.route_step) of up to this many bytes of arrivals and outputs go through a pinned block of the
+# router's: the kernels read the arrivals from it and write the outputs to it, so that a call is its launches and one wait
+# (one cluster, every output: 49 us; with a tensor and a copy per array 215 us).  Faster at every size tried, up to 42 MB;
+# the bound keeps the pinned memory of a router small (HOST_BLOCKS of them at most).
+HOST_BLOCK_MAX_BYTES = 1 << 24
+HOST_BLOCKS = 4
+
+
+class _HostBlock:
+    """Pinned host memory that one router's host calls pass their arrays through: arrivals in, outputs back."""
+
+    def __init__(self, router, cap: int, scores: bool, matrix: bool):
+        N, G, Q, Pq = router.N, router.G, router.Q, router.Pq
+        f32, i32, i64 = np.float32, np.int32, np.int64
+        self.N, self.Pq, self.cap = N, Pq, 0
+        parts = [("count", (N,), i32), ("s", (N, cap), i32), ("o", (N, cap), i32), ("id", (N, cap), i32)]
+        if Pq:
+            parts.append(("pred", (N, cap, Pq), f32))
+        self.n_in = len(parts)
+        parts += [("assign", (N, Q), i32), ("assign_id", (N, Q), i32), ("stats", (N, NSTATS), i64)]
+        if scores:
+            parts += [("best_g", (N, Q), i32), ("best_i", (N, G), i32)]
+            if matrix:
+                parts.append(("F", (N, Q, G), f32 if router.H > 0 else i32))
+        self.parts, self.nbytes = [], 0
+        for name, shape, dt in parts:
+            size = int(np.prod(shape)) * np.dtype(dt).itemsize
+            self.parts.append((name, shape, dt, self.nbytes, size))
+            self.nbytes += (size + 255) & ~255
+
+    def allocate(self, torch):
+        self.mem = torch.empty(self.nbytes, dtype=torch.uint8, pin_memory=True)
+        self.raw, base = self.mem.numpy(), self.mem.data_ptr()
+        addr = {name: base + off for name, _, _, off, _ in self.parts}
+        self.outputs = [(name, self.raw[off:off + size].view(dt).reshape(shape)) for name, shape, dt, off, size in self.parts[self.n_in:]]
+        self.arrivals = Arrivals(count=addr["count"], s=addr["s"], o=addr["o"], id=addr["id"], pred=addr.get("pred"))
+        self.out = StepOut(**{name: addr.get(name) for name, _ in StepOut._fields_})
+
+    def rows_of(self, cap: int):
+        """Lays the arrival arrays out for rows of `cap` entries (at most what the block was made for)."""
+        if self.cap != cap:
+            self.cap = self.arrivals.arr_cap = cap
+            self.inputs = []
+            for name, shape, dt, off, _ in self.parts[:self.n_in]:
+                shape = shape[:1] + ((cap,) + shape[2:] if len(shape) > 1 else ())
+                self.inputs.append((name, self.raw[off:off + int(np.prod(shape)) * 4].view(dt).reshape(shape)))
 
 
 class Router:
@@ -205,6 +260,8 @@ class Router:
         self.layout = lay
         self.Bs = lay.B_stride
         self._out: Dict[str, object] = {}
+        self._host_blocks: Dict[tuple, _HostBlock] = {}  # freed with the router
+        self._host_lock = threading.Lock()
 
     # -- outputs -------------------------------------------------------
     def alloc_outputs(self, scores: bool = True, matrix: bool = True) -> Dict[str, object]:
@@ -250,8 +307,14 @@ class Router:
                "br_route_advance", self.ctx)
 
     def route_step(self, arr=None, scores: bool = True, matrix: bool = True, advance: int = 0):
-        """Convenience for tests: host arrays in, numpy out (synchronises).  advance > 0 takes the
-        fused entry point (round + that many decode steps)."""
+        """Host arrays in, numpy out (synchronises).  advance > 0 takes the fused entry point (round + that many
+        decode steps)."""
+        cap = _check_arrivals(arr, self.Pq)[1] if arr is not None else 0
+        if arr is None or len(arr.count) == self.N:
+            with self._host_lock:  # a block is in use until the outputs have been copied out of it
+                block = self._host_block(cap, scores, matrix)
+                if block is not None:
+                    return self._route_step_block(block, arr, cap, advance)
         darr = DeviceArrivals(arr, self.device, self.Pq) if arr is not None else None
         out = self.alloc_outputs(scores, matrix)
         if advance > 0:
@@ -260,6 +323,36 @@ class Router:
             self.route_step_device(darr, out)
         self.stream.synchronize()
         return {k: v.cpu().numpy() for k, v in out.items()}
+
+    def _host_block(self, cap: int, scores: bool, matrix: bool) -> Optional[_HostBlock]:
+        key = (max(16, 1 << (cap - 1).bit_length() if cap > 1 else 1), bool(scores), bool(matrix))
+        block = self._host_blocks.get(key)
+        if block is None:
+            block = _HostBlock(self, *key)
+            if block.nbytes > HOST_BLOCK_MAX_BYTES:
+                return None
+            if len(self._host_blocks) >= HOST_BLOCKS:
+                self._host_blocks.pop(next(iter(self._host_blocks)))
+            block.allocate(self.torch)
+            self._host_blocks[key] = block
+        return block
+
+    def _route_step_block(self, block: _HostBlock, arr, cap: int, advance: int):
+        a = None
+        if arr is not None:
+            block.rows_of(cap)
+            for name, view in block.inputs:
+                view[...] = getattr(arr, name)
+            a = C.byref(block.arrivals)
+        rc = self.lib.br_route_advance(self.ctx, a, C.byref(block.out), max(int(advance), 0))
+        self.stream.synchronize()
+        _check(rc, "br_route_step", self.ctx)
+        res = {name: view.copy() for name, view in block.outputs}
+        if "F" in res:  # rows at or beyond the queue length are not written: zero, as in a fresh matrix
+            F, qlen = res["F"], res["stats"][:, ST["qlen"]]
+            for i in np.flatnonzero(qlen < self.Q):
+                F[i, qlen[i]:] = 0
+        return res
 
     def route_bypass_device(self, darr: DeviceArrivals, out) -> None:
         """Enqueue the pool-bypass dispatch of one batch of arrivals (BR-0); no synchronisation."""

@@ -741,6 +741,33 @@ def test_graph_capture_and_replay(name, over):
     r.close()
 
 
+@pytest.mark.parametrize("through_block", [True, False])
+def test_host_calls_with_varying_rows(through_block, monkeypatch):
+    """Router.route_step over row lengths that vary from call to call (and with no arrivals at all), through the pinned
+    block and past it: outputs against the oracle, unwritten matrix rows zero, earlier results untouched by later calls."""
+    if not through_block:
+        monkeypatch.setattr(binding, "HOST_BLOCK_MAX_BYTES", 0)
+    cfg, init, _ = wl.random_case(41, N=3, G=6, B=10, max_wait=70, H=3, gate_pfin=0.0)
+    oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
+    kept = []
+    for k, (rows, matrix) in enumerate([(5, True), (1, False), (33, True), (16, True), (0, True), (70, True), (200, False)]):
+        _say(f"rows {rows} matrix {matrix}")
+        arr = wl.random_case(50 + k, N=3, G=6, B=10, max_wait=70, H=3, n_wait=rows)[2] if rows else None
+        ref = oc.route_step(arr if rows else wl.random_case(50, N=3, G=6, B=10, max_wait=70, H=3, n_wait=0)[2])
+        out = r.route_step(arr, matrix=matrix, advance=1)
+        compare_outputs(ref, out, cfg, f"rows {rows}")
+        if matrix:
+            for i in range(cfg.n_inst):
+                assert not out["F"][i, ref["stats"][i, br_oracle.ST["qlen"]]:].any()
+        oc.advance(1)
+        compare_state(oc, r.state(), cfg, f"rows {rows}")
+        kept.append((out, {n: v.copy() for n, v in out.items()}))
+    assert len(r._host_blocks) == (binding.HOST_BLOCKS if through_block else 0)
+    for out, was in kept:
+        assert all(np.array_equal(out[n], was[n]) for n in out)
+    r.close()
+
+
 def test_determinism():
     cfg, init, arr = wl.random_case(31, N=16, G=16, B=24, max_wait=256, H=4, gate_pfin=0.0, tie_heavy=True)
     outs = []
