@@ -7,7 +7,7 @@
 
 void br_launch_assign_bigr(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
   if (p.H > 0)
-    br_launch_assign_sized<true, true>(p, a, o, st);
+    br_launch_assign_sized<BR_HP, true>(p, a, o, st);
   else
-    br_launch_assign_sized<false, true>(p, a, o, st);
+    br_launch_assign_sized<0, true>(p, a, o, st);
 }

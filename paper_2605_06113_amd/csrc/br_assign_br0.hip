@@ -13,14 +13,14 @@ __global__ __launch_bounds__(256) void br_k_route4(BrParams p, BrArr a, BrOut o)
   constexpr int E = 4;
   const int w = threadIdx.x >> 6, inst = (int)blockIdx.x * 4 + w;
   if (inst >= p.N) return;
-  BrScoreIn<E, false> in;  // loaded once, used by both parts
-  br_score_wave_load<E, false>(p, a, inst, br_lane(), in);
-  br_score_wave_run<E, false>(p, o, inst, br_lane(), in);
-  br_assign_body<E, false, ADV>(p, a, o, lds_all + w * (3 * E * BR_WAVE + BR_WAVE + 8), inst, 0, &in);
+  BrScoreIn<E, 0> in;  // loaded once, used by both parts
+  br_score_wave_load<E, 0>(p, a, inst, br_lane(), in);
+  br_score_wave_run<E, 0>(p, o, inst, br_lane(), in);
+  br_assign_body<E, 0, ADV>(p, a, o, lds_all + w * BR_ROUND_WORDS(E, false), inst, 0, &in);
 }
 
 void br_launch_route4(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
-  const size_t lds = (size_t)(4 * (3 * 4 * BR_WAVE + BR_WAVE + 8)) * sizeof(int);
+  const size_t lds = (size_t)4 * BR_ROUND_WORDS(4, false) * sizeof(int);
   const dim3 grid((unsigned)((p.N + 3) / 4)), block(256);
   if (p.adv_t > 0)
     hipLaunchKernelGGL(br_k_route4<true>, grid, block, lds, st, p, a, o);
@@ -29,5 +29,5 @@ void br_launch_route4(const BrParams &p, const BrArr &a, const BrOut &o, hipStre
 }
 
 void br_launch_assign_br0(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
-  br_launch_assign_sized<false>(p, a, o, st);
+  br_launch_assign_sized<0>(p, a, o, st);
 }

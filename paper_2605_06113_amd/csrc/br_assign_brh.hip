@@ -1,5 +1,5 @@
-// BR-H instantiations of the assignment kernel (Alg. BR-H), and the dispatch between the
-// integer kernel, the register-horizon kernel and the long-horizon kernel.
+// BR-H instantiations of the assignment kernel (Alg. BR-H) for horizons of 5..8 offsets, and the dispatch between the
+// integer kernel, the register-horizon kernels and the long-horizon kernel.
 #include "br_assign_kernel.h"
 
 void br_launch_assign(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
@@ -7,8 +7,10 @@ void br_launch_assign(const BrParams &p, const BrArr &a, const BrOut &o, hipStre
     br_launch_assign_long(p, a, o, st);
   else if (p.R_max > 8)
     br_launch_assign_bigr(p, a, o, st);
+  else if (p.H > BR_HP / 2)
+    br_launch_assign_sized<BR_HP>(p, a, o, st);
   else if (p.H > 0)
-    br_launch_assign_sized<true>(p, a, o, st);
+    br_launch_assign_brh4(p, a, o, st);
   else
     br_launch_assign_br0(p, a, o, st);
 }

@@ -1,7 +1,8 @@
 // Shared tail of the assignment kernels: writes the admitted requests into their workers'
 // lists, emits the per-entry outputs in arrival order, compacts the waiting queue in place and
-// stores worker state and statistics.  Everything here is lane-parallel; `adm` (by sorted
-// position: worker << 16 | slot, or -1) and the sorted keys in `skey` come from the round.
+// stores worker state and statistics.  Everything here is lane-parallel over arrival positions; `bound` (by arrival
+// position: worker << 16 | slot, or -1) comes from the round.  An entry's words are read once, whether it leaves for a
+// list or stays in the queue: one memory round trip per group of four blocks of 64 entries.
 #pragma once
 
 #include "br_device.h"
@@ -51,117 +52,90 @@ __device__ __forceinline__ BrTailArgs br_tail_args() {
   return t;
 }
 
-// ---- pieces of the epilogue, each over GR blocks of 64 positions starting at block j0 ----
+// ---- pieces of the epilogue, each over GR blocks of 64 arrival positions starting at block j0 ----
 
-// Commit of the admitted requests at sorted positions [j0*64, (j0+GR)*64) into their workers' dense
-// lists: what the group reads from the queue and the arrivals is requested before its first store.
-template <int GR>
-__device__ __forceinline__ void br_commit_group(const BrTailArgs &t, int inst, int lane, int j0, int q0, int qn,
-                                                const int *skey, const int *adm, int *who, float c0) {
-  constexpr int IDX_MASK = (1 << BR_IDX_BITS) - 1;
-  const int G = t.G;
+// What those positions hold and where they went.  PRED: prediction rows travel with the requests.
+template <int GR, bool PRED>
+struct BrQueueGroup {
+  int bound[GR], id[GR], sq[GR], oq[GR];
+  float pr[PRED ? GR : 1][BR_HP];
+};
+
+template <int GR, bool PRED>
+__device__ __forceinline__ void br_queue_load(const BrTailArgs &t, int inst, int lane, int j0, int q0, int qn, const int *bound,
+                                              BrQueueGroup<GR, PRED> &v) {
   const int64_t qrow = (int64_t)inst * t.Q, arow = (int64_t)inst * t.arr_cap;
-  int64_t row[GR];
-  int idx[GR], kvv[GR], remv[GR];
-  float pr[GR][BR_HP];
-  bool ok[GR];
 #pragma unroll
   for (int u = 0; u < GR; ++u) {
-    const int pos = (j0 + u) * BR_WAVE + lane;
-    ok[u] = false;
-    idx[u] = 0, kvv[u] = 0, remv[u] = 1, row[u] = 0;
-    if (pos < qn) {
-      const int ad = adm[pos];
-      if (ad >= 0) {
-        const int key = skey[pos];
-        idx[u] = IDX_MASK - (key & IDX_MASK);
-        const int g = ad >> 16, slot = ad & 0xffff;
-        if (g < G && slot < t.B && idx[u] < qn) {
-          ok[u] = true;
-          row[u] = ((int64_t)inst * G + g) * t.Bs + slot;
-          kvv[u] = key >> BR_IDX_BITS;
-          const bool old = idx[u] < q0;
-          remv[u] = old ? t.qo[qrow + idx[u]] : max(t.ao[arow + (idx[u] - q0)], 1);
+    const int i = (j0 + u) * BR_WAVE + lane;
+    v.bound[u] = -1, v.id[u] = -1, v.sq[u] = 1, v.oq[u] = 1;
+    if (i < qn) {
+      const bool old = i < q0;
+      const int64_t aat = arow + (i - q0);
+      v.bound[u] = bound[i];
+      v.sq[u] = *(old ? t.qs + (qrow + i) : t.as + aat);
+      v.oq[u] = *(old ? t.qo + (qrow + i) : t.ao + aat);
+      v.id[u] = old ? t.qid[qrow + i] : (t.aid ? t.aid[aat] : i - q0);
+      if constexpr (PRED) {
+        const float *src = old ? t.qpred + (qrow + i) * t.Pq : t.apred + aat * t.Pq;
 #pragma unroll
-          for (int q = 0; q < BR_HP; ++q)
-            if (q < t.Pq)
-              pr[u][q] = old ? t.qpred[(qrow + idx[u]) * t.Pq + q] : t.apred[(arow + (idx[u] - q0)) * t.Pq + q];
-          who[idx[u]] = g;
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < GR; ++u) {
-    if (ok[u]) {
-      t.kv[row[u]] = kvv[u];
-      t.rem[row[u]] = remv[u];
-#pragma unroll
-      for (int q = 0; q < BR_HP; ++q)
-        if (q < t.Pq) t.pred[row[u] * t.P + q] = pr[u][q];
-      if (t.P == 3 && t.Pq == 0) {  // maintained estimate: first query at age 0, nothing generated yet
-        t.pred[row[u] * 3] = c0;
-        t.pred[row[u] * 3 + 1] = 0.0f;
-        t.pred[row[u] * 3 + 2] = 0.0f;
+        for (int q = 0; q < BR_HP; ++q)
+          if (q < t.Pq) v.pr[u][q] = src[q];
       }
     }
   }
 }
 
-// What the arrival positions [j0*64, (j0+GR)*64) hold and where they went.
-template <int GR>
-struct BrQueueGroup {
-  int wg[GR], id[GR], sq[GR], oq[GR];
-  float pr[GR][BR_HP];
-  bool keep[GR];
-};
-
-template <int GR>
-__device__ __forceinline__ void br_queue_load(const BrTailArgs &t, int inst, int lane, int j0, int q0, int qn,
-                                              const int *who, BrQueueGroup<GR> &v) {
-  const int64_t qrow = (int64_t)inst * t.Q, arow = (int64_t)inst * t.arr_cap;
+// List entries of the requests that were bound.
+template <int GR, bool PRED>
+__device__ __forceinline__ void br_commit_store(const BrTailArgs &t, int inst, const BrQueueGroup<GR, PRED> &v, float c0) {
 #pragma unroll
   for (int u = 0; u < GR; ++u) {
-    const int i = (j0 + u) * BR_WAVE + lane;
-    const bool in = i < qn, old = i < q0;
-    v.wg[u] = in ? who[i] : -1;
-    v.id[u] = -1;
-    if (in) v.id[u] = old ? t.qid[qrow + i] : (t.aid ? t.aid[arow + (i - q0)] : i - q0);
-    v.keep[u] = in && v.wg[u] < 0;
-    v.sq[u] = 1, v.oq[u] = 1;
-    if (v.keep[u]) {
-      v.sq[u] = old ? t.qs[qrow + i] : t.as[arow + (i - q0)];
-      v.oq[u] = old ? t.qo[qrow + i] : t.ao[arow + (i - q0)];
+    const int g = v.bound[u] >> 16, slot = v.bound[u] & 0xffff;
+    if (v.bound[u] >= 0 && g < t.G && slot < t.B) {
+      const int64_t row = ((int64_t)inst * t.G + g) * t.Bs + slot;
+      t.kv[row] = min(max(v.sq[u], 1), BR_MAX_S_DEV);
+      t.rem[row] = max(v.oq[u], 1);
+      if constexpr (PRED) {
 #pragma unroll
-      for (int q = 0; q < BR_HP; ++q)
-        if (q < t.Pq) v.pr[u][q] = old ? t.qpred[(qrow + i) * t.Pq + q] : t.apred[(arow + (i - q0)) * t.Pq + q];
+        for (int q = 0; q < BR_HP; ++q)
+          if (q < t.Pq) t.pred[row * t.P + q] = v.pr[u][q];
+        if (t.P == 3 && t.Pq == 0) {  // maintained estimate: first query at age 0, nothing generated yet
+          t.pred[row * 3] = c0;
+          t.pred[row * 3 + 1] = 0.0f;
+          t.pred[row * 3 + 2] = 0.0f;
+        }
+      }
     }
   }
 }
 
 // Outputs of those positions in arrival order, and their deferred requests to queue positions `kept`
 // onwards (order preserved); `kept` moves on by the number stored.
-template <int GR>
-__device__ __forceinline__ void br_queue_store(const BrTailArgs &t, int inst, int lane, int j0, int q0,
-                                               const BrQueueGroup<GR> &v, int &kept) {
+template <int GR, bool PRED>
+__device__ __forceinline__ void br_queue_store(const BrTailArgs &t, int inst, int lane, int j0, int q0, int qn,
+                                               const BrQueueGroup<GR, PRED> &v, int &kept) {
   const int64_t qrow = (int64_t)inst * t.Q;
 #pragma unroll
   for (int u = 0; u < GR; ++u) {
     const int i = (j0 + u) * BR_WAVE + lane;
     if ((j0 + u) * BR_WAVE < t.Q) {
       if (i < t.Q) {
-        if (t.assign) t.assign[qrow + i] = v.wg[u];
+        if (t.assign) t.assign[qrow + i] = v.bound[u] >> 16;
         if (t.assign_id) t.assign_id[qrow + i] = v.id[u];
       }
-      const unsigned long long bal = br_ballot(v.keep[u]);
+      const bool keep = i < qn && v.bound[u] < 0;
+      const unsigned long long bal = br_ballot(keep);
       const int ni = kept + br_rank_below(bal);
-      if (v.keep[u] && (ni != i || i >= q0)) {
+      if (keep && (ni != i || i >= q0)) {
         t.qs[qrow + ni] = min(max(v.sq[u], 1), BR_MAX_S_DEV);
         t.qo[qrow + ni] = max(v.oq[u], 1);
         t.qid[qrow + ni] = v.id[u];
+        if constexpr (PRED) {
 #pragma unroll
-        for (int q = 0; q < BR_HP; ++q)
-          if (q < t.Pq) t.qpred[(qrow + ni) * t.Pq + q] = v.pr[u][q];
+          for (int q = 0; q < BR_HP; ++q)
+            if (q < t.Pq) t.qpred[(qrow + ni) * t.Pq + q] = v.pr[u][q];
+        }
       }
       kept += __builtin_popcountll(bal);
     }
@@ -209,63 +183,54 @@ __device__ __forceinline__ void br_write_state(const BrTailArgs &t, int inst, in
   }
 }
 
-// The epilogue on the wave that ran the round.  Blocks are taken GR at a time so that the loads of a
-// group overlap (each block is a round trip to memory otherwise).  The queue is compacted in place: a
-// deferred entry moves to a position at or below its own, inside or before its group, and later groups
-// read only beyond it.
-template <int E>
-__device__ __forceinline__ void br_assign_epilogue(int inst, int lane, int q0, int qn, int cnt, const int *skey,
-                                                   const int *adm, int *who, int Lcur, int nn,
+// The epilogue on the wave that ran the round.  The queue is compacted in place: a deferred entry moves to a position
+// at or below its own, inside or before its group, and later groups read only beyond it.
+template <int E, bool PRED>
+__device__ __forceinline__ void br_assign_epilogue(int inst, int lane, int q0, int qn, int cnt, const int *bound, int Lcur, int nn,
                                                    const BrRoundCounts &rc, float c0) {
   const BrTailArgs t = br_tail_args();
   constexpr int GR = E < 4 ? E : 4;
-  if (rc.admitted > 0) {
-#pragma unroll
-    for (int j0 = 0; j0 < E; j0 += GR)
-      if (j0 * BR_WAVE < qn) br_commit_group<GR>(t, inst, lane, j0, q0, qn, skey, adm, who, c0);
-  }
-  br_wave_sync();
   int kept = 0;
 #pragma unroll
   for (int j0 = 0; j0 < E; j0 += GR) {
     if (j0 * BR_WAVE < t.Q) {
-      BrQueueGroup<GR> v;
-      br_queue_load<GR>(t, inst, lane, j0, q0, qn, who, v);
-      br_queue_store<GR>(t, inst, lane, j0, q0, v, kept);
+      BrQueueGroup<GR, PRED> v;
+      br_queue_load(t, inst, lane, j0, q0, qn, bound, v);
+      br_commit_store(t, inst, v, c0);
+      br_queue_store(t, inst, lane, j0, q0, qn, v, kept);
     }
   }
   br_write_state(t, inst, lane, q0, qn, cnt, kept, Lcur, nn, rc);
 }
 
-// The epilogue on the four waves of a block (queues of up to 2048 entries): wave w owns the sorted
-// positions and the arrival positions [w*512, (w+1)*512).  Every wave requests all it will read of the
-// queue before the barrier that precedes the first store, so the in-place compaction needs no order
-// between waves; the counts of deferred requests per wave go through `sh` (4 words of LDS).
-// With `share_workers` wave 0's per-worker (load, count) are handed to every wave (for a decode step split
-// among the waves) and wave 0 leaves their store to that step.
-__device__ __forceinline__ void br_assign_epilogue_block4(int inst, int lane, int w, int q0, int qn, int cnt, int *skey,
-                                                          const int *adm, int *who, int *sh, int &Lcur, int &nn,
-                                                          const BrRoundCounts &rc, float c0, bool share_workers) {
+// The epilogue on the four waves of a block (queues of up to 2048 entries): wave w owns the arrival positions
+// [w*512, (w+1)*512).  Every wave requests all it will read of the queue before the barrier that precedes the first
+// store, so the in-place compaction needs no order between waves; the counts of deferred requests per wave go through
+// `sh` (4 words of LDS).  With `share_workers` wave 0's per-worker (load, count) are handed to every wave through `wk`
+// (2 x 64 words, for a decode step split among the waves) and wave 0 leaves their store to that step.
+template <bool PRED>
+__device__ __forceinline__ void br_assign_epilogue_block4(int inst, int lane, int w, int q0, int qn, int cnt, const int *bound,
+                                                          int *sh, int *wk, int &Lcur, int &nn, const BrRoundCounts &rc, float c0,
+                                                          bool share_workers) {
   const BrTailArgs t = br_tail_args();
-  __syncthreads();  // the round is over: adm[] is complete
-  br_commit_group<4>(t, inst, lane, w * 8, q0, qn, skey, adm, who, c0);
-  br_commit_group<4>(t, inst, lane, w * 8 + 4, q0, qn, skey, adm, who, c0);
-  __syncthreads();  // who[] is complete
-  BrQueueGroup<4> va, vb;
-  br_queue_load<4>(t, inst, lane, w * 8, q0, qn, who, va);
-  br_queue_load<4>(t, inst, lane, w * 8 + 4, q0, qn, who, vb);
+  if (share_workers && w == 0) wk[lane] = Lcur, wk[BR_WAVE + lane] = nn;
+  __syncthreads();  // the round is over: bound[] is complete
+  if (share_workers) Lcur = wk[lane], nn = wk[BR_WAVE + lane];
+  BrQueueGroup<4, PRED> va, vb;
+  br_queue_load(t, inst, lane, w * 8, q0, qn, bound, va);
+  br_queue_load(t, inst, lane, w * 8 + 4, q0, qn, bound, vb);
   int mine = 0;
 #pragma unroll
-  for (int u = 0; u < 4; ++u) mine += __builtin_popcountll(br_ballot(va.keep[u])) + __builtin_popcountll(br_ballot(vb.keep[u]));
+  for (int u = 0; u < 4; ++u)
+    mine += __builtin_popcountll(br_ballot((w * 8 + u) * BR_WAVE + lane < qn && va.bound[u] < 0)) +
+            __builtin_popcountll(br_ballot((w * 8 + 4 + u) * BR_WAVE + lane < qn && vb.bound[u] < 0));
   // the loaded values must have arrived before any wave stores
   asm volatile("" ::"v"(va.sq[0]), "v"(va.sq[1]), "v"(va.sq[2]), "v"(va.sq[3]), "v"(vb.sq[0]), "v"(vb.sq[1]), "v"(vb.sq[2]),
                "v"(vb.sq[3])
                : "memory");
   __builtin_amdgcn_s_waitcnt(0);
   if (lane == 0) sh[w] = mine;
-  if (share_workers && w == 0) skey[lane] = Lcur, skey[BR_WAVE + lane] = nn;  // the sorted keys are no longer needed
   __syncthreads();
-  if (share_workers) Lcur = skey[lane], nn = skey[BR_WAVE + lane];
   int kept = 0, total = 0;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -273,9 +238,12 @@ __device__ __forceinline__ void br_assign_epilogue_block4(int inst, int lane, in
     kept += k < w ? c : 0;
     total += c;
   }
-  br_queue_store<4>(t, inst, lane, w * 8, q0, va, kept);
-  br_queue_store<4>(t, inst, lane, w * 8 + 4, q0, vb, kept);
+  br_commit_store(t, inst, va, c0);
+  br_commit_store(t, inst, vb, c0);
+  br_queue_store(t, inst, lane, w * 8, q0, qn, va, kept);
+  br_queue_store(t, inst, lane, w * 8 + 4, q0, qn, vb, kept);
   if (w == 0) br_write_state(t, inst, lane, q0, qn, cnt, total, Lcur, nn, rc, !share_workers);
+  if (share_workers) __syncthreads();  // the lists that a wave goes on to hold entries stored by the others
 }
 
 // Late copy of the whole parameter block from the kernel-argument segment (same reason as above).
@@ -294,8 +262,9 @@ __device__ __forceinline__ BrParams br_late_params() {
 // requested before the first is used.  `Lcur`, `nn`: load and list length of worker `lane` after the round.
 // STORE = false: loads and counts are not stored; lane g returns its list's load change in `dL_out` and its new
 // length in `n_out` instead (the split kernels, where another wave owns the workers' final state).
-template <int UB, bool BRH, bool STORE = true>
-__device__ __forceinline__ void br_advance_cluster(int inst, int lane, int Lcur, int nn, int g0 = 0, int g1 = 64,
+// PK as for br_adv_apply; `map` (PK 1): UB x 256 16-bit entries of this wave's LDS.
+template <int UB, int PK, bool STORE = true>
+__device__ __forceinline__ void br_advance_cluster_as(int inst, int lane, int Lcur, int nn, short *map, int g0 = 0, int g1 = 64,
                                                    int *dL_out = nullptr, int *n_out = nullptr) {
   const BrParams p = br_late_params();
   const int t = p.adv_t;
@@ -306,6 +275,7 @@ __device__ __forceinline__ void br_advance_cluster(int inst, int lane, int Lcur,
   int dLw = 0, nw = nn;     // lane g: load change and new length of worker g
   int kept = 0, gone = 0;   // running state of the list in progress: survivors, kv that left
   int gl = g0, cl = 0, gp = g0, cp = 0;  // (list, chunk) cursors of the load and the update pass
+  int gm = g0, cm = 0;                   // ... and of the pass that moves prediction rows
   const int32_t *kl = p.kv + rowa * p.Bs, *rl = p.rem + rowa * p.Bs;  // list the load pass is at
   int32_t *kw = p.kv + rowa * p.Bs, *rw = p.rem + rowa * p.Bs;        // list the update pass is at
   float *pw = p.pred + rowa * p.Bs * p.P;
@@ -317,17 +287,34 @@ __device__ __forceinline__ void br_advance_cluster(int inst, int lane, int Lcur,
       if (gl < G) br_adv_load(kl, rl, cl * 256 + 4 * lane, __builtin_amdgcn_readlane(nn, gl), kv[k], rem[k]);
       if (++cl == NC) cl = 0, ++gl, kl += p.Bs, rl += p.Bs;
     }
+    unsigned long long froms = 0ull;  // PK 1: first slot whose row moves + 1, 16 bits per unit
 #pragma unroll
     for (int k = 0; k < UB; ++k) {
       if (gp < G) {
         const int ng = __builtin_amdgcn_readlane(nn, gp);
-        if (cp * 256 < ng) br_adv_apply<BRH>(p, t, cp * 256 + 4 * lane, ng, cp * 256, kv[k], rem[k], kw, rw, pw, kept, gone);
+        if (cp * 256 < ng) {
+          int from;
+          br_adv_apply<PK>(p, t, cp * 256 + 4 * lane, ng, cp * 256, kv[k], rem[k], kw, rw, pw, kept, gone, map + k * 256, from);
+          if constexpr (PK == 1) froms |= (unsigned long long)(unsigned)(from + 1) << (16 * (k & 3));
+        }
         if (++cp == NC) {
           if (lane == gp) dLw = kept * t - gone, nw = kept;  // survivors gain t tokens each
           kept = 0, gone = 0, cp = 0, ++gp;
           kw += p.Bs, rw += p.Bs, pw += (int64_t)p.Bs * p.P;
         }
       }
+    }
+    if constexpr (PK == 1) {
+      static_assert(PK != 1 || UB <= 4, "16 bits per unit");
+      br_wave_sync();
+      for (int k = 0; k < UB && gm < G; ++k) {  // in order: a chunk's rows may move into the chunk before it
+        const int from = (int)((froms >> (16 * k)) & 0xffffull) - 1;
+        if (from >= 0)
+          br_rows_move(p.pred + (row0 + gm) * p.Bs * p.P, p.P, map + k * 256, cm * 256, from,
+                       min(__builtin_amdgcn_readlane(nn, gm), cm * 256 + 256), lane);
+        if (++cm == NC) cm = 0, ++gm;
+      }
+      br_wave_sync();  // the maps are rewritten by the next units
     }
   }
   if constexpr (STORE) {
@@ -338,6 +325,20 @@ __device__ __forceinline__ void br_advance_cluster(int inst, int lane, int Lcur,
   } else {
     *dL_out = dLw;
     *n_out = nw;
+  }
+}
+
+template <int UB, bool BRH>
+__device__ __forceinline__ void br_advance_cluster(const BrParams &p, int inst, int lane, int Lcur, int nn, int *lds, int g0 = 0,
+                                                   int g1 = 64) {
+  short *map = reinterpret_cast<short *>(lds);  // (512 words)
+  if constexpr (BRH) {
+    if (p.pred_mode == 2)
+      br_advance_cluster_as<UB, 2>(inst, lane, Lcur, nn, map, g0, g1);
+    else
+      br_advance_cluster_as<UB, 1>(inst, lane, Lcur, nn, map, g0, g1);
+  } else {
+    br_advance_cluster_as<UB, 0>(inst, lane, Lcur, nn, map, g0, g1);
   }
 }
 
@@ -360,16 +361,16 @@ __device__ __forceinline__ void br_split_helper(const BrParams &p, const BrArr &
   const bool act = lane < p.G;
   int n0;
   if (o.best_g || o.best_i) {
-    BrScoreIn<E, false> in;
-    br_score_wave_load<E, false>(p, a, inst, lane, in);
-    br_score_wave_run<E, false>(p, o, inst, lane, in);
+    BrScoreIn<E, 0> in;
+    br_score_wave_load<E, 0>(p, a, inst, lane, in);
+    br_score_wave_run<E, 0>(p, o, inst, lane, in);
     n0 = in.n;
   } else {
     n0 = act ? p.n[(int64_t)inst * p.G + lane] : p.B;
   }
   n0 = act ? min(max(n0, 0), p.B) : 0;
   int dL = 0, kept = n0;
-  br_advance_cluster<UB, false, false>(inst, lane, 0, n0, 0, 64, &dL, &kept);
+  br_advance_cluster_as<UB, 0, false>(inst, lane, 0, n0, nullptr, 0, 64, &dL, &kept);
   split[4 + lane] = n0 - kept;
   split[4 + BR_WAVE + lane] = dL;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // the lists are in place before the flag is seen
@@ -379,13 +380,13 @@ __device__ __forceinline__ void br_split_helper(const BrParams &p, const BrArr &
 
 // The epilogue of the wave that ran the round, in a split kernel.  nn0: list lengths at the start of the step.
 template <int E>
-__device__ __forceinline__ void br_assign_epilogue_split(int inst, int lane, int q0, int qn, int cnt, const int *skey,
-                                                         const int *adm, int *who, int Lcur, int nn, int nn0,
-                                                         const BrRoundCounts &rc, int *split) {
+__device__ __forceinline__ void br_assign_epilogue_split(int inst, int lane, int q0, int qn, int cnt, const int *bound, int Lcur,
+                                                         int nn, int nn0, const BrRoundCounts &rc, int *split) {
   const BrTailArgs t = br_tail_args();
-  constexpr int IDX_MASK = (1 << BR_IDX_BITS) - 1;
   const int G = t.G, tt = t.adv_t;
-  const int64_t qrow = (int64_t)inst * t.Q, arow = (int64_t)inst * t.arr_cap;
+  // everything that will be read of the queue and the arrivals is requested before the wait for the helper
+  BrQueueGroup<E, false> v;
+  br_queue_load(t, inst, lane, 0, q0, qn, bound, v);
   // the helper is done with this cluster's lists (it never waits for anything: the flag always comes)
   while (__atomic_load_n(split, __ATOMIC_RELAXED) == 0) __builtin_amdgcn_s_sleep(4);
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
@@ -394,54 +395,23 @@ __device__ __forceinline__ void br_assign_epilogue_split(int inst, int lane, int
   int nfin = kept0 + a_g, Lfin = Lcur + dold + a_g * tt;               // if every admitted request outlives the t steps
   bool slow = false;
   if (rc.admitted > 0) {
-    // every admitted request of the cluster, E sorted positions per lane: all reads before the first store
-    int64_t row[E];
-    int kvv[E], remv[E];
-    bool ok[E];
     bool short_one = false;
 #pragma unroll
-    for (int u = 0; u < E; ++u) {
-      const int pos = u * BR_WAVE + lane;
-      ok[u] = false;
-      kvv[u] = 0, remv[u] = 1, row[u] = 0;
-      if (pos < qn) {
-        const int ad = adm[pos];
-        if (ad >= 0) {
-          const int key = skey[pos];
-          const int idx = IDX_MASK - (key & IDX_MASK);
-          const int g = ad >> 16, slot = ad & 0xffff;
-          if (g < G && slot < t.B && idx < qn) {
-            ok[u] = true;
-            row[u] = ((int64_t)inst * G + g) * t.Bs + (slot - split[4 + g]);  // behind the old survivors
-            kvv[u] = key >> BR_IDX_BITS;
-            remv[u] = idx < q0 ? t.qo[qrow + idx] : max(t.ao[arow + (idx - q0)], 1);
-            short_one |= remv[u] <= tt;
-            who[idx] = g;
-          }
-        }
-      }
-    }
+    for (int u = 0; u < E; ++u) short_one |= v.bound[u] >= 0 && max(v.oq[u], 1) <= tt;
     slow = br_ballot(short_one) != 0ull;  // some admitted request ends within the t steps: lists are compacted below
     const int add = slow ? 0 : tt;
 #pragma unroll
     for (int u = 0; u < E; ++u) {
-      if (ok[u]) {
-        t.kv[row[u]] = kvv[u] + add;
-        t.rem[row[u]] = remv[u] - add;
+      const int g = v.bound[u] >> 16, slot = v.bound[u] & 0xffff;
+      if (v.bound[u] >= 0 && g < G && slot < t.B) {
+        const int64_t row = ((int64_t)inst * G + g) * t.Bs + (slot - split[4 + g]);  // behind the old survivors
+        t.kv[row] = min(max(v.sq[u], 1), BR_MAX_S_DEV) + add;
+        t.rem[row] = max(v.oq[u], 1) - add;
       }
     }
   }
-  br_wave_sync();
   int keptq = 0;
-  constexpr int GR = E < 4 ? E : 4;
-#pragma unroll
-  for (int j0 = 0; j0 < E; j0 += GR) {
-    if (j0 * BR_WAVE < t.Q) {
-      BrQueueGroup<GR> v;
-      br_queue_load<GR>(t, inst, lane, j0, q0, qn, who, v);
-      br_queue_store<GR>(t, inst, lane, j0, q0, v, keptq);
-    }
-  }
+  br_queue_store(t, inst, lane, 0, q0, qn, v, keptq);
   br_write_state(t, inst, lane, q0, qn, cnt, keptq, Lcur, nn, rc, false);  // statistics: the state right after the round
   if (slow) {
     // The admissions sit behind the old survivors as admitted (kv = s, rem = o); per worker the decode steps

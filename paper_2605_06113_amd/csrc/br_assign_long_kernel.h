@@ -99,7 +99,7 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
   const int H1 = p.H + 1, HS = BR_HS(p.H);
   int *skey = lds;                  // [NP] sorted keys (s << 11 | 2047 - arrival position)
   int *adm = lds + NP;              // [NP] by sorted position: worker << 16 | slot, or -1
-  int *who = lds + 2 * NP;          // [NP] by arrival position: worker, or -1
+  int *who = lds + 2 * NP;          // [NP] by arrival position: worker << 16 | slot, or -1 (filled after the round)
   int *win = lds + 3 * NP;          // [64] Stage-1 level: k-th alive request (s << 11 | sorted position);
                                     //      Stage 2: the candidate window, same packing (16-byte aligned)
   int *pm = win + BR_WAVE;          // [64] partial horizon-min margins (offsets split over the lanes)
@@ -760,6 +760,12 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
     br_wave_sync();
   }
 
+#pragma unroll
+  for (int j = 0; j < E; ++j) {
+    const int pos = j * BR_WAVE + lane;
+    if (pos < qn && adm[pos] >= 0) who[IDX_MASK - (skey[pos] & IDX_MASK)] = adm[pos];
+  }
+  br_wave_sync();
   BrRoundCounts rc;
   rc.admitted = admitted;
   rc.stage1 = stage1;
@@ -767,8 +773,8 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
   rc.guard = guard;
   rc.wdrop = wdrop;
   rc.I_before = I_before;
-  br_assign_epilogue<E>(inst, lane, q0, qn, cnt, skey, adm, who, Lcur, nn, rc, c0);
-  if constexpr (ADV) br_advance_cluster<4, true>(inst, lane, Lcur, nn);
+  br_assign_epilogue<E, true>(inst, lane, q0, qn, cnt, who, Lcur, nn, rc, c0);
+  if constexpr (ADV) br_advance_cluster<4, true>(p, inst, lane, Lcur, nn, adm);
 }
 
 template <int E>

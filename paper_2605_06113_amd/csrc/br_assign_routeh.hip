@@ -4,30 +4,36 @@
 #include "br_assign_kernel.h"
 #include "br_score_wave.h"
 
-template <int E, bool ADV>
+template <int E, int HB, bool ADV>
 __global__ __launch_bounds__(256, E == 8 ? 4 : 1) void br_k_route_h(BrParams p, BrArr a, BrOut o) {
   extern __shared__ int lds_all[];
   const int w = threadIdx.x >> 6, inst = (int)blockIdx.x * 4 + w;
   if (inst >= p.N) return;
-  BrScoreIn<E, true> in;  // queue lengths, prefill lengths and counts are loaded once, for both parts
-  br_score_wave_load<E, true>(p, a, inst, br_lane(), in);
-  br_score_wave_run<E, true>(p, o, inst, br_lane(), in);
-  br_assign_body<E, true, ADV>(p, a, o, lds_all + w * (3 * E * BR_WAVE + BR_WAVE + 8), inst, 0, &in);
+  BrScoreIn<E, HB> in;  // queue lengths, prefill lengths and counts are loaded once, for both parts
+  br_score_wave_load<E, HB>(p, a, inst, br_lane(), in);
+  br_score_wave_run<E, HB>(p, o, inst, br_lane(), in);
+  br_assign_body<E, HB, ADV>(p, a, o, lds_all + w * BR_ROUND_WORDS(E, false), inst, 0, &in);
 }
 
-template <int E>
+template <int E, int HB>
 static void launch_route_h(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
-  const size_t lds = (size_t)(4 * (3 * E * BR_WAVE + BR_WAVE + 8)) * sizeof(int);
+  const size_t lds = (size_t)4 * BR_ROUND_WORDS(E, false) * sizeof(int);
   const dim3 grid((unsigned)((p.N + 3) / 4)), block(256);
   if (p.adv_t > 0)
-    hipLaunchKernelGGL((br_k_route_h<E, true>), grid, block, lds, st, p, a, o);
+    hipLaunchKernelGGL((br_k_route_h<E, HB, true>), grid, block, lds, st, p, a, o);
   else
-    hipLaunchKernelGGL((br_k_route_h<E, false>), grid, block, lds, st, p, a, o);
+    hipLaunchKernelGGL((br_k_route_h<E, HB, false>), grid, block, lds, st, p, a, o);
 }
 
 void br_launch_route_h(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
-  if (p.Q <= 256)
-    launch_route_h<4>(p, a, o, st);
-  else
-    launch_route_h<8>(p, a, o, st);
+  if (p.H <= BR_HP / 2) {
+    if (p.Q <= 256)
+      launch_route_h<4, BR_HP / 2>(p, a, o, st);
+    else
+      launch_route_h<8, BR_HP / 2>(p, a, o, st);
+  } else if (p.Q <= 256) {
+    launch_route_h<4, BR_HP>(p, a, o, st);
+  } else {
+    launch_route_h<8, BR_HP>(p, a, o, st);
+  }
 }

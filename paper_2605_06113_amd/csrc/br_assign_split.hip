@@ -10,7 +10,7 @@
 template <int E, int RPB, int NH>
 __global__ __launch_bounds__((RPB + NH) * BR_WAVE) void br_k_route_split(BrParams p, BrArr a, BrOut o) {
   extern __shared__ int lds_all[];
-  constexpr int WORDS = 3 * E * BR_WAVE + BR_WAVE + 8 + BR_SPLIT_WORDS;  // skey, adm, who, slots, win, split area
+  constexpr int WORDS = BR_ROUND_WORDS(E, false) + BR_SPLIT_WORDS;
   constexpr int SPLIT_AT = WORDS - BR_SPLIT_WORDS;
   const int w = threadIdx.x >> 6, lane = br_lane();
   const int first = (int)blockIdx.x * RPB;
@@ -20,7 +20,7 @@ __global__ __launch_bounds__((RPB + NH) * BR_WAVE) void br_k_route_split(BrParam
     const int inst = first + w;
     if (inst >= p.N) return;
     int *lds = lds_all + w * WORDS;
-    br_assign_body<E, false, false>(p, a, o, lds, inst, 0, nullptr, lds + SPLIT_AT);
+    br_assign_body<E, 0, false>(p, a, o, lds, inst, 0, nullptr, lds + SPLIT_AT);
   } else {
     for (int c = w - RPB; c < RPB; c += NH) {  // helper h takes clusters h, h + NH, ...
       const int inst = first + c;
@@ -32,7 +32,7 @@ __global__ __launch_bounds__((RPB + NH) * BR_WAVE) void br_k_route_split(BrParam
 
 template <int E, int RPB, int NH>
 static void launch_split(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
-  const size_t lds = (size_t)RPB * (3 * E * BR_WAVE + BR_WAVE + 8 + BR_SPLIT_WORDS) * sizeof(int);
+  const size_t lds = (size_t)RPB * (BR_ROUND_WORDS(E, false) + BR_SPLIT_WORDS) * sizeof(int);
   const dim3 grid((unsigned)((p.N + RPB - 1) / RPB)), block((RPB + NH) * BR_WAVE);
   hipLaunchKernelGGL((br_k_route_split<E, RPB, NH>), grid, block, lds, st, p, a, o);
 }

@@ -131,6 +131,23 @@ __device__ __forceinline__ int br_row_rank_step(int key, int acc) {
 
 __device__ __forceinline__ int br_row_rank(int key) { return br_row_rank_step<1>(key, 0); }
 
+// Maximum over the lane and all lanes below it.
+__device__ __forceinline__ int br_scan_max(int x) {
+  x = max(x, br_dpp<0x111>(INT32_MIN, x));       // row_shr:1
+  x = max(x, br_dpp<0x112>(INT32_MIN, x));       // row_shr:2
+  x = max(x, br_dpp<0x114>(INT32_MIN, x));       // row_shr:4
+  x = max(x, br_dpp<0x118>(INT32_MIN, x));       // row_shr:8
+  x = max(x, br_dpp<0x142, 0xA>(INT32_MIN, x));  // row_bcast:15 into rows 1 and 3
+  x = max(x, br_dpp<0x143, 0xC>(INT32_MIN, x));  // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
+// For lanes with `in` set and distinct positions `at` in 0..63: lane k receives the number of the lane whose `at` is k
+// (any lane's number where there is none).
+__device__ __forceinline__ int br_ranks_to_lanes(bool in, int at, int lane) {
+  return __builtin_amdgcn_ds_permute((in ? at : 63) << 2, lane);
+}
+
 __device__ __forceinline__ unsigned long long br_ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
 __device__ __forceinline__ int br_lane() { return (int)(threadIdx.x & 63u); }
@@ -173,7 +190,9 @@ __device__ __forceinline__ int br_score0(int G, int m, int delta) {
 // accumulated from h = 0 upwards with one fused multiply-add per offset (pen = fma(d_h, (Delta - m_h)_+, pen),
 // a single rounding), the two products and the difference of the last line are rounded one by one.  Offsets beyond H carry
 // a zero discount and add exactly +0.
-__device__ __forceinline__ float br_scoreh(const BrParams &p, const int (&m)[BR_HP + 1], int delta) {
+// `m`: one margin per offset the caller carries (N - 1 = 4 where H <= 4, else BR_HP).
+template <int N>
+__device__ __forceinline__ float br_scoreh(const BrParams &p, const int (&m)[N], int delta) {
   // The excess (Delta - m)_+ is formed in fp32, one operation less per offset than in integers and the same
   // value: Delta <= 2^19 is an exact float; a margin below Delta is one too and so is the difference; a margin
   // at or above Delta stays so after rounding and the term is zero either way.  (The conversions of the margins
@@ -181,11 +200,11 @@ __device__ __forceinline__ float br_scoreh(const BrParams &p, const int (&m)[BR_
   const float fd = (float)delta;
   float pen = 0.0f;
 #pragma unroll
-  for (int h = 0; h <= BR_HP / 2; ++h)
+  for (int h = 0; h < min(N, BR_HP / 2 + 1); ++h)
     pen = __fmaf_rn(p.d[h], fmaxf(__fsub_rn(fd, (float)m[h]), 0.0f), pen);
-  if (p.H > BR_HP / 2) {  // short horizons: the remaining terms are +0 and leave the sum as it is
+  if (N > BR_HP / 2 + 1 && p.H > BR_HP / 2) {  // short horizons: the remaining terms are +0 and leave the sum as it is
 #pragma unroll
-    for (int h = BR_HP / 2 + 1; h <= BR_HP; ++h)
+    for (int h = BR_HP / 2 + 1; h < N; ++h)
       pen = __fmaf_rn(p.d[h], fmaxf(__fsub_rn(fd, (float)m[h]), 0.0f), pen);
   }
   return __fsub_rn(__fmul_rn(p.aD, fd), __fmul_rn(p.beta, pen));
@@ -428,8 +447,8 @@ __device__ __forceinline__ float br_scoreh_long_from(float aD, float beta, int d
   return __fsub_rn(__fmul_rn(aD, (float)delta), __fmul_rn(beta, penalty));
 }
 
-template <bool BRH>
-__device__ __forceinline__ int br_score_key(const BrParams &p, const int (&m)[BR_HP + 1], int delta) {
+template <bool BRH, int N>
+__device__ __forceinline__ int br_score_key(const BrParams &p, const int (&m)[N], int delta) {
   if constexpr (BRH) return br_ord(br_scoreh(p, m, delta));
   else return br_score0(p.G, m[0], delta);
 }
@@ -554,10 +573,53 @@ __device__ __forceinline__ void br_adv_load(const int32_t *kl, const int32_t *rl
   }
 }
 
-template <bool PRED>
+// Prediction rows of a list's slots [from, to) of one chunk move with their requests: slot j's row (P floats, taken V at
+// a time) goes to slot map[j - chunk0] (< 0: it left).  Lanes walk the rows as contiguous memory, 4 x 64 units requested
+// before the first is stored; destinations lie at or below their sources, so no store reaches a source not yet read.
+// (A lane that moved its own four slots' rows float by float made the decode step of 4096 clusters with rows of four
+// hazards, 40 steps, every list losing requests, take 277 us; 126 us so.)
+template <class V>
+__device__ __forceinline__ void br_rows_move_as(float *pw, int P, const short *map, int chunk0, int from, int to, int lane) {
+  const int upr = P / (int)(sizeof(V) / sizeof(float));  // units per row, 1..8
+  const unsigned inv = 65536u / (unsigned)upr + 1u;      // x / upr for x < 2048 by multiplication
+  const V *rows = reinterpret_cast<const V *>(pw) + (int64_t)chunk0 * upr;
+  const int end = (to - chunk0) * upr;
+  auto dest = [&](int x) -> int {  // where unit x of the chunk goes, relative to the list, or -1
+    const int j = (int)(((unsigned)x * inv) >> 16);
+    const int to_slot = map[j];
+    return to_slot >= 0 && to_slot != chunk0 + j ? to_slot * upr + (x - j * upr) : -1;
+  };
+  V *dst = reinterpret_cast<V *>(pw);
+  for (int x0 = (from - chunk0) * upr + lane; x0 - lane < end; x0 += 4 * BR_WAVE) {
+    // (lanes beyond the end repeat its last unit)
+    const int xa = min(x0, end - 1), xb = min(x0 + BR_WAVE, end - 1);
+    const int xc = min(x0 + 2 * BR_WAVE, end - 1), xd = min(x0 + 3 * BR_WAVE, end - 1);
+    const V va = rows[xa], vb = rows[xb], vc = rows[xc], vd = rows[xd];
+    const int da = dest(xa), db = dest(xb), dc = dest(xc), dd = dest(xd);
+    if (da >= 0) dst[da] = va;
+    if (db >= 0) dst[db] = vb;
+    if (dc >= 0) dst[dc] = vc;
+    if (dd >= 0) dst[dd] = vd;
+  }
+}
+
+__device__ __forceinline__ void br_rows_move(float *pw, int P, const short *map, int chunk0, int from, int to, int lane) {
+  if ((P & 3) == 0)
+    br_rows_move_as<float4>(pw, P, map, chunk0, from, to, lane);
+  else if ((P & 1) == 0)
+    br_rows_move_as<float2>(pw, P, map, chunk0, from, to, lane);
+  else
+    br_rows_move_as<float>(pw, P, map, chunk0, from, to, lane);
+}
+
+// PK: what a request carries: 0 nothing, 1 a prediction row that moves with it, 2 a maintained estimate (c_hat, age, since).
+// PK 1: the rows themselves are left to the caller (br_rows_move): `map` (256 entries of this wave's LDS) receives the new
+// slot of every request of the chunk, `from` the first slot whose row moves; both only if one does (else from = -1).
+template <int PK>
 __device__ __forceinline__ void br_adv_apply(const BrParams &p, int t, int e0, int ng, int chunk0, const int4 &kv4,
                                              const int4 &rem4, int32_t *kw, int32_t *rw, float *pw, int &kept,
-                                             int &gone) {
+                                             int &gone, short *map, int &from) {
+  from = -1;
   const int kv[4] = {kv4.x, kv4.y, kv4.z, kv4.w}, rem[4] = {rem4.x, rem4.y, rem4.z, rem4.w};
   bool stay[4], leave[4];
   unsigned long long bs[4];
@@ -575,11 +637,9 @@ __device__ __forceinline__ void br_adv_apply(const BrParams &p, int t, int e0, i
   // maintained estimates: the rows of the lane's four requests are read and brought up to date before anything
   // is written (every lane goes through the update: its look-ups are taken by the whole wave)
   float ch[4] = {0.0f, 0.0f, 0.0f, 0.0f}, age[4] = {0.0f, 0.0f, 0.0f, 0.0f}, since[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  if constexpr (PRED) {
-    if (p.pred_mode == 2) {
-      if (e0 < ng) br_rows3_load(pw + (int64_t)e0 * 3, ch, age, since);
-      br_refresh_update4(p, t, stay, ch, age, since);
-    }
+  if constexpr (PK == 2) {
+    if (e0 < ng) br_rows3_load(pw + (int64_t)e0 * 3, ch, age, since);
+    br_refresh_update4(p, t, stay, ch, age, since);
   }
   const bool shifted = kept != chunk0;  // an earlier chunk of this list lost a request
   if (!shifted && br_ballot(any_leave) == 0ull) {
@@ -589,14 +649,12 @@ __device__ __forceinline__ void br_adv_apply(const BrParams &p, int t, int e0, i
       *reinterpret_cast<int4 *>(rw + e0) = make_int4(rem[0] - (stay[0] ? t : 0), rem[1] - (stay[1] ? t : 0),
                                                       rem[2] - (stay[2] ? t : 0), rem[3] - (stay[3] ? t : 0));
     }
-    if constexpr (PRED) {
-      if (p.pred_mode == 2) {
-        float *q = pw + (int64_t)e0 * 3;
-        if (e0 < ng) {  // rows beyond the list go back as they came
-          *reinterpret_cast<float4 *>(q) = make_float4(ch[0], age[0], since[0], ch[1]);
-          *reinterpret_cast<float4 *>(q + 4) = make_float4(age[1], since[1], ch[2], age[2]);
-          *reinterpret_cast<float4 *>(q + 8) = make_float4(since[2], ch[3], age[3], since[3]);
-        }
+    if constexpr (PK == 2) {
+      float *q = pw + (int64_t)e0 * 3;
+      if (e0 < ng) {  // rows beyond the list go back as they came
+        *reinterpret_cast<float4 *>(q) = make_float4(ch[0], age[0], since[0], ch[1]);
+        *reinterpret_cast<float4 *>(q + 4) = make_float4(age[1], since[1], ch[2], age[2]);
+        *reinterpret_cast<float4 *>(q + 8) = make_float4(since[2], ch[3], age[3], since[3]);
       }
     }
   } else {
@@ -604,32 +662,27 @@ __device__ __forceinline__ void br_adv_apply(const BrParams &p, int t, int e0, i
 #pragma unroll
     for (int k = 0; k < 4; ++k) below += br_rank_below(bs[k]);
     int pos = kept + below;
-    if constexpr (PRED) {
-      // prediction rows move with their requests: all rows of the lane are read before the first is written
-      float pr[4][BR_HP];
-      if (p.pred_mode == 2) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) pr[k][0] = ch[k], pr[k][1] = age[k], pr[k][2] = since[k];
-      } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          if (stay[k]) {
-#pragma unroll
-            for (int q = 0; q < BR_HP; ++q)
-              if (q < p.P) pr[k][q] = pw[(int64_t)(e0 + k) * p.P + q];
-          }
-        }
-      }
+    if constexpr (PK == 2) {
       int pp = pos;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         if (stay[k]) {
-#pragma unroll
-          for (int q = 0; q < BR_HP; ++q)
-            if (q < p.P) pw[(int64_t)pp * p.P + q] = pr[k][q];
+          float *q = pw + (int64_t)pp * 3;
+          q[0] = ch[k], q[1] = age[k], q[2] = since[k];
           ++pp;
         }
       }
+    }
+    if constexpr (PK == 1) {
+      int pp[4], at = pos;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        pp[k] = stay[k] ? at : -1;
+        at += stay[k] ? 1 : 0;
+      }
+      *reinterpret_cast<short4 *>(map + (e0 - chunk0)) = make_short4((short)pp[0], (short)pp[1], (short)pp[2], (short)pp[3]);
+      // of the chunk's first slot on if an earlier chunk lost a request, else of the first leaver's
+      from = shifted ? chunk0 : chunk0 + 4 * (int)__builtin_ctzll(br_ballot(any_leave));
     }
     int lost = 0;
 #pragma unroll

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(256) void br_k_load_init(BrParams p, const int32_t 
 // footprint goes with it.  t steps are applied in closed form: a request with rem <= t
 // leaves (net load change -kv), the others gain t tokens.  One wave owns one worker's dense
 // list and compacts it in place, order preserved (writes never run ahead of reads).
-template <int NC, int RW, bool PRED>
+template <int NC, int RW, int PK>
 __global__ __launch_bounds__(256) void br_k_advance(BrParams p, int t) {
   // each wave owns RW consecutive worker lists, NC chunks of 256 slots each, four slots per lane;
   // everything it will touch is requested before the first result is needed, so that enough bytes
@@ -61,6 +61,8 @@ __global__ __launch_bounds__(256) void br_k_advance(BrParams p, int t) {
   const int64_t rows = (int64_t)p.N * p.G;
   if (row0 >= rows) return;
   const int lane = br_lane();
+  __shared__ __align__(16) short maps[PK == 1 ? 4 * 256 : 4];
+  short *map = PK == 1 ? maps + (threadIdx.x >> 6) * 256 : nullptr;
   int n_g[RW];
   int4 kv[RW][NC], rem[RW][NC];
 #pragma unroll
@@ -79,8 +81,14 @@ __global__ __launch_bounds__(256) void br_k_advance(BrParams p, int t) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       if (c * 256 < n_g[r]) {
-        br_adv_apply<PRED>(p, t, c * 256 + 4 * lane, n_g[r], c * 256, kv[r][c], rem[r][c], p.kv + base, p.rem + base,
-                           PRED ? p.pred + base * p.P : nullptr, kept, gone);
+        int from;
+        br_adv_apply<PK>(p, t, c * 256 + 4 * lane, n_g[r], c * 256, kv[r][c], rem[r][c], p.kv + base, p.rem + base,
+                           PK > 0 ? p.pred + base * p.P : nullptr, kept, gone, map, from);
+        if (PK == 1 && from >= 0) {
+          br_wave_sync();
+          br_rows_move(p.pred + base * p.P, p.P, map, c * 256, from, min(n_g[r], c * 256 + 256), lane);
+          br_wave_sync();  // the map is rewritten by the next chunk
+        }
       }
     }
     if (lane == 0) {
@@ -713,14 +721,14 @@ __global__ __launch_bounds__(256) void br_k_score_combine(BrParams p, BrOut o, c
 }
 
 // K2 + K3, one wave per cluster (br_score_wave.h)
-template <int E, bool BRH>
+template <int E, int HB>
 __global__ __launch_bounds__(256) void br_k_score_wave(BrParams p, BrArr a, BrOut o) {
   const int inst = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
   if (inst >= p.N) return;
   const int lane = br_lane();
-  BrScoreIn<E, BRH> in;
-  br_score_wave_load<E, BRH>(p, a, inst, lane, in);
-  br_score_wave_run<E, BRH>(p, o, inst, lane, in);
+  BrScoreIn<E, HB> in;
+  br_score_wave_load<E, HB>(p, a, inst, lane, in);
+  br_score_wave_run<E, HB>(p, o, inst, lane, in);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -738,13 +746,17 @@ void br_launch_load_init(const BrParams &p, const int32_t *n, const int32_t *kv,
 
 template <int NC, int RW>
 static void launch_advance(const BrParams &p, int t, hipStream_t st) {
-  constexpr int RWP = NC == 1 ? 2 : 1;  // lists that carry prediction rows: at most four chunks per wave (code size)
+  constexpr int RWP = 1;  // lists that carry prediction rows: at most four chunks per wave (code size)
   if (p.P) {
     const int64_t waves = ((int64_t)p.N * p.G + RWP - 1) / RWP;
-    hipLaunchKernelGGL((br_k_advance<NC, RWP, true>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, p, t);
+    const dim3 grid((unsigned)((waves + 3) / 4)), block(256);
+    if (p.pred_mode == 2)
+      hipLaunchKernelGGL((br_k_advance<NC, RWP, 2>), grid, block, 0, st, p, t);
+    else
+      hipLaunchKernelGGL((br_k_advance<NC, RWP, 1>), grid, block, 0, st, p, t);
   } else {
     const int64_t waves = ((int64_t)p.N * p.G + RW - 1) / RW;
-    hipLaunchKernelGGL((br_k_advance<NC, RW, false>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, p, t);
+    hipLaunchKernelGGL((br_k_advance<NC, RW, 0>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, p, t);
   }
 }
 
@@ -896,14 +908,14 @@ static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut 
     const dim3 grid((unsigned)((p.N + 3) / 4)), block(256);
     if (p.H > 0) {
       if (p.Q <= 256)
-        hipLaunchKernelGGL((br_k_score_wave<4, true>), grid, block, 0, st, p, a, o);
+        hipLaunchKernelGGL((br_k_score_wave<4, BR_HP>), grid, block, 0, st, p, a, o);
       else
-        hipLaunchKernelGGL((br_k_score_wave<8, true>), grid, block, 0, st, p, a, o);
+        hipLaunchKernelGGL((br_k_score_wave<8, BR_HP>), grid, block, 0, st, p, a, o);
     } else {
       if (p.Q <= 256)
-        hipLaunchKernelGGL((br_k_score_wave<4, false>), grid, block, 0, st, p, a, o);
+        hipLaunchKernelGGL((br_k_score_wave<4, 0>), grid, block, 0, st, p, a, o);
       else
-        hipLaunchKernelGGL((br_k_score_wave<8, false>), grid, block, 0, st, p, a, o);
+        hipLaunchKernelGGL((br_k_score_wave<8, 0>), grid, block, 0, st, p, a, o);
     }
     return;
   }

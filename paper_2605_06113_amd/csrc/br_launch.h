@@ -28,6 +28,8 @@ int br_long_waves(const BrParams &p);
 // candidate windows of 9..16 requests (H <= BR_HP); no fused decode steps
 void br_launch_assign_bigr(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
 void br_launch_assign_br0(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
+// BR-H, H <= 4
+void br_launch_assign_brh4(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
 // BR-0, Q <= 256: snapshot reductions and assignment of four clusters per block in one launch
 void br_launch_route4(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
 // BR-H (H <= BR_HP), Q <= 512: the same in one launch per four clusters

@@ -9,21 +9,23 @@
 
 #include "br_device.h"
 
-template <int E, bool BRH>
+// HB: offsets beyond h = 0 that are carried (0: BR-0, 4: H <= 4, BR_HP).
+template <int E, int HB>
 struct BrScoreIn {
-  static constexpr int NH = BRH ? BR_HP + 1 : 1;
+  static constexpr int NH = HB + 1;
   int qn, q0, cnt, L, cap, n;  // queue length with and without this round's arrivals, arrivals taken; lane g: load,
                                // free slots and request count of worker g as stored
   int m[NH];  // BR-H: margins of the step-start projection; BR-0: filled by br_score_wave_run
   int s[E];
 };
 
-template <int E, bool BRH>
+template <int E, int HB>
 __device__ __forceinline__ void br_score_wave_load(const BrParams &p, const BrArr &a, int inst, int lane,
-                                                   BrScoreIn<E, BRH> &in) {
+                                                   BrScoreIn<E, HB> &in) {
   // every load that does not need the queue length is requested before the first result is used, and the waiting
   // set comes in one batch of unconditional loads (addresses chosen by select, an entry beyond the set reads the
   // cluster's first queue word): two memory round trips for the whole cluster
+  constexpr bool BRH = HB > 0;
   const int q0_raw = p.qlen[inst];
   const int cnt_raw = a.count ? a.count[inst] : 0;
   const int64_t qrow = (int64_t)inst * p.Q, arow = (int64_t)inst * a.arr_cap;
@@ -31,17 +33,17 @@ __device__ __forceinline__ void br_score_wave_load(const BrParams &p, const BrAr
   const int64_t wrow = (int64_t)inst * p.G + lane;
   const int64_t wrow_ld = act ? wrow : (int64_t)inst * p.G;  // lanes without a worker read worker 0's words (unused)
   const int L_raw = p.L[wrow_ld], n_raw = p.n[wrow_ld];
-  int m_raw[BrScoreIn<E, BRH>::NH];
+  int m_raw[BrScoreIn<E, HB>::NH];
   if constexpr (BRH) {
 #pragma unroll
-    for (int h = 0; h < BrScoreIn<E, BRH>::NH; ++h) m_raw[h] = p.mh[wrow_ld * (p.H + 1) + min(h, p.H)];
+    for (int h = 0; h < BrScoreIn<E, HB>::NH; ++h) m_raw[h] = p.mh[wrow_ld * (p.H + 1) + min(h, p.H)];
   }
   in.L = act ? L_raw : BR_LOW;
   in.n = act ? n_raw : p.B;
   in.cap = act ? p.B - in.n : 0;
   if constexpr (BRH) {
 #pragma unroll
-    for (int h = 0; h < BrScoreIn<E, BRH>::NH; ++h) in.m[h] = (act && h <= p.H) ? m_raw[h] : 0;
+    for (int h = 0; h < BrScoreIn<E, HB>::NH; ++h) in.m[h] = (act && h <= p.H) ? m_raw[h] : 0;
   } else {
     in.m[0] = 0;
   }
@@ -65,10 +67,11 @@ __device__ __forceinline__ void br_score_wave_load(const BrParams &p, const BrAr
   }
 }
 
-template <int E, bool BRH>
+template <int E, int HB>
 __device__ __forceinline__ void br_score_wave_run(const BrParams &p, const BrOut &o, int inst, int lane,
-                                                  const BrScoreIn<E, BRH> &in) {
-  constexpr int NH = BrScoreIn<E, BRH>::NH;
+                                                  const BrScoreIn<E, HB> &in) {
+  constexpr bool BRH = HB > 0;
+  constexpr int NH = BrScoreIn<E, HB>::NH;
   constexpr int IDX_MASK = (1 << BR_IDX_BITS) - 1;
   const int G = p.G, qn = in.qn;
   const bool act = lane < G;
@@ -91,9 +94,7 @@ __device__ __forceinline__ void br_score_wave_run(const BrParams &p, const BrOut
 
   int bi_mine = -1;  // lane g: best request of worker g
   for (int g = 0; g < G; ++g) {
-    int mg[BR_HP + 1];
-#pragma unroll
-    for (int h = 0; h <= BR_HP; ++h) mg[h] = 0;
+    int mg[NH];
 #pragma unroll
     for (int h = 0; h < NH; ++h) mg[h] = __builtin_amdgcn_readlane(m[h], g);
     const int Lg = __builtin_amdgcn_readlane(L, g);

@@ -176,8 +176,8 @@ __device__ __forceinline__ void br_dp_build_helper(const BrParams &p, const int 
 // br_dp_cluster_words(KM) words of workspace.  Returns the chosen mask (0: no admissible subset) and its score key.
 // `svc` (or null): the mailbox of a block whose four waves share LDS builds: wave 0 (the caller) posts the plan,
 // the others join through br_dp_build_helper between the block barriers.
-template <bool BRH>
-__device__ __forceinline__ void br_subset_dp(const BrParams &p, const int (&mg)[BR_HP + 1], const int *win, int w,
+template <bool BRH, int N>
+__device__ __forceinline__ void br_subset_dp(const BrParams &p, const int (&mg)[N], const int *win, int w,
                                              int kmax, int room, int lane, int *rows_lds, int *ws, unsigned &bestmask,
                                              int &bestkey, int *svc = nullptr) {
   constexpr int RW = BR_DP_ROW_WORDS;
@@ -193,7 +193,7 @@ __device__ __forceinline__ void br_subset_dp(const BrParams &p, const int (&mg)[
   int minm = mg[0];
   if constexpr (BRH) {
 #pragma unroll
-    for (int h = 1; h <= BR_HP; ++h) minm = h <= p.H ? min(minm, mg[h]) : minm;
+    for (int h = 1; h < N; ++h) minm = min(minm, mg[h]);  // (offsets beyond H repeat the margin of the last one)
   }
   const bool two_probe = !BRH && p.G > 1;
   int R = min(min(top, room), BR_DP_MAX_SUM);
