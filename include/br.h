@@ -233,11 +233,11 @@ int32_t br_advance_decode(br_ctx *ctx, int32_t n_steps);
  * n_steps decode steps of br_advance_decode (Sec. 2.2; Alg. BR-0 / Alg. BR-H), with exactly their
  * results: same outputs (written as br_route_step writes them, statistics describe the state
  * right after the round) and same workspace contents afterwards as the two calls in sequence.
- * Where the shape allows, the assignment launch itself applies the decode steps (the wave that has
- * routed a cluster goes on to that cluster's lists, so clusters that finish their round early stream
- * their lists while others are still routing; small BR-0 batches use a second wave per cluster for
- * them); candidate windows beyond 8 requests and long-horizon rounds that several waves share are
- * followed by the decode kernel as a launch of its own on the same stream.
+ * For BR-0 with candidate windows of up to 8 requests the assignment launch itself applies the decode steps
+ * where that pays (batches of 2048 clusters and more: the wave that has routed a cluster goes on to that cluster's
+ * lists, so clusters that finish their round early stream their lists while others are still routing; smaller
+ * batches with queues of up to 512: a second wave per cluster); otherwise the decode kernel follows as a launch of
+ * its own on the same stream.
  * Arguments, ownership and errors as for br_route_step; n_steps >= 0 (0: identical to
  * br_route_step), BR_EINVAL otherwise.
  */

@@ -257,14 +257,13 @@ __device__ __forceinline__ BrParams br_late_params() {
   return p;
 }
 
-// Decode advance of one cluster by the wave that has just routed it: br_adv_apply (the arithmetic of
+// Decode advance of one BR-0 cluster by the wave that has just routed it: br_adv_apply (the arithmetic of
 // the stand-alone advance kernel) over the cluster's G lists in (list, 256-slot chunk) units, UB units
 // requested before the first is used.  `Lcur`, `nn`: load and list length of worker `lane` after the round.
 // STORE = false: loads and counts are not stored; lane g returns its list's load change in `dL_out` and its new
 // length in `n_out` instead (the split kernels, where another wave owns the workers' final state).
-// PK as for br_adv_apply; `map` (PK 1): UB x 256 16-bit entries of this wave's LDS.
-template <int UB, int PK, bool STORE = true>
-__device__ __forceinline__ void br_advance_cluster_as(int inst, int lane, int Lcur, int nn, short *map, int g0 = 0, int g1 = 64,
+template <int UB, bool STORE = true>
+__device__ __forceinline__ void br_advance_cluster(int inst, int lane, int Lcur, int nn, int g0 = 0, int g1 = 64,
                                                    int *dL_out = nullptr, int *n_out = nullptr) {
   const BrParams p = br_late_params();
   const int t = p.adv_t;
@@ -275,10 +274,8 @@ __device__ __forceinline__ void br_advance_cluster_as(int inst, int lane, int Lc
   int dLw = 0, nw = nn;     // lane g: load change and new length of worker g
   int kept = 0, gone = 0;   // running state of the list in progress: survivors, kv that left
   int gl = g0, cl = 0, gp = g0, cp = 0;  // (list, chunk) cursors of the load and the update pass
-  int gm = g0, cm = 0;                   // ... and of the pass that moves prediction rows
   const int32_t *kl = p.kv + rowa * p.Bs, *rl = p.rem + rowa * p.Bs;  // list the load pass is at
   int32_t *kw = p.kv + rowa * p.Bs, *rw = p.rem + rowa * p.Bs;        // list the update pass is at
-  float *pw = p.pred + rowa * p.Bs * p.P;
   for (int u0 = 0; u0 < U; u0 += UB) {
     int4 kv[UB], rem[UB];
 #pragma unroll
@@ -287,34 +284,20 @@ __device__ __forceinline__ void br_advance_cluster_as(int inst, int lane, int Lc
       if (gl < G) br_adv_load(kl, rl, cl * 256 + 4 * lane, __builtin_amdgcn_readlane(nn, gl), kv[k], rem[k]);
       if (++cl == NC) cl = 0, ++gl, kl += p.Bs, rl += p.Bs;
     }
-    unsigned long long froms = 0ull;  // PK 1: first slot whose row moves + 1, 16 bits per unit
 #pragma unroll
     for (int k = 0; k < UB; ++k) {
       if (gp < G) {
         const int ng = __builtin_amdgcn_readlane(nn, gp);
         if (cp * 256 < ng) {
           int from;
-          br_adv_apply<PK>(p, t, cp * 256 + 4 * lane, ng, cp * 256, kv[k], rem[k], kw, rw, pw, kept, gone, map + k * 256, from);
-          if constexpr (PK == 1) froms |= (unsigned long long)(unsigned)(from + 1) << (16 * (k & 3));
+          br_adv_apply<0>(p, t, cp * 256 + 4 * lane, ng, cp * 256, kv[k], rem[k], kw, rw, nullptr, kept, gone, nullptr, from);
         }
         if (++cp == NC) {
           if (lane == gp) dLw = kept * t - gone, nw = kept;  // survivors gain t tokens each
           kept = 0, gone = 0, cp = 0, ++gp;
-          kw += p.Bs, rw += p.Bs, pw += (int64_t)p.Bs * p.P;
+          kw += p.Bs, rw += p.Bs;
         }
       }
-    }
-    if constexpr (PK == 1) {
-      static_assert(PK != 1 || UB <= 4, "16 bits per unit");
-      br_wave_sync();
-      for (int k = 0; k < UB && gm < G; ++k) {  // in order: a chunk's rows may move into the chunk before it
-        const int from = (int)((froms >> (16 * k)) & 0xffffull) - 1;
-        if (from >= 0)
-          br_rows_move(p.pred + (row0 + gm) * p.Bs * p.P, p.P, map + k * 256, cm * 256, from,
-                       min(__builtin_amdgcn_readlane(nn, gm), cm * 256 + 256), lane);
-        if (++cm == NC) cm = 0, ++gm;
-      }
-      br_wave_sync();  // the maps are rewritten by the next units
     }
   }
   if constexpr (STORE) {
@@ -325,20 +308,6 @@ __device__ __forceinline__ void br_advance_cluster_as(int inst, int lane, int Lc
   } else {
     *dL_out = dLw;
     *n_out = nw;
-  }
-}
-
-template <int UB, bool BRH>
-__device__ __forceinline__ void br_advance_cluster(const BrParams &p, int inst, int lane, int Lcur, int nn, int *lds, int g0 = 0,
-                                                   int g1 = 64) {
-  short *map = reinterpret_cast<short *>(lds);  // (512 words)
-  if constexpr (BRH) {
-    if (p.pred_mode == 2)
-      br_advance_cluster_as<UB, 2>(inst, lane, Lcur, nn, map, g0, g1);
-    else
-      br_advance_cluster_as<UB, 1>(inst, lane, Lcur, nn, map, g0, g1);
-  } else {
-    br_advance_cluster_as<UB, 0>(inst, lane, Lcur, nn, map, g0, g1);
   }
 }
 
@@ -370,7 +339,7 @@ __device__ __forceinline__ void br_split_helper(const BrParams &p, const BrArr &
   }
   n0 = act ? min(max(n0, 0), p.B) : 0;
   int dL = 0, kept = n0;
-  br_advance_cluster_as<UB, 0, false>(inst, lane, 0, n0, nullptr, 0, 64, &dL, &kept);
+  br_advance_cluster<UB, false>(inst, lane, 0, n0, 0, 64, &dL, &kept);
   split[4 + lane] = n0 - kept;
   split[4 + BR_WAVE + lane] = dL;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // the lists are in place before the flag is seen

@@ -33,7 +33,7 @@
 // (most free slots, then largest horizon-min margin, then lowest index); equal request scores
 // resolve to the lowest sorted position; equal subset scores to the lowest mask.
 //
-// ADV: the wave goes on to apply the decode steps to the lists of the cluster it has routed
+// ADV (BR-0): the wave goes on to apply the decode steps to the lists of the cluster it has routed
 // (br_route_advance); a separate instantiation, so that the two kinds of launch carry distinct
 // kernel names in profiles.
 #pragma once
@@ -785,6 +785,7 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
                                                int w = 0, const BrScoreIn<EM, HB> *pre = nullptr, int *split = nullptr,
                                                bool shared = false) {
   static_assert(!COOP || EM == 32, "the four-wave sort covers 4 x 512 keys");
+  static_assert(!ADV || HB == 0, "decode steps ride along with BR-0 rounds only");
   constexpr bool BRH = HB > 0;
   constexpr int NH = HB + 1;
   if (inst >= p.N) return;
@@ -937,7 +938,7 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
     br_assign_epilogue_block4<BRH>(inst, lane, w, q0, qn, cnt, bound, slots, lst, Lw, st.nn, rc, c0, ADV);
     if constexpr (ADV) {
       const int per = (G + 3) >> 2;
-      br_advance_cluster<4, BRH>(p, inst, lane, Lw, st.nn, lst + w * 512, min(w * per, G), min(w * per + per, G));
+      br_advance_cluster<8>(inst, lane, Lw, st.nn, min(w * per, G), min(w * per + per, G));
     }
   } else {
     bool done = false;
@@ -949,7 +950,7 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
     }
     if (!done) {
       br_assign_epilogue<EM, BRH>(inst, lane, q0, qn, cnt, bound, st.Lh[0], st.nn, rc, c0);
-      if constexpr (ADV) br_advance_cluster<(BRH ? 4 : 8), BRH>(p, inst, lane, st.Lh[0], st.nn, bound);  // BR-H units carry the estimator code: fewer unrolled
+      if constexpr (ADV) br_advance_cluster<8>(inst, lane, st.Lh[0], st.nn);
     }
   }
 }
@@ -980,7 +981,8 @@ static void br_launch_assign_one(const BrParams &p, const BrArr &a, const BrOut 
   const int wpb = (E <= 8 && !dp) ? 4 : 1;  // clusters per block
   const size_t lds = ((size_t)wpb * BR_ROUND_WORDS(E, BIGR) + (dp ? BR_DP_LDS_WORDS : 0)) * sizeof(int);
   const dim3 grid((unsigned)((p.N + wpb - 1) / wpb)), block(E == 32 ? 4 * BR_WAVE : BR_WAVE * wpb);
-  if constexpr (BIGR) {  // no fused decode steps for these: the caller launches the decode kernel
+  // (decode steps ride along for BR-0 with windows of up to 8 requests only; elsewhere the caller launches the decode kernel)
+  if constexpr (BIGR) {
     // windows of 9..16 requests on a batch that leaves room on the chip (registers allow about 4 / 3 / 2 waves per
     // SIMD for queues of up to 256 / 512 / 1024, one less for BR-H): a block of four waves per cluster, the scans shared
     const long long room = 1024ll * max(1, (E == 4 ? 4 : E == 8 ? 3 : 2) - (HB > 0 ? 1 : 0));
@@ -990,6 +992,8 @@ static void br_launch_assign_one(const BrParams &p, const BrArr &a, const BrOut 
     } else {
       hipLaunchKernelGGL((br_k_assign<E, HB, false, true>), grid, block, lds, st, p, a, o, 0);
     }
+  } else if constexpr (HB > 0) {
+    hipLaunchKernelGGL((br_k_assign<E, HB, false>), grid, block, lds, st, p, a, o, 0);
   } else {
     if (p.adv_t > 0)
       hipLaunchKernelGGL((br_k_assign<E, HB, true>), grid, block, lds, st, p, a, o, 0);

@@ -23,7 +23,7 @@
 //     (pick_single: the score is concave in the length, the waiting set is sorted by length);
 //   - Stage 2 goes straight to the starvation guard when the window's smallest entry scores clearly below
 //     zero (then every subset does).
-// Waiting set, sticky binding, epilogue and the optional decode steps are those of the short-horizon
+// Waiting set, sticky binding and epilogue are those of the short-horizon
 // kernel (br_sort.h, br_assign_common.h).
 //
 // With fewer clusters than the chip has room for waves (NW = 2 or 4 waves per cluster) the searches, which
@@ -31,8 +31,7 @@
 // margins are there already), every wave does its share between two block barriers: of the probes' offset
 // groups in a bracketing search (the order of that sum is free), or of the sorted positions in a full scan
 // (wave 0 takes the best of the partial results; the share of a later wave holds higher positions, so only a
-// strictly better score wins).  The helper waves leave when wave 0 posts the end of the round; decode steps
-// then follow as a launch of their own.
+// strictly better score wins).  The helper waves leave when wave 0 posts the end of the round.
 #pragma once
 
 #include "br_device.h"
@@ -82,10 +81,9 @@ __device__ __forceinline__ void br_long_slice_best(const BrParams &p, const floa
   }
 }
 
-template <int E, bool ADV, int NW>
+template <int E, int NW>
 // (queues of up to 256: four waves per SIMD are asked for, which is what br_long_waves counts on)
 __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrParams p, BrArr a, BrOut o) {
-  static_assert(NW == 1 || !ADV, "decode steps ride along only with one wave per cluster");
   static_assert(E % NW == 0, "every wave takes whole blocks of 64 sorted positions");
   constexpr int EW = E / NW;  // blocks of 64 sorted positions per wave in a shared search
   // four-offset groups of wave 0 when the probes of a bracketing search are shared: every NW-th, wave w takes the
@@ -774,7 +772,6 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
   rc.wdrop = wdrop;
   rc.I_before = I_before;
   br_assign_epilogue<E, true>(inst, lane, q0, qn, cnt, who, Lcur, nn, rc, c0);
-  if constexpr (ADV) br_advance_cluster<4, true>(p, inst, lane, Lcur, nn, adm);
 }
 
 template <int E>
@@ -785,11 +782,9 @@ void br_launch_assign_long_one(const BrParams &p, const BrArr &a, const BrOut &o
                       (p.R_max > 8 ? 1024 : 0) + (nw > 1 ? 16 : 0)) * sizeof(int);
   const dim3 grid((unsigned)p.N), block(BR_WAVE * nw);
   if (nw == 4)
-    hipLaunchKernelGGL((br_k_assign_long<E, false, 4>), grid, block, lds, st, p, a, o);
+    hipLaunchKernelGGL((br_k_assign_long<E, 4>), grid, block, lds, st, p, a, o);
   else if (nw == 2)
-    hipLaunchKernelGGL((br_k_assign_long<E, false, 2>), grid, block, lds, st, p, a, o);
-  else if (p.adv_t > 0)
-    hipLaunchKernelGGL((br_k_assign_long<E, true, 1>), grid, block, lds, st, p, a, o);
+    hipLaunchKernelGGL((br_k_assign_long<E, 2>), grid, block, lds, st, p, a, o);
   else
-    hipLaunchKernelGGL((br_k_assign_long<E, false, 1>), grid, block, lds, st, p, a, o);
+    hipLaunchKernelGGL((br_k_assign_long<E, 1>), grid, block, lds, st, p, a, o);
 }

@@ -1,10 +1,10 @@
 // BR-H counterpart of br_k_route4: for large batches of clusters with queues of up to 512 entries the wave that
 // owns a cluster first computes the snapshot reductions (K2 + K3, on the step-start margins of the projection
-// kernels), then runs the two-stage assignment (K4, and the decode step with ADV), in one launch.
+// kernels), then runs the two-stage assignment (K4), in one launch.
 #include "br_assign_kernel.h"
 #include "br_score_wave.h"
 
-template <int E, int HB, bool ADV>
+template <int E, int HB>
 __global__ __launch_bounds__(256, E == 8 ? 4 : 1) void br_k_route_h(BrParams p, BrArr a, BrOut o) {
   extern __shared__ int lds_all[];
   const int w = threadIdx.x >> 6, inst = (int)blockIdx.x * 4 + w;
@@ -12,17 +12,14 @@ __global__ __launch_bounds__(256, E == 8 ? 4 : 1) void br_k_route_h(BrParams p, 
   BrScoreIn<E, HB> in;  // queue lengths, prefill lengths and counts are loaded once, for both parts
   br_score_wave_load<E, HB>(p, a, inst, br_lane(), in);
   br_score_wave_run<E, HB>(p, o, inst, br_lane(), in);
-  br_assign_body<E, HB, ADV>(p, a, o, lds_all + w * BR_ROUND_WORDS(E, false), inst, 0, &in);
+  br_assign_body<E, HB, false>(p, a, o, lds_all + w * BR_ROUND_WORDS(E, false), inst, 0, &in);
 }
 
 template <int E, int HB>
 static void launch_route_h(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
   const size_t lds = (size_t)4 * BR_ROUND_WORDS(E, false) * sizeof(int);
   const dim3 grid((unsigned)((p.N + 3) / 4)), block(256);
-  if (p.adv_t > 0)
-    hipLaunchKernelGGL((br_k_route_h<E, HB, true>), grid, block, lds, st, p, a, o);
-  else
-    hipLaunchKernelGGL((br_k_route_h<E, HB, false>), grid, block, lds, st, p, a, o);
+  hipLaunchKernelGGL((br_k_route_h<E, HB>), grid, block, lds, st, p, a, o);
 }
 
 void br_launch_route_h(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {

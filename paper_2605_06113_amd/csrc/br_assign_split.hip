@@ -43,9 +43,11 @@ static void launch_split(const BrParams &p, const BrArr &a, const BrOut &o, hipS
 // fit 80 registers, which spills in the round's loops (measured on 4096 clusters of the c4 shape: 153 us against
 // 134 us for the one-wave kernel; 163 us with five waves per SIMD and one helper for four clusters, which then
 // is the last to finish).
-bool br_split_serves(const BrParams &p) {
-  return p.adv_t > 0 && p.H == 0 && p.R_max <= 8 && p.Q <= 512 && p.N < BR_SCORE_WAVE_MIN_N;
+bool br_split_shape(const BrParams &p) {
+  return p.H == 0 && p.R_max <= 8 && p.Q <= 512 && p.N < BR_SCORE_WAVE_MIN_N;
 }
+
+bool br_split_serves(const BrParams &p) { return p.adv_t > 0 && br_split_shape(p); }
 
 void br_launch_route_split(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
   if (p.Q <= 256)
