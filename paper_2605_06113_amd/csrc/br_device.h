@@ -458,22 +458,29 @@ __device__ __forceinline__ int br_score_key(const BrParams &p, const int (&m)[N]
 // p_fin = (F(a+H) - F(a)) / (1 - F(a)), mu_rem = mean of (o_j - a) over a < o_j <= a+H, then the
 // composite, gate, floor and clip of eq. (composite) / "Refresh logic".  All counts and the sum of
 // remainders are exact integers below 2^24, so each quotient is one correctly rounded division.
-// Number of history entries <= x[q], NQ look-ups side by side: a fixed number of halving steps (set by the
-// history length alone, the same on every lane), each with the NQ loads in flight together, so that the
-// latency of a step is paid once for all of them.
+// Number of history entries <= x[q], NQ look-ups side by side: a fixed number of steps (set by the history length alone,
+// the same on every lane) that quarter the range, three pivots each, with all loads of a step in flight together: the
+// chain is half as long as a halving search's (8000 entries: 7 steps), and what it costs is the latency of its steps.
 template <int NQ>
 __device__ __forceinline__ void br_hist_ranks(const BrParams &p, const int (&x)[NQ], int (&r)[NQ]) {
   const int n = p.hist_n;
   int step = 1;
-  while (step <= n) step <<= 1;
+  while (step <= n >> 2) step <<= 2;
 #pragma unroll
   for (int q = 0; q < NQ; ++q) r[q] = 0;
-  for (step >>= 1; step > 0; step >>= 1) {
-    int v[NQ];
+  for (; step > 0; step >>= 2) {
+    int v[NQ][3];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) v[q] = p.hist[min(r[q] + step, n) - 1];
+    for (int q = 0; q < NQ; ++q)
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) r[q] += (r[q] + step <= n && v[q] <= x[q]) ? step : 0;
+      for (int k = 0; k < 3; ++k) v[q][k] = p.hist[min(r[q] + (k + 1) * step, n) - 1];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      int up = 0;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) up += (r[q] + (k + 1) * step <= n && v[q][k] <= x[q]) ? step : 0;
+      r[q] += up;
+    }
   }
 }
 
@@ -503,42 +510,46 @@ __device__ __forceinline__ float br_survival(const BrParams &p, int age) {
 
 // Appendix "Refresh logic", for the four requests a lane holds (`on`: the request stays active over t more
 // generated tokens): per token one step less of in-window contribution; the estimator is queried again every
-// `refresh` tokens and whenever c_hat would fall below its floor of one.  The four are taken together token by
-// token, so that the look-ups of those that query the estimator run side by side (eight ranks per lane in flight)
-// instead of one after the other.  Every lane of the wave must call.
+// `refresh` tokens and whenever c_hat would fall below its floor of one.  A few of a wave's requests query in a given
+// step; they are gathered through LDS so that one look-up per lane serves them all (`ask_lds`: 256 words of the wave's),
+// where a look-up by the lane that holds the request took all eight of its ranks through every step.
+// Every lane of the wave must call.
 __device__ __forceinline__ void br_refresh_update4(const BrParams &p, int t, const bool (&on)[4], float (&ch)[4],
-                                                   float (&age)[4], float (&since)[4]) {
+                                                   float (&age)[4], float (&since)[4], int *ask_lds, int lane) {
   for (int u = 0; u < t; ++u) {
-    bool ask[4];
-    int x[8];
-    bool any = false;
+    int at[4], total = 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      ask[k] = false;
+      bool ask = false;
       if (on[k]) {
         age[k] = __fadd_rn(age[k], 1.0f);
         since[k] = __fadd_rn(since[k], 1.0f);
         const float dec = __fsub_rn(ch[k], 1.0f);
-        ask[k] = (int)since[k] >= p.refresh || dec < 1.0f;
-        if (!ask[k]) ch[k] = dec;
+        ask = (int)since[k] >= p.refresh || dec < 1.0f;
+        if (!ask) ch[k] = dec;
       }
-      any |= ask[k];
-      x[2 * k] = ask[k] ? (int)age[k] : 0;
-      x[2 * k + 1] = x[2 * k] + p.H;
+      const unsigned long long bal = br_ballot(ask);
+      at[k] = ask ? total + br_rank_below(bal) : -1;
+      total += __builtin_popcountll(bal);
+      if (ask) ask_lds[at[k]] = (int)age[k];
     }
-    if (br_ballot(any) == 0ull) continue;
-    int r[8];
-    br_hist_ranks<8>(p, x, r);
-    long long hs[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) hs[q] = p.hsum[r[q]];
+    if (total == 0) continue;
+    br_wave_sync();
+    for (int i0 = 0; i0 < total; i0 += BR_WAVE) {
+      const int i = i0 + lane;
+      const int a = ask_lds[min(i, total - 1)];
+      const float c = br_survival(p, a);
+      if (i < total) ask_lds[i] = __float_as_int(c);
+    }
+    br_wave_sync();
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      if (ask[k]) {
-        ch[k] = br_survival_at(p, x[2 * k], r[2 * k], r[2 * k + 1], hs[2 * k], hs[2 * k + 1]);
+      if (at[k] >= 0) {
+        ch[k] = __int_as_float(ask_lds[at[k]]);
         since[k] = 0.0f;
       }
     }
+    br_wave_sync();
   }
 }
 
@@ -615,6 +626,7 @@ __device__ __forceinline__ void br_rows_move(float *pw, int P, const short *map,
 // PK: what a request carries: 0 nothing, 1 a prediction row that moves with it, 2 a maintained estimate (c_hat, age, since).
 // PK 1: the rows themselves are left to the caller (br_rows_move): `map` (256 entries of this wave's LDS) receives the new
 // slot of every request of the chunk, `from` the first slot whose row moves; both only if one does (else from = -1).
+// PK 2: `map` is 256 words of this wave's LDS for the estimator's queries.
 template <int PK>
 __device__ __forceinline__ void br_adv_apply(const BrParams &p, int t, int e0, int ng, int chunk0, const int4 &kv4,
                                              const int4 &rem4, int32_t *kw, int32_t *rw, float *pw, int &kept,
@@ -639,7 +651,7 @@ __device__ __forceinline__ void br_adv_apply(const BrParams &p, int t, int e0, i
   float ch[4] = {0.0f, 0.0f, 0.0f, 0.0f}, age[4] = {0.0f, 0.0f, 0.0f, 0.0f}, since[4] = {0.0f, 0.0f, 0.0f, 0.0f};
   if constexpr (PK == 2) {
     if (e0 < ng) br_rows3_load(pw + (int64_t)e0 * 3, ch, age, since);
-    br_refresh_update4(p, t, stay, ch, age, since);
+    br_refresh_update4(p, t, stay, ch, age, since, reinterpret_cast<int *>(map), br_lane());
   }
   const bool shifted = kept != chunk0;  // an earlier chunk of this list lost a request
   if (!shifted && br_ballot(any_leave) == 0ull) {

@@ -741,6 +741,33 @@ def test_graph_capture_and_replay(name, over):
     r.close()
 
 
+@pytest.mark.parametrize("H,pred_mode", [(0, 0), (4, 0), (8, 0), (3, 0), (6, 1), (5, 3), (80, 2)])
+@pytest.mark.parametrize("B", [3, 64, 65, 128, 131, 256, 260, 515])
+def test_decode_step_list_widths(B, H, pred_mode):
+    """The decode step at the widths where lists per wave and chunks per list change, for every kind of prediction row:
+    full, empty and partly filled lists, few and many leavers, a last wave with no list for some of its lanes."""
+    N, G = 3, 7
+    rng = np.random.default_rng(B * 131 + H)
+    cfg, init, _ = wl.random_case(60 + B, N=N, G=G, B=B, max_wait=8, H=H, fill=0.8, pred_mode=pred_mode)
+    init.n[0, 0], init.n[0, 1], init.n[1, 2] = 0, B, B
+    used = np.arange(B)[None, None, :] < init.n[:, :, None]
+    init.kv[:] = np.where(used, rng.integers(1, 5000, size=(N, G, B)), 0)
+    init.rem[:] = np.where(used, rng.choice([1, 2, 3, 9, 30, 200], size=(N, G, B)), 0)
+    init.rem[0, 1], init.rem[1, 2] = 500, 1            # nobody leaves, everybody leaves
+    if init.pred is not None:
+        init.pred[:] = rng.uniform(0.01, 0.9, size=init.pred.shape).astype(np.float32)
+        if pred_mode == 2:
+            init.pred[:] = wl.maintained_triples(rng, cfg, (N, G, B))
+    hist = wl.output_history(cfg, 700) if pred_mode == 2 else None
+    oc, r = br_oracle.OracleCluster(cfg, init, hist=hist), binding.Router(cfg, init, hist=hist)
+    for t in (1, 2, 7):
+        _say(f"B={B} H={H} mode={pred_mode} t={t}")
+        oc.advance(t)
+        r.advance(t)
+        compare_state(oc, r.state(), cfg, f"B={B} H={H} t={t}")
+    r.close()
+
+
 @pytest.mark.parametrize("through_block", [True, False])
 def test_host_calls_with_varying_rows(through_block, monkeypatch):
     """Router.route_step over row lengths that vary from call to call (and with no arrivals at all), through the pinned
