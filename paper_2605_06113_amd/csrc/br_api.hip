@@ -48,7 +48,7 @@ bool config_ok(const br_config *c) {
 // `dl`: byte offset of the discount table that horizons beyond BR_HP keep in the workspace (after the
 // arrays of the public layout), or 0
 void make_layout(const br_config &c, br_layout *l, uint64_t *dl = nullptr, uint64_t *score_scratch = nullptr,
-                 uint64_t *pol = nullptr, uint64_t *dp = nullptr) {
+                 uint64_t *pol = nullptr, uint64_t *dp = nullptr, uint64_t *c0 = nullptr) {
   const uint64_t N = (uint64_t)c.n_inst, G = (uint64_t)c.G, Q = (uint64_t)c.max_wait, H1 = (uint64_t)c.H + 1;
   const uint64_t P = (uint64_t)pred_width(c), Pq = (uint64_t)queue_pred_width(c);
   const uint64_t Bs = ((uint64_t)c.B + 3u) & ~(uint64_t)3u;
@@ -82,6 +82,8 @@ void make_layout(const br_config &c, br_layout *l, uint64_t *dl = nullptr, uint6
   // windows beyond 16 requests: bit rows and first-request table of the subset search, per cluster (private)
   const uint64_t dp_at = c.R_max > 16 ? take(N * (uint64_t)br_dp_cluster_words(c.B < c.R_max ? c.B : c.R_max)) : 0;
   if (dp) *dp = dp_at;
+  const uint64_t c0_at = c.pred_mode == 2 ? take(1) : 0;  // the estimate at age 0 (private)
+  if (c0) *c0 = c0_at;
   l->total_bytes = off;
   l->B_stride = (int32_t)Bs;
   l->P = (int32_t)P;
@@ -174,8 +176,8 @@ int32_t br_init(const br_config *cfg, const br_init_state *init, br_ctx **out) {
   if (!out || !config_ok(cfg) || !cfg->workspace) return BR_EINVAL;
   if (((uintptr_t)cfg->workspace & 255u) != 0) return BR_EINVAL;
   br_layout l;
-  uint64_t dl_at = 0, ss_at = 0, pol_at = 0, dp_at = 0;
-  make_layout(*cfg, &l, &dl_at, &ss_at, &pol_at, &dp_at);
+  uint64_t dl_at = 0, ss_at = 0, pol_at = 0, dp_at = 0, c0_at = 0;
+  make_layout(*cfg, &l, &dl_at, &ss_at, &pol_at, &dp_at, &c0_at);
   if (cfg->workspace_bytes < l.total_bytes) return BR_ENOMEM;
   const int P = pred_width(*cfg);
   if (init && (!init->n || !init->kv || !init->rem || (P > 0 && !init->pred))) return BR_EINVAL;
@@ -222,6 +224,8 @@ int32_t br_init(const br_config *cfg, const br_init_state *init, br_ctx **out) {
     acc = acc + dh;
   }
   volatile float aD = cfg->alpha * acc;
+  p.dsum = acc;
+  p.pad = 0;
   p.aD = cfg->H > 0 ? (float)aD : 1.0f;
   p.beta = cfg->H > 0 ? cfg->beta : (float)cfg->G;
 
@@ -242,6 +246,7 @@ int32_t br_init(const br_config *cfg, const br_init_state *init, br_ctx **out) {
   p.minm = (int32_t *)(base + l.minm);
   p.dl = dl_at ? (const float *)(base + dl_at) : nullptr;
   p.dp = dp_at ? (int32_t *)(base + dp_at) : nullptr;
+  p.c0 = c0_at ? (float *)(base + c0_at) : nullptr;
   ctx->score_scratch = ss_at ? (int *)(base + ss_at) : nullptr;
   ctx->pol = (int *)(base + pol_at);
   // set-up of the allocation-free entry point: the device address of the fixed scratch array, looked up once per

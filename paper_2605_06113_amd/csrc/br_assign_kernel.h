@@ -170,10 +170,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
   float e2 = 0.0f, dscale = 0.0f;
   int ho = -1;
   if constexpr (BRH) {
-    float Dsum = 0.0f;
-#pragma unroll
-    for (int h = 0; h < NH; ++h) Dsum += p.d[h];
-    dscale = p.aD + p.beta * Dsum;
+    dscale = p.aD + p.beta * p.dsum;
     e2 = 1.6e-6f * dscale * (float)(br_uniform((int)(x[0] >> BR_IDX_BITS)));
 #pragma unroll
     for (int h = 0; h < NH; ++h) ho = (h <= p.H && p.beta * p.d[h] - p.aD > e2) ? h : ho;  // (d falls with h)
@@ -857,7 +854,7 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
   // first estimate of a newly admitted request when the library maintains c_hat (age 0)
   float c0 = 0.0f;
   if constexpr (BRH) {
-    if (p.pred_mode == 2) c0 = br_survival(p, 0);
+    if (p.pred_mode == 2) c0 = *p.c0;
   }
 
   // ---- worker state, one worker per lane

@@ -118,6 +118,28 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
   const int qn = q0 + min(cnt, p.Q - q0);
   const int64_t qrow = (int64_t)inst * p.Q, arow = (int64_t)inst * a.arr_cap;
 
+  // the step-start projections, as contiguous memory: all waves of the block, four words per thread in flight
+  {
+    const int32_t *src = p.Lh + (int64_t)inst * G * H1;
+    const int words = G * H1, nt = 64 * NW;
+    const unsigned inv = 0xffffffffu / (unsigned)H1 + 1u;  // e / H1 by a multiply-high (e < 2^14)
+    for (int e0 = (int)threadIdx.x; e0 < words; e0 += 4 * nt) {
+      int v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = src[min(e0 + u * nt, words - 1)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int e = min(e0 + u * nt, words - 1);
+        const int g = (int)__umulhi((unsigned)e, inv);
+        sL[(e - g * H1) * LS + g] = v[u];
+      }
+    }
+    for (int h = (int)threadIdx.x; h < HS; h += nt) {  // a column beyond G and offsets beyond H read as "no worker"
+      if (LS > G) sL[h * LS + G] = BR_LOW;
+      if (h >= H1)
+        for (int g = 0; g < G; ++g) sL[h * LS + g] = BR_LOW;
+    }
+  }
   if constexpr (NW > 1) {
     const int w = (int)(threadIdx.x >> 6);
     if (w != 0) {  // serves wave 0's searches: every wave of the block meets at both barriers of each, wave 0 ends the loop
@@ -148,7 +170,7 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
   }
 
   float c0 = 0.0f;  // first estimate of a newly admitted request when the library maintains c_hat
-  if (p.pred_mode == 2) c0 = br_survival(p, 0);
+  if (p.pred_mode == 2) c0 = *p.c0;
 
   // ---- worker state: lane g holds worker g
   const bool act = lane < G;
@@ -168,12 +190,6 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
       sM[h] = Mr[u];
       sd[h] = p.dl[h];
       smg[h] = 0.0f;
-    }
-  }
-  for (int g = 0; g < LS; ++g) {  // a column beyond G and offsets beyond H read as "no worker"
-    for (int h0 = 0; h0 < HS; h0 += BR_WAVE) {
-      const int h = h0 + lane;
-      if (h < HS) sL[h * LS + g] = (g < G && h < H1) ? p.Lh[((int64_t)inst * G + g) * H1 + h] : BR_LOW;
     }
   }
   int S_tot = br_wave_sum(cap);
@@ -268,15 +284,7 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
   // Rounding of one evaluation of eq. (brh-Fscore) in fp32: at most H + 5 roundings, each relative 2^-24 on terms
   // bounded by (alpha D + beta D) Delta, so a computed score differs from the exact one by at most
   // err_unit * Delta (a quarter of slack on top covers the rounding of this bound itself).
-  float err_unit;
-  {
-    float Dsum = 0.0f;
-    for (int h = 0; h < HS; h += 4) {
-      const float4 q = *reinterpret_cast<const float4 *>(sd + h);
-      Dsum += (q.x + q.y) + (q.z + q.w);
-    }
-    err_unit = 1.25f * (float)(p.H + 5) * 5.9604645e-8f * (p.aD + p.beta * Dsum);
-  }
+  const float err_unit = 1.25f * (float)(p.H + 5) * 5.9604645e-8f * (p.aD + p.beta * p.dsum);
 
   // argmax_i F_g({i}) over alive, admissible requests against the margins in smg (lowest sorted
   // position on ties); false when no request is admissible.

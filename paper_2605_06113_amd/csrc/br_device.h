@@ -32,6 +32,9 @@ struct BrParams {
   const long long *hsum;    // their prefix sums
   const float *dl;          // H > BR_HP: discount vector d[0..H], then zeros up to BR_HS(H) entries
   int32_t *dp;              // R_max > 16: per-cluster areas for the subset search by reachable sums (br_subset_dp.h)
+  float *c0;                // pred_mode 2: estimate at age 0, written by the projection of every round
+  float dsum;               // sum of the discounts
+  int32_t pad;
 };
 
 struct BrArr {  // arrivals of one round (device pointers, may be null when none)
@@ -139,6 +142,17 @@ __device__ __forceinline__ int br_scan_max(int x) {
   x = max(x, br_dpp<0x118>(INT32_MIN, x));       // row_shr:8
   x = max(x, br_dpp<0x142, 0xA>(INT32_MIN, x));  // row_bcast:15 into rows 1 and 3
   x = max(x, br_dpp<0x143, 0xC>(INT32_MIN, x));  // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
+// Sum over the lane and all lanes below it.
+__device__ __forceinline__ int br_scan_sum(int x) {
+  x += br_dpp<0x111>(0, x);
+  x += br_dpp<0x112>(0, x);
+  x += br_dpp<0x114>(0, x);
+  x += br_dpp<0x118>(0, x);
+  x += br_dpp<0x142, 0xA>(0, x);
+  x += br_dpp<0x143, 0xC>(0, x);
   return x;
 }
 

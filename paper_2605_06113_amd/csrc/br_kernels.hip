@@ -383,91 +383,108 @@ __global__ __launch_bounds__(256) void br_k_project_rows(BrParams p) {
 // every fourth worker list and leaves its row in an LDS tile as well; then, with threads mapped to offsets,
 // the envelope M_h = max_g L_g(k+h) and the margins, and with threads mapped to workers the horizon-min
 // margin (what br_k_envelope does for short horizons in a launch of its own).
+// The lists of a wave are taken in units of 64 slots with the next unit requested before the one in hand is used; suffix
+// sums are wave-wide DPP scans with lanes mapped to offsets in descending order (a walk over all bins on every lane took
+// 750 instructions per list).  2048 clusters, G = 8, B = 64, H = 80: 36 -> 10 us.  A last block writes the
+// estimate at age 0 that newly admitted requests get (pred_mode 2).
+#define BR_BINS 192  // offsets 0..BR_HL in whole waves
 __global__ __launch_bounds__(256) void br_k_project_long(BrParams p) {
   extern __shared__ int lds[];
   const int wave = threadIdx.x >> 6, lane = br_lane(), tid = threadIdx.x;
   const int inst = blockIdx.x;
+  if (inst == p.N) {
+    if (wave == 0) {
+      const float c = br_survival(p, 0);
+      if (lane == 0) *p.c0 = c;
+    }
+    return;
+  }
   const int G = p.G, H = p.H, H1 = H + 1, HS = BR_HS(H);
-  int *tile = lds;                              // [G][HS] projections, then margins
-  int *cnt = lds + G * HS + wave * 2 * HS;      // this wave's histogram: requests whose last offset is c
-  int *kvs = cnt + HS;                          // ... and the sum of their kv
+  int *tile = lds;                                     // [G][HS] projections
+  int *sM = lds + G * HS;                              // [HS] envelope
+  int *cnt = sM + HS + wave * 2 * BR_BINS;             // this wave's histogram: requests whose last offset is c
+  int *kvs = cnt + BR_BINS;                            // ... and the sum of their kv
   const float Hf = (float)H;
+  const int64_t row0 = (int64_t)inst * G;
+  const int mine = wave + 4 * lane;                    // lane i: length of this wave's i-th list
+  const int nn = mine < G ? min(max(p.n[row0 + mine], 0), p.B) : 0;
+#pragma unroll
+  for (int u = 0; u < BR_BINS / BR_WAVE; ++u) cnt[u * BR_WAVE + lane] = 0, kvs[u * BR_WAVE + lane] = 0;
+  br_wave_sync();
+  auto fetch = [&](int g, int j0, int &kv, float &c, float &c2) {  // (whole rows: no wait for the length)
+    const int64_t at = (row0 + g) * p.Bs + min(j0 + lane, p.Bs - 1);
+    kv = p.kv[at];
+    c = p.pred[at * p.P];  // pred_mode 1 and 2 keep c_hat first
+    c2 = p.pred_mode == 3 ? p.pred[at * p.P + 1] : 0.0f;
+  };
+  int kv_n = 0;
+  float c_n = 0.0f, c2_n = 0.0f;
+  if (wave < G) fetch(wave, 0, kv_n, c_n, c2_n);
   for (int g = wave; g < G; g += 4) {
-    const int64_t row = (int64_t)inst * G + g;
-    for (int h = lane; h < HS; h += BR_WAVE) cnt[h] = 0, kvs[h] = 0;
-    br_wave_sync();
-    const int n = min(max(p.n[row], 0), p.B);
-    const int64_t base = row * p.Bs;
+    const int64_t row = row0 + g;
+    const int n = __builtin_amdgcn_readlane(nn, (g - wave) >> 2);
     int topc = 0, topk = 0;  // requests that reach the last offset (the gate's anchor: the common case)
-    for (int j0 = 0; j0 < n; j0 += BR_WAVE) {
+    for (int j0 = 0; j0 < max(n, 1); j0 += BR_WAVE) {
       const int j = j0 + lane;
-      int kv = 0, hm = -1;
-      if (j < n) {
-        kv = p.kv[base + j];
-        float c = p.pred[(base + j) * p.P];  // pred_mode 1 and 2 keep c_hat first
-        if (p.pred_mode == 3) {              // the pair (p_fin, mu_rem): eq. (composite) and the gate
-          const float pf = c, mu = p.pred[(base + j) * p.P + 1];
-          c = __fadd_rn(__fmul_rn(__fsub_rn(1.0f, pf), Hf), __fmul_rn(pf, mu));
-          if (p.gate > 0.0f && pf < p.gate) c = Hf;
-        }
-        c = c < 1.0f ? 1.0f : c;
-        c = c > Hf ? Hf : c;
-        if (c >= 0.0f) hm = min((int)c, H);  // offsets h with (float)h <= c_hat are 0..floor(c_hat); a NaN counts nowhere
+      const int kv = kv_n;
+      float c = c_n;
+      const float mu = c2_n;
+      const int gn = j0 + BR_WAVE < n ? g : g + 4, jn = j0 + BR_WAVE < n ? j0 + BR_WAVE : 0;  // the next unit
+      if (gn < G) fetch(gn, jn, kv_n, c_n, c2_n);
+      if (p.pred_mode == 3) {              // the pair (p_fin, mu_rem): eq. (composite) and the gate
+        const float pf = c;
+        c = __fadd_rn(__fmul_rn(__fsub_rn(1.0f, pf), Hf), __fmul_rn(pf, mu));
+        if (p.gate > 0.0f && pf < p.gate) c = Hf;
       }
+      c = c < 1.0f ? 1.0f : c;
+      c = c > Hf ? Hf : c;
+      int hm = -1;
+      if (j < n && c >= 0.0f) hm = min((int)c, H);  // offsets h with (float)h <= c_hat are 0..floor(c_hat); a NaN counts nowhere
       const bool top = hm == H;
       topc += __builtin_popcountll(br_ballot(top));
-      topk += br_wave_sum(top ? kv : 0);
+      topk += top ? kv : 0;
       if (hm >= 0 && !top) {
         atomicAdd(&cnt[hm], 1);
         atomicAdd(&kvs[hm], kv);
       }
     }
+    topk = br_wave_sum(topk);
     br_wave_sync();
-    if (lane == 0) cnt[H] += topc, kvs[H] += topk;
-    br_wave_sync();
-    // suffix sums, four bins per trip: lane handles offsets lane, lane + 64, lane + 128
-    int C[3] = {0, 0, 0}, K[3] = {0, 0, 0};
-    for (int c4 = HS - 4; c4 >= 0; c4 -= 4) {
-      const int4 cc = *reinterpret_cast<const int4 *>(cnt + c4);
-      const int4 kk = *reinterpret_cast<const int4 *>(kvs + c4);
-      const int cv[4] = {cc.x, cc.y, cc.z, cc.w}, kv4[4] = {kk.x, kk.y, kk.z, kk.w};
+    // suffix sums: lane l of chunk u stands for offset 64 u + 63 - l; the chunks above are in the carry
+    int Cc = topc, Kc = topk;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-#pragma unroll
-        for (int u = 0; u < 3; ++u) {
-          const bool in = c4 + e >= lane + u * BR_WAVE;
-          C[u] += in ? cv[e] : 0;
-          K[u] += in ? kv4[e] : 0;
+    for (int u = BR_BINS / BR_WAVE - 1; u >= 0; --u) {
+      if (u * BR_WAVE < H1) {
+        const int h = u * BR_WAVE + 63 - lane;
+        const int C = br_scan_sum(cnt[h]) + Cc, K = br_scan_sum(kvs[h]) + Kc;
+        cnt[h] = 0, kvs[h] = 0;
+        Cc = __builtin_amdgcn_readlane(C, 63), Kc = __builtin_amdgcn_readlane(K, 63);
+        if (h < H1) {
+          const int v = K + h * C;
+          p.Lh[row * H1 + h] = v;
+          tile[g * HS + h] = v;
         }
       }
     }
-#pragma unroll
-    for (int u = 0; u < 3; ++u) {
-      const int h = lane + u * BR_WAVE;
-      if (h < H1) {
-        const int v = K[u] + h * C[u];
-        p.Lh[row * H1 + h] = v;
-        tile[g * HS + h] = v;
-      }
-    }
-    br_wave_sync();  // the histogram is cleared again for this wave's next list
+    br_wave_sync();  // the histogram is filled again for this wave's next list
   }
   __syncthreads();
   if (tid < H1) {  // thread = offset
     int M = tile[tid];
     for (int g = 1; g < G; ++g) M = max(M, tile[g * HS + tid]);
     p.Mh[(int64_t)inst * H1 + tid] = M;
-    for (int g = 0; g < G; ++g) {
-      const int m = max(M - tile[g * HS + tid], 0);
-      p.mh[((int64_t)inst * G + g) * H1 + tid] = m;
-      tile[g * HS + tid] = m;
-    }
+    sM[tid] = M;
   }
   __syncthreads();
-  if (tid < G) {  // thread = worker
+  for (int g = wave; g < G; g += 4) {  // wave = worker, lane = offset
     int mn = INT32_MAX;
-    for (int h = 0; h < H1; ++h) mn = min(mn, tile[tid * HS + h]);
-    p.minm[(int64_t)inst * G + tid] = mn;
+    for (int h = lane; h < H1; h += BR_WAVE) {
+      const int m = max(sM[h] - tile[g * HS + h], 0);
+      p.mh[(row0 + g) * H1 + h] = m;
+      mn = min(mn, m);
+    }
+    mn = br_wave_min(mn);
+    if (lane == 0) p.minm[row0 + g] = mn;
   }
 }
 
@@ -486,8 +503,12 @@ __global__ void br_k_discounts(BrParams p, float gamma) {
 // one wave per cluster, lane g holds worker g.
 __global__ __launch_bounds__(256) void br_k_envelope(BrParams p) {
   const int inst = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
-  if (inst >= p.N) return;
   const int lane = br_lane();
+  if (inst == p.N && p.pred_mode == 2) {  // one wave beyond the clusters: the estimate at age 0 (newly admitted requests)
+    const float c = br_survival(p, 0);
+    if (lane == 0) *p.c0 = c;
+  }
+  if (inst >= p.N) return;
   const bool act = lane < p.G;
   const int H1 = p.H + 1;
   const int64_t wrow = (int64_t)inst * p.G + lane;
@@ -512,9 +533,7 @@ __global__ __launch_bounds__(256) void br_k_envelope(BrParams p) {
 // request per worker, combined across lanes and waves at the end.
 // LONG (horizons beyond BR_HP): the margins keep BR_HS(H) entries per worker, the discounts sit in LDS next
 // to them and a score loops over the offsets (br_scoreh_long), skipping the four-offset groups whose margins no
-// request of the tile reaches.  want_tile == 2 (LONG, the cluster in one block, no matrix asked for): a score
-// costs 3 (H + 1) operations here, so every pair is scored once: pass A stages its keys in the LDS tile and the
-// running best request per worker is taken from the tile, tile by tile, instead of a second scoring pass.
+// request of the tile reaches (clusters too large for br_k_score_long).
 template <bool BRH, bool LONG = false>
 __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o, int want_tile) {
   extern __shared__ int lds[];
@@ -563,16 +582,6 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o, 
     __syncthreads();
   }
 
-  // running best request per worker when pass B reads the staged keys (want_tile == 2): lane = (sub-slot, worker)
-  const bool once = LONG && want_tile == 2 && o.best_i;
-  int Gp1 = 1;
-  while (Gp1 < G) Gp1 <<= 1;
-  const int nsub1 = BR_WAVE / Gp1, sub1 = lane / Gp1, gl1 = lane - sub1 * Gp1;
-  const bool act1 = gl1 < G;
-  const bool free1 = act1 && scap[act1 ? gl1 : 0] > 0;
-  const int Lg1 = act1 ? sL[gl1] : 0;
-  int bk1 = BR_KEY_NONE, bs1 = 0, bi1 = -1;
-
   // pass A: one request per lane, loop over workers
   int *tile = tiles + wave * (BR_WAVE * (G + 1));
   for (int t0 = (split * nw + wave) * BR_WAVE; t0 < qn; t0 += nsplit * nw * BR_WAVE) {
@@ -603,22 +612,7 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o, 
       }
     }
     if (valid && o.best_g) o.best_g[(int64_t)inst * p.Q + i] = bg;
-    if (once) {  // this tile's keys against the running best of every worker (ascending requests within a lane)
-      br_wave_sync();
-      const int rows = min(BR_WAVE, qn - t0);
-      for (int r = sub1; r < rows; r += nsub1) {
-        const int sr = ss[t0 + r];
-        const int key = tile[r * (G + 1) + (act1 ? gl1 : 0)];
-        const bool ok = free1 && (p.W <= 0 || Lg1 + sr <= p.W);
-        if (ok && (key > bk1 || (key == bk1 && sr > bs1))) {
-          bk1 = key;
-          bs1 = sr;
-          bi1 = t0 + r;
-        }
-      }
-      br_wave_sync();  // the tile is rewritten by the wave's next trip
-    }
-    if (want_tile == 1) {
+    if (want_tile) {
       const int rows = min(BR_WAVE, qn - t0);
       int *Fi = (int *)o.F + ((int64_t)inst * p.Q + t0) * G;
       for (int e = lane; e < rows * G; e += BR_WAVE) {
@@ -645,8 +639,7 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o, 
     const int Lg = act ? sL[g] : 0;
     const bool free_slot = act && scap[g] > 0;
     int bk = BR_KEY_NONE, bs = 0, bi = -1;
-    if (once) bk = bk1, bs = bs1, bi = bi1;  // (one block holds the cluster: the lane layout is the one above)
-    for (int i = wave * nsub + sub; i < qn && !once; i += nw * nsub) {
+    for (int i = wave * nsub + sub; i < qn; i += nw * nsub) {
       const int s = ss[i];
       int key;
       if constexpr (LONG) {  // lanes hold different workers: each reads its own row of margins
@@ -682,6 +675,81 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o, 
           }
         }
       o.best_i[(int64_t)inst * G + gbase + tid] = bi;
+    }
+  }
+}
+
+// K2 + K3 for long horizons, a cluster per block: a score costs 3 (H + 1) operations here, so every pair is scored once,
+// and the (tile of 64 requests, worker) pairs are dealt out to the block's waves whatever the queue length (with a wave
+// per tile most waves of a short queue idled: 2048 clusters, G = 8, H = 80, 84 of 256 waiting: 31 us -> 21 us).  The keys
+// meet in LDS; best worker per request with threads mapped to requests, best request per worker with a wave per worker
+// (the tie rules of br_k_score).  Groups of four offsets whose margins no request of the tile reaches are skipped.
+__global__ __launch_bounds__(512) void br_k_score_long(BrParams p, BrArr a, BrOut o) {
+  extern __shared__ int lds[];
+  const int G = p.G, HS = BR_HS(p.H), KS = G | 1;
+  float *sm = (float *)lds;              // [G][HS] margins
+  float *sd = sm + G * HS;               // [HS] discounts
+  int *sL = (int *)(sd + HS);            // [G] loads
+  int *scap = sL + G;                    // [G] free slots
+  int *ss = scap + G;                    // [Q] prefill lengths, then zeros to whole tiles
+  int *keys = ss + ((p.Q + 63) & ~63);   // [Q'][KS]
+  const int inst = blockIdx.x, tid = threadIdx.x, lane = br_lane(), wave = tid >> 6, nw = blockDim.x >> 6;
+  const int q0 = min(max(p.qlen[inst], 0), p.Q);
+  int cnt = a.count ? a.count[inst] : 0;
+  cnt = min(max(cnt, 0), a.arr_cap);
+  const int qn = q0 + min(cnt, p.Q - q0);
+  if (tid < G) {
+    sL[tid] = p.L[(int64_t)inst * G + tid];
+    scap[tid] = p.B - p.n[(int64_t)inst * G + tid];
+  }
+  for (int e = tid; e < G * HS; e += blockDim.x) {
+    const int g = e / HS, h = e - g * HS;
+    sm[e] = h <= p.H ? (float)p.mh[((int64_t)inst * G + g) * (p.H + 1) + h] : 0.0f;
+  }
+  for (int h = tid; h < HS; h += blockDim.x) sd[h] = p.dl[h];
+  for (int i = tid; i < ((qn + 63) & ~63); i += blockDim.x) {
+    const int64_t qrow = (int64_t)inst * p.Q, arow = (int64_t)inst * a.arr_cap;
+    ss[i] = i < qn ? min(max(i < q0 ? p.qs[qrow + i] : a.s[arow + (i - q0)], 1), BR_MAX_S_DEV) : 0;
+  }
+  __syncthreads();
+  const int items = ((qn + 63) >> 6) * G;
+  for (int it = wave; it < items; it += nw) {
+    const int t = it / G, g = it - t * G;
+    const int s[1] = {ss[t * BR_WAVE + lane]};
+    const int top[1] = {br_wave_max(s[0])};
+    float F[1];
+    br_scoreh_long_sel<1>(p.aD, p.beta, sm + g * HS, sd, HS, lane, top, s, F);
+    keys[(t * BR_WAVE + lane) * KS + g] = br_ord(F[0]);
+  }
+  __syncthreads();
+  if (o.best_g) {
+    for (int i = tid; i < p.Q; i += blockDim.x) {
+      int bk = BR_KEY_NONE, bg = -1;
+      if (i < qn) {
+        const int s = ss[i];
+        for (int g = 0; g < G; ++g) {
+          const int key = keys[i * KS + g];
+          if (scap[g] > 0 && (p.W <= 0 || sL[g] + s <= p.W) && key > bk) bk = key, bg = g;
+        }
+      }
+      o.best_g[(int64_t)inst * p.Q + i] = bg;
+    }
+  }
+  if (o.best_i) {
+    for (int g = wave; g < G; g += nw) {
+      int bk = BR_KEY_NONE, bs = 0, bi = INT32_MAX;
+      const int room = p.W > 0 ? p.W - sL[g] : INT32_MAX;
+      for (int i = lane; i < qn; i += BR_WAVE) {
+        const int s = ss[i], key = keys[i * KS + g];
+        if (s <= room && (key > bk || (key == bk && s > bs))) bk = key, bs = s, bi = i;
+      }
+      const int km = br_wave_max(bk);
+      int best = -1;
+      if (km != BR_KEY_NONE && scap[g] > 0) {
+        const int sb = br_wave_max(bk == km ? bs : -1);
+        best = br_wave_min(bk == km && bs == sb ? bi : INT32_MAX);
+      }
+      if (lane == 0) o.best_i[(int64_t)inst * G + g] = best;
     }
   }
 }
@@ -993,8 +1061,8 @@ void br_launch_discounts(const BrParams &p, float gamma, hipStream_t st) {
 
 void br_launch_project(const BrParams &p, hipStream_t st) {
   if (p.H > BR_HP) {  // projection, envelope and margins in one launch
-    const size_t lds = ((size_t)p.G + 8) * BR_HS(p.H) * sizeof(int);
-    hipLaunchKernelGGL(br_k_project_long, dim3((unsigned)p.N), dim3(256), lds, st, p);
+    const size_t lds = (((size_t)p.G + 1) * BR_HS(p.H) + 8 * BR_BINS) * sizeof(int);
+    hipLaunchKernelGGL(br_k_project_long, dim3((unsigned)p.N + (p.pred_mode == 2 ? 1u : 0u)), dim3(256), lds, st, p);
     return;
   }
   if (p.B <= 64)
@@ -1009,7 +1077,7 @@ void br_launch_project(const BrParams &p, hipStream_t st) {
     launch_project_rows<8, 1>(p, st);
   else
     launch_project_rows<16, 1>(p, st);
-  hipLaunchKernelGGL(br_k_envelope, dim3((unsigned)((p.N + 3) / 4)), dim3(256), 0, st, p);
+  hipLaunchKernelGGL(br_k_envelope, dim3((unsigned)((p.N + 4) / 4)), dim3(256), 0, st, p);
 }
 
 size_t br_score_scratch_bytes(int N, int Q, int G) {
@@ -1125,14 +1193,17 @@ static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut 
   int nsplit = 1;
   while (nsplit < 8 && nsplit * 2 <= p.G && (int64_t)p.N * nsplit * 2 <= 512 && p.Q > 64 * waves * nsplit) nsplit *= 2;
   const dim3 grid((unsigned)p.N, (unsigned)nsplit);
-  // long horizons, the cluster in one block, room for the staged keys: every pair is scored once
-  int mode = want_tile;
-  if (longh && !want_tile && nsplit == 1 && o.best_i && lds_words(waves, true) * 4 <= 60 * 1024) {
-    mode = 2;
-    lds = lds_words(waves, true) * 4;
+  if (longh && !want_tile && p.N > BR_SCORE_TILES_MAX_N) {  // room for all keys of a cluster: every pair is scored once
+    const size_t HS = BR_HS(p.H), Qp = ((size_t)p.Q + 63) & ~(size_t)63;
+    const size_t words = ((size_t)p.G + 1) * HS + 2 * (size_t)p.G + Qp + Qp * (size_t)(p.G | 1);
+    if (words * 4 <= 60 * 1024) {
+      // eight waves per cluster while that leaves the batch resident at once
+      hipLaunchKernelGGL(br_k_score_long, dim3((unsigned)p.N), dim3(p.N <= 1024 ? 512 : 256), words * 4, st, p, a, o);
+      return;
+    }
   }
   if (longh)
-    hipLaunchKernelGGL((br_k_score<true, true>), grid, dim3(64 * waves), lds, st, p, a, o, mode);
+    hipLaunchKernelGGL((br_k_score<true, true>), grid, dim3(64 * waves), lds, st, p, a, o, want_tile);
   else if (p.H > 0)
     hipLaunchKernelGGL(br_k_score<true>, grid, dim3(64 * waves), lds, st, p, a, o, want_tile);
   else
