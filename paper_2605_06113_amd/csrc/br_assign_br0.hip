@@ -3,20 +3,15 @@
 #include "br_assign_kernel.h"
 #include "br_score_wave.h"
 
-// The whole round of a cluster with a short queue on one wave, in one launch: first the snapshot
-// reductions (per-request best worker, per-worker best request: K2 + K3), then the two-stage assignment
-// (K4, and the decode step with ADV).  The reductions read the step-start state before the assignment
-// changes it, cost the wave about a tenth more instructions, and save a launch of their own.
+// The whole round of a cluster with a short queue on one wave, in one launch: the snapshot
+// reductions (per-request best worker, per-worker best request: K2 + K3) on the step-start state, then the two-stage
+// assignment on the same sorted list (K4, and the decode step with ADV).
 template <bool ADV>
 __global__ __launch_bounds__(256) void br_k_route4(BrParams p, BrArr a, BrOut o) {
   extern __shared__ int lds_all[];
   constexpr int E = 4;
-  const int w = threadIdx.x >> 6, inst = (int)blockIdx.x * 4 + w;
-  if (inst >= p.N) return;
-  BrScoreIn<E, 0> in;  // loaded once, used by both parts
-  br_score_wave_load<E, 0>(p, a, inst, br_lane(), in);
-  br_score_wave_run<E, 0>(p, o, inst, br_lane(), in);
-  br_assign_body<E, 0, ADV>(p, a, o, lds_all + w * BR_ROUND_WORDS(E, false), inst, 0, &in);
+  const int w = threadIdx.x >> 6;
+  br_assign_body<E, 0, ADV, false, false, true>(p, a, o, lds_all + w * BR_ROUND_WORDS(E, false), (int)blockIdx.x * 4 + w);
 }
 
 void br_launch_route4(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {

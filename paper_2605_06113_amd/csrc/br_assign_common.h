@@ -326,17 +326,10 @@ __device__ __forceinline__ void br_advance_cluster(int inst, int lane, int Lcur,
 // UB: (list, chunk) units requested before the first is used
 template <int E, int UB>
 __device__ __forceinline__ void br_split_helper(const BrParams &p, const BrArr &a, const BrOut &o, int inst, int lane,
-                                                int *split) {
+                                                int *split, int *lst) {
   const bool act = lane < p.G;
-  int n0;
-  if (o.best_g || o.best_i) {
-    BrScoreIn<E, 0> in;
-    br_score_wave_load<E, 0>(p, a, inst, lane, in);
-    br_score_wave_run<E, 0>(p, o, inst, lane, in);
-    n0 = in.n;
-  } else {
-    n0 = act ? p.n[(int64_t)inst * p.G + lane] : p.B;
-  }
+  if (o.best_g || o.best_i) br_score_wave_run<E, 0>(p, a, o, inst, lane, lst);
+  int n0 = act ? p.n[(int64_t)inst * p.G + lane] : p.B;
   n0 = act ? min(max(n0, 0), p.B) : 0;
   int dL = 0, kept = n0;
   br_advance_cluster<UB, false>(inst, lane, 0, n0, 0, 64, &dL, &kept);

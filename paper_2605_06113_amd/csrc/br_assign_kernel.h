@@ -102,17 +102,6 @@ __device__ __forceinline__ void br_bigr_scan(const BrParams &p, const int (&mg)[
 }
 
 
-// Worker state of a round: lane g holds worker g; envelope and totals are uniform.  HB: offsets beyond h = 0 that are
-// carried (0: BR-0, 4: H <= 4, BR_HP); those beyond H repeat offset H, so that a minimum over all of them is one over
-// the horizon (their discount is zero).
-template <int HB>
-struct BrRoundState {
-  static constexpr int NH = HB + 1;
-  int nn, cap;        // requests held, free slots
-  int Lh[NH], Mh[NH]; // projected loads, envelope
-  int S_tot;
-};
-
 // The two stages on one wave.  x: the qn waiting requests as a sorted list.  bound [arrival position]: worker << 16 | slot
 // of the requests admitted (the others keep what is there).  lst, slots, win, hitab: LDS (see BR_ROUND_WORDS).
 // svc (BIGR, shared): mailbox of the block's other three waves, which serve the subset searches.
@@ -163,18 +152,11 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
     br_wave_sync();
   };
 
-  // BR-H: bounds used by the pick.  e = 8e-7 (alpha D + beta D) s_max bounds the distance of a computed score of a single
-  // request from the exact one: at most H + 5 <= 13 roundings, each relative 2^-24 on terms of at most
-  // (alpha D + beta D) Delta.  Offsets h <= ho have beta d_h - alpha D > 2 e: exceeding the margin there alone makes the
-  // score fall by more than rounding can hide, per token.
   float e2 = 0.0f, dscale = 0.0f;
   int ho = -1;
   if constexpr (BRH) {
     dscale = p.aD + p.beta * p.dsum;
-    e2 = 1.6e-6f * dscale * (float)(br_uniform((int)(x[0] >> BR_IDX_BITS)));
-#pragma unroll
-    for (int h = 0; h < NH; ++h) ho = (h <= p.H && p.beta * p.d[h] - p.aD > e2) ? h : ho;  // (d falls with h)
-    ho = br_uniform(ho);
+    br_peak_bounds<HB>(p, br_uniform((int)(x[0] >> BR_IDX_BITS)), e2, ho);
   }
 
   // argmax_i F_g({i}) over the waiting, admissible requests (lowest position on ties) as a list entry; false when none
@@ -734,52 +716,18 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
   rc.wdrop = wdrop;
 }
 
-// Keys of the waiting set, unsorted (E * 64 of them, the set's qn first), straight from the queue and the arrivals: one
-// batch of unconditional loads (addresses by select, an entry beyond the set reads the cluster's first queue word).
-template <int E>
-__device__ __forceinline__ void br_keys_load(const BrParams &p, const BrArr &a, int inst, int q0, int qn, int first, int lane,
-                                             unsigned (&x)[E]) {
-  constexpr int IDX_MASK = (1 << BR_IDX_BITS) - 1;
-  const int64_t qrow = (int64_t)inst * p.Q, arow = (int64_t)inst * a.arr_cap;
-  int v[E];
-#pragma unroll
-  for (int j = 0; j < E; ++j) {
-    const int i = first + j * BR_WAVE + lane;
-    const bool ina = i >= q0 && i < qn;
-    v[j] = *(ina ? a.s + (arow + (i - q0)) : p.qs + (qrow + (i < q0 ? i : 0)));
-  }
-#pragma unroll
-  for (int j = 0; j < E; ++j) {
-    const int i = first + j * BR_WAVE + lane;
-    const int s = min(max(v[j], 1), BR_MAX_S_DEV);
-    x[j] = i < qn ? ((unsigned)s << BR_IDX_BITS) | (unsigned)(IDX_MASK - i) : 0u;
-  }
-}
-
-// The same from lengths that the snapshot reductions of the wave have already loaded (E of EP blocks of 64).
-template <int E, int EP>
-__device__ __forceinline__ void br_keys_from(const int (&s)[EP], int qn, int lane, unsigned (&x)[E]) {
-  constexpr int IDX_MASK = (1 << BR_IDX_BITS) - 1;
-#pragma unroll
-  for (int j = 0; j < E; ++j) {
-    const int i = j * BR_WAVE + lane;
-    x[j] = i < qn ? ((unsigned)s[j] << BR_IDX_BITS) | (unsigned)(IDX_MASK - i) : 0u;
-  }
-}
-
 // One cluster's round on one wave.  EM: the queue holds up to EM * 64 entries; the list is made for 64 or 256 where no
 // more are waiting.  COOP (EM = 32): the block has four waves; all of them sort a long waiting set together
 // (br_sort_desc_block4) and share the epilogue and the decode step, wave 0 runs the round.
-// `pre`: what the snapshot reductions of the same wave have already loaded for this cluster (queue lengths,
-// prefill lengths in arrival order, worker loads and counts), or null: the round then loads them itself.
+// SCORES: the snapshot reductions (best_g / best_i where asked for) are taken on the way (br_score_wave.h).
 // `split`: the cluster's BR_SPLIT_WORDS of LDS in a split kernel (another wave applies the decode steps to the old
 // list entries meanwhile), or null.
 // `shared` (BIGR without COOP, one cluster per block of four waves): waves 1-3 serve the subset searches of wave 0
 // (every fourth trip of a mask scan, every fourth run of 64 words of the rows of reachable sums) through the
 // mailbox `svc` and two block barriers per search.
-template <int EM, int HB, bool ADV, bool COOP = false, bool BIGR = false>
+template <int EM, int HB, bool ADV, bool COOP = false, bool BIGR = false, bool SCORES = false>
 __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a, const BrOut &o, int *lds, int inst,
-                                               int w = 0, const BrScoreIn<EM, HB> *pre = nullptr, int *split = nullptr,
+                                               int w = 0, int *split = nullptr,
                                                bool shared = false) {
   static_assert(!COOP || EM == 32, "the four-wave sort covers 4 x 512 keys");
   static_assert(!ADV || HB == 0, "decode steps ride along with BR-0 rounds only");
@@ -819,36 +767,10 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
     }
   }
   const int G = p.G;
-  // Loads: everything that does not need the queue length is requested before the first result is used, and the
-  // waiting set then comes in one batch of unconditional loads: two memory round trips for the cluster.
-  const bool act = lane < G;
-  const int64_t wrow = (int64_t)inst * G + lane;
-  int q0_raw = 0, cnt_raw = 0, n_raw = p.B, L_raw[NH];
-#pragma unroll
-  for (int h = 0; h < NH; ++h) L_raw[h] = BR_LOW;
-  const int64_t wrow_ld = act ? wrow : (int64_t)inst * G;  // lanes without a worker read worker 0's words (unused)
-  if (!pre) {
-    q0_raw = p.qlen[inst];
-    cnt_raw = a.count ? a.count[inst] : 0;
-    n_raw = p.n[wrow_ld];
-    if constexpr (!BRH) L_raw[0] = p.L[wrow_ld];
-  }
-  if constexpr (BRH) {
-#pragma unroll
-    for (int h = 0; h < NH; ++h) L_raw[h] = p.Lh[wrow_ld * (p.H + 1) + min(h, p.H)];
-  }
-  if (!act) {
-    n_raw = p.B;
-#pragma unroll
-    for (int h = 0; h < NH; ++h) L_raw[h] = BR_LOW;
-  }
-  int q0, cnt;
-  if (pre) {
-    q0 = pre->q0, cnt = pre->cnt;
-  } else {
-    q0 = br_uniform(min(max(q0_raw, 0), p.Q));
-    cnt = br_uniform(min(max(cnt_raw, 0), a.arr_cap));
-  }
+  // two memory round trips for the cluster: these words, then the waiting set
+  BrClusterIn<HB> in;
+  br_cluster_load<HB>(p, a, inst, lane, in);
+  const int q0 = in.q0, cnt = in.cnt;
   const int qn = q0 + min(cnt, p.Q - q0);
 
   // first estimate of a newly admitted request when the library maintains c_hat (age 0)
@@ -859,22 +781,12 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
 
   // ---- worker state, one worker per lane
   BrRoundState<HB> st;
-  st.nn = act ? min(max(pre ? pre->n : n_raw, 0), p.B) : p.B;
-  st.cap = p.B - st.nn;
+  br_round_state<HB>(p, lane, in.n, in.L, st);
   const int nn_start = st.nn;
-  if constexpr (BRH) {
-#pragma unroll
-    for (int h = 0; h < NH; ++h) st.Lh[h] = L_raw[h];
-  } else {
-    st.Lh[0] = act ? (pre ? pre->L : L_raw[0]) : BR_LOW;
-  }
-#pragma unroll
-  for (int h = 0; h < NH; ++h) st.Mh[h] = br_wave_max(st.Lh[h]);
-  st.S_tot = br_wave_sum(st.cap);
 
   BrRoundCounts rc = {};
   if (o.stats) {  // sum of loads in two 16-bit halves (each partial sum fits int32 for loads below 2^25)
-    const int L0 = act ? st.Lh[0] : 0;
+    const int L0 = lane < G ? st.Lh[0] : 0;
     rc.I_before = (long long)G * st.Mh[0] - (((long long)br_wave_sum(L0 >> 16) << 16) + br_wave_sum(L0 & 0xffff));
   }
 
@@ -899,6 +811,9 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
     for (int j = 0; j < EM; ++j)
       if (j * BR_WAVE < qn) bound[j * BR_WAVE + lane] = -1;
   }
+  if constexpr (SCORES) {
+    if (!run) br_snapshot_none(p, o, inst, lane);
+  }
   if (run && lead) {
     auto with = [&](auto e) {
       constexpr int E = decltype(e)::value;
@@ -906,11 +821,7 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
       if constexpr (COOP && E == 32) {
         br_list_load<32>(x, lst, lane, 0, qn);
       } else {
-        if (pre)
-          br_keys_from<E, EM>(pre->s, qn, lane, x);
-        else
-          br_keys_load<E>(p, a, inst, q0, qn, 0, lane, x);
-        br_list_sort<E>(x, lane);
+        br_list_build<E, HB, SCORES>(p, a, o, inst, lane, q0, qn, lst, st, x);
       }
       br_wave_sync();
       br_round<E, HB, BIGR>(p, inst, lane, qn, x, bound, lst, slots, win, hitab, svc, dprows, shared, st, rc);
@@ -966,7 +877,7 @@ __global__ __launch_bounds__(256, (HB > 0 && E == 8 && !BIGR) ? 4 : 1) void br_k
   if constexpr (E == 32)  // one cluster per block, four waves for the sort
     br_assign_body<E, HB, ADV, true, BIGR>(p, a, o, lds_all, (int)blockIdx.x, w);
   else if (BIGR && share)
-    br_assign_body<E, HB, ADV, false, BIGR>(p, a, o, lds_all, (int)blockIdx.x, w, nullptr, nullptr, true);
+    br_assign_body<E, HB, ADV, false, BIGR>(p, a, o, lds_all, (int)blockIdx.x, w, nullptr, true);
   else
     br_assign_body<E, HB, ADV, false, BIGR>(p, a, o, lds_all + w * WORDS, (int)(blockIdx.x * (blockDim.x >> 6)) + w);
 }

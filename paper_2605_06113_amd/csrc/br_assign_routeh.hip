@@ -7,12 +7,8 @@
 template <int E, int HB>
 __global__ __launch_bounds__(256, E == 8 ? 4 : 1) void br_k_route_h(BrParams p, BrArr a, BrOut o) {
   extern __shared__ int lds_all[];
-  const int w = threadIdx.x >> 6, inst = (int)blockIdx.x * 4 + w;
-  if (inst >= p.N) return;
-  BrScoreIn<E, HB> in;  // queue lengths, prefill lengths and counts are loaded once, for both parts
-  br_score_wave_load<E, HB>(p, a, inst, br_lane(), in);
-  br_score_wave_run<E, HB>(p, o, inst, br_lane(), in);
-  br_assign_body<E, HB, false>(p, a, o, lds_all + w * BR_ROUND_WORDS(E, false), inst, 0, &in);
+  const int w = threadIdx.x >> 6;
+  br_assign_body<E, HB, false, false, false, true>(p, a, o, lds_all + w * BR_ROUND_WORDS(E, false), (int)blockIdx.x * 4 + w);
 }
 
 template <int E, int HB>

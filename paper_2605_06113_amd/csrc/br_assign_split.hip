@@ -11,6 +11,7 @@ template <int E, int RPB, int NH>
 __global__ __launch_bounds__((RPB + NH) * BR_WAVE) void br_k_route_split(BrParams p, BrArr a, BrOut o) {
   extern __shared__ int lds_all[];
   constexpr int WORDS = BR_ROUND_WORDS(E, false) + BR_SPLIT_WORDS;
+  constexpr int HELP = BR_LIST_WORDS(E);  // the helper's list (snapshot reductions), after the clusters' areas
   constexpr int SPLIT_AT = WORDS - BR_SPLIT_WORDS;
   const int w = threadIdx.x >> 6, lane = br_lane();
   const int first = (int)blockIdx.x * RPB;
@@ -20,19 +21,19 @@ __global__ __launch_bounds__((RPB + NH) * BR_WAVE) void br_k_route_split(BrParam
     const int inst = first + w;
     if (inst >= p.N) return;
     int *lds = lds_all + w * WORDS;
-    br_assign_body<E, 0, false>(p, a, o, lds, inst, 0, nullptr, lds + SPLIT_AT);
+    br_assign_body<E, 0, false>(p, a, o, lds, inst, 0, lds + SPLIT_AT);
   } else {
     for (int c = w - RPB; c < RPB; c += NH) {  // helper h takes clusters h, h + NH, ...
       const int inst = first + c;
       if (inst >= p.N) break;
-      br_split_helper<E, 8>(p, a, o, inst, lane, lds_all + c * WORDS + SPLIT_AT);
+      br_split_helper<E, 8>(p, a, o, inst, lane, lds_all + c * WORDS + SPLIT_AT, lds_all + RPB * WORDS + (w - RPB) * HELP);
     }
   }
 }
 
 template <int E, int RPB, int NH>
 static void launch_split(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
-  const size_t lds = (size_t)RPB * (BR_ROUND_WORDS(E, false) + BR_SPLIT_WORDS) * sizeof(int);
+  const size_t lds = ((size_t)RPB * (BR_ROUND_WORDS(E, false) + BR_SPLIT_WORDS) + (size_t)NH * BR_LIST_WORDS(E)) * sizeof(int);
   const dim3 grid((unsigned)((p.N + RPB - 1) / RPB)), block((RPB + NH) * BR_WAVE);
   hipLaunchKernelGGL((br_k_route_split<E, RPB, NH>), grid, block, lds, st, p, a, o);
 }

@@ -969,14 +969,12 @@ __global__ __launch_bounds__(256) void br_k_score_combine(BrParams p, BrOut o, c
 }
 
 // K2 + K3, one wave per cluster (br_score_wave.h)
-template <int E, int HB>
+template <int EM, int HB>
 __global__ __launch_bounds__(256) void br_k_score_wave(BrParams p, BrArr a, BrOut o) {
-  const int inst = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
+  extern __shared__ int lds[];
+  const int w = threadIdx.x >> 6, inst = (int)(blockIdx.x * (blockDim.x >> 6)) + w;
   if (inst >= p.N) return;
-  const int lane = br_lane();
-  BrScoreIn<E, HB> in;
-  br_score_wave_load<E, HB>(p, a, inst, lane, in);
-  br_score_wave_run<E, HB>(p, o, inst, lane, in);
+  br_score_wave_run<EM, HB>(p, a, o, inst, br_lane(), lds + w * BR_LIST_WORDS(EM));
 }
 
 // ------------------------------------------------------------------ launchers
@@ -1142,6 +1140,18 @@ void br_launch_score(const BrParams &p, const BrArr &a, const BrOut &o, int *par
   br_launch_reductions(p, a, o, partials, st);
 }
 
+template <int HB>
+static void launch_score_wave(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
+  const int wpb = p.N >= 1024 ? 4 : 1;  // small batches spread over the CUs
+  const dim3 grid((unsigned)((p.N + wpb - 1) / wpb)), block(BR_WAVE * wpb);
+  if (p.Q <= 256)
+    hipLaunchKernelGGL((br_k_score_wave<4, HB>), grid, block, wpb * BR_LIST_WORDS(4) * sizeof(int), st, p, a, o);
+  else if (p.Q <= 512)
+    hipLaunchKernelGGL((br_k_score_wave<8, HB>), grid, block, wpb * BR_LIST_WORDS(8) * sizeof(int), st, p, a, o);
+  else
+    hipLaunchKernelGGL((br_k_score_wave<16, HB>), grid, block, wpb * BR_LIST_WORDS(16) * sizeof(int), st, p, a, o);
+}
+
 static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut &o, int *partials, hipStream_t st) {
   int waves = (p.Q + 63) / 64;  // one wave per tile of 64 requests, at most 8 waves
   waves = waves < 1 ? 1 : (waves > 8 ? 8 : waves);
@@ -1150,7 +1160,7 @@ static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut 
   {  // few clusters, long queues, no matrix: a wave per (tile of requests, group of workers), then a combine
     const int T = (p.Q + BR_WAVE - 1) / BR_WAVE;
     const int wpg = (p.G + BR_TILE_GROUPS - 1) / BR_TILE_GROUPS, WGN = (p.G + wpg - 1) / wpg;  // at most 4 groups
-    if (partials && !want_tile && p.N <= BR_SCORE_TILES_MAX_N && T * WGN >= 8) {
+    if (partials && !want_tile && p.N <= BR_SCORE_TILES_MAX_N && T * WGN >= 8 && !(p.H == 0 && p.Q <= 512)) {
       const dim3 grid((unsigned)T, (unsigned)WGN, (unsigned)p.N), block(BR_WAVE);
       const int HS = longh ? BR_HS(p.H) : BR_HP + 1;
       const size_t lds = ((size_t)BR_TILE_WORKERS * HS + (longh ? HS + 4 : 0) + 2 * BR_TILE_WORKERS) * sizeof(int);
@@ -1166,19 +1176,14 @@ static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut 
       return;
     }
   }
-  if (!longh && !want_tile && p.Q <= 512 && p.N >= BR_SCORE_WAVE_MIN_N) {  // many small clusters: one wave each
-    const dim3 grid((unsigned)((p.N + 3) / 4)), block(256);
-    if (p.H > 0) {
-      if (p.Q <= 256)
-        hipLaunchKernelGGL((br_k_score_wave<4, BR_HP>), grid, block, 0, st, p, a, o);
-      else
-        hipLaunchKernelGGL((br_k_score_wave<8, BR_HP>), grid, block, 0, st, p, a, o);
-    } else {
-      if (p.Q <= 256)
-        hipLaunchKernelGGL((br_k_score_wave<4, 0>), grid, block, 0, st, p, a, o);
-      else
-        hipLaunchKernelGGL((br_k_score_wave<8, 0>), grid, block, 0, st, p, a, o);
-    }
+  // Queues of up to 1024: one wave per cluster.
+  if (!longh && !want_tile && p.Q <= 1024) {
+    if (p.H == 0)
+      launch_score_wave<0>(p, a, o, st);
+    else if (p.H <= BR_HP / 2)
+      launch_score_wave<BR_HP / 2>(p, a, o, st);
+    else
+      launch_score_wave<BR_HP>(p, a, o, st);
     return;
   }
   auto lds_words = [&](int w, bool tile) {

@@ -1,138 +1,288 @@
-// K2 + K3 for large batches of small clusters: one wavefront per cluster, no LDS and no barrier.
-// Lane g holds worker g (margins of eq. (br0-Fscore) / eq. (brh-Fscore)); each lane holds E waiting
-// requests in arrival order.  For every worker (margins broadcast by readlane) all requests are
-// scored once; the same score feeds the running best worker of each request (ties: lowest g) and
-// the best request of this worker (ties: larger s, then earlier arrival), the latter finished by two
-// wave reductions.  Results equal br_k_score's; the score matrix itself is not written here.
-// Split in two so that a caller can have the inputs of several clusters in registers before it scores.
+// K2 + K3 on one wavefront per cluster: the snapshot reductions best_g (best worker of each waiting request) and best_i
+// (best request of each worker), without scoring every pair where the scores' shape decides.
+//
+// best_g, lanes = requests in arrival order.  BR-0: eq. (br0-Fscore) does not fall with the margin, and every worker
+// whose margin the request does not exceed gives it the same score, its length.  So the best worker is the one of lowest
+// index among the eligible workers with L_g <= M - s, and if there is none the lightest eligible one (lowest index on
+// ties): two instructions per (worker, register) instead of a score.  BR-H: every pair is scored.
+// best_i, lanes = workers: over the sorted list (br_list.h, copied to LDS) each worker finds the neighbours of its
+// smallest margin by binary search and compares their two scores, all workers side by side (why those two: see pick in
+// br_assign_kernel.h); where the peak of eq. (brh-Fscore) may be elsewhere the worker's requests are all scored.
+// The round of the same wave goes on with the sorted list.
+// 4096 clusters, G = 32, H = 4: merged launch 151 -> 135 us; 1531 clusters, G = 13, queues of 307, BR-0: 17.7 -> 8.8 us
+// (a block per cluster that scored all pairs twice).
 #pragma once
 
 #include "br_device.h"
+#include "br_list.h"
 
-// HB: offsets beyond h = 0 that are carried (0: BR-0, 4: H <= 4, BR_HP).
-template <int E, int HB>
-struct BrScoreIn {
+// Worker state of a round: lane g holds worker g; envelope and totals are uniform.  HB: offsets beyond h = 0 that are
+// carried (0: BR-0, 4: H <= 4, BR_HP); those beyond H repeat offset H, so that a minimum over all of them is one over
+// the horizon (their discount is zero).
+template <int HB>
+struct BrRoundState {
   static constexpr int NH = HB + 1;
-  int qn, q0, cnt, L, cap, n;  // queue length with and without this round's arrivals, arrivals taken; lane g: load,
-                               // free slots and request count of worker g as stored
-  int m[NH];  // BR-H: margins of the step-start projection; BR-0: filled by br_score_wave_run
-  int s[E];
+  int nn, cap;        // requests held, free slots
+  int Lh[NH], Mh[NH]; // projected loads, envelope
+  int S_tot;
 };
 
+// BR-H: bounds used where only the neighbours of the smallest margin are scored.  e = 8e-7 (alpha D + beta D) s_max bounds
+// the distance of a computed score of a single request from the exact one: at most H + 5 <= 13 roundings, each relative
+// 2^-24 on terms of at most (alpha D + beta D) Delta.  Offsets h <= ho have beta d_h - alpha D > 2 e: exceeding the margin
+// there alone makes the score fall by more than rounding can hide, per token.
+template <int HB>
+__device__ __forceinline__ void br_peak_bounds(const BrParams &p, int s_max, float &e2, int &ho) {
+  e2 = 1.6e-6f * (p.aD + p.beta * p.dsum) * (float)s_max;
+  ho = -1;
+#pragma unroll
+  for (int h = 0; h <= HB; ++h) ho = (h <= p.H && p.beta * p.d[h] - p.aD > e2) ? h : ho;  // (d falls with h)
+  ho = br_uniform(ho);
+}
+
+// x: keys in arrival order (position j * 64 + lane)
 template <int E, int HB>
-__device__ __forceinline__ void br_score_wave_load(const BrParams &p, const BrArr &a, int inst, int lane,
-                                                   BrScoreIn<E, HB> &in) {
-  // every load that does not need the queue length is requested before the first result is used, and the waiting
-  // set comes in one batch of unconditional loads (addresses chosen by select, an entry beyond the set reads the
-  // cluster's first queue word): two memory round trips for the whole cluster
-  constexpr bool BRH = HB > 0;
-  const int q0_raw = p.qlen[inst];
-  const int cnt_raw = a.count ? a.count[inst] : 0;
-  const int64_t qrow = (int64_t)inst * p.Q, arow = (int64_t)inst * a.arr_cap;
-  const bool act = lane < p.G;
-  const int64_t wrow = (int64_t)inst * p.G + lane;
-  const int64_t wrow_ld = act ? wrow : (int64_t)inst * p.G;  // lanes without a worker read worker 0's words (unused)
-  const int L_raw = p.L[wrow_ld], n_raw = p.n[wrow_ld];
-  int m_raw[BrScoreIn<E, HB>::NH];
-  if constexpr (BRH) {
+__device__ __forceinline__ void br_snapshot_best_g(const BrParams &p, const BrOut &o, int inst, int lane, int qn,
+                                                   const unsigned (&x)[E], const BrRoundState<HB> &st) {
+  const int G = p.G;
+  const int64_t qrow = (int64_t)inst * p.Q;
+  int bg[E];
 #pragma unroll
-    for (int h = 0; h < BrScoreIn<E, HB>::NH; ++h) m_raw[h] = p.mh[wrow_ld * (p.H + 1) + min(h, p.H)];
-  }
-  in.L = act ? L_raw : BR_LOW;
-  in.n = act ? n_raw : p.B;
-  in.cap = act ? p.B - in.n : 0;
-  if constexpr (BRH) {
+  for (int j = 0; j < E; ++j) bg[j] = -1;
+  const unsigned long long freem = br_ballot(lane < G && st.cap > 0);
+  if constexpr (HB == 0) {
+    const int Lmin = br_wave_min((freem >> lane) & 1ull ? st.Lh[0] : INT32_MAX);
+    if (freem != 0ull) {
+      const int glight = (int)__builtin_ctzll(br_ballot(((freem >> lane) & 1ull) && st.Lh[0] == Lmin));
+      int thr[E];  // eligible and safe below it (the watermark bounds both)
 #pragma unroll
-    for (int h = 0; h < BrScoreIn<E, HB>::NH; ++h) in.m[h] = (act && h <= p.H) ? m_raw[h] : 0;
+      for (int j = 0; j < E; ++j) {
+        const int s = (int)(x[j] >> BR_IDX_BITS);
+        thr[j] = st.Mh[0] - s;
+        if (p.W > 0) thr[j] = min(thr[j], p.W - s);
+        bg[j] = p.W <= 0 || Lmin + s <= p.W ? glight : -1;
+      }
+      for (unsigned long long m = freem; m != 0ull;) {  // from the highest index down: the lowest one stays
+        const int g = 63 - (int)__builtin_clzll(m);
+        m &= ~(1ull << g);
+        const int Lg = __builtin_amdgcn_readlane(st.Lh[0], g);
+#pragma unroll
+        for (int j = 0; j < E; ++j) bg[j] = Lg <= thr[j] ? g : bg[j];
+      }
+    }
   } else {
-    in.m[0] = 0;
+    int bk[E];
+#pragma unroll
+    for (int j = 0; j < E; ++j) bk[j] = BR_KEY_NONE;
+    for (unsigned long long m = freem; m != 0ull; m &= m - 1ull) {
+      const int g = (int)__builtin_ctzll(m);
+      int mg[HB + 1];
+#pragma unroll
+      for (int h = 0; h <= HB; ++h) mg[h] = max(st.Mh[h] - __builtin_amdgcn_readlane(st.Lh[h], g), 0);
+      const int room = p.W > 0 ? p.W - __builtin_amdgcn_readlane(st.Lh[0], g) : INT32_MAX;
+#pragma unroll
+      for (int j = 0; j < E; ++j) {
+        if (E > 4 && j * BR_WAVE >= qn) continue;
+        const int s = (int)(x[j] >> BR_IDX_BITS);
+        const int k = br_ord(br_scoreh(p, mg, s));
+        const bool better = s <= room && k > bk[j];
+        bk[j] = better ? k : bk[j];
+        bg[j] = better ? g : bg[j];
+      }
+    }
   }
-  const int q0 = br_uniform(min(max(q0_raw, 0), p.Q));
-  const int cnt = br_uniform(min(max(cnt_raw, 0), a.arr_cap));
-  in.qn = q0 + min(cnt, p.Q - q0);
-  in.q0 = q0;
-  in.cnt = cnt;
+#pragma unroll
+  for (int j = 0; j < E; ++j) {
+    const int i = j * BR_WAVE + lane;
+    if (i < p.Q) o.best_g[qrow + i] = i < qn ? bg[j] : -1;
+  }
+  for (int i = E * BR_WAVE + lane; i < p.Q; i += BR_WAVE) o.best_g[qrow + i] = -1;
+}
+
+// first position of the LDS list (n entries) whose key lies below T
+template <int E>
+__device__ __forceinline__ int br_list_first_below(const int *lst, int n, unsigned T) {
+  int b = 0;
+#pragma unroll
+  for (int step = E * BR_WAVE; step > 0; step >>= 1) {
+    const int q = b + step;
+    const unsigned e = (unsigned)lst[br_list_at<E>(min(q, n) - 1)];
+    b = q <= n && e >= T ? q : b;
+  }
+  return b;
+}
+
+// x: the sorted list, lst: its LDS copy; qn >= 1
+template <int E, int HB>
+__device__ __forceinline__ void br_snapshot_best_i(const BrParams &p, const BrOut &o, int inst, int lane, int qn,
+                                                   const unsigned (&x)[E], const int *lst, const BrRoundState<HB> &st) {
+  constexpr int IDX_MASK = (1 << BR_IDX_BITS) - 1;
+  const int G = p.G;
+  const bool act = lane < G && st.cap > 0;
+  const int room = p.W > 0 ? p.W - st.Lh[0] : INT32_MAX;
+  const int room1 = min(room, BR_MAX_S_DEV) + 1;  // lengths below it are admissible
+  int m[HB + 1], mn;
+#pragma unroll
+  for (int h = 0; h <= HB; ++h) m[h] = max(st.Mh[h] - st.Lh[h], 0);
+  mn = m[0];
+#pragma unroll
+  for (int h = 1; h <= HB; ++h) mn = min(mn, m[h]);
+  bool two = true;
+  if constexpr (HB > 0) {
+    float e2;
+    int ho;
+    br_peak_bounds<HB>(p, br_uniform((int)(x[0] >> BR_IDX_BITS)), e2, ho);
+    int mo = INT32_MAX;
+#pragma unroll
+    for (int h = 0; h <= HB; ++h) mo = h <= ho ? min(mo, m[h]) : mo;
+    two = mo == mn;
+  } else {
+    if (G == 1) mn = BR_MAX_S_DEV + 1;  // every score is zero: the first admissible entry
+  }
+  const unsigned T = (unsigned)max(min(mn, room1), 1) << BR_IDX_BITS;
+  const int b = br_list_first_below<E>(lst, qn, T);
+  const unsigned lo = b < qn ? (unsigned)lst[br_list_at<E>(b)] : 0u;
+  unsigned hi = b > 0 ? (unsigned)lst[br_list_at<E>(b - 1)] : 0u;
+  const int sh = (int)(hi >> BR_IDX_BITS), sl = (int)(lo >> BR_IDX_BITS);
+  if (sh >= room1) hi = 0u;
+  int kh, kl;
+  if constexpr (HB > 0) {
+    kh = br_ord(br_scoreh(p, m, sh)), kl = br_ord(br_scoreh(p, m, sl));
+  } else {
+    kh = sh - G * max(sh - mn, 0), kl = sl;
+  }
+  const bool useh = hi != 0u && (lo == 0u || kh >= kl);
+  unsigned key = lo;
+  if (br_ballot(useh && act) != 0ull) {  // the first of its length
+    const int b2 = br_list_first_below<E>(lst, qn, (unsigned)(sh + 1) << BR_IDX_BITS);
+    if (useh) key = (unsigned)lst[br_list_at<E>(min(b2, qn - 1))];
+  }
+  if constexpr (HB > 0) {
+    for (unsigned long long bad = br_ballot(act && !two); bad != 0ull; bad &= bad - 1ull) {
+      const int g = (int)__builtin_ctzll(bad);
+      int mg[HB + 1];
+#pragma unroll
+      for (int h = 0; h <= HB; ++h) mg[h] = __builtin_amdgcn_readlane(m[h], g);
+      const unsigned Tr = (unsigned)max(__builtin_amdgcn_readlane(room1, g), 1) << BR_IDX_BITS;
+      int bk = BR_KEY_NONE;
+      unsigned bx = 0u;
+#pragma unroll
+      for (int j = 0; j < E; ++j) {  // positions rise with j and with the lane: the first best stays
+        const int k = br_ord(br_scoreh(p, mg, (int)(x[j] >> BR_IDX_BITS)));
+        if (x[j] != 0u && x[j] < Tr && k > bk) bk = k, bx = x[j];
+      }
+      const int km = br_wave_max(bk);
+      const unsigned best = km == BR_KEY_NONE ? 0u
+                                              : (unsigned)__builtin_amdgcn_readlane((int)bx, (int)__builtin_ctzll(br_ballot(bk == km)));
+      key = lane == g ? best : key;
+    }
+  }
+  if (lane < G) o.best_i[(int64_t)inst * G + lane] = act && key != 0u ? IDX_MASK - (int)(key & IDX_MASK) : -1;
+}
+
+// nothing waits or no worker has a free slot
+__device__ __forceinline__ void br_snapshot_none(const BrParams &p, const BrOut &o, int inst, int lane) {
+  if (o.best_g)
+    for (int i = lane; i < p.Q; i += BR_WAVE) o.best_g[(int64_t)inst * p.Q + i] = -1;
+  if (o.best_i && lane < p.G) o.best_i[(int64_t)inst * p.G + lane] = -1;
+}
+
+// Worker state of a cluster (step-start loads or projections), envelope and totals; lanes beyond G hold no worker.
+template <int HB>
+__device__ __forceinline__ void br_round_state(const BrParams &p, int lane, int n_raw, const int (&L_raw)[HB + 1],
+                                               BrRoundState<HB> &st) {
+  const bool act = lane < p.G;
+  st.nn = act ? min(max(n_raw, 0), p.B) : p.B;
+  st.cap = p.B - st.nn;
+#pragma unroll
+  for (int h = 0; h <= HB; ++h) st.Lh[h] = act ? L_raw[h] : BR_LOW;
+#pragma unroll
+  for (int h = 0; h <= HB; ++h) st.Mh[h] = br_wave_max(st.Lh[h]);
+  st.S_tot = br_wave_sum(st.cap);
+}
+
+// Loads of a cluster's worker words and queue lengths: everything that does not need the queue length, requested before
+// the first result is used (lanes without a worker read worker 0's words).
+template <int HB>
+struct BrClusterIn {
+  int q0, cnt, n, L[HB + 1];
+};
+template <int HB>
+__device__ __forceinline__ void br_cluster_load(const BrParams &p, const BrArr &a, int inst, int lane, BrClusterIn<HB> &in) {
+  const int64_t wrow = (int64_t)inst * p.G + (lane < p.G ? lane : 0);
+  const int q0 = p.qlen[inst], cnt = a.count ? a.count[inst] : 0;
+  in.n = p.n[wrow];
+  if constexpr (HB == 0) {
+    in.L[0] = p.L[wrow];
+  } else {
+#pragma unroll
+    for (int h = 0; h <= HB; ++h) in.L[h] = p.Lh[wrow * (p.H + 1) + min(h, p.H)];
+  }
+  in.q0 = br_uniform(min(max(q0, 0), p.Q));
+  in.cnt = br_uniform(min(max(cnt, 0), a.arr_cap));
+}
+
+// Keys of the waiting set in arrival order (E * 64 of them from position `first` on, the set's qn first), straight from
+// the queue and the arrivals: one batch of unconditional loads (addresses by select, an entry beyond the set reads the
+// cluster's first queue word).
+template <int E>
+__device__ __forceinline__ void br_keys_load(const BrParams &p, const BrArr &a, int inst, int q0, int qn, int first, int lane,
+                                             unsigned (&x)[E]) {
+  constexpr int IDX_MASK = (1 << BR_IDX_BITS) - 1;
+  const int64_t qrow = (int64_t)inst * p.Q, arow = (int64_t)inst * a.arr_cap;
   int v[E];
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int i = e * BR_WAVE + lane;
-    const bool ina = i >= q0 && i < in.qn;
-    const int32_t *src = ina ? a.s + (arow + (i - q0)) : p.qs + (qrow + (i < q0 ? i : 0));
-    v[e] = *src;
+  for (int j = 0; j < E; ++j) {
+    const int i = first + j * BR_WAVE + lane;
+    const bool ina = i >= q0 && i < qn;
+    v[j] = *(ina ? a.s + (arow + (i - q0)) : p.qs + (qrow + (i < q0 ? i : 0)));
   }
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int i = e * BR_WAVE + lane;
-    in.s[e] = i < in.qn ? min(max(v[e], 1), BR_MAX_S_DEV) : 1;
+  for (int j = 0; j < E; ++j) {
+    const int i = first + j * BR_WAVE + lane;
+    const int s = min(max(v[j], 1), BR_MAX_S_DEV);
+    x[j] = i < qn ? ((unsigned)s << BR_IDX_BITS) | (unsigned)(IDX_MASK - i) : 0u;
   }
 }
 
-template <int E, int HB>
-__device__ __forceinline__ void br_score_wave_run(const BrParams &p, const BrOut &o, int inst, int lane,
-                                                  const BrScoreIn<E, HB> &in) {
-  constexpr bool BRH = HB > 0;
-  constexpr int NH = BrScoreIn<E, HB>::NH;
-  constexpr int IDX_MASK = (1 << BR_IDX_BITS) - 1;
-  const int G = p.G, qn = in.qn;
-  const bool act = lane < G;
-  const int64_t qrow = (int64_t)inst * p.Q, wrow = (int64_t)inst * G + lane;
-  const int L = in.L, cap = in.cap;
-  int m[NH];
-#pragma unroll
-  for (int h = 0; h < NH; ++h) m[h] = in.m[h];
-  if constexpr (!BRH) m[0] = br_wave_max(L) - L;  // M(k) = max_g L_g, m_g = M - L_g
-
-  int s[E], sec[E], bk[E], bg[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int i = e * BR_WAVE + lane;
-    s[e] = in.s[e];
-    sec[e] = i < qn ? ((s[e] << BR_IDX_BITS) | (IDX_MASK - i)) : -1;  // larger s first, then earlier arrival
-    bk[e] = BR_KEY_NONE;
-    bg[e] = -1;
+// The list of a cluster of qn >= 1 requests, sorted (and copied to `lst` where `copy` or best_i asks for it), with the
+// snapshot reductions on the way if they are asked for.
+template <int E, int HB, bool SCORES>
+__device__ __forceinline__ void br_list_build(const BrParams &p, const BrArr &a, const BrOut &o, int inst, int lane, int q0,
+                                              int qn, int *lst, const BrRoundState<HB> &st, unsigned (&x)[E]) {
+  br_keys_load<E>(p, a, inst, q0, qn, 0, lane, x);
+  if constexpr (SCORES) {
+    if (o.best_g) br_snapshot_best_g<E, HB>(p, o, inst, lane, qn, x, st);
   }
-
-  int bi_mine = -1;  // lane g: best request of worker g
-  for (int g = 0; g < G; ++g) {
-    int mg[NH];
-#pragma unroll
-    for (int h = 0; h < NH; ++h) mg[h] = __builtin_amdgcn_readlane(m[h], g);
-    const int Lg = __builtin_amdgcn_readlane(L, g);
-    const bool free_slot = __builtin_amdgcn_readlane(cap, g) > 0;
-    int bi = -1;
-    if (free_slot) {
-      const int room = p.W > 0 ? p.W - Lg : INT32_MAX;
-      int kk[E], lmax = BR_KEY_NONE;
-#pragma unroll
-      for (int e = 0; e < E; ++e) {  // straight-line selects; lanes without a request carry sec = -1
-        if (E > 4 && e * BR_WAVE >= qn) {  // wide layouts: skip the registers beyond the queue
-          kk[e] = BR_KEY_NONE;
-          continue;
-        }
-        const int key = br_score_key<BRH>(p, mg, s[e]);
-        kk[e] = ((sec[e] >= 0) & (s[e] <= room)) ? key : BR_KEY_NONE;
-        const bool newg = kk[e] > bk[e];
-        bk[e] = newg ? kk[e] : bk[e];
-        bg[e] = newg ? g : bg[e];
-        lmax = max(lmax, kk[e]);
-      }
-      const int km = br_wave_max(lmax);
-      if (km != BR_KEY_NONE) {  // among the requests that reach the best score: larger s, then earlier arrival
-        int w2 = -1;
-#pragma unroll
-        for (int e = 0; e < E; ++e) w2 = max(w2, kk[e] == km ? sec[e] : -1);
-        bi = IDX_MASK - (br_wave_max(w2) & IDX_MASK);
-      }
-    }
-    bi_mine = lane == g ? bi : bi_mine;
-  }
-
-  if (o.best_g) {
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int i = e * BR_WAVE + lane;
-      if (i < p.Q) o.best_g[qrow + i] = i < qn ? bg[e] : -1;
+  br_list_sort<E>(x, lane);
+  if constexpr (SCORES) {
+    if (o.best_i) {
+      br_list_store<E>(x, lst, lane);
+      br_wave_sync();
+      br_snapshot_best_i<E, HB>(p, o, inst, lane, qn, x, lst, st);
+      br_wave_sync();
     }
   }
-  if (o.best_i && act) o.best_i[wrow] = bi_mine;
+}
+
+// The snapshot reductions of one cluster alone, on one wave; `lst`: BR_LIST_WORDS(EM) words of LDS.
+template <int EM, int HB>
+__device__ __forceinline__ void br_score_wave_run(const BrParams &p, const BrArr &a, const BrOut &o, int inst, int lane, int *lst) {
+  BrClusterIn<HB> in;
+  br_cluster_load<HB>(p, a, inst, lane, in);
+  BrRoundState<HB> st;
+  br_round_state<HB>(p, lane, in.n, in.L, st);
+  const int qn = in.q0 + min(in.cnt, p.Q - in.q0);
+  if (st.S_tot == 0 || qn == 0) {
+    br_snapshot_none(p, o, inst, lane);
+  } else if (qn <= BR_WAVE) {
+    unsigned x[1];
+    br_list_build<1, HB, true>(p, a, o, inst, lane, in.q0, qn, lst, st, x);
+  } else if (EM == 4 || qn <= 4 * BR_WAVE) {
+    unsigned x[4];
+    br_list_build<4, HB, true>(p, a, o, inst, lane, in.q0, qn, lst, st, x);
+  } else if constexpr (EM > 4) {
+    unsigned x[EM];
+    br_list_build<EM, HB, true>(p, a, o, inst, lane, in.q0, qn, lst, st, x);
+  }
 }
