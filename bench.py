@@ -639,8 +639,8 @@ def main():
     st_a = stats[:, binding.ST["admitted"]].astype(np.float64)
     ops_assign = 4.0 * float((st_a * st_q - st_a * (st_a - 1) / 2).sum())
     counters = profile_counters()
-    kname = {(True, "assign"): "br_k_route4<true>", (False, "assign"): "br_k_route4<false>",
-             (True, "advance"): "br_k_advance<1,2,false>", (False, "advance"): "br_k_advance<1,2,false>"}
+    kname = {(True, "assign"): "br_k_route<4, true>", (False, "assign"): "br_k_route<4, false>",
+             (True, "advance"): "br_k_advance_seg<64, 2, 0>", (False, "advance"): "br_k_advance_seg<64, 2, 0>"}
 
     def kernel_table(kern, fused):
         tab = {}
@@ -654,7 +654,7 @@ def main():
             elif k == "score":
                 nb = bytes_score + qn * 4 + N * G * 8
             elif k == "assign":
-                # on this workload the snapshot reductions ride in the round's launch (br_k_route4); the fused
+                # on this workload the snapshot reductions ride in the round's launch (br_k_route<4>); the fused
                 # launch also applies the decode step
                 nb = bytes_assign + bytes_score + (bytes_advance if fused else 0)
                 ops = ops_assign + 4.0 * pairs_per_step

@@ -314,30 +314,26 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
   p.adv_t = split_adv ? 0 : adv_t;
   int32_t rc = BR_OK;
   if (p.H > 0) rc = enqueue(ctx, BR_K_PROJECT, [&] { br_launch_project(p, ctx->st); }, br);
-  // large batches of clusters with short queues: the reductions ride along in the assignment launch
-  const bool together = (o.best_g || o.best_i) && !o.F && p.N >= BR_SCORE_WAVE_MIN_N && p.R_max <= 8 &&
-                        (p.H == 0 ? p.Q <= 256 : (p.H <= BR_HP && p.Q <= 512));
-  // BR-0 with decode steps: round and decode steps on two waves per cluster; the reductions ride on the helper wave
-  // unless the matrix is asked for (then the score kernel writes all three outputs)
+  // The reductions ride along in the assignment launch (or on the helper wave of the split kernel) where one wave can do
+  // both: their sorted list is the round's, and a launch of their own would wait in line before it.
+  const bool best = o.best_g || o.best_i;
   const bool split = br_split_serves(p);
-  if (split) {
-    BrOut o2 = o;
-    if (o.F) {
-      rc = enqueue(ctx, BR_K_SCORE, [&] { br_launch_score(p, a, o, partials, ctx->st); }, br);
-      o2.F = nullptr, o2.best_g = nullptr, o2.best_i = nullptr;
-    }
-    if (rc == BR_OK) rc = enqueue(ctx, BR_K_ASSIGN, [&] { br_launch_route_split(p, a, o2, ctx->st); }, br);
-    return rc;
-  }
-  if (rc == BR_OK && !together && (o.F || o.best_g || o.best_i))
-    rc = enqueue(ctx, BR_K_SCORE, [&] { br_launch_score(p, a, o, partials, ctx->st); }, br);
+  const bool together = best && p.R_max <= 8 && (p.H == 0 ? p.Q <= 1024 : (p.H <= BR_HP && p.Q <= 512));
+  BrOut first = o;  // what the score kernels write
+  if (split || together) first.best_g = nullptr, first.best_i = nullptr;
+  if (rc == BR_OK && (first.F || first.best_g || first.best_i))
+    rc = enqueue(ctx, BR_K_SCORE, [&] { br_launch_score(p, a, first, partials, ctx->st); }, br);
   if (rc == BR_OK) {
-    if (together && p.H > 0)
-      rc = enqueue(ctx, BR_K_ASSIGN, [&] { br_launch_route_h(p, a, o, ctx->st); }, br);
-    else if (together)
-      rc = enqueue(ctx, BR_K_ASSIGN, [&] { br_launch_route4(p, a, o, ctx->st); }, br);
-    else
-      rc = enqueue(ctx, BR_K_ASSIGN, [&] { br_launch_assign(p, a, o, ctx->st); }, br);
+    rc = enqueue(ctx, BR_K_ASSIGN, [&] {
+      if (split)
+        br_launch_route_split(p, a, o, ctx->st);
+      else if (together && p.H > 0)
+        br_launch_route_h(p, a, o, ctx->st);
+      else if (together)
+        br_launch_route(p, a, o, ctx->st);
+      else
+        br_launch_assign(p, a, o, ctx->st);
+    }, br);
   }
   if (rc == BR_OK && split_adv) rc = enqueue(ctx, BR_K_ADVANCE, [&] { br_launch_advance(p, adv_t, ctx->st); }, br);
   return rc;

@@ -882,11 +882,14 @@ __global__ __launch_bounds__(256, (HB > 0 && E == 8 && !BIGR) ? 4 : 1) void br_k
     br_assign_body<E, HB, ADV, false, BIGR>(p, a, o, lds_all + w * WORDS, (int)(blockIdx.x * (blockDim.x >> 6)) + w);
 }
 
+// Clusters of one wave each per block: four, so that the chip's block slots do not cap a large batch; one where the batch
+// leaves room, so that the clusters spread evenly over the SIMDs.
+static inline int br_clusters_per_block(int N, int E) { return E <= 8 && N > 2048 ? 4 : 1; }
+
 template <int E, int HB, bool BIGR = false>
 static void br_launch_assign_one(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
-  // several single-wave clusters share a block so that the chip's per-CU block slots do not cap residency
   const bool dp = BIGR && p.R_max > 16;   // windows beyond 16 requests: one cluster per block, with LDS for the bit rows
-  const int wpb = (E <= 8 && !dp) ? 4 : 1;  // clusters per block
+  const int wpb = dp ? 1 : br_clusters_per_block(p.N, E);
   const size_t lds = ((size_t)wpb * BR_ROUND_WORDS(E, BIGR) + (dp ? BR_DP_LDS_WORDS : 0)) * sizeof(int);
   const dim3 grid((unsigned)((p.N + wpb - 1) / wpb)), block(E == 32 ? 4 * BR_WAVE : BR_WAVE * wpb);
   // (decode steps ride along for BR-0 with windows of up to 8 requests only; elsewhere the caller launches the decode kernel)

@@ -1,4 +1,4 @@
-// BR-H counterpart of br_k_route4: for large batches of clusters with queues of up to 512 entries the wave that
+// BR-H counterpart of br_k_route: for clusters with queues of up to 512 entries the wave that
 // owns a cluster first computes the snapshot reductions (K2 + K3, on the step-start margins of the projection
 // kernels), then runs the two-stage assignment (K4), in one launch.
 #include "br_assign_kernel.h"
@@ -8,13 +8,15 @@ template <int E, int HB>
 __global__ __launch_bounds__(256, E == 8 ? 4 : 1) void br_k_route_h(BrParams p, BrArr a, BrOut o) {
   extern __shared__ int lds_all[];
   const int w = threadIdx.x >> 6;
-  br_assign_body<E, HB, false, false, false, true>(p, a, o, lds_all + w * BR_ROUND_WORDS(E, false), (int)blockIdx.x * 4 + w);
+  br_assign_body<E, HB, false, false, false, true>(p, a, o, lds_all + w * BR_ROUND_WORDS(E, false),
+                                                 (int)(blockIdx.x * (blockDim.x >> 6)) + w);
 }
 
 template <int E, int HB>
 static void launch_route_h(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
-  const size_t lds = (size_t)4 * BR_ROUND_WORDS(E, false) * sizeof(int);
-  const dim3 grid((unsigned)((p.N + 3) / 4)), block(256);
+  const int wpb = br_clusters_per_block(p.N, E);
+  const size_t lds = (size_t)wpb * BR_ROUND_WORDS(E, false) * sizeof(int);
+  const dim3 grid((unsigned)((p.N + wpb - 1) / wpb)), block(BR_WAVE * wpb);
   hipLaunchKernelGGL((br_k_route_h<E, HB>), grid, block, lds, st, p, a, o);
 }
 

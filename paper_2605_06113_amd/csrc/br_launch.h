@@ -30,9 +30,9 @@ void br_launch_assign_bigr(const BrParams &p, const BrArr &a, const BrOut &o, hi
 void br_launch_assign_br0(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
 // BR-H, H <= 4
 void br_launch_assign_brh4(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
-// BR-0, Q <= 256: snapshot reductions and assignment of four clusters per block in one launch
-void br_launch_route4(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
-// BR-H (H <= BR_HP), Q <= 512: the same in one launch per four clusters
+// BR-0, Q <= 1024: snapshot reductions and assignment in one launch
+void br_launch_route(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
+// BR-H (H <= BR_HP), Q <= 512: the same in one launch
 void br_launch_route_h(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
 void br_launch_bypass(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
 // comparison policies (Random, RR, P2C, JSQ): FIFO dispatch of the waiting queue, BR-0 contexts
