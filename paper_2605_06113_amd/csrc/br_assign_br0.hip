@@ -6,20 +6,32 @@
 // The whole round of a cluster on one wave, in one launch: the snapshot
 // reductions (per-request best worker, per-worker best request: K2 + K3) on the step-start state, then the two-stage
 // assignment on the same sorted list (K4, and the decode step with ADV).
+// ADV: for a few decode steps, half of the waves apply them to their lists as they stand before the round (and append
+// what they admit already advanced), the other half after it.  With one order for all, the memory idles while every wave
+// routes and the issue slots idle while every wave streams.  4096 clusters, G = 16, B = 144: one step, 6 admissions 52 -> 49
+// us.  After many steps rounds are long (a burst of 246 admissions in 48 steps) and the streaming hides in their
+// tail anyway: 112 us, 115 with both orders.
 template <int E, bool ADV>
 __global__ __launch_bounds__(256) void br_k_route(BrParams p, BrArr a, BrOut o) {
   extern __shared__ int lds_all[];
-  const int w = threadIdx.x >> 6;
-  br_assign_body<E, 0, ADV, false, false, true>(p, a, o, lds_all + w * BR_ROUND_WORDS(E, false),
-                                                (int)(blockIdx.x * (blockDim.x >> 6)) + w);
+  constexpr bool MIX = ADV && E <= 8;
+  constexpr int WORDS = BR_ROUND_WORDS(E, false) + (MIX ? BR_SPLIT_WORDS : 0);
+  const int w = threadIdx.x >> 6, b = (int)blockIdx.x, inst = b * (int)(blockDim.x >> 6) + w;
+  int *lds = lds_all + w * WORDS, *split = nullptr;
+  if (MIX && p.adv_t <= 8 && ((b + (b >> 8) + w) & 1) && inst < p.N) {  // (blocks 256 apart share a CU: both orders on every SIMD)
+    split = lds + BR_ROUND_WORDS(E, false);
+    br_split_advance<8>(p, inst, br_lane(), split);
+  }
+  br_assign_body<E, 0, ADV, false, false, true>(p, a, o, lds, inst, 0, split);
 }
 
 template <int E>
 static void launch_route(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
   const int wpb = br_clusters_per_block(p.N, E);
-  const size_t lds = (size_t)wpb * BR_ROUND_WORDS(E, false) * sizeof(int);
+  const bool adv = p.adv_t > 0;
+  const size_t lds = (size_t)wpb * (BR_ROUND_WORDS(E, false) + (adv && E <= 8 ? BR_SPLIT_WORDS : 0)) * sizeof(int);
   const dim3 grid((unsigned)((p.N + wpb - 1) / wpb)), block(BR_WAVE * wpb);
-  if (p.adv_t > 0)
+  if (adv)
     hipLaunchKernelGGL((br_k_route<E, true>), grid, block, lds, st, p, a, o);
   else
     hipLaunchKernelGGL((br_k_route<E, false>), grid, block, lds, st, p, a, o);

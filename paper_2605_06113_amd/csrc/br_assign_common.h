@@ -321,16 +321,12 @@ __device__ __forceinline__ void br_advance_cluster(int inst, int lane, int Lcur,
 // [68..132) per worker: load change of the old entries.
 #define BR_SPLIT_WORDS 132
 
-// The helper's part for one cluster: snapshot reductions if asked for (they read what the round's epilogue will
-// overwrite, and the epilogue waits for the flag), the decode steps of the old entries, then the flag.
-// UB: (list, chunk) units requested before the first is used
-template <int E, int UB>
-__device__ __forceinline__ void br_split_helper(const BrParams &p, const BrArr &a, const BrOut &o, int inst, int lane,
-                                                int *split, int *lst) {
+// The decode steps of a cluster's lists as they stand, what they lost and by how much their loads change, then the flag.
+template <int UB>
+__device__ __forceinline__ void br_split_advance(const BrParams &p, int inst, int lane, int *split) {
   const bool act = lane < p.G;
-  if (o.best_g || o.best_i) br_score_wave_run<E, 0>(p, a, o, inst, lane, lst);
-  int n0 = act ? p.n[(int64_t)inst * p.G + lane] : p.B;
-  n0 = act ? min(max(n0, 0), p.B) : 0;
+  const int n_raw = p.n[(int64_t)inst * p.G + (act ? lane : 0)];
+  const int n0 = act ? min(max(n_raw, 0), p.B) : 0;
   int dL = 0, kept = n0;
   br_advance_cluster<UB, false>(inst, lane, 0, n0, 0, 64, &dL, &kept);
   split[4 + lane] = n0 - kept;
@@ -340,10 +336,23 @@ __device__ __forceinline__ void br_split_helper(const BrParams &p, const BrArr &
   if (lane == 0) split[0] = 1;
 }
 
-// The epilogue of the wave that ran the round, in a split kernel.  nn0: list lengths at the start of the step.
+// The helper's part for one cluster: snapshot reductions if asked for (they read what the round's epilogue will
+// overwrite, and the epilogue waits for the flag), the decode steps of the old entries, then the flag.
+// UB: (list, chunk) units requested before the first is used
+template <int E, int UB>
+__device__ __forceinline__ void br_split_helper(const BrParams &p, const BrArr &a, const BrOut &o, int inst, int lane,
+                                                int *split, int *lst) {
+  if (o.best_g || o.best_i) br_score_wave_run<E, 0>(p, a, o, inst, lane, lst);
+  br_split_advance<UB>(p, inst, lane, split);
+}
+
+// The epilogue of the wave that ran the round where the decode steps of the old entries are (being) applied apart: by
+// another wave (split kernels), or by this one before the round.  nn0: list lengths at the start of the step.
+// Admitted requests whose output is used up within the t steps leave at once: who they are per worker is collected in
+// bit masks (by order of admission) in `lds` (320 words), so that the others go straight to their final slots.
 template <int E>
 __device__ __forceinline__ void br_assign_epilogue_split(int inst, int lane, int q0, int qn, int cnt, const int *bound, int Lcur,
-                                                         int nn, int nn0, const BrRoundCounts &rc, int *split) {
+                                                         int nn, int nn0, const BrRoundCounts &rc, int *split, int *lds) {
   const BrTailArgs t = br_tail_args();
   const int G = t.G, tt = t.adv_t;
   // everything that will be read of the queue and the arrivals is requested before the wait for the helper
@@ -351,24 +360,57 @@ __device__ __forceinline__ void br_assign_epilogue_split(int inst, int lane, int
   br_queue_load(t, inst, lane, 0, q0, qn, bound, v);
   // the helper is done with this cluster's lists (it never waits for anything: the flag always comes)
   while (__atomic_load_n(split, __ATOMIC_RELAXED) == 0) __builtin_amdgcn_s_sleep(4);
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // (or this wave's own stores to the lists)
   const int lost = split[4 + lane], dold = split[4 + BR_WAVE + lane];  // lane g: worker g
   const int kept0 = nn0 - lost, a_g = nn - nn0;                        // old survivors, admissions of this round
   int nfin = kept0 + a_g, Lfin = Lcur + dold + a_g * tt;               // if every admitted request outlives the t steps
   bool slow = false;
   if (rc.admitted > 0) {
-    bool short_one = false;
+    int *dead = lds, *dead_kv = lds + 2 * BR_WAVE, *first = lds + 3 * BR_WAVE;  // per worker
+    bool short_one = false, far = false;
 #pragma unroll
     for (int u = 0; u < E; ++u) short_one |= v.bound[u] >= 0 && max(v.oq[u], 1) <= tt;
-    slow = br_ballot(short_one) != 0ull;  // some admitted request ends within the t steps: lists are compacted below
+    const bool some = br_ballot(short_one) != 0ull;
+    if (some) {
+      dead[2 * lane] = 0, dead[2 * lane + 1] = 0, dead_kv[lane] = 0, first[lane] = nn0;
+      br_wave_sync();
+#pragma unroll
+      for (int u = 0; u < E; ++u) {
+        if (v.bound[u] >= 0 && max(v.oq[u], 1) <= tt) {
+          const int g = (v.bound[u] >> 16) & 63, k = (v.bound[u] & 0xffff) - first[g];
+          far |= k >= BR_WAVE;
+          if (k < BR_WAVE) {
+            atomicOr(&dead[2 * g + (k >> 5)], 1 << (k & 31));
+            atomicAdd(&dead_kv[g], min(max(v.sq[u], 1), BR_MAX_S_DEV));
+          }
+        }
+      }
+      slow = br_ballot(far) != 0ull;  // beyond the masks: the lists are compacted below
+      br_wave_sync();
+      if (!slow) {
+        const int gone = __builtin_popcount(dead[2 * lane]) + __builtin_popcount(dead[2 * lane + 1]);
+        nfin -= gone;
+        Lfin = Lcur + dold - dead_kv[lane] + (a_g - gone) * tt;
+      }
+    }
     const int add = slow ? 0 : tt;
 #pragma unroll
     for (int u = 0; u < E; ++u) {
       const int g = v.bound[u] >> 16, slot = v.bound[u] & 0xffff;
       if (v.bound[u] >= 0 && g < G && slot < t.B) {
-        const int64_t row = ((int64_t)inst * G + g) * t.Bs + (slot - split[4 + g]);  // behind the old survivors
-        t.kv[row] = min(max(v.sq[u], 1), BR_MAX_S_DEV) + add;
-        t.rem[row] = max(v.oq[u], 1) - add;
+        int64_t row = ((int64_t)inst * G + g) * t.Bs + (slot - split[4 + g]);  // behind the old survivors
+        bool live = true;
+        if (some && !slow) {
+          const int k = slot - first[g];
+          const unsigned lo = (unsigned)dead[2 * g], hi = (unsigned)dead[2 * g + 1];
+          live = max(v.oq[u], 1) > tt;
+          row -= k >= 32 ? __builtin_popcount(lo) + __builtin_popcount(k < 64 ? hi & ((1u << (k & 31)) - 1u) : hi)
+                         : __builtin_popcount(lo & ((1u << k) - 1u));
+        }
+        if (live) {
+          t.kv[row] = min(max(v.sq[u], 1), BR_MAX_S_DEV) + add;
+          t.rem[row] = max(v.oq[u], 1) - add;
+        }
       }
     }
   }

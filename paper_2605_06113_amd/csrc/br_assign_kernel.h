@@ -720,8 +720,8 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
 // more are waiting.  COOP (EM = 32): the block has four waves; all of them sort a long waiting set together
 // (br_sort_desc_block4) and share the epilogue and the decode step, wave 0 runs the round.
 // SCORES: the snapshot reductions (best_g / best_i where asked for) are taken on the way (br_score_wave.h).
-// `split`: the cluster's BR_SPLIT_WORDS of LDS in a split kernel (another wave applies the decode steps to the old
-// list entries meanwhile), or null.
+// `split`: the cluster's BR_SPLIT_WORDS of LDS where the decode steps of the old list entries are applied apart (by
+// another wave meanwhile, or by this one before the round), or null.
 // `shared` (BIGR without COOP, one cluster per block of four waves): waves 1-3 serve the subset searches of wave 0
 // (every fourth trip of a mask scan, every fourth run of 64 words of the rows of reachable sums) through the
 // mailbox `svc` and two block barriers per search.
@@ -850,9 +850,9 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
     }
   } else {
     bool done = false;
-    if constexpr (!BRH && !BIGR && !ADV && EM <= 8) {
+    if constexpr (!BRH && !BIGR && EM <= 8) {
       if (split != nullptr) {
-        br_assign_epilogue_split<EM>(inst, lane, q0, qn, cnt, bound, st.Lh[0], st.nn, nn_start, rc, split);
+        br_assign_epilogue_split<EM>(inst, lane, q0, qn, cnt, bound, st.Lh[0], st.nn, nn_start, rc, split, lst);
         done = true;
       }
     }
