@@ -46,29 +46,38 @@
 #include "br_sort.h"
 #include "br_assign_common.h"
 #include "br_subset_dp.h"
+#include "br_subset_halves.h"
 #include "br_subset_list.h"
 #include "br_score_wave.h"
 
 // LDS of a cluster whose queue holds up to EM * 64 entries: bound [EM * 64], list copy, slots [64], Stage-2 window and
 // table (BIGR), then the mailbox of shared subset searches and the bit rows of br_subset_dp.h where they are used
-#define BR_ROUND_WORDS(EM, BIGR) ((EM) * BR_WAVE + BR_LIST_WORDS(EM) + BR_WAVE + ((BIGR) ? 32 + 1024 : 0))
+#define BR_SEARCH_WORDS 1344
+#define BR_ROUND_WORDS(EM, BIGR) ((EM) * BR_WAVE + BR_LIST_WORDS(EM) + BR_WAVE + ((BIGR) ? 32 + BR_SEARCH_WORDS : 0))
+static_assert(BR_SEARCH_WORDS >= BR_HALVES_WORDS && BR_SEARCH_WORDS >= 1024, "LDS of a subset search");
 
-// Subset search of a window of up to 16 requests (Stage 2, BIGR), this wave's share of it.  With at most half of the
-// window per subset the admissible masks are taken from a list (br_subset_list.h; `hitab`: its byte tables).
-// Otherwise a scan over all masks: lane l keeps the lower six mask bits, the upper bits c run as passes over the table `hitab` of their partial sums, four passes per
-// trip; the wave takes the trips wv, wv + nwv, ... (trips whose upper bits alone exceed the cardinality limit are
-// skipped).  A lane sees its masks in ascending order and keeps the first best: returns the lane's best key and
-// its lowest mask.
+// Trips of 256 masks from which a block's four waves share a search: fewer are not worth two barriers.
+#define BR_SHARE_TRIPS 4
+// BR-0: trips from which the sums of the window's halves decide instead (br_subset_halves.h: about 5800 cycles at kmax = 4
+// and 200 more per request beyond; a trip is 350 to 600 cycles on one wave).
+#define BR_HALVES_TRIPS 6
+
+// Subset search of a window of up to 16 requests (Stage 2, BIGR), this wave's share of it: the best key and its lowest
+// mask (uniform).  With at most half of the window per subset the admissible masks are taken from a list
+// (br_subset_list.h; `hitab`: its byte tables, made here with `build`).
+// Otherwise a scan over all masks: lane l keeps the lower six mask bits, the upper bits c run as passes over the table
+// `hitab` of their partial sums, four passes per trip; the wave takes the trips wv, wv + nwv, ... (trips whose upper bits
+// alone exceed the cardinality limit are skipped).  A lane sees its masks in ascending order and keeps the first best.
 template <bool BRH, int N>
-__device__ __forceinline__ void br_bigr_scan(const BrParams &p, const int (&mg)[N], const int *win, const int *hitab,
-                                             int w, int kmax, int room, int lane, int wv, int nwv, int &bk, int &bm) {
+__device__ __forceinline__ void br_bigr_scan(const BrParams &p, const int (&mg)[N], const int *win, int *hitab, int w, int kmax,
+                                             int room, int lane, int wv, int nwv, bool build, int &best, int &mask) {
   if (br_list_serves(w, kmax)) {
-    br_list_walk<4>(hitab, w, kmax, room, lane, wv, nwv,
-                    [&](const int(&delta)[4], int(&key)[4]) {
+    br_list_walk(win, hitab, w, kmax, room, lane, wv, nwv, build,
+                 [&](const int(&delta)[4], int(&key)[4]) {
 #pragma unroll
-                      for (int u = 0; u < 4; ++u) key[u] = br_score_key<BRH>(p, mg, delta[u]);
-                    },
-                    bk, bm);
+                   for (int u = 0; u < 4; ++u) key[u] = br_score_key<BRH>(p, mg, delta[u]);
+                 },
+                 best, mask);
     return;
   }
   const int nhi = w > 6 ? 1 << (w - 6) : 1;
@@ -77,7 +86,7 @@ __device__ __forceinline__ void br_bigr_scan(const BrParams &p, const int (&mg)[
   for (int b = 0; b < min(w, 6); ++b) base += ((lane >> b) & 1) * (win[b] >> BR_IDX_BITS);
   const int klim = kmax - __builtin_popcount(lane);  // bits the upper part of a mask may still add on this lane
   const bool lane_ok = lane < nmask;                  // (windows below six requests use the lower lanes only)
-  bk = BR_KEY_NONE, bm = INT32_MAX;
+  int bk = BR_KEY_NONE, bm = INT32_MAX;
   for (int c0 = 4 * wv; c0 < nhi; c0 += 4 * nwv) {  // four passes per trip: one 16-byte table read, independent scores
     if (__builtin_popcount(c0) > kmax) continue;     // c0 + u has at least the bits of c0: too many for every lane
     const int4 h4 = *reinterpret_cast<const int4 *>(hitab + c0);
@@ -99,6 +108,8 @@ __device__ __forceinline__ void br_bigr_scan(const BrParams &p, const int (&mg)[
         bm = (c0 + u) * BR_WAVE + lane;
       }
   }
+  best = br_wave_max(bk);
+  mask = best == BR_KEY_NONE ? INT32_MAX : br_wave_min(bk == best ? bm : INT32_MAX);
 }
 
 
@@ -574,44 +585,54 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
                             p.dp + (size_t)inst * br_dp_cluster_words(min(p.B, p.R_max)), bestmask, bestkey,
                             shared ? svc : nullptr);
         } else {
-          int trips;  // of 256 masks each
-          if (br_list_serves(w, kmax)) {
-            br_list_tables(win, w, hitab, lane);
-            trips = (br_list_size(w, kmax) + 255) >> 8;
-          } else {
-            const int nhi = w > 6 ? 1 << (w - 6) : 1;
-            for (int c0 = 0; c0 < nhi; c0 += BR_WAVE) {
-              const int c = c0 + lane;
-              int sum = 0;
-              for (int b = 6; b < w; ++b) sum += ((c >> (b - 6)) & 1) * (win[b] >> BR_IDX_BITS);
-              if (c < nhi) hitab[c] = sum;
-            }
-            trips = nhi >> 2;
-          }
-          br_wave_sync();
-          int bk, bm;
-          const bool shared_scan = shared && trips >= 4;  // (a few trips are not worth two barriers)
-          if (shared_scan) {
+          auto score4 = [&](const int(&delta)[4], int(&key)[4]) {
 #pragma unroll
-            for (int h = 0; h < NH; ++h) svc[1 + h] = mg[h];
-            svc[2 + BR_HP] = room, svc[3 + BR_HP] = w, svc[4 + BR_HP] = kmax;
-            svc[0] = 1;
-            __syncthreads();
-            br_bigr_scan<BRH>(p, mg, win, hitab, w, kmax, room, lane, 0, 4, bk, bm);
+            for (int u = 0; u < 4; ++u) key[u] = br_score_key<BRH>(p, mg, delta[u]);
+          };
+          const bool listed = br_list_serves(w, kmax);
+          const int trips = ((listed ? br_list_size(w, kmax) : 1 << w) + 255) >> 8;  // of 256 masks each
+          const bool halves = !BRH && trips >= BR_HALVES_TRIPS;
+          if (kmax <= 3) {
+            int mbest;
+            br_wave_sync();
+            br_small_search(win, w, kmax, room, lane, score4, bestkey, mbest);
+            bestmask = bestkey == BR_KEY_NONE ? 0u : (unsigned)mbest;
+          } else if (halves) {
+            br_subset_halves(G, mg[0], win, w, kmax, room, lane, hitab, bestkey, bestmask);
           } else {
-            br_bigr_scan<BRH>(p, mg, win, hitab, w, kmax, room, lane, 0, 1, bk, bm);
-          }
-          bestkey = br_wave_max(bk);
-          int mbest = bestkey == BR_KEY_NONE ? INT32_MAX : br_wave_min(bk == bestkey ? bm : INT32_MAX);
-          if (shared_scan) {  // the best of the four shares: lowest mask among equal scores
-            __syncthreads();
-#pragma unroll
-            for (int u = 1; u < 4; ++u) {
-              const int ku = svc[16 + 2 * u], mu = svc[17 + 2 * u];
-              if (ku > bestkey || (ku == bestkey && mu < mbest)) bestkey = ku, mbest = mu;
+            if (!listed) {
+              const int nhi = w > 6 ? 1 << (w - 6) : 1;
+              for (int c0 = 0; c0 < nhi; c0 += BR_WAVE) {
+                const int c = c0 + lane;
+                int sum = 0;
+                for (int b = 6; b < w; ++b) sum += ((c >> (b - 6)) & 1) * (win[b] >> BR_IDX_BITS);
+                if (c < nhi) hitab[c] = sum;
+              }
             }
+            int mbest;
+            const bool shared_scan = shared && trips >= BR_SHARE_TRIPS;
+            if (shared_scan) {
+              if (listed) br_list_tables(win, w, hitab, lane);
+#pragma unroll
+              for (int h = 0; h < NH; ++h) svc[1 + h] = mg[h];
+              svc[2 + BR_HP] = room, svc[3 + BR_HP] = w, svc[4 + BR_HP] = kmax;
+              svc[0] = 1;
+              __syncthreads();
+              br_bigr_scan<BRH>(p, mg, win, hitab, w, kmax, room, lane, 0, 4, false, bestkey, mbest);
+            } else {
+              br_wave_sync();
+              br_bigr_scan<BRH>(p, mg, win, hitab, w, kmax, room, lane, 0, 1, true, bestkey, mbest);
+            }
+            if (shared_scan) {  // the best of the four shares: lowest mask among equal scores
+              __syncthreads();
+#pragma unroll
+              for (int u = 1; u < 4; ++u) {
+                const int ku = svc[16 + 2 * u], mu = svc[17 + 2 * u];
+                if (ku > bestkey || (ku == bestkey && mu < mbest)) bestkey = ku, mbest = mu;
+              }
+            }
+            bestmask = bestkey == BR_KEY_NONE ? 0u : (unsigned)mbest;
           }
-          bestmask = bestkey == BR_KEY_NONE ? 0u : (unsigned)mbest;
         }
       } else {
         // exhaustive subset search, one subset mask per lane (ascending masks, strict improvement)
@@ -738,8 +759,8 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
   int *lst = bound + EM * BR_WAVE;               // copy of the list
   int *slots = lst + BR_LIST_WORDS(EM);          // [64] requests of a bulk step in order of admission
   int *win = slots + BR_WAVE;                // BIGR: [32] Stage-2 candidate window
-  int *hitab = win + 32;                         // BIGR: [1024] subset-sum tables
-  int *svc = hitab + 1024;                       // BIGR, shared: [32] mailbox
+  int *hitab = win + 32;                         // BIGR: [BR_SEARCH_WORDS] subset-sum tables
+  int *svc = hitab + BR_SEARCH_WORDS;            // BIGR, shared: [32] mailbox
   int *dprows = svc + (shared ? 32 : 0);         // BIGR, R_max > 16: bit rows of the subset search
 
   const int lane = br_lane();
@@ -755,10 +776,9 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
           int mgq[NH];
 #pragma unroll
           for (int h = 0; h < NH; ++h) mgq[h] = svc[1 + h];
-          int bk, bm;
-          br_bigr_scan<BRH>(p, mgq, win, hitab, svc[3 + BR_HP], svc[4 + BR_HP], svc[2 + BR_HP], lane, w, 4, bk, bm);
-          const int km = br_wave_max(bk);
-          const int mm = km == BR_KEY_NONE ? INT32_MAX : br_wave_min(bk == km ? bm : INT32_MAX);
+          int km, mm;
+          const int w_q = br_uniform(svc[3 + BR_HP]), k_q = br_uniform(svc[4 + BR_HP]), room_q = br_uniform(svc[2 + BR_HP]);
+          br_bigr_scan<BRH>(p, mgq, win, hitab, w_q, k_q, room_q, lane, w, 4, false, km, mm);
           if (lane == 0) svc[16 + 2 * w] = km, svc[17 + 2 * w] = mm;
         }
         __syncthreads();
@@ -894,10 +914,11 @@ static void br_launch_assign_one(const BrParams &p, const BrArr &a, const BrOut 
   const dim3 grid((unsigned)((p.N + wpb - 1) / wpb)), block(E == 32 ? 4 * BR_WAVE : BR_WAVE * wpb);
   // (decode steps ride along for BR-0 with windows of up to 8 requests only; elsewhere the caller launches the decode kernel)
   if constexpr (BIGR) {
-    // windows of 9..16 requests on a batch that leaves room on the chip (registers allow about 4 / 3 / 2 waves per
-    // SIMD for queues of up to 256 / 512 / 1024, one less for BR-H): a block of four waves per cluster, the scans shared
+    // windows beyond 8 requests on a batch that leaves room on the chip (registers allow about 4 / 3 / 2 waves per
+    // SIMD for queues of up to 256 / 512 / 1024, one less for BR-H): a block of four waves per cluster, the searches shared
+    // (BR-0 up to a window of 16 has none that is long enough)
     const long long room = 1024ll * max(1, (E == 4 ? 4 : E == 8 ? 3 : 2) - (HB > 0 ? 1 : 0));
-    if (E <= 16 && (long long)p.N * 4 <= room) {
+    if ((HB > 0 || dp) && E <= 16 && (long long)p.N * 4 <= room) {
       const size_t lds1 = ((size_t)BR_ROUND_WORDS(E, true) + 32 + (dp ? BR_DP_LDS_WORDS : 0)) * sizeof(int);
       hipLaunchKernelGGL((br_k_assign<E, HB, false, true>), dim3((unsigned)p.N), dim3(4 * BR_WAVE), lds1, st, p, a, o, 1);
     } else {

@@ -606,9 +606,7 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
         }
         const bool listed = br_list_serves(w, kw);
         const int nhi = w > 6 ? 1 << (w - 6) : 1;
-        if (listed) {
-          br_list_tables(win, w, hitab, lane);
-        } else {
+        if (!listed) {
           for (int c0 = 0; c0 < nhi; c0 += BR_WAVE) {
             const int c = c0 + lane;
             int sum = 0;
@@ -625,10 +623,11 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
 #pragma unroll
           for (int u = 0; u < 4; ++u) key[u] = br_ord(Fv[u]);
         };
-        int bk = BR_KEY_NONE, bm = INT32_MAX;
         if (listed) {
-          br_list_walk<4>(hitab, w, kw, room, lane, 0, 1, score4, bk, bm);
+          br_list_walk(win, hitab, w, kw, room, lane, 0, 1, true, score4, bestkey, bestmask);
+          if (bestkey == BR_KEY_NONE) bestmask = 0;
         } else {
+          int bk = BR_KEY_NONE, bm = INT32_MAX;
           const int klim = kw - lpop;
           const bool lane_ok = lane < nmask;
           for (int c0 = 0; c0 < nhi; c0 += 4) {
@@ -652,9 +651,9 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
               }
             }
           }
+          bestkey = br_wave_max(bk);
+          bestmask = bestkey == BR_KEY_NONE ? 0 : br_wave_min(bk == bestkey ? bm : INT32_MAX);
         }
-        bestkey = br_wave_max(bk);
-        bestmask = bestkey == BR_KEY_NONE ? 0 : br_wave_min(bk == bestkey ? bm : INT32_MAX);
         br_wave_sync();
       } else {
       {

@@ -631,6 +631,19 @@ def test_wide_window_by_free_slots(R_max, H, pred_mode):
         r.close()
 
 
+@pytest.mark.parametrize("R_max,free,wm", [(9, 8, 0), (11, 5, 0), (12, 4, 0), (16, 4, 30000), (16, 7, 0), (16, 12, 20000), (24, 16, 0)])
+def test_window_halves(R_max, free, wm):
+    """BR-0 windows whose subsets are found from the sums of the two halves: windows of 9..16 down to the last requests,
+    more slots than a half holds, watermarks below and above the margin, runs of equal lengths, requests of length 1."""
+    for tie, s_hi in [(False, 4096), (True, 4096), (False, 3)]:
+        cfg, init, arr = wl.random_case(950 + R_max + free, N=4, G=5, B=24, max_wait=40, s_hi=s_hi, tie_heavy=tie, n_wait=30,
+                                        R_max=R_max, S_greedy=10 ** 6, fill=1.0, token_watermark=wm)
+        init.n[:] = cfg.B - free
+        _say(f"halves: window {R_max}, free slots {free}, watermark {wm}, ties {tie}, lengths to {s_hi}")
+        oc, r = run_pair(cfg, init, arr, tag=f"halves {R_max} {free}")
+        r.close()
+
+
 def test_wide_window_long_requests_reach_the_row_bound():
     """Windows of 32 requests with lengths up to 32768 and room for many per pop: subset sums beyond the length of
     the bit rows (131071) exist and are not candidates on either side; rows too long for LDS go to the workspace."""
