@@ -182,13 +182,15 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
   // envelope: lane l also keeps the offsets l, l + 64, l + 128 in registers (the LDS copy serves the reads that
   // need other lanes' offsets); Lg: the same offsets of the step-start projection of the worker in hand
   int Mr[3] = {0, 0, 0}, Lg[3] = {0, 0, 0};
+  float mr[3] = {0.0f, 0.0f, 0.0f}, dr[3] = {0.0f, 0.0f, 0.0f};  // margins of the worker in hand and discounts, likewise
 #pragma unroll
   for (int u = 0; u < 3; ++u) {
     const int h = u * BR_WAVE + lane;
     if (h < HS) {
       Mr[u] = h < H1 ? p.Mh[(int64_t)inst * H1 + h] : 0;
       sM[h] = Mr[u];
-      sd[h] = p.dl[h];
+      dr[u] = p.dl[h];
+      sd[h] = dr[u];
       smg[h] = 0.0f;
     }
   }
@@ -251,7 +253,8 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
       const int h = u * BR_WAVE + lane;
       if (h < H1) {
         Lg[u] = sL[h * LS + g];
-        smg[h] = (float)max(Mr[u] - (Lg[u] + ag), 0);
+        mr[u] = (float)max(Mr[u] - (Lg[u] + ag), 0);
+        smg[h] = mr[u];
       }
     }
     br_wave_sync();
@@ -303,14 +306,7 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
   // everything left out computes strictly below a score that was kept.
   int span_fa = -1, span_la = -1;
   bool span_dirty = true;
-  // `sure_pos` >= 0 (Stage 2): the sorted position of the window's smallest entry.  The search then first decides,
-  // from the probe at or after that position (a request no longer than that entry), whether the pop is certain to
-  // end in the starvation guard: eq. (brh-Fscore) is concave with F(0) = 0, so F(Delta) <= F(s) Delta / s for every
-  // Delta >= s; if that probe scores at or below -3 e(s) in the order-free evaluation, its exact score is at or
-  // below -2 e(s), every subset of the window (all of them sum to at least s) has an exact score at or below
-  // -2 e(Delta) and computes below zero.  If so the search goes on and returns the guard's pick; if not, it stops
-  // with *unsure set and the caller enumerates the subsets.
-  auto pick_single = [&](int room, int &pos, int &swin, int sure_pos = -1, bool *unsure = nullptr) -> bool {
+  auto pick_single = [&](int room, int &pos, int &swin) -> bool {
     int bk, bp, km;
     {
       // first and last sorted position of a request in question: kept from search to search while the alive set
@@ -330,7 +326,7 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
         span_dirty = false;
       }
       const int fa = span_fa, la = span_la;
-      if (fa < 0) return false;  // (no request in question: no subset of the window is admissible either)
+      if (fa < 0) return false;
       salive[lane] = (int)alive;
       br_wave_sync();
       const int p1 = lane * E;  // probe position
@@ -352,20 +348,6 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
         pen1 = br_long_penalty_part(smg, sd, HS, lane, top1, s1, ~0ull);
       }
       const float F1 = br_scoreh_long_from(p.aD, p.beta, s1, pen1);
-      if (sure_pos >= 0) {
-        const int lw = (sure_pos + E - 1) / E;  // first probe at or after the window's smallest entry
-        bool sure = false;
-        if (lw < BR_WAVE && lw * E < qn) {
-          const float Fw = __builtin_amdgcn_readlane(F1, lw);
-          const int sw = __builtin_amdgcn_readlane(s1, lw);
-          sure = Fw <= -3.0f * err_unit * (float)sw;
-        }
-        if (!sure) {
-          *unsure = true;
-          br_wave_sync();
-          return false;
-        }
-      }
       const int k1 = q1 ? br_ord(F1) : BR_KEY_NONE;
       const int km1 = br_wave_max(k1);
       if (km1 != BR_KEY_NONE) {
@@ -577,11 +559,22 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
       const int nmask = 1 << w;
       int bestmask = 0, bestkey = BR_KEY_NONE;
       int wv[8], ws[8];
-      // certain guard (decided inside the search from its probes): then `picked` holds the guard's pick already
-      int gpos = 0, gswin = 0;
-      bool unsure = false;
-      const bool picked = pick_single(room, gpos, gswin, br_uniform(win[w - 1] & IDX_MASK), &unsure);
-      const bool guard_sure = !unsure;
+      // Is the pop certain to end in the starvation guard?  eq. (brh-Fscore) is concave with F(0) = 0, so F(Delta) <=
+      // F(s) Delta / s for every Delta >= s = the window's smallest entry.  If F(s), summed across the lanes in any order
+      // (at most 12 roundings), is at or below -3 e(s), its exact value is at or below -2 e(s), every subset of the
+      // window (all of them sum to at least s) has an exact score at or below -2 e(Delta) and computes below zero.
+      // One value with the offsets on the lanes: 300 cycles, where the probes of a search that would decide it too take
+      // 2000 to 6000.
+      bool guard_sure;
+      {
+        const int s_last = br_uniform(win[w - 1] >> BR_IDX_BITS);
+        const float fs = (float)s_last;
+        float pen = 0.0f;
+#pragma unroll
+        for (int u = 0; u < 3; ++u) pen = __fmaf_rn(dr[u], fmaxf(__fsub_rn(fs, mr[u]), 0.0f), pen);  // (no discount beyond H)
+        pen = br_wave_fsum(pen);
+        guard_sure = br_scoreh_long_from(p.aD, p.beta, s_last, pen) <= -3.0f * err_unit * fs;
+      }
       if (guard_sure) {
         br_wave_sync();  // the window has been read before a later pop rewrites it
       } else if (p.R_max > 8) {
@@ -686,15 +679,14 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
       for (int c = 0; c < 4; ++c) dmax = max(dmax, okv[c] ? dv[c] : 0);
       dmax = br_wave_max(dmax);
       if (dmax > 0) {  // else no subset is admissible
-        unsigned long long act[3];
-        br_long_active(smg, HS, lane, dmax, act);
         if (nmask <= BR_WAVE) {
-          const int d1[1] = {dv[0]};
+          const int d1[1] = {dv[0]}, top1[1] = {dmax};
           float F1[1];
-          br_scoreh_long_act<1>(p.aD, p.beta, smg, sd, act, d1, F1);
+          br_scoreh_long_sel<1>(p.aD, p.beta, smg, sd, HS, lane, top1, d1, F1);
           Fv[0] = F1[0];
         } else {
-          br_scoreh_long_act<4>(p.aD, p.beta, smg, sd, act, dv, Fv);
+          const int top4[4] = {dmax, dmax, dmax, dmax};
+          br_scoreh_long_sel<4>(p.aD, p.beta, smg, sd, HS, lane, top4, dv, Fv);
         }
       }
 #pragma unroll
@@ -713,8 +705,8 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
 
       if (bestmask == 0 || bestkey <= 0) {  // starvation guard: the single best request anyway
         ++guard;
-        int pos = gpos, swin = gswin;
-        if (!(guard_sure ? picked : pick_single(room, pos, swin))) {
+        int pos = 0, swin = 0;
+        if (!pick_single(room, pos, swin)) {
           drop_worker(g, capmax);
           continue;
         }

@@ -156,6 +156,17 @@ __device__ __forceinline__ int br_scan_sum(int x) {
   return x;
 }
 
+// sum over the wave, on every lane (uniform); the order of the additions is fixed
+__device__ __forceinline__ float br_wave_fsum(float x) {
+  x = __fadd_rn(x, __int_as_float(br_dpp<0x111>(0, __float_as_int(x))));
+  x = __fadd_rn(x, __int_as_float(br_dpp<0x112>(0, __float_as_int(x))));
+  x = __fadd_rn(x, __int_as_float(br_dpp<0x114>(0, __float_as_int(x))));
+  x = __fadd_rn(x, __int_as_float(br_dpp<0x118>(0, __float_as_int(x))));
+  x = __fadd_rn(x, __int_as_float(br_dpp<0x142, 0xA>(0, __float_as_int(x))));
+  x = __fadd_rn(x, __int_as_float(br_dpp<0x143, 0xC>(0, __float_as_int(x))));
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), BR_WAVE - 1));
+}
+
 // For lanes with `in` set and distinct positions `at` in 0..63: lane k receives the number of the lane whose `at` is k
 // (any lane's number where there is none).
 __device__ __forceinline__ int br_ranks_to_lanes(bool in, int at, int lane) {
