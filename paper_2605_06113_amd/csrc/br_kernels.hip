@@ -527,15 +527,14 @@ __global__ __launch_bounds__(256) void br_k_envelope(BrParams p) {
 // ------------------------------------------------------------------ F-score matrix + reductions
 // Scores every (waiting request, worker) pair on the step-start snapshot: eq. (br0-Fscore) in
 // int32 or eq. (brh-Fscore) in fp32.  Pass A maps lanes to requests (coalesced request-major
-// reads, worker margins broadcast from LDS), reduces over workers in registers (best worker per
-// request) and, if asked, stages the 64 x G tile in LDS so that the matrix leaves in full-width
-// contiguous stores.  Pass B maps lanes to (request sub-slot, worker) and keeps a running best
+// reads, worker margins broadcast from LDS) and reduces over workers in registers (best worker per
+// request).  Pass B maps lanes to (request sub-slot, worker) and keeps a running best
 // request per worker, combined across lanes and waves at the end.
 // LONG (horizons beyond BR_HP): the margins keep BR_HS(H) entries per worker, the discounts sit in LDS next
 // to them and a score loops over the offsets (br_scoreh_long), skipping the four-offset groups whose margins no
 // request of the tile reaches (clusters too large for br_k_score_long).
 template <bool BRH, bool LONG = false>
-__global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o, int want_tile) {
+__global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o) {
   extern __shared__ int lds[];
   const int G = p.G;
   const int HS = LONG ? BR_HS(p.H) : BR_HP + 1;  // margins per worker
@@ -545,7 +544,6 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o, 
   int *scap = sL + G;                    // [G]
   int *ss = scap + G;                    // [Q] prefill lengths of the waiting set
   int *cand = ss + p.Q;                  // [3][blockDim] candidates of pass B
-  int *tiles = cand + 3 * blockDim.x;    // [waves][64][G+1] when the matrix is written out
   // a cluster may be spread over gridDim.y blocks: block `split` scores its share of the requests
   // against all workers (pass A) and all requests against its share of the workers (pass B), so no
   // result needs combining across blocks
@@ -583,7 +581,6 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o, 
   }
 
   // pass A: one request per lane, loop over workers
-  int *tile = tiles + wave * (BR_WAVE * (G + 1));
   for (int t0 = (split * nw + wave) * BR_WAVE; t0 < qn; t0 += nsplit * nw * BR_WAVE) {
     const int i = t0 + lane;
     const bool valid = i < qn;
@@ -604,7 +601,6 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o, 
         for (int h = 0; h <= BR_HP; ++h) m[h] = (BRH || h == 0) ? sm[g * (BR_HP + 1) + h] : 0;
         key = br_score_key<BRH>(p, m, s);
       }
-      if (want_tile) tile[lane * (G + 1) + g] = key;
       const bool ok = scap[g] > 0 && (p.W <= 0 || sL[g] + s <= p.W);
       if (ok && key > bk) {
         bk = key;
@@ -612,15 +608,6 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o, 
       }
     }
     if (valid && o.best_g) o.best_g[(int64_t)inst * p.Q + i] = bg;
-    if (want_tile) {
-      const int rows = min(BR_WAVE, qn - t0);
-      int *Fi = (int *)o.F + ((int64_t)inst * p.Q + t0) * G;
-      for (int e = lane; e < rows * G; e += BR_WAVE) {
-        const int r = e / G, g = e - r * G;
-        const int key = tile[r * (G + 1) + g];
-        Fi[e] = BRH ? __float_as_int(br_unord(key)) : key;
-      }
-    }
   }
   if (o.best_g && split == 0)
     for (int i = qn + tid; i < p.Q; i += blockDim.x) o.best_g[(int64_t)inst * p.Q + i] = -1;
@@ -1155,12 +1142,11 @@ static void launch_score_wave(const BrParams &p, const BrArr &a, const BrOut &o,
 static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut &o, int *partials, hipStream_t st) {
   int waves = (p.Q + 63) / 64;  // one wave per tile of 64 requests, at most 8 waves
   waves = waves < 1 ? 1 : (waves > 8 ? 8 : waves);
-  const int want_tile = o.F != nullptr;
   const bool longh = p.H > BR_HP;
-  {  // few clusters, long queues, no matrix: a wave per (tile of requests, group of workers), then a combine
+  {  // few clusters, long queues: a wave per (tile of requests, group of workers), then a combine
     const int T = (p.Q + BR_WAVE - 1) / BR_WAVE;
     const int wpg = (p.G + BR_TILE_GROUPS - 1) / BR_TILE_GROUPS, WGN = (p.G + wpg - 1) / wpg;  // at most 4 groups
-    if (partials && !want_tile && p.N <= BR_SCORE_TILES_MAX_N && T * WGN >= 8 && !(p.H == 0 && p.Q <= 512)) {
+    if (partials && p.N <= BR_SCORE_TILES_MAX_N && T * WGN >= 8 && !(p.H == 0 && p.Q <= 512)) {
       const dim3 grid((unsigned)T, (unsigned)WGN, (unsigned)p.N), block(BR_WAVE);
       const int HS = longh ? BR_HS(p.H) : BR_HP + 1;
       const size_t lds = ((size_t)BR_TILE_WORKERS * HS + (longh ? HS + 4 : 0) + 2 * BR_TILE_WORKERS) * sizeof(int);
@@ -1177,7 +1163,7 @@ static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut 
     }
   }
   // Queues of up to 1024: one wave per cluster.
-  if (!longh && !want_tile && p.Q <= 1024) {
+  if (!longh && p.Q <= 1024) {
     if (p.H == 0)
       launch_score_wave<0>(p, a, o, st);
     else if (p.H <= BR_HP / 2)
@@ -1186,20 +1172,15 @@ static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut 
       launch_score_wave<BR_HP>(p, a, o, st);
     return;
   }
-  auto lds_words = [&](int w, bool tile) {
-    const size_t HS = longh ? BR_HS(p.H) : BR_HP + 1;
-    size_t words = (size_t)p.G * HS + (longh ? HS : 0) + 2 * (size_t)p.G + (size_t)p.Q + 3 * 64 * (size_t)w;
-    if (tile) words += (size_t)w * 64 * (size_t)(p.G + 1);
-    return words;
-  };
-  while (waves > 1 && lds_words(waves, want_tile) * 4 > 60 * 1024) --waves;  // stay within the default 64 KiB of LDS per block
-  size_t lds = lds_words(waves, want_tile) * 4;
+  // LDS: 48 KiB at most (64 workers at a horizon of 128, queues of 2048), within the default 64 KiB per block
+  const size_t HS = longh ? BR_HS(p.H) : BR_HP + 1;
+  const size_t lds = ((size_t)p.G * HS + (longh ? HS : 0) + 2 * (size_t)p.G + (size_t)p.Q + 3 * 64 * (size_t)waves) * sizeof(int);
   // few clusters: spread each over several blocks (at most 8, at most one per worker) to fill more CUs
   int nsplit = 1;
   while (nsplit < 8 && nsplit * 2 <= p.G && (int64_t)p.N * nsplit * 2 <= 512 && p.Q > 64 * waves * nsplit) nsplit *= 2;
   const dim3 grid((unsigned)p.N, (unsigned)nsplit);
-  if (longh && !want_tile && p.N > BR_SCORE_TILES_MAX_N) {  // room for all keys of a cluster: every pair is scored once
-    const size_t HS = BR_HS(p.H), Qp = ((size_t)p.Q + 63) & ~(size_t)63;
+  if (longh && p.N > BR_SCORE_TILES_MAX_N) {  // room for all keys of a cluster: every pair is scored once
+    const size_t Qp = ((size_t)p.Q + 63) & ~(size_t)63;
     const size_t words = ((size_t)p.G + 1) * HS + 2 * (size_t)p.G + Qp + Qp * (size_t)(p.G | 1);
     if (words * 4 <= 60 * 1024) {
       // eight waves per cluster while that leaves the batch resident at once
@@ -1208,9 +1189,9 @@ static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut 
     }
   }
   if (longh)
-    hipLaunchKernelGGL((br_k_score<true, true>), grid, dim3(64 * waves), lds, st, p, a, o, want_tile);
+    hipLaunchKernelGGL((br_k_score<true, true>), grid, dim3(64 * waves), lds, st, p, a, o);
   else if (p.H > 0)
-    hipLaunchKernelGGL(br_k_score<true>, grid, dim3(64 * waves), lds, st, p, a, o, want_tile);
+    hipLaunchKernelGGL(br_k_score<true>, grid, dim3(64 * waves), lds, st, p, a, o);
   else
-    hipLaunchKernelGGL(br_k_score<false>, grid, dim3(64 * waves), lds, st, p, a, o, want_tile);
+    hipLaunchKernelGGL(br_k_score<false>, grid, dim3(64 * waves), lds, st, p, a, o);
 }
