@@ -315,10 +315,12 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
   int32_t rc = BR_OK;
   if (p.H > 0) rc = enqueue(ctx, BR_K_PROJECT, [&] { br_launch_project(p, ctx->st); }, br);
   // The reductions ride along in the assignment launch (or on the helper wave of the split kernel) where one wave can do
-  // both: their sorted list is the round's, and a launch of their own would wait in line before it.
+  // both: their sorted list is the round's, and a launch of their own would wait in line before it.  Not for a few BR-H
+  // clusters whose pairs are too many for one wave (br_score_in_tiles).
   const bool best = o.best_g || o.best_i;
   const bool split = br_split_serves(p);
-  const bool together = best && p.R_max <= 8 && (p.H == 0 ? p.Q <= 1024 : (p.H <= BR_HP && p.Q <= 512));
+  const bool together = best && p.R_max <= 8 &&
+                        (p.H == 0 ? p.Q <= 1024 : (p.H <= BR_HP && p.Q <= 512 && !br_score_in_tiles(p)));
   BrOut first = o;  // what the score kernels write
   if (split || together) first.best_g = nullptr, first.best_i = nullptr;
   if (rc == BR_OK && (first.F || first.best_g || first.best_i))

@@ -589,6 +589,7 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o) 
     int tile_top[1] = {0};
     if constexpr (LONG) tile_top[0] = br_wave_max(valid ? s : 0);  // the longest request of the tile
     for (int g = 0; g < G; ++g) {
+      if (scap[g] <= 0) continue;  // (no candidate)
       int key;
       if constexpr (LONG) {
         const int dv[1] = {s};
@@ -601,7 +602,7 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o) 
         for (int h = 0; h <= BR_HP; ++h) m[h] = (BRH || h == 0) ? sm[g * (BR_HP + 1) + h] : 0;
         key = br_score_key<BRH>(p, m, s);
       }
-      const bool ok = scap[g] > 0 && (p.W <= 0 || sL[g] + s <= p.W);
+      const bool ok = p.W <= 0 || sL[g] + s <= p.W;
       if (ok && key > bk) {
         bk = key;
         bg = g;
@@ -879,6 +880,11 @@ __global__ __launch_bounds__(64) void br_k_score_tiles(BrParams p, BrArr a, int 
   s = min(max(s, 1), BR_MAX_S_DEV);
   int bk = BR_KEY_NONE, bg = -1;
   for (int gl = 0; gl < gn; ++gl) {
+    const size_t at = (size_t)tile * G + g0 + gl;
+    if (scap[gl] <= 0) {  // no candidate
+      if (lane == 0) pi_key[at] = BR_KEY_NONE, pi_s[at] = 0, pi_i[at] = -1;
+      continue;
+    }
     int key;
     if constexpr (LONG) {
       const int dv[1] = {s};
@@ -891,7 +897,7 @@ __global__ __launch_bounds__(64) void br_k_score_tiles(BrParams p, BrArr a, int 
       for (int h = 0; h <= BR_HP; ++h) m[h] = (BRH || h == 0) ? sm[gl * HS + h] : 0;
       key = br_score_key<BRH>(p, m, s);
     }
-    const bool ok = valid && scap[gl] > 0 && (p.W <= 0 || sL[gl] + s <= p.W);
+    const bool ok = valid && (p.W <= 0 || sL[gl] + s <= p.W);
     if (ok && key > bk) {  // workers in ascending order: the first best stays
       bk = key;
       bg = g0 + gl;
@@ -904,10 +910,7 @@ __global__ __launch_bounds__(64) void br_k_score_tiles(BrParams p, BrArr a, int 
       sbest = br_wave_max(kk == km ? s : -1);
       ibest = br_wave_min((kk == km && s == sbest) ? i : INT32_MAX);
     }
-    if (lane == 0) {
-      const size_t at = (size_t)tile * G + g0 + gl;
-      pi_key[at] = km, pi_s[at] = sbest, pi_i[at] = ibest;
-    }
+    if (lane == 0) pi_key[at] = km, pi_s[at] = sbest, pi_i[at] = ibest;
   }
   if (i < p.Q) {
     pg_key[(size_t)wg * p.Q + i] = bk;
@@ -1139,14 +1142,52 @@ static void launch_score_wave(const BrParams &p, const BrArr &a, const BrOut &o,
     hipLaunchKernelGGL((br_k_score_wave<16, HB>), grid, block, wpb * BR_LIST_WORDS(16) * sizeof(int), st, p, a, o);
 }
 
+// What best_g costs one wave that scores every (waiting request, worker with a free slot) pair of a BR-H cluster, every
+// worker having one: units of 64 requests x worker x offset (and two more for the score's frame), about a dozen cycles.
+static int br_pair_units(const BrParams &p) {
+  return ((p.Q + BR_WAVE - 1) / BR_WAVE) * p.G * ((p.H <= BR_HP / 2 ? BR_HP / 2 : BR_HP) + 2);
+}
+
+// Which kernel takes the reductions.  BR-0 needs no score per pair (br_score_wave.h): one wave up to queues of 1024.  For
+// BR-H one wave is bound by the pairs and more waves per cluster cost launches of their own, so what is faster depends on
+// how many workers have a free slot, which is not known here.  Whole pass (round and one decode step, B = 32..64), us,
+// workers full / a token watermark that keeps slots free everywhere:
+//   few clusters, Q <= 512        one wave       tiles
+//     N =  1  G =  8 H = 4 Q = 256   15 / 24        20 / 27       (192 units)
+//     N = 16  G = 32 H = 4 Q = 256   26 / 50        30 / 49       (768)
+//     N =  1  G = 16 H = 8 Q = 512   23 / 53        28 / 45       (1280)
+//     N = 16  G = 32 H = 4 Q = 512   32 / 62        35 / 54       (1536)
+//     N =  1  G = 64 H = 8 Q = 512   33 / 121       37 / 78       (5120)
+//   hence tiles from 1024 units on.  Queues of 513..1024: the tiles at any width (N = 1, G = 8, H = 4: 30 / 46 and 28 / 37).
+//   more clusters, queues of 513..1024   one wave    block of eight waves
+//     N =   64  G =  8 H = 4             45 / 55        56 / 62   (768)
+//     N =  256  G = 16 H = 4             49 / 67        55 / 65   (1536)
+//     N =  256  G = 16 H = 8             58 / 119       62 / 94   (2560)
+//     N =   64  G = 64 H = 8             73 / 186       75 / 124  (10240)
+//     N = 1024  G = 16 H = 8             79 / 132       90 / 120
+//     N = 2047  G = 16 H = 8            107 / 159      136 / 163
+//   hence the block from 2048 units on while its eight waves leave the batch resident at half of the chip (512 clusters).
+//   Queues of up to 512 stay on one wave there (N = 64, G = 64, H = 8: 50 / 129 and, in blocks, 63 / 110).
+#define BR_UNITS_TILES 1024
+#define BR_UNITS_BLOCK 2048
+#define BR_BLOCK_MAX_N 512
+
+bool br_score_in_tiles(const BrParams &p) {
+  const int T = (p.Q + BR_WAVE - 1) / BR_WAVE, wpg = (p.G + BR_TILE_GROUPS - 1) / BR_TILE_GROUPS, WGN = (p.G + wpg - 1) / wpg;
+  if (p.N > BR_SCORE_TILES_MAX_N || T * WGN < 8) return false;
+  if (p.H == 0) return p.Q > 512;
+  // (windows beyond 8 requests: no round's launch to ride in)
+  return p.H > BR_HP || p.Q > 512 || p.R_max > 8 || br_pair_units(p) >= BR_UNITS_TILES;
+}
+
 static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut &o, int *partials, hipStream_t st) {
   int waves = (p.Q + 63) / 64;  // one wave per tile of 64 requests, at most 8 waves
   waves = waves < 1 ? 1 : (waves > 8 ? 8 : waves);
   const bool longh = p.H > BR_HP;
-  {  // few clusters, long queues: a wave per (tile of requests, group of workers), then a combine
+  {  // a wave per (tile of requests, group of workers), then a combine
     const int T = (p.Q + BR_WAVE - 1) / BR_WAVE;
     const int wpg = (p.G + BR_TILE_GROUPS - 1) / BR_TILE_GROUPS, WGN = (p.G + wpg - 1) / wpg;  // at most 4 groups
-    if (partials && p.N <= BR_SCORE_TILES_MAX_N && T * WGN >= 8 && !(p.H == 0 && p.Q <= 512)) {
+    if (partials && br_score_in_tiles(p)) {
       const dim3 grid((unsigned)T, (unsigned)WGN, (unsigned)p.N), block(BR_WAVE);
       const int HS = longh ? BR_HS(p.H) : BR_HP + 1;
       const size_t lds = ((size_t)BR_TILE_WORKERS * HS + (longh ? HS + 4 : 0) + 2 * BR_TILE_WORKERS) * sizeof(int);
@@ -1162,8 +1203,8 @@ static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut 
       return;
     }
   }
-  // Queues of up to 1024: one wave per cluster.
-  if (!longh && p.Q <= 1024) {
+  const bool block = p.H > 0 && p.Q > 512 && p.N <= BR_BLOCK_MAX_N && br_pair_units(p) >= BR_UNITS_BLOCK;
+  if (!longh && p.Q <= 1024 && !block) {  // one wave per cluster
     if (p.H == 0)
       launch_score_wave<0>(p, a, o, st);
     else if (p.H <= BR_HP / 2)

@@ -16,6 +16,8 @@ void br_launch_discounts(const BrParams &p, float gamma, hipStream_t st);
 // `partials`: br_score_scratch_bytes() of device memory for the partial results of the tiled path, or null
 void br_launch_score(const BrParams &p, const BrArr &a, const BrOut &o, int *partials, hipStream_t st);
 size_t br_score_scratch_bytes(int N, int Q, int G);
+// the snapshot reductions of these shapes go to a wave per (tile of requests, group of workers)
+bool br_score_in_tiles(const BrParams &p);
 // the library's fixed scratch array (for the entry point that may not use workspace scratch): its size, and its
 // device address on the current device
 size_t br_static_scratch_bytes();

@@ -808,6 +808,48 @@ def test_host_calls_with_varying_rows(through_block, monkeypatch):
     r.close()
 
 
+def _score_launches(r, arr):
+    """Launches of a kernel for the snapshot alone in a round on host arrays (best_g / best_i, no matrix), and its outputs."""
+    r.profile_read()
+    r.profile(True)
+    out = r.route_step(arr, matrix=False)
+    r.profile(False)
+    return r.profile_read()["score"][1], out
+
+
+@pytest.mark.parametrize("N,G,H,Q,R_max,own", [
+    # up to 16 clusters, queues of up to 512: tiles from 1024 units (tiles x workers x offsets) on, one wave below
+    (16, 32, 4, 320, 4, False), (16, 32, 4, 321, 4, True), (16, 28, 4, 384, 4, False), (17, 32, 4, 321, 4, False),
+    (1, 64, 8, 128, 4, True), (2, 26, 8, 256, 4, True), (2, 25, 8, 256, 4, False), (3, 13, 5, 512, 8, True), (16, 64, 8, 512, 1, True),
+    # queues of 513..1024 (never in the round's launch): tiles, blocks of eight waves from 2048 units on, one wave
+    (16, 8, 4, 513, 4, True), (17, 38, 4, 513, 4, True), (17, 37, 4, 513, 4, True), (512, 16, 8, 1024, 4, True),
+    (513, 16, 8, 1024, 4, True), (40, 5, 3, 700, 4, True),
+    # windows beyond 8 requests, and BR-0 with them: one wave over queues of up to 1024
+    (20, 9, 6, 400, 12, True), (40, 6, 0, 700, 12, True), (18, 7, 0, 1024, 9, True),
+])
+def test_snapshot_reductions_by_their_work(N, G, H, Q, R_max, own):
+    """The kernels that share out the snapshot reductions, on both sides of the lines between them: workers all full, some
+    full, all free under a watermark, one cluster with nothing waiting; `own`: they come as a launch of their own."""
+    kw = dict(gate_pfin=0.5) if H else {}
+    for wm in (0, 9000):
+        cfg, init, arr = wl.random_case(610 + G + Q + wm, N=N, G=G, B=6, max_wait=Q, H=H, R_max=R_max, fill=0.6, token_watermark=wm, **kw)
+        init.n[0, ::2], init.n[-1] = cfg.B, cfg.B if wm == 0 else 1
+        arr.count[N // 2] = 0 if N > 2 else Q
+        arr.count[-1] = Q
+        _say(f"reductions N={N} G={G} H={H} Q={Q} R_max={R_max} W={wm}")
+        oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
+        for rnd in range(2):
+            a = arr if rnd == 0 else None
+            ref = oc.route_step(arr if rnd == 0 else wl.Arrivals(np.zeros_like(arr.count), arr.s, arr.o, arr.id, arr.pred))
+            launches, out = _score_launches(r, a)
+            assert launches == (1 if own else 0), (launches, own)
+            compare_outputs(ref, out, cfg, f"reductions r{rnd}")
+            oc.advance(2)
+            r.advance(2)
+        compare_state(oc, r.state(), cfg, "reductions")
+        r.close()
+
+
 def test_determinism():
     cfg, init, arr = wl.random_case(31, N=16, G=16, B=24, max_wait=256, H=4, gate_pfin=0.0, tie_heavy=True)
     outs = []
