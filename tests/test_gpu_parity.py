@@ -850,6 +850,47 @@ def test_snapshot_reductions_by_their_work(N, G, H, Q, R_max, own):
         r.close()
 
 
+@pytest.mark.parametrize("steps", [1, 2, 8, 9, 40])
+@pytest.mark.parametrize("G,Q", [(5, 200), (3, 512), (3, 700)])
+def test_large_batches_decode_orders(G, Q, steps):
+    """Batches beyond 2048 BR-0 clusters with decode steps in the round's launch: for few steps half of the waves stream
+    their lists before the round and append what they admit already advanced, the other half after it; requests that end
+    within the steps, more admissions per worker than the append's masks hold, a last block that is not full."""
+    N, B = 2051, 6
+    cfg, init, arr = wl.random_case(1200 + Q + steps, N=N, G=G, B=B, max_wait=Q, fill=0.7, n_wait=Q // 3)
+    few = slice(0, N, 7)
+    arr.count[few] = np.arange(len(arr.count[few])) % 9
+    arr.o[:, ::3] = 1 + arr.o[:, ::3] % (2 * steps)
+    _say(f"decode orders G={G} Q={Q} steps={steps}")
+    oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
+    for rnd in range(3):
+        ref = oc.route_step(arr)
+        out = r.route_step(arr, matrix=False, scores=rnd != 1, advance=steps)
+        if rnd == 1:
+            ref = {k: v for k, v in ref.items() if k in out}
+        compare_outputs(ref, out, cfg, f"decode orders r{rnd}")
+        oc.advance(steps)
+        compare_state(oc, r.state(), cfg, f"decode orders r{rnd}")
+    r.close()
+
+
+def test_large_batch_appends_beyond_the_masks():
+    """The same with workers that take more than 64 requests in a round (empty workers, short requests), some of which end
+    within the steps: the append's bit masks do not hold them."""
+    N, G, B, Q, steps = 2050, 2, 100, 200, 3
+    cfg, init, arr = wl.random_case(1300, N=N, G=G, B=B, max_wait=Q, fill=0.1, n_wait=Q, s_hi=300)
+    arr.o[:] = 1 + arr.o % 7
+    _say("append beyond the masks")
+    oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
+    ref = oc.route_step(arr)
+    out = r.route_step(arr, matrix=False, advance=steps)
+    compare_outputs(ref, out, cfg, "beyond the masks")
+    assert (np.bincount(ref["assign"][0][ref["assign"][0] >= 0], minlength=G) > 64).any()
+    oc.advance(steps)
+    compare_state(oc, r.state(), cfg, "beyond the masks")
+    r.close()
+
+
 def test_determinism():
     cfg, init, arr = wl.random_case(31, N=16, G=16, B=24, max_wait=256, H=4, gate_pfin=0.0, tie_heavy=True)
     outs = []
