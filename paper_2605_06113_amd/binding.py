@@ -237,6 +237,8 @@ class Router:
         c = make_config(cfg, stream=self.stream.cuda_stream, workspace=self.ws.data_ptr(),
                         workspace_bytes=self.ws.numel() * 4, **hargs)
         ini = None
+        self._host_blocks: Dict[tuple, _HostBlock] = {}  # given back by close()
+        self._host_lock = threading.Lock()
         self._keep = []
         if init is not None:
             if np.shape(init.n) != (self.N, self.G):
@@ -260,8 +262,6 @@ class Router:
         self.layout = lay
         self.Bs = lay.B_stride
         self._out: Dict[str, object] = {}
-        self._host_blocks: Dict[tuple, _HostBlock] = {}  # freed with the router
-        self._host_lock = threading.Lock()
 
     # -- outputs -------------------------------------------------------
     def alloc_outputs(self, scores: bool = True, matrix: bool = True) -> Dict[str, object]:
@@ -308,7 +308,9 @@ class Router:
 
     def route_step(self, arr=None, scores: bool = True, matrix: bool = True, advance: int = 0):
         """Host arrays in, numpy out (synchronises).  advance > 0 takes the fused entry point (round + that many
-        decode steps)."""
+        decode steps).  Calls of up to HOST_BLOCK_MAX_BYTES of arrivals and outputs pass them through pinned host memory
+        that the router keeps for the next call: a block per combination of outputs and row length (rounded up to a
+        power of two), HOST_BLOCKS of them at most, 64 MB in all, until close()."""
         cap = _check_arrivals(arr, self.Pq)[1] if arr is not None else 0
         if arr is None or len(arr.count) == self.N:
             with self._host_lock:  # a block is in use until the outputs have been copied out of it
@@ -434,6 +436,8 @@ class Router:
             self.stream.synchronize()
             self.lib.br_free(self.ctx)
             self.ctx = None
+            with self._host_lock:
+                self._host_blocks.clear()
 
     def __del__(self):
         try:

@@ -98,3 +98,17 @@ def test_binding_checks_sizes_before_anything_reaches_a_kernel():
     a.o = np.ones((2, 4), np.int32)
     with pytest.raises(binding.BrError):
         binding.DeviceArrivals(a, "cpu", 0)
+
+
+def test_close_gives_the_host_blocks_back():
+    """The pinned blocks of a router's host calls go when it is closed, after its stream has been waited for."""
+    import threading
+    log = []
+    r = object.__new__(binding.Router)
+    r.ctx, r._host_lock, r._host_blocks = C.c_void_p(1), threading.Lock(), {(16, True, True): object()}
+    r.stream = type("Stream", (), {"synchronize": lambda self: log.append(("wait", len(r._host_blocks)))})()
+    r.lib = type("Lib", (), {"br_free": lambda self, ctx: log.append(("free", len(r._host_blocks)))})()
+    r.close()
+    assert log == [("wait", 1), ("free", 1)] and not r._host_blocks and r.ctx is None
+    r.close()                                                                          # a second time: nothing to do
+    assert len(log) == 2
