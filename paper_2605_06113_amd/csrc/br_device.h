@@ -10,7 +10,6 @@
 #define BR_HL 128        // longest horizon; beyond BR_HP the per-offset state lives in LDS (the *_long kernels)
 #define BR_HS(H) (((H) + 4) & ~3)  // H + 1 offsets padded to whole 16-byte groups
 #define BR_LOW (-(1 << 30))  // "minus infinity" load of a lane that holds no worker
-#define BR_MAX_G_DEV 64
 #define BR_MAX_S_DEV 32768
 #define BR_IDX_BITS 11   // queue positions fit 11 bits (max_wait <= 2048)
 #define BR_SCORE_TILES_MAX_N 16    // up to this many clusters, long queues are scored a wave per (request tile, worker group)

@@ -1,5 +1,5 @@
 // Stage-2 subsets of a window of 9..16 requests when a subset may hold at most half of them: the admissible subsets
-// are enumerated themselves, from a constant list of all 16-bit masks ordered by (number of bits, value).
+// are enumerated themselves, from a constant list of the 16-bit masks of up to eight bits, ordered by (number of bits, value).
 //
 // Stage 2 runs where free slots are scarce, so the limit kmax = min(free slots of the worker, R_max) is usually a few:
 // of the 65535 masks of a window of 16, 696 have at most three bits.  Those need neither masks nor tables
@@ -15,19 +15,19 @@
 
 #include "br_device.h"
 
-#define BR_LIST_TABLE_WORDS 512  // LDS words of the two byte tables
+#define BR_LIST_MASKS 39203  // masks of at most eight bits, the empty one among them (br_list_serves asks for no more)
 
 // An entry holds the byte offsets of the two table reads, the upper byte's in the upper half: entries order as their
-// masks do.
+// masks do.  (157 KB; present in the code objects whose kernels search by it: br_assign_bigr and the br_assign_long ones.)
 struct BrMaskList {
-  unsigned v[65536];
+  unsigned v[BR_LIST_MASKS];
 };
 
 constexpr BrMaskList br_make_mask_list() {
   BrMaskList t{};
-  int at[17] = {};
+  int at[10] = {};
   int count = 1;  // C(16, c)
-  for (int c = 0; c < 16; ++c) {
+  for (int c = 0; c <= 8; ++c) {
     at[c + 1] = at[c] + count;
     count = count * (16 - c) / (c + 1);
   }
@@ -36,12 +36,13 @@ constexpr BrMaskList br_make_mask_list() {
     b = (b & 0x3333) + ((b >> 2) & 0x3333);
     b = (b + (b >> 4)) & 0x0f0f;
     b = (b + (b >> 8)) & 0x1f;
-    t.v[at[b]++] = (unsigned)((256 + (v >> 8)) * 4) << 16 | (unsigned)((v & 255) * 4);
+    if (b <= 8) t.v[at[b]++] = (unsigned)((256 + (v >> 8)) * 4) << 16 | (unsigned)((v & 255) * 4);
   }
   return t;
 }
 
 static __device__ constexpr BrMaskList br_mask_list = br_make_mask_list();
+static_assert(br_mask_list.v[BR_LIST_MASKS - 1] == ((256u + 255u) * 4u << 16 | 0u), "eight bits: the largest mask is the last one");
 
 __device__ __forceinline__ int br_list_mask(unsigned v) { return (int)(((v >> 18) - 256u) << 8 | (v & 0xffffu) >> 2); }
 
