@@ -309,7 +309,7 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
   // as two launches).  Everywhere else they follow as a launch of their own, which streams the lists with more loads in
   // flight than the round's waves can hold (BR-H, H = 4, G = 16: 512 clusters 38 us against 46, 4096 clusters 78 against
   // 76; one cluster, H = 8: 26 against 33; BR-0, 512 clusters with queues of 1024: 40 against 44).
-  const bool fused_adv = p.H == 0 && p.R_max <= 8 && (br_split_shape(p) || p.N >= BR_SCORE_WAVE_MIN_N);
+  const bool fused_adv = p.H == 0 && p.R_max <= 8 && (br_split_shape(p) || p.N >= BR_FULL_BATCH_N);
   const bool split_adv = adv_t > 0 && !fused_adv;
   p.adv_t = split_adv ? 0 : adv_t;
   int32_t rc = BR_OK;

@@ -902,9 +902,8 @@ __global__ __launch_bounds__(256, (HB > 0 && E == 8 && !BIGR) ? 4 : 1) void br_k
     br_assign_body<E, HB, ADV, false, BIGR>(p, a, o, lds_all + w * WORDS, (int)(blockIdx.x * (blockDim.x >> 6)) + w);
 }
 
-// Clusters of one wave each per block: four, so that the chip's block slots do not cap a large batch; one where the batch
-// leaves room, so that the clusters spread evenly over the SIMDs.
-static inline int br_clusters_per_block(int N, int E) { return E <= 8 && N > 2048 ? 4 : 1; }
+// Clusters of one wave each per block (one where the queues are long and so the LDS of a cluster is large).
+static inline int br_clusters_per_block(int N, int E) { return E <= 8 ? br_waves_per_block(N) : 1; }
 
 template <int E, int HB, bool BIGR = false>
 static void br_launch_assign_one(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {

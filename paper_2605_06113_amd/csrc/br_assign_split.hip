@@ -45,7 +45,7 @@ static void launch_split(const BrParams &p, const BrArr &a, const BrOut &o, hipS
 // 134 us for the one-wave kernel; 163 us with five waves per SIMD and one helper for four clusters, which then
 // is the last to finish).
 bool br_split_shape(const BrParams &p) {
-  return p.H == 0 && p.R_max <= 8 && p.Q <= 512 && p.N < BR_SCORE_WAVE_MIN_N;
+  return p.H == 0 && p.R_max <= 8 && p.Q <= 512 && p.N < BR_FULL_BATCH_N;
 }
 
 bool br_split_serves(const BrParams &p) { return p.adv_t > 0 && br_split_shape(p); }

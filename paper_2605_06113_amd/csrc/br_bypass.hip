@@ -126,6 +126,6 @@ __global__ __launch_bounds__(256) void br_k_bypass(BrParams p, BrArr a, BrOut o)
 }
 
 void br_launch_bypass(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
-  const int wpb = p.N > 2048 ? 4 : 1;  // small batches spread over the CUs
+  const int wpb = br_waves_per_block(p.N);
   hipLaunchKernelGGL(br_k_bypass, dim3((unsigned)((p.N + wpb - 1) / wpb)), dim3(BR_WAVE * wpb), 0, st, p, a, o);
 }

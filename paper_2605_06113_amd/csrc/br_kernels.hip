@@ -1132,7 +1132,7 @@ void br_launch_score(const BrParams &p, const BrArr &a, const BrOut &o, int *par
 
 template <int HB>
 static void launch_score_wave(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
-  const int wpb = p.N >= 1024 ? 4 : 1;  // small batches spread over the CUs
+  const int wpb = br_waves_per_block(p.N);
   const dim3 grid((unsigned)((p.N + wpb - 1) / wpb)), block(BR_WAVE * wpb);
   if (p.Q <= 256)
     hipLaunchKernelGGL((br_k_score_wave<4, HB>), grid, block, wpb * BR_LIST_WORDS(4) * sizeof(int), st, p, a, o);

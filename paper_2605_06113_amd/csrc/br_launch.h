@@ -5,6 +5,10 @@
 
 #include "br_device.h"
 
+// One wave per cluster: waves per block.  768..4096 clusters take the same time either way (BR-0 and BR-H rounds,
+// pool-bypass, reductions: within 1 us of 14..80); four keep larger batches within the chip's block slots.
+static inline int br_waves_per_block(int N) { return N > BR_FULL_BATCH_N ? 4 : 1; }
+
 // `pol`: per-cluster state of the comparison policies (round-robin cursor, draws made), [N][2]
 void br_launch_clear(const BrParams &p, int *pol, hipStream_t st);
 void br_launch_load_init(const BrParams &p, const int32_t *n, const int32_t *kv, const int32_t *rem, const float *pred,
