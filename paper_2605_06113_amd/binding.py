@@ -163,8 +163,8 @@ class DeviceArrivals:
 
 # Host calls (Router.route_step) of up to this many bytes of arrivals and outputs go through a pinned block of the
 # router's: the kernels read the arrivals from it and write the outputs to it, so that a call is its launches and one wait
-# (one cluster, every output: 49 us; with a tensor and a copy per array 215 us).  Faster at every size tried, up to 42 MB;
-# the bound keeps the pinned memory of a router small (HOST_BLOCKS of them at most).
+# (one cluster, G=16, 256 waiting, every output: 39 us; with a tensor and a copy per array 232 us).  Faster at every size
+# tried, up to 42 MB; the bound keeps the pinned memory of a router small (HOST_BLOCKS of them at most).
 HOST_BLOCK_MAX_BYTES = 1 << 24
 HOST_BLOCKS = 4
 
@@ -300,7 +300,7 @@ class Router:
         return int(self.lib.br_route_step_static(self.ctx, C.byref(a) if a is not None else None, C.byref(o)))
 
     def route_advance_device(self, darr: Optional[DeviceArrivals], out, n_steps: int = 1) -> None:
-        """Enqueue one round and n_steps decode steps as one launch; no synchronisation."""
+        """Enqueue one round and n_steps decode steps (one launch for BR-0 where that pays); no synchronisation."""
         a = darr.struct() if darr is not None else None
         o = self.out_struct(out)
         _check(self.lib.br_route_advance(self.ctx, C.byref(a) if a is not None else None, C.byref(o), int(n_steps)),

@@ -8,9 +8,13 @@
 // assignment on the same sorted list (K4, and the decode step with ADV).
 // ADV: for a few decode steps, half of the waves apply them to their lists as they stand before the round (and append
 // what they admit already advanced), the other half after it.  With one order for all, the memory idles while every wave
-// routes and the issue slots idle while every wave streams.  4096 clusters, G = 16, B = 144: one step, 6 admissions 52 -> 49
-// us.  After many steps rounds are long (a burst of 246 admissions in 48 steps) and the streaming hides in their
-// tail anyway: 112 us, 115 with both orders.
+// routes and the issue slots idle while every wave streams.  After many steps rounds are long (many admissions) and the
+// streaming hides in their tail anyway.  Both orders / one order, us, offered load 1.3 times what the workers serve:
+//   4096 clusters, G = 16, B = 144    1 step 43 / 43   4: 62 / 61    8: 82 / 80     16: 98 / 97     48: 119 / 117
+//   2048 clusters, G = 16, B = 144    1 step 33 / 34   4: 49 / 49    8: 63 / 64     16: 76 / 76     48: 93 / 92
+//   4096 clusters, G =  8, B = 64     1 step 22 / 23   4: 31 / 32    8: 40 / 40     16: 52 / 53     48: 69 / 68
+//   4096 clusters, G = 32, B = 96     1 step 62 / 64   4: 95 / 95    8: 120 / 121   16: 164 / 164   48: 188 / 188
+// At 0.7 times the load both orders are ahead by up to 1.3 us up to 8 steps (first shape: 44 / 43 at 8 steps).
 template <int E, bool ADV>
 __global__ __launch_bounds__(256) void br_k_route(BrParams p, BrArr a, BrOut o) {
   extern __shared__ int lds_all[];

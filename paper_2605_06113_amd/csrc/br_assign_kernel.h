@@ -913,9 +913,14 @@ static void br_launch_assign_one(const BrParams &p, const BrArr &a, const BrOut 
   const dim3 grid((unsigned)((p.N + wpb - 1) / wpb)), block(E == 32 ? 4 * BR_WAVE : BR_WAVE * wpb);
   // (decode steps ride along for BR-0 with windows of up to 8 requests only; elsewhere the caller launches the decode kernel)
   if constexpr (BIGR) {
-    // windows beyond 8 requests on a batch that leaves room on the chip (registers allow about 4 / 3 / 2 waves per
-    // SIMD for queues of up to 256 / 512 / 1024, one less for BR-H): a block of four waves per cluster, the searches shared
-    // (BR-0 up to a window of 16 has none that is long enough)
+    // windows beyond 8 requests on a batch that leaves room on the chip: a block of four waves per cluster, the searches
+    // shared (BR-0 up to a window of 16 has none that is long enough).  Registers let two of these waves share a SIMD, so
+    // up to 512 clusters are resident at once; beyond, what a search costs decides.  Whole pass, us, shared / one wave each
+    // (G = 8, B = 48, 5 pops a round), queues of 256 | 1024:
+    //   H = 4, window 12    512 clusters 42 / 42 | 58 / 60      768: 57 / 45 | 83 / 65      1024: 64 / 46 | 98 / 68
+    //   H = 8, window 16    512 clusters 50 / 75 | 69 / 97      768: 68 / 83 | 96 / 105     1024: 75 / 102 | 113 / 111
+    //   H = 0, window 24    512 clusters 229 / 438 | 193 / 510  768: 225 / 444 | 224 / 558  1024: 285 / 513 | 289 / 574
+    // The lines: 768 / 512 / 256 clusters for BR-H with queues of up to 256 / 512 / 1024, 1024 / 768 / 512 for reachable sums.
     const long long room = 1024ll * max(1, (E == 4 ? 4 : E == 8 ? 3 : 2) - (HB > 0 ? 1 : 0));
     if ((HB > 0 || dp) && E <= 16 && (long long)p.N * 4 <= room) {
       const size_t lds1 = ((size_t)BR_ROUND_WORDS(E, true) + 32 + (dp ? BR_DP_LDS_WORDS : 0)) * sizeof(int);

@@ -1,6 +1,6 @@
 // Round and decode steps of a BR-0 cluster on two waves (br_route_advance for queues of up to 512 entries,
 // windows of up to 8 requests, small batches): a block holds RPB waves that each run the round of one cluster
-// (Alg. BR-0) and NH helper waves that, meanwhile, compute the snapshot reductions of those clusters (if asked for) and applies the
+// (Alg. BR-0) and NH helper waves that, meanwhile, compute the snapshot reductions of those clusters (if asked for) and apply the
 // decode steps (Sec. 2.2) to their lists as they stand at the start of the step.  The wave that ran the round
 // appends its admissions behind the old survivors, already advanced (br_assign_epilogue_split).  The decode step
 // streams the lists from HBM while the rounds, dependent chains that leave the memory system idle, are still
@@ -38,12 +38,12 @@ static void launch_split(const BrParams &p, const BrArr &a, const BrOut &o, hipS
   hipLaunchKernelGGL((br_k_route_split<E, RPB, NH>), grid, block, lds, st, p, a, o);
 }
 
-// For batches that leave most SIMDs to a single wave (fewer clusters than two waves per SIMD): one round and one
-// helper per block.  Larger batches keep the one-wave kernels: with four or more waves per SIMD the decode step
-// already overlaps other clusters' rounds, and a block of four rounds and two helpers (six waves per SIMD) has to
-// fit 80 registers, which spills in the round's loops (measured on 4096 clusters of the c4 shape: 153 us against
-// 134 us for the one-wave kernel; 163 us with five waves per SIMD and one helper for four clusters, which then
-// is the last to finish).
+// For batches below two one-wave clusters per SIMD: one round and one helper per block.  Beyond, with four or more waves
+// per SIMD, the decode step overlaps other clusters' rounds on the one-wave kernels as well.  Whole pass with reductions,
+// us, two waves / one wave per cluster (G = 16):
+//   B = 96, 256 waiting, one step      1024 clusters 19 / 27   2047: 24 / 31   3072: 29 / 35   4096: 39 / 38
+//   B = 144, 246 admitted, 48 steps    1024 clusters 66 / 76   2047: 80 / 88   3072: 95 / 98   4096: 116 / 111
+// (two waves are ahead up to about 3500 clusters: the line is on the safe side).
 bool br_split_shape(const BrParams &p) {
   return p.H == 0 && p.R_max <= 8 && p.Q <= 512 && p.N < BR_FULL_BATCH_N;
 }

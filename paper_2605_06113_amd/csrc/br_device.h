@@ -611,8 +611,9 @@ __device__ __forceinline__ void br_adv_load(const int32_t *kl, const int32_t *rl
 // Prediction rows of a list's slots [from, to) of one chunk move with their requests: slot j's row (P floats, taken V at
 // a time) goes to slot map[j - chunk0] (< 0: it left).  Lanes walk the rows as contiguous memory, 4 x 64 units requested
 // before the first is stored; destinations lie at or below their sources, so no store reaches a source not yet read.
-// (A lane that moved its own four slots' rows float by float made the decode step of 4096 clusters with rows of four
-// hazards, 40 steps, every list losing requests, take 277 us; 126 us so.)
+// (When lists of 96 slots still came this way, 4096 clusters, G = 32, rows of four hazards, 40 steps, every list losing
+// requests: 277 us with a lane moving its own four slots' rows float by float, 126 us so.  Lists of up to 256 slots are now
+// taken by br_k_advance_seg.)
 template <class V>
 __device__ __forceinline__ void br_rows_move_as(float *pw, int P, const short *map, int chunk0, int from, int to, int lane) {
   const int upr = P / (int)(sizeof(V) / sizeof(float));  // units per row, 1..8
