@@ -234,8 +234,8 @@ int32_t br_advance_decode(br_ctx *ctx, int32_t n_steps);
  * results: same outputs (written as br_route_step writes them, statistics describe the state
  * right after the round) and same workspace contents afterwards as the two calls in sequence.
  * For BR-0 with candidate windows of up to 8 requests the assignment launch itself applies the decode steps
- * where that pays (batches of 2048 clusters and more: the wave that has routed a cluster goes on to that cluster's
- * lists, so clusters that finish their round early stream their lists while others are still routing; smaller
+ * where that pays (batches of 2048 clusters and more: the wave that routes a cluster also applies them to that
+ * cluster's lists, so that some clusters stream their lists while others are routing; smaller
  * batches with queues of up to 512: a second wave per cluster); otherwise the decode kernel follows as a launch of
  * its own on the same stream.
  * Arguments, ownership and errors as for br_route_step; n_steps >= 0 (0: identical to
