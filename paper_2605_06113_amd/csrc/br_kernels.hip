@@ -669,7 +669,7 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o) 
 
 // K2 + K3 for long horizons, a cluster per block: a score costs 3 (H + 1) operations here, so every pair is scored once,
 // and the (tile of 64 requests, worker) pairs are dealt out to the block's waves whatever the queue length (with a wave
-// per tile most waves of a short queue idled: 2048 clusters, G = 8, H = 80, 84 of 256 waiting: 31 us -> 21 us).  The keys
+// per tile most waves of a short queue idled: 2048 clusters, G = 8, H = 80, 101 of 256 waiting: 28 us -> 14 us).  The keys
 // meet in LDS; best worker per request with threads mapped to requests, best request per worker with a wave per worker
 // (the tie rules of br_k_score).  Groups of four offsets whose margins no request of the tile reaches are skipped.
 __global__ __launch_bounds__(512) void br_k_score_long(BrParams p, BrArr a, BrOut o) {

@@ -31,7 +31,7 @@ void br_launch_assign(const BrParams &p, const BrArr &a, const BrOut &o, hipStre
 void br_launch_assign_long(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
 // waves per cluster of that kernel (1, 2 or 4)
 int br_long_waves(const BrParams &p);
-// candidate windows of 9..16 requests (H <= BR_HP); no fused decode steps
+// candidate windows of 9..32 requests (H <= BR_HP); no fused decode steps
 void br_launch_assign_bigr(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
 void br_launch_assign_br0(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
 // BR-H, H <= 4
@@ -45,7 +45,7 @@ void br_launch_bypass(const BrParams &p, const BrArr &a, const BrOut &o, hipStre
 void br_launch_baseline(const BrParams &p, const BrArr &a, const BrOut &o, int *pol, int policy, unsigned long long seed,
                         hipStream_t st);
 // BR-0 with decode steps, queues of up to 512, windows of up to 8: round and decode steps on two waves per cluster;
-// the snapshot reductions (best_g / best_i, when asked for without the matrix) ride on the helper wave
+// the snapshot reductions (best_g / best_i, where asked for) ride on the helper wave
 bool br_split_shape(const BrParams &p);   // a shape it serves (when there are decode steps)
 bool br_split_serves(const BrParams &p);
 void br_launch_route_split(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
