@@ -1150,34 +1150,33 @@ static int br_pair_units(const BrParams &p) {
 
 // Which kernel takes the reductions.  BR-0 needs no score per pair (br_score_wave.h): one wave up to queues of 1024.  For
 // BR-H one wave is bound by the pairs and more waves per cluster cost launches of their own, so what is faster depends on
-// how many workers have a free slot, which is not known here.  Whole pass (round and one decode step, B = 32..64), us,
-// workers full / a token watermark that keeps slots free everywhere:
-//   few clusters, Q <= 512        one wave       tiles
-//     N =  1  G =  8 H = 4 Q = 256   15 / 24        20 / 27       (192 units)
-//     N = 16  G = 32 H = 4 Q = 256   26 / 50        30 / 49       (768)
-//     N =  1  G = 16 H = 8 Q = 512   23 / 53        28 / 45       (1280)
-//     N = 16  G = 32 H = 4 Q = 512   32 / 62        35 / 54       (1536)
-//     N =  1  G = 64 H = 8 Q = 512   33 / 121       37 / 78       (5120)
-//   hence tiles from 1024 units on.  Queues of 513..1024: the tiles at any width (N = 1, G = 8, H = 4: 30 / 46 and 28 / 37).
-//   more clusters, queues of 513..1024   one wave    block of eight waves
-//     N =   64  G =  8 H = 4             45 / 55        56 / 62   (768)
-//     N =  256  G = 16 H = 4             49 / 67        55 / 65   (1536)
-//     N =  256  G = 16 H = 8             58 / 119       62 / 94   (2560)
-//     N =   64  G = 64 H = 8             73 / 186       75 / 124  (10240)
-//     N = 1024  G = 16 H = 8             79 / 132       90 / 120
-//     N = 2047  G = 16 H = 8            107 / 159      136 / 163
-//   hence the block from 2048 units on while its eight waves leave the batch resident at half of the chip (512 clusters).
-//   Queues of up to 512 stay on one wave there (N = 64, G = 64, H = 8: 50 / 129 and, in blocks, 63 / 110).
-#define BR_UNITS_TILES 1024
-#define BR_UNITS_BLOCK 2048
-#define BR_BLOCK_MAX_N 512
+// how many workers have a free slot and how many requests wait, which is not known here.  Whole pass (round and one decode
+// step), us: workers full / queue nearly empty / a token watermark that keeps slots free everywhere and the queue full.
+//   few clusters, Q <= 512             one wave          tiles
+//     N =  1  G = 16  H = 8  Q = 512   25 / 25 / 53      30 / 26 / 44    (1280 units)
+//     N = 16  G = 32  H = 4  Q = 512   32 / 27 / 62      36 / 30 / 54    (1536)
+//     N =  1  G = 64  H = 8  Q = 256   30 / 36 / 89      34 / 35 / 73    (2560)
+//     N = 16  G = 32  H = 8  Q = 512   40 / 34 / 79      40 / 35 / 61    (2560)
+//     N =  1  G = 64  H = 8  Q = 512   36 / 40 / 121     38 / 36 / 79    (5120)
+//   hence tiles from 2048 units on.  Queues of 513..1024: the tiles at any width (N = 1, G = 8, H = 4: 30 / - / 46 and 28 / - / 37).
+//   more clusters, Q = 1024            one wave          block of eight waves
+//     N =  64  G =  8  H = 4           45 / - / 55       56 / - / 62     (768)
+//     N = 256  G = 16  H = 4           49 / - / 67       55 / - / 65     (1536)
+//     N = 256  G = 16  H = 8           58 / - / 119      62 / - / 94     (2560)
+//     N =  64  G = 64  H = 8           74 / 50 / 185     74 / 54 / 123   (10240)
+//     N = 256  G = 64  H = 8           85 / 56 / 193     90 / 61 / 138
+//     N = 512  G = 64  H = 8           89 / - / 149      115 / - / 141
+//   hence the block from 2048 units on, for up to a block per CU.  Queues of up to 512 stay on one wave there (N = 64, G = 64,
+//   H = 8, Q = 512: 50 / 47 / 129 and, in blocks, 63 / 52 / 109).
+#define BR_UNITS_ONE_WAVE 2048
+#define BR_BLOCK_MAX_N 256
 
 bool br_score_in_tiles(const BrParams &p) {
   const int T = (p.Q + BR_WAVE - 1) / BR_WAVE, wpg = (p.G + BR_TILE_GROUPS - 1) / BR_TILE_GROUPS, WGN = (p.G + wpg - 1) / wpg;
   if (p.N > BR_SCORE_TILES_MAX_N || T * WGN < 8) return false;
   if (p.H == 0) return p.Q > 512;
   // (windows beyond 8 requests: no round's launch to ride in)
-  return p.H > BR_HP || p.Q > 512 || p.R_max > 8 || br_pair_units(p) >= BR_UNITS_TILES;
+  return p.H > BR_HP || p.Q > 512 || p.R_max > 8 || br_pair_units(p) >= BR_UNITS_ONE_WAVE;
 }
 
 static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut &o, int *partials, hipStream_t st) {
@@ -1203,7 +1202,7 @@ static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut 
       return;
     }
   }
-  const bool block = p.H > 0 && p.Q > 512 && p.N <= BR_BLOCK_MAX_N && br_pair_units(p) >= BR_UNITS_BLOCK;
+  const bool block = p.H > 0 && p.Q > 512 && p.N <= BR_BLOCK_MAX_N && br_pair_units(p) >= BR_UNITS_ONE_WAVE;
   if (!longh && p.Q <= 1024 && !block) {  // one wave per cluster
     if (p.H == 0)
       launch_score_wave<0>(p, a, o, st);
