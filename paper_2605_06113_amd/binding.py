@@ -311,8 +311,10 @@ class Router:
         decode steps).  Calls of up to HOST_BLOCK_MAX_BYTES of arrivals and outputs pass them through pinned host memory
         that the router keeps for the next call: a block per combination of outputs and row length (rounded up to a
         power of two), HOST_BLOCKS of them at most, 64 MB in all, until close()."""
-        cap = _check_arrivals(arr, self.Pq)[1] if arr is not None else 0
-        if arr is None or len(arr.count) == self.N:
+        rows, cap = _check_arrivals(arr, self.Pq) if arr is not None else (self.N, 0)
+        if rows < self.N:  # (the kernels read a row per cluster)
+            raise BrError(f"arrivals for {rows} clusters, the router has {self.N}")
+        if rows == self.N:
             with self._host_lock:  # a block is in use until the outputs have been copied out of it
                 block = self._host_block(cap, scores, matrix)
                 if block is not None:

@@ -112,3 +112,14 @@ def test_close_gives_the_host_blocks_back():
     assert log == [("wait", 1), ("free", 1)] and not r._host_blocks and r.ctx is None
     r.close()                                                                          # a second time: nothing to do
     assert len(log) == 2
+
+
+def test_arrivals_for_too_few_clusters_are_refused():
+    """A round on host arrays reads a row of arrivals per cluster: fewer rows are refused before anything is enqueued."""
+    import numpy as np
+    r = object.__new__(binding.Router)
+    r.N, r.Pq, r.ctx = 3, 0, None
+    a = wl.Arrivals(count=np.zeros(2, np.int32), s=np.ones((2, 5), np.int32), o=np.ones((2, 5), np.int32),
+                    id=np.zeros((2, 5), np.int32), pred=None)
+    with pytest.raises(binding.BrError):
+        r.route_step(a)
