@@ -668,31 +668,44 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o) 
 }
 
 // K2 + K3 for long horizons, a cluster per block: a score costs 3 (H + 1) operations here, so every pair is scored once,
-// and the (tile of 64 requests, worker) pairs are dealt out to the block's waves whatever the queue length (with a wave
-// per tile most waves of a short queue idled: 2048 clusters, G = 8, H = 80, 101 of 256 waiting: 28 us -> 14 us).  The keys
-// meet in LDS; best worker per request with threads mapped to requests, best request per worker with a wave per worker
-// (the tie rules of br_k_score).  Groups of four offsets whose margins no request of the tile reaches are skipped.
+// pairs of a worker without a free slot (no candidate on either side) not at all, and the (tile of 64 requests, worker)
+// pairs left are dealt out to the block's waves whatever the queue length.  The keys meet in LDS, a column per worker
+// with a free slot; best worker per request with threads mapped to requests, best request per worker with a wave per
+// worker (the tie rules of br_k_score).  Groups of four offsets whose margins no request of the tile reaches are skipped.
+// Overloaded clusters are nearly full most of the time: 2048 clusters, G = 8, H = 80, 135 waiting, 1.2 free slots each:
+// whole pass 89.6 us with every worker scored, 75.1 so.
 __global__ __launch_bounds__(512) void br_k_score_long(BrParams p, BrArr a, BrOut o) {
   extern __shared__ int lds[];
   const int G = p.G, HS = BR_HS(p.H), KS = G | 1;
   float *sm = (float *)lds;              // [G][HS] margins
   float *sd = sm + G * HS;               // [HS] discounts
   int *sL = (int *)(sd + HS);            // [G] loads
-  int *scap = sL + G;                    // [G] free slots
-  int *ss = scap + G;                    // [Q] prefill lengths, then zeros to whole tiles
-  int *keys = ss + ((p.Q + 63) & ~63);   // [Q'][KS]
+  int *sf = sL + G;                      // [G] the workers with a free slot, ascending
+  int *ss = sf + G;                      // [Q] prefill lengths, then zeros to whole tiles
+  int *keys = ss + ((p.Q + 63) & ~63);   // [Q'][KS] by position in sf
   const int inst = blockIdx.x, tid = threadIdx.x, lane = br_lane(), wave = tid >> 6, nw = blockDim.x >> 6;
+  const int64_t wrow = (int64_t)inst * G;
   const int q0 = min(max(p.qlen[inst], 0), p.Q);
   int cnt = a.count ? a.count[inst] : 0;
   cnt = min(max(cnt, 0), a.arr_cap);
   const int qn = q0 + min(cnt, p.Q - q0);
-  if (tid < G) {
-    sL[tid] = p.L[(int64_t)inst * G + tid];
-    scap[tid] = p.B - p.n[(int64_t)inst * G + tid];
+  // (every wave reads the counts: what is free decides what it does next)
+  const int n_raw = p.n[wrow + min(lane, G - 1)];
+  const unsigned long long freem = br_ballot(lane < G && n_raw < p.B);
+  const int nf = __builtin_popcountll(freem);
+  if (nf == 0 || qn == 0) {
+    if (o.best_g)
+      for (int i = tid; i < p.Q; i += blockDim.x) o.best_g[(int64_t)inst * p.Q + i] = -1;
+    if (o.best_i && tid < G) o.best_i[wrow + tid] = -1;
+    return;
   }
-  for (int e = tid; e < G * HS; e += blockDim.x) {
-    const int g = e / HS, h = e - g * HS;
-    sm[e] = h <= p.H ? (float)p.mh[((int64_t)inst * G + g) * (p.H + 1) + h] : 0.0f;
+  if (tid < G) {
+    sL[tid] = p.L[wrow + tid];
+    if ((freem >> tid) & 1ull) sf[br_rank_below(freem)] = tid;
+  }
+  for (int g = wave; g < G; g += nw) {
+    if (!((freem >> g) & 1ull)) continue;
+    for (int h = lane; h < HS; h += BR_WAVE) sm[g * HS + h] = h <= p.H ? (float)p.mh[(wrow + g) * (p.H + 1) + h] : 0.0f;
   }
   for (int h = tid; h < HS; h += blockDim.x) sd[h] = p.dl[h];
   for (int i = tid; i < ((qn + 63) & ~63); i += blockDim.x) {
@@ -700,14 +713,14 @@ __global__ __launch_bounds__(512) void br_k_score_long(BrParams p, BrArr a, BrOu
     ss[i] = i < qn ? min(max(i < q0 ? p.qs[qrow + i] : a.s[arow + (i - q0)], 1), BR_MAX_S_DEV) : 0;
   }
   __syncthreads();
-  const int items = ((qn + 63) >> 6) * G;
+  const int items = ((qn + 63) >> 6) * nf;
   for (int it = wave; it < items; it += nw) {
-    const int t = it / G, g = it - t * G;
+    const int t = it / nf, c = it - t * nf, g = br_uniform(sf[c]);
     const int s[1] = {ss[t * BR_WAVE + lane]};
     const int top[1] = {br_wave_max(s[0])};
     float F[1];
     br_scoreh_long_sel<1>(p.aD, p.beta, sm + g * HS, sd, HS, lane, top, s, F);
-    keys[(t * BR_WAVE + lane) * KS + g] = br_ord(F[0]);
+    keys[(t * BR_WAVE + lane) * KS + c] = br_ord(F[0]);
   }
   __syncthreads();
   if (o.best_g) {
@@ -715,29 +728,31 @@ __global__ __launch_bounds__(512) void br_k_score_long(BrParams p, BrArr a, BrOu
       int bk = BR_KEY_NONE, bg = -1;
       if (i < qn) {
         const int s = ss[i];
-        for (int g = 0; g < G; ++g) {
-          const int key = keys[i * KS + g];
-          if (scap[g] > 0 && (p.W <= 0 || sL[g] + s <= p.W) && key > bk) bk = key, bg = g;
+        for (int c = 0; c < nf; ++c) {
+          const int key = keys[i * KS + c], g = sf[c];
+          if ((p.W <= 0 || sL[g] + s <= p.W) && key > bk) bk = key, bg = g;
         }
       }
       o.best_g[(int64_t)inst * p.Q + i] = bg;
     }
   }
   if (o.best_i) {
-    for (int g = wave; g < G; g += nw) {
+    if (tid < G && !((freem >> tid) & 1ull)) o.best_i[wrow + tid] = -1;
+    for (int c = wave; c < nf; c += nw) {
+      const int g = br_uniform(sf[c]);
       int bk = BR_KEY_NONE, bs = 0, bi = INT32_MAX;
       const int room = p.W > 0 ? p.W - sL[g] : INT32_MAX;
       for (int i = lane; i < qn; i += BR_WAVE) {
-        const int s = ss[i], key = keys[i * KS + g];
+        const int s = ss[i], key = keys[i * KS + c];
         if (s <= room && (key > bk || (key == bk && s > bs))) bk = key, bs = s, bi = i;
       }
       const int km = br_wave_max(bk);
       int best = -1;
-      if (km != BR_KEY_NONE && scap[g] > 0) {
+      if (km != BR_KEY_NONE) {
         const int sb = br_wave_max(bk == km ? bs : -1);
         best = br_wave_min(bk == km && bs == sb ? bi : INT32_MAX);
       }
-      if (lane == 0) o.best_i[(int64_t)inst * G + g] = best;
+      if (lane == 0) o.best_i[wrow + g] = best;
     }
   }
 }

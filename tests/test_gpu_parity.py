@@ -850,6 +850,20 @@ def test_snapshot_reductions_by_their_work(N, G, H, Q, R_max, own):
         r.close()
 
 
+@pytest.mark.parametrize("G,H,Q,wm", [(3, 40, 70, 0), (8, 80, 256, 0), (13, 9, 130, 9000), (64, 17, 65, 0)])
+def test_long_horizon_reductions_by_free_workers(G, H, Q, wm):
+    """Only workers with a free slot are scored: none, one, some, all of them free; nothing waiting."""
+    cfg, init, arr = wl.random_case(640 + G + H, N=20, G=G, B=5, max_wait=Q, H=H, pred_mode=1, token_watermark=wm)
+    init.kv[:], init.rem[:] = np.maximum(init.kv, 1), np.maximum(init.rem, 1)  # (slots that the next lines take)
+    for i in range(20):
+        init.n[i, :max(G - i, 0)] = cfg.B   # worker g is full in the clusters below G - g
+    arr.count[5] = 0
+    arr.count[7] = Q
+    _say(f"long reductions G={G} H={H} Q={Q} W={wm}")
+    oc, r = run_pair(cfg, init, arr, matrix=False, tag="long reductions")
+    r.close()
+
+
 @pytest.mark.parametrize("steps", [1, 2, 8, 9, 40])
 @pytest.mark.parametrize("G,Q", [(5, 200), (3, 512), (3, 700)])
 def test_large_batches_decode_orders(G, Q, steps):
