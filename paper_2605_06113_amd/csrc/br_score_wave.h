@@ -4,13 +4,15 @@
 // best_g, lanes = requests in arrival order.  BR-0: eq. (br0-Fscore) does not fall with the margin, and every worker
 // whose margin the request does not exceed gives it the same score, its length.  So the best worker is the one of lowest
 // index among the eligible workers with L_g <= M - s, and if there is none the lightest eligible one (lowest index on
-// ties): two instructions per (worker, register) instead of a score.  BR-H: every pair is scored.
+// ties): two instructions per (worker, register) instead of a score.  BR-H: likewise the worker of lowest index whose
+// horizon-min margin the request does not exceed (br_penalty_shows); the few requests that exceed all of them are scored,
+// one at a time with the workers side by side, or against one worker after the other where they are many.
 // best_i, lanes = workers: over the sorted list (br_list.h, copied to LDS) each worker finds the neighbours of its
 // smallest margin by binary search and compares their two scores, all workers side by side (why those two: see pick in
 // br_assign_kernel.h); where the peak of eq. (brh-Fscore) may be elsewhere the worker's requests are all scored.
 // The round of the same wave goes on with the sorted list.
-// 4096 clusters, G = 32, H = 4: merged launch 151 -> 135 us; 1531 clusters, G = 13, queues of 307, BR-0: 17.7 -> 8.8 us
-// (a block per cluster that scored all pairs twice).
+// 4096 clusters, G = 32, H = 4, 250 waiting: whole pass 297 us with every pair scored for best_g, 281.5 by the margins;
+// 1531 clusters, G = 13, queues of 307, BR-0: 17.7 us in a block per cluster that scored all pairs twice, 8.8 so.
 #pragma once
 
 #include "br_device.h"
@@ -38,6 +40,16 @@ __device__ __forceinline__ void br_peak_bounds(const BrParams &p, int s_max, flo
 #pragma unroll
   for (int h = 0; h <= HB; ++h) ho = (h <= p.H && p.beta * p.d[h] - p.aD > e2) ? h : ho;  // (d falls with h)
   ho = br_uniform(ho);
+}
+
+// BR-H: does a request that exceeds any one margin compute strictly below alpha D s, what it scores within all of them?
+// The penalty then sums to at least d_H (rounding keeps order), so it is enough that fl(beta d_H) reaches one unit in the
+// last place of the longest request's alpha D s, 2^-23 alpha D 32768 = 0.0039 alpha D.
+__device__ __forceinline__ bool br_penalty_shows(const BrParams &p) {
+  float d_H = p.d[0];
+#pragma unroll
+  for (int h = 1; h <= BR_HP; ++h) d_H = h <= p.H ? p.d[h] : d_H;
+  return p.beta * d_H >= 0.004f * p.aD;
 }
 
 // x: keys in arrival order (position j * 64 + lane)
@@ -71,23 +83,60 @@ __device__ __forceinline__ void br_snapshot_best_g(const BrParams &p, const BrOu
       }
     }
   } else {
-    int bk[E];
+    const int n_free = __builtin_popcountll(freem);
+    int m[HB + 1], safe = INT32_MAX;  // of the worker this lane holds: margins; the longest request within all of them
 #pragma unroll
-    for (int j = 0; j < E; ++j) bk[j] = BR_KEY_NONE;
-    for (unsigned long long m = freem; m != 0ull; m &= m - 1ull) {
-      const int g = (int)__builtin_ctzll(m);
-      int mg[HB + 1];
+    for (int h = 0; h <= HB; ++h) m[h] = max(st.Mh[h] - st.Lh[h], 0), safe = min(safe, m[h]);
+    const int room = p.W > 0 ? p.W - st.Lh[0] : INT32_MAX;
+    safe = min(safe, room);
+    const bool exact = br_penalty_shows(p);
+    if (exact) {
+      for (unsigned long long f = freem; f != 0ull;) {  // from the highest index down: the lowest one stays
+        const int g = 63 - (int)__builtin_clzll(f);
+        f &= ~(1ull << g);
+        const int Tg = __builtin_amdgcn_readlane(safe, g);
 #pragma unroll
-      for (int h = 0; h <= HB; ++h) mg[h] = max(st.Mh[h] - __builtin_amdgcn_readlane(st.Lh[h], g), 0);
-      const int room = p.W > 0 ? p.W - __builtin_amdgcn_readlane(st.Lh[0], g) : INT32_MAX;
+        for (int j = 0; j < E; ++j) bg[j] = (int)(x[j] >> BR_IDX_BITS) <= Tg ? g : bg[j];
+      }
+    }
+    bool many[E], any = false;
 #pragma unroll
-      for (int j = 0; j < E; ++j) {
-        if (E > 4 && j * BR_WAVE >= qn) continue;
-        const int s = (int)(x[j] >> BR_IDX_BITS);
-        const int k = br_ord(br_scoreh(p, mg, s));
-        const bool better = s <= room && k > bk[j];
-        bk[j] = better ? k : bk[j];
-        bg[j] = better ? g : bg[j];
+    for (int j = 0; j < E; ++j) {
+      many[j] = false;
+      if (j * BR_WAVE >= qn) continue;
+      const int s = (int)(x[j] >> BR_IDX_BITS);
+      unsigned long long left = br_ballot(bg[j] < 0 && x[j] != 0u);
+      many[j] = !exact || 2 * __builtin_popcountll(left) > n_free;
+      any |= many[j];
+      if (many[j]) continue;
+      for (; left != 0ull; left &= left - 1ull) {  // a few: one at a time, all workers side by side
+        const int l = (int)__builtin_ctzll(left);
+        const int sl = __builtin_amdgcn_readlane(s, l);
+        const int k = ((freem >> lane) & 1ull) && sl <= room ? br_ord(br_scoreh(p, m, sl)) : BR_KEY_NONE;
+        const int km = br_wave_max(k);
+        const int g = km == BR_KEY_NONE ? -1 : (int)__builtin_ctzll(br_ballot(k == km));
+        bg[j] = lane == l ? g : bg[j];
+      }
+    }
+    if (any) {  // one worker after the other, 64 requests side by side
+      int bk[E];
+#pragma unroll
+      for (int j = 0; j < E; ++j) bk[j] = BR_KEY_NONE;
+      for (unsigned long long f = freem; f != 0ull; f &= f - 1ull) {
+        const int g = (int)__builtin_ctzll(f);
+        int mg[HB + 1];
+#pragma unroll
+        for (int h = 0; h <= HB; ++h) mg[h] = __builtin_amdgcn_readlane(m[h], g);
+        const int room_g = __builtin_amdgcn_readlane(room, g);
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+          if (!many[j]) continue;
+          const int s = (int)(x[j] >> BR_IDX_BITS);
+          const int k = br_ord(br_scoreh(p, mg, s));
+          const bool better = s <= room_g && k > bk[j];
+          bk[j] = better ? k : bk[j];
+          bg[j] = better ? g : bg[j];
+        }
       }
     }
   }

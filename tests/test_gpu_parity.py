@@ -864,6 +864,22 @@ def test_long_horizon_reductions_by_free_workers(G, H, Q, wm):
     r.close()
 
 
+@pytest.mark.parametrize("beta", [-1.0, 0.05, 1e-4, 0.0])
+@pytest.mark.parametrize("G,H,Q,wm", [(24, 4, 200, 0), (5, 8, 300, 0), (33, 7, 130, 20000)])
+def test_horizon_best_worker_within_and_beyond_margins(G, H, Q, wm, beta):
+    """best_g of a horizon score by the margins: requests within some worker's margins, a few beyond all of them, most of
+    them beyond (equal loads), and penalties too small to show in a score (beta down to zero)."""
+    cfg, init, arr = wl.random_case(650 + G + H, N=4, G=G, B=8, max_wait=Q, H=H, beta=beta, token_watermark=wm, gate_pfin=0.0)
+    arr.count[:] = Q
+    init.kv[0], init.rem[0], init.n[0], init.pred[0] = 500, 30, 4, 0.0  # equal loads: every margin is zero
+    init.kv[1, 0] += 3000                                              # wide margins
+    arr.s[2, : Q - 3] = np.minimum(arr.s[2, : Q - 3], 40)              # a few long requests
+    arr.s[2, Q - 3:] = 30000
+    _say(f"best worker G={G} H={H} Q={Q} W={wm} beta={beta}")
+    oc, r = run_pair(cfg, init, arr, matrix=False, tag="best worker")
+    r.close()
+
+
 @pytest.mark.parametrize("steps", [1, 2, 8, 9, 40])
 @pytest.mark.parametrize("G,Q", [(5, 200), (3, 512), (3, 700)])
 def test_large_batches_decode_orders(G, Q, steps):
