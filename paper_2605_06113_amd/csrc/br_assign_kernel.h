@@ -803,6 +803,9 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
   BrRoundState<HB> st;
   br_round_state<HB>(p, lane, in.n, in.L, st);
   const int nn_start = st.nn;
+  if constexpr (BRH) {
+    if (w == 0) br_store_margins<HB>(p, inst, lane, st);
+  }
 
   BrRoundCounts rc = {};
   if (o.stats) {  // sum of loads in two 16-bit halves (each partial sum fits int32 for loads below 2^25)

@@ -289,6 +289,15 @@ __global__ __launch_bounds__(256) void br_k_advance(BrParams p, int t) {
 template <int NC, int RW, int HB, bool EXACT, int PK>
 __global__ __launch_bounds__(256) void br_k_project_rows(BrParams p) {
   constexpr bool HAZ = PK == 0;
+  if constexpr (PK == 1) {
+    if (p.pred_mode == 2 && blockIdx.x == gridDim.x - 1) {  // a last block: the estimate at age 0, for this round's admissions
+      if (threadIdx.x < BR_WAVE) {
+        const float c = br_survival(p, 0);
+        if (threadIdx.x == 0) *p.c0 = c;
+      }
+      return;
+    }
+  }
   const int64_t row0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * RW;
   const int64_t rows = (int64_t)p.N * p.G;
   if (row0 >= rows) return;
@@ -382,7 +391,7 @@ __global__ __launch_bounds__(256) void br_k_project_rows(BrParams p) {
 // offset.  Integer sums, so the order of accumulation does not matter.  One block per cluster: each wave takes
 // every fourth worker list and leaves its row in an LDS tile as well; then, with threads mapped to offsets,
 // the envelope M_h = max_g L_g(k+h) and the margins, and with threads mapped to workers the horizon-min
-// margin (what br_k_envelope does for short horizons in a launch of its own).
+// margin (short horizons: by the round's wave, br_store_margins).
 // The lists of a wave are taken in units of 64 slots with the next unit requested before the one in hand is used; suffix
 // sums are wave-wide DPP scans with lanes mapped to offsets in descending order (a walk over all bins on every lane took
 // 750 instructions per list).  2048 clusters, G = 8, B = 64, H = 80: 36 -> 10 us.  A last block writes the
@@ -499,29 +508,18 @@ __global__ void br_k_discounts(BrParams p, float gamma) {
   }
 }
 
-// Part 2: envelope M_h = max_g L_g(k+h), margins m_{g,h} = (M_h - L_g(k+h))_+ and min_h m_{g,h};
-// one wave per cluster, lane g holds worker g.
-__global__ __launch_bounds__(256) void br_k_envelope(BrParams p) {
-  const int inst = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
-  const int lane = br_lane();
-  if (inst == p.N && p.pred_mode == 2) {  // one wave beyond the clusters: the estimate at age 0 (newly admitted requests)
-    const float c = br_survival(p, 0);
-    if (lane == 0) *p.c0 = c;
+// Step-start margins m_{g,h} = (M_h - L_g(k+h))_+ of the workers [g0, g0 + gn) of a cluster with a short horizon, from the
+// projections, into sm (stride words per worker, zeros beyond offset H), by one wave: lane = worker.
+__device__ __forceinline__ void br_margins_to_lds(const BrParams &p, int inst, int lane, int g0, int gn, int *sm, int stride) {
+  const int64_t wrow = (int64_t)inst * p.G + min(lane, p.G - 1);
+  int l[BR_HP + 1];
+#pragma unroll
+  for (int h = 0; h <= BR_HP; ++h) l[h] = p.Lh[wrow * (p.H + 1) + min(h, p.H)];  // (lanes beyond G repeat the last worker)
+#pragma unroll
+  for (int h = 0; h <= BR_HP; ++h) {
+    const int m = br_wave_max(l[h]) - l[h];
+    if (lane >= g0 && lane < g0 + gn) sm[(lane - g0) * stride + h] = h <= p.H ? m : 0;
   }
-  if (inst >= p.N) return;
-  const bool act = lane < p.G;
-  const int H1 = p.H + 1;
-  const int64_t wrow = (int64_t)inst * p.G + lane;
-  int mn = INT32_MAX;
-  for (int h = 0; h < H1; ++h) {
-    const int lh = act ? p.Lh[wrow * H1 + h] : BR_LOW;
-    const int M = br_wave_max(lh);
-    const int m = max(M - lh, 0);
-    mn = min(mn, m);
-    if (act) p.mh[wrow * H1 + h] = m;
-    if (lane == 0) p.Mh[(int64_t)inst * H1 + h] = M;
-  }
-  if (act) p.minm[wrow] = mn;
 }
 
 // ------------------------------------------------------------------ F-score matrix + reductions
@@ -559,10 +557,13 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o) 
     sL[tid] = p.L[(int64_t)inst * G + tid];
     scap[tid] = p.B - p.n[(int64_t)inst * G + tid];
   }
-  for (int e = tid; e < G * HS; e += blockDim.x) {
-    const int g = e / HS, h = e - g * HS;
-    const int m = (BRH && h <= p.H) ? p.mh[((int64_t)inst * G + g) * (p.H + 1) + h] : 0;
-    sm[e] = LONG ? __float_as_int((float)m) : m;  // br_scoreh_long takes the margins as floats
+  if constexpr (LONG) {  // br_scoreh_long takes the margins as floats
+    for (int e = tid; e < G * HS; e += blockDim.x) {
+      const int g = e / HS, h = e - g * HS;
+      sm[e] = __float_as_int(h <= p.H ? (float)p.mh[((int64_t)inst * G + g) * (p.H + 1) + h] : 0.0f);
+    }
+  } else if constexpr (BRH) {
+    if (wave == 0) br_margins_to_lds(p, inst, lane, 0, G, sm, HS);
   }
   if constexpr (LONG)
     for (int h = tid; h < HS; h += blockDim.x) sd[h] = p.dl[h];
@@ -779,10 +780,13 @@ __global__ __launch_bounds__(256) void br_k_score_matrix(BrParams p, BrArr a, Br
   cnt = min(max(cnt, 0), a.arr_cap);
   const int qn = q0 + min(cnt, p.Q - q0);
   if (!BRH && tid < G) sL[tid] = p.L[(int64_t)inst * G + tid];
-  for (int e = tid; e < G * HS; e += blockDim.x) {
-    const int g = e / HS, h = e - g * HS;
-    const int m = (BRH && h <= p.H) ? p.mh[((int64_t)inst * G + g) * (p.H + 1) + h] : 0;
-    sm[e] = LONG ? __float_as_int((float)m) : m;
+  if constexpr (LONG) {
+    for (int e = tid; e < G * HS; e += blockDim.x) {
+      const int g = e / HS, h = e - g * HS;
+      sm[e] = __float_as_int(h <= p.H ? (float)p.mh[((int64_t)inst * G + g) * (p.H + 1) + h] : 0.0f);
+    }
+  } else if constexpr (BRH) {
+    if (tid < BR_WAVE) br_margins_to_lds(p, inst, tid, 0, G, sm, HS);
   }
   if constexpr (LONG)
     for (int h = tid; h < HS + 4; h += blockDim.x) sd[h] = h < HS ? p.dl[h] : 0.0f;
@@ -874,15 +878,19 @@ __global__ __launch_bounds__(64) void br_k_score_tiles(BrParams p, BrArr a, int 
     sL[lane] = p.L[(int64_t)inst * G + g0 + lane];
     scap[lane] = p.B - p.n[(int64_t)inst * G + g0 + lane];
   }
-  for (int e = lane; e < gn * HS; e += BR_WAVE) {
-    const int gl = e / HS, h = e - gl * HS;
-    int m = 0;
-    if (BRH) {
-      if (h <= p.H) m = p.mh[((int64_t)inst * G + g0 + gl) * (p.H + 1) + h];
-    } else if (h == 0) {
-      m = M - p.L[(int64_t)inst * G + g0 + gl];
+  if constexpr (BRH && !LONG) {
+    br_margins_to_lds(p, inst, lane, g0, gn, sm, HS);
+  } else {
+    for (int e = lane; e < gn * HS; e += BR_WAVE) {
+      const int gl = e / HS, h = e - gl * HS;
+      int m = 0;
+      if (LONG) {
+        if (h <= p.H) m = p.mh[((int64_t)inst * G + g0 + gl) * (p.H + 1) + h];
+      } else if (h == 0) {
+        m = M - p.L[(int64_t)inst * G + g0 + gl];
+      }
+      sm[e] = LONG ? __float_as_int((float)m) : m;
     }
-    sm[e] = LONG ? __float_as_int((float)m) : m;
   }
   if constexpr (LONG)
     for (int h = lane; h < HS + 4; h += BR_WAVE) sd[h] = h < HS ? p.dl[h] : 0.0f;
@@ -1037,7 +1045,7 @@ void br_launch_advance(const BrParams &p, int t, hipStream_t st) {
 template <int NC, int RW, int HB, bool EXACT>
 static void launch_project_rows_h(const BrParams &p, hipStream_t st) {
   const int64_t waves = ((int64_t)p.N * p.G + RW - 1) / RW;
-  const dim3 grid((unsigned)((waves + 3) / 4)), block(256);
+  const dim3 grid((unsigned)((waves + 3) / 4) + (p.pred_mode == 2 ? 1u : 0u)), block(256);
   if (p.pred_mode == 0)
     hipLaunchKernelGGL((br_k_project_rows<NC, RW, HB, EXACT, 0>), grid, block, 0, st, p);
   else if (p.pred_mode == 3)
@@ -1080,7 +1088,6 @@ void br_launch_project(const BrParams &p, hipStream_t st) {
     launch_project_rows<8, 1>(p, st);
   else
     launch_project_rows<16, 1>(p, st);
-  hipLaunchKernelGGL(br_k_envelope, dim3((unsigned)((p.N + 4) / 4)), dim3(256), 0, st, p);
 }
 
 size_t br_score_scratch_bytes(int N, int Q, int G) {
