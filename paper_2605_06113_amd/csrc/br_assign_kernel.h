@@ -194,23 +194,20 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
       br_list_around<E>(x, T, hi, lo);
       none_below = lo == 0u;
       const int sh = (int)(hi >> BR_IDX_BITS), sl = (int)(lo >> BR_IDX_BITS);
-      const bool okh = hi != 0u && hi != BR_ENTRY_GONE && sh < room1, okl = lo != 0u;
-      if (!okh && !okl) return false;
-      bool useh = okh;
-      if (okh && okl) {
-        if constexpr (BRH) {
-          const int F = br_ord(br_scoreh(p, mg, lane == 0 ? sh : sl));
-          useh = __builtin_amdgcn_readlane(F, 0) >= __builtin_amdgcn_readlane(F, 1);  // (equal: the lower position)
-        } else {
-          useh = sh - G * (sh - m) >= sl;
-        }
+      const bool okh = (hi != 0u) & (hi != BR_ENTRY_GONE) & (sh < room1), okl = lo != 0u;
+      bool useh;
+      if constexpr (BRH) {
+        const int F = br_ord(br_scoreh(p, mg, lane == 0 ? sh : sl));
+        useh = okh & (!okl | (__builtin_amdgcn_readlane(F, 0) >= __builtin_amdgcn_readlane(F, 1)));  // (equal: the lower position)
+      } else {
+        useh = okh & (!okl | (sh - G * (sh - m) >= sl));
       }
       key = lo;
       if (useh) {  // the first of its length
         unsigned before;
         br_list_around<E>(x, (unsigned)(sh + 1) << BR_IDX_BITS, before, key);
       }
-      return true;
+      return okh | okl;
     }
     if constexpr (BRH) {
       none_below = false;
@@ -491,6 +488,119 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
     stale = true;
     br_wave_sync();
   }
+  // Windows of up to four requests: 16 masks, one per lane of the wave's first row, which alone decides.  A loop of its own:
+  // a pop is a chain of about 100 instructions on one wave, in which a taken branch costs 25 to 85 cycles (seven to twenty
+  // instructions) and a scalar instruction that reads a vector result waits for four, so what is common goes straight
+  // down.  In one loop with the window of eight a pop took 2400 to 3000 cycles alone on its SIMD, so 1250 to 1500 (1500 to 2000
+  // through the guard).  Whole pass: 1531 clusters, G = 13, 10 admissions each 46.6 -> 42.7 us; 4096, G = 16, 6 admissions
+  // 48.9 -> 47.1; one, G = 64, a queue of 2048 under a watermark 52.9 -> 49.1.
+  if (!BIGR && p.R_max <= 4) {
+    // all ones at the length of window entry b on the lanes whose mask holds it (an entry beyond R_max never; one beyond
+    // the list reads as zero, so its masks repeat lower ones, which win)
+    unsigned len[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) len[b] = ((lane >> b) & 1) && b < p.R_max ? ~(unsigned)IDX_MASK : 0u;
+    const int bits = __builtin_popcount(lane & 15);
+    const int limit = p.W > 0 ? p.W : 1 << 29;           // of a load (none: beyond every load and length)
+    // length of the shortest waiting request as last looked up: it only rises, so a worker that cannot take a request of
+    // this length is out for good; one that turns out to be too full when its turn comes has it looked up again
+    int shortest = p.W > 0 ? tail_len() : 0;
+    // (every turn admits a request, sets a worker aside, or goes on to a lower free-slot count after such a turn)
+    for (int it = 0; it < 2 * bound_it && n_alive > 0 && S_tot > 0; ++it) {
+      // priority (free slots, horizon-min margin), lowest index on ties.  Workers for which even the shortest request is
+      // too long are set aside when their turn comes; those whose turn comes before the first other one's go together
+      // (nothing is admitted in between).
+      const int prio = (int)(((unsigned)lane_minm() << 6) | (unsigned)(63 - lane));
+      const bool member = cap == capmax_cur, takes = limit - Lh[0] >= shortest;
+      int top = br_wave_max(member && takes ? prio : -1);
+      const bool out = member && !takes && prio > top;
+      const unsigned long long outm = br_ballot(out);
+      if (__builtin_expect((outm != 0ull) | (top < 0), 0)) {
+        const int n_out = __builtin_popcountll(outm);
+        cap = out ? 0 : cap;
+        S_tot -= capmax_cur * n_out;
+        wdrop += n_out;
+        pops += n_out;
+        guard += n_out;
+        if (top < 0) {
+          const unsigned long long left = br_ballot(cap == capmax_cur);
+          if (left == 0ull) {  // the next lower free-slot count that has a member
+            cap_max();
+            continue;
+          }
+          top = 63 - (int)__builtin_ctzll(left);  // (loads beyond what the priorities order: the lowest index)
+        }
+      }
+      const int g = 63 - (top & 63);
+      ++pops;
+      int Lg[NH], mg[NH];
+      margins_of(g, Lg, mg);
+      const int room = p.W > 0 ? p.W - Lg[0] : INT32_MAX;
+      unsigned wv[4];  // the window: the first entries of the list
+#pragma unroll
+      for (int b = 0; b < 4; ++b) wv[b] = (unsigned)__builtin_amdgcn_readlane((int)x[b % E], b / E);
+      const int delta =
+          (int)(((wv[0] & len[0]) + (wv[1] & len[1]) + (wv[2] & len[2]) + (wv[3] & len[3])) >> BR_IDX_BITS);
+      const bool ok = bits <= capmax_cur && delta <= room;
+      unsigned mask;
+      bool found;  // a subset scores above zero (the empty one scores zero: the guard's case like any other)
+      if constexpr (!BRH) {
+        const int F = br_score0(G, mg[0], delta);
+        const int best = br_row0_max(ok ? F * 64 + (63 - lane) : INT32_MIN);
+        found = best >= 64;
+        mask = 63u - ((unsigned)best & 63u);
+      } else {
+        const int F = br_score_key<BRH>(p, mg, delta);
+        const int best = br_row0_max(ok ? F : BR_KEY_NONE);
+        found = best > 0;
+        mask = (unsigned)__builtin_ctzll(br_ballot(ok && F == best) | (1ull << 63));
+      }
+      int slot = __builtin_amdgcn_readlane(nn, g);
+      if (__builtin_expect(found, 1)) {
+        const int sum = __builtin_amdgcn_readlane(delta, (int)mask);
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          if (__builtin_expect((mask >> b) & 1u, 1)) bind(wv[b], g, slot++);  // slots follow the order of the window
+        add_load(g, Lg, sum, __builtin_popcount(mask));
+      } else {
+        // starvation guard: the single best request anyway
+        ++guard;
+        unsigned key = 0u;
+        bool none_below = false;
+        const bool some = pick(mg, room, key, none_below);
+        int done = 0;
+        if constexpr (!BRH) {
+          if (none_below && tail_bulk_ok) {
+            // This worker takes the shortest waiting request through the guard and the envelope becomes
+            // its new load.  The next pop goes to the next lightest worker that still has this many free
+            // slots; its margin is at most the length just admitted.  While the lengths admitted stay
+            // at or below (G-1)/G of the window's smallest entry, the window is untouched, that entry
+            // still scores <= 0 for every such margin (so the guard fires again) and no waiting request
+            // is below the margin: the pops of this free-slot count follow in one step.
+            const int w = min(p.R_max, n_alive);
+            int s_last = (int)(wv[0] >> BR_IDX_BITS);
+#pragma unroll
+            for (int b = 1; b < 4; ++b) s_last = b < w ? (int)(wv[b] >> BR_IDX_BITS) : s_last;
+            const int K = min((int)__builtin_popcountll(br_ballot(member)), n_alive - w);
+            if (K >= 3 && br_score0(G, mg[0], s_last) <= 0) {
+              const int rank = rank_of(member ? (int)(((unsigned)Lh[0] << 6) | (unsigned)lane) : INT32_MAX);
+              done = tail_bulk(member ? rank : BR_WAVE, 0, K, (G - 1) * s_last / G);
+              if (done > 0) pops += done - 1, guard += done - 1;
+            }
+          }
+        }
+        if (done == 0) {
+          if (some) {
+            bind(key, g, slot);
+            add_load(g, Lg, (int)(key >> BR_IDX_BITS), 1);
+          } else {
+            drop_worker(g, capmax_cur);
+            shortest = tail_len();
+          }
+        }
+      }
+    }
+  } else {
   // lane-constant pieces of the subset enumeration: lane l of pass c stands for mask c*64 + l
   int lbit[6];
 #pragma unroll
@@ -726,6 +836,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
       }
       add_load(g, Lg, delta, __builtin_popcount(bestmask));
     }
+  }
   }
 #pragma unroll
   for (int h = 0; h < NH; ++h) st.Lh[h] = Lh[h];

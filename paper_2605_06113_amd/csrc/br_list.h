@@ -102,14 +102,27 @@ __device__ __forceinline__ void br_list_narrow(const unsigned (&x)[E], int l, un
 }
 
 // Last entry at or above T (0: none) and first entry below it (0: none), uniform.  1 <= T < BR_ENTRY_GONE.
+// Lists of one or four registers: by selects throughout (a branch costs as much as four or more instructions).
 template <int E>
 __device__ __forceinline__ void br_list_around(const unsigned (&x)[E], unsigned T, unsigned &at_or_above, unsigned &below) {
   const int l = __builtin_popcountll(br_ballot(x[0] >= T)) - 1;  // the lane in which the list crosses T
-  const unsigned next = l < 63 ? (unsigned)__builtin_amdgcn_readlane((int)x[0], (l + 1) & 63) : 0u;
-  at_or_above = 0u, below = next;
-  if (l >= 0) {
-    at_or_above = (unsigned)__builtin_amdgcn_readlane((int)x[0], l);
-    br_list_narrow<0, E>(x, l, T, at_or_above, below);
+  if constexpr (E <= 4) {
+    unsigned r[E];
+#pragma unroll
+    for (int j = 0; j < E; ++j) r[j] = (unsigned)__builtin_amdgcn_readlane((int)x[j], max(l, 0));
+    const unsigned next = (unsigned)__builtin_amdgcn_readlane((int)x[0], (l + 1) & 63);
+    at_or_above = 0u, below = l < 63 ? next : 0u;
+#pragma unroll
+    for (int j = 0; j < E; ++j) at_or_above = r[j] >= T ? r[j] : at_or_above;
+#pragma unroll
+    for (int j = E - 1; j >= 0; --j) below = r[j] < T ? r[j] : below;
+  } else {
+    const unsigned next = l < 63 ? (unsigned)__builtin_amdgcn_readlane((int)x[0], (l + 1) & 63) : 0u;
+    at_or_above = 0u, below = next;
+    if (l >= 0) {
+      at_or_above = (unsigned)__builtin_amdgcn_readlane((int)x[0], l);
+      br_list_narrow<0, E>(x, l, T, at_or_above, below);
+    }
   }
 }
 

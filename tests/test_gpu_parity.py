@@ -880,6 +880,30 @@ def test_horizon_best_worker_within_and_beyond_margins(G, H, Q, wm, beta):
     r.close()
 
 
+@pytest.mark.parametrize("H", [0, 3, 8])
+@pytest.mark.parametrize("R_max", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("G,Q", [(1, 5), (16, 64), (17, 256), (64, 300)])
+def test_narrow_windows(G, Q, R_max, H):
+    """Stage 2 over windows of one to four requests (and five, the other loop): every admission through it, fewer requests
+    than the window holds, one to four free slots per worker, watermarks that only the shortest requests pass and that set
+    workers aside in every position, all workers equal, lengths that exceed every margin."""
+    for wm, slots in ((0, 2), (5200, 3), (9000, 4)):
+        cfg, init, arr = wl.random_case(660 + G + 7 * R_max + H + wm, N=14, G=G, B=6, max_wait=Q, H=H, R_max=R_max,
+                                        S_greedy=G * 6, token_watermark=wm, gate_pfin=0.0)
+        init.kv[:], init.rem[:] = np.maximum(init.kv, 1), np.maximum(init.rem, 1)
+        init.n[:] = 6 - np.random.default_rng(G + R_max).integers(0, slots + 1, size=init.n.shape)
+        arr.count[:] = Q
+        arr.count[:3] = (1, min(2, Q), min(R_max, Q))
+        init.kv[3], init.n[3] = 900, 5        # equal workers, one slot each
+        arr.s[4] = 20000 + arr.s[4]           # longer than any margin
+        arr.s[5, ::2] = 1 + arr.s[5, ::2] % 300
+        if H:
+            init.pred[3], init.rem[3] = 0.0, 30
+        _say(f"narrow windows G={G} Q={Q} R_max={R_max} H={H} W={wm}")
+        oc, r = run_pair(cfg, init, arr, matrix=False, tag="narrow windows")
+        r.close()
+
+
 @pytest.mark.parametrize("steps", [1, 2, 8, 9, 40])
 @pytest.mark.parametrize("G,Q", [(5, 200), (3, 512), (3, 700)])
 def test_large_batches_decode_orders(G, Q, steps):
