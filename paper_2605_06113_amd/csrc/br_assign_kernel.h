@@ -910,6 +910,12 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
     if (p.pred_mode == 2) c0 = *p.c0;
   }
 
+  // (not where four waves share a SIMD anyway: 4096 clusters with decode steps 47.2 us without, 47.9 with)
+  constexpr bool AHEAD = !COOP && !BRH && !ADV && EM <= 8;
+  BrQueueWords<EM> words;
+  if constexpr (AHEAD)
+    br_queue_words<EM>(p.qs, p.qo, p.qid, a.s, a.o, a.id, (int64_t)inst * p.Q, (int64_t)inst * a.arr_cap, lane, 0, q0, qn, words);
+
   // ---- worker state, one worker per lane
   BrRoundState<HB> st;
   br_round_state<HB>(p, lane, in.n, in.L, st);
@@ -986,12 +992,12 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
     bool done = false;
     if constexpr (!BRH && !BIGR && EM <= 8) {
       if (split != nullptr) {
-        br_assign_epilogue_split<EM>(inst, lane, q0, qn, cnt, bound, st.Lh[0], st.nn, nn_start, rc, split, lst);
+        br_assign_epilogue_split<EM>(inst, lane, q0, qn, cnt, bound, st.Lh[0], st.nn, nn_start, rc, split, lst, AHEAD ? &words : nullptr);
         done = true;
       }
     }
     if (!done) {
-      br_assign_epilogue<EM, BRH>(inst, lane, q0, qn, cnt, bound, st.Lh[0], st.nn, rc, c0);
+      br_assign_epilogue<EM, BRH>(inst, lane, q0, qn, cnt, bound, st.Lh[0], st.nn, rc, c0, AHEAD ? &words : nullptr);
       if constexpr (ADV) br_advance_cluster<8>(inst, lane, st.Lh[0], st.nn);
     }
   }
