@@ -24,6 +24,7 @@ __global__ __launch_bounds__(256) void br_k_route(BrParams p, BrArr a, BrOut o) 
   int *lds = lds_all + w * WORDS, *split = nullptr;
   if (MIX && p.adv_t <= 8 && ((b + (b >> 8) + w) & 1) && inst < p.N) {  // (blocks 256 apart share a CU: both orders on every SIMD)
     split = lds + BR_ROUND_WORDS(E, false);
+    if (br_lane() == 0) split[1] = 1;  // (no other wave reads this cluster)
     br_split_advance<8>(p, inst, br_lane(), split);
   }
   br_assign_body<E, 0, ADV, false, false, true>(p, a, o, lds, inst, 0, split);
@@ -48,6 +49,15 @@ void br_launch_route(const BrParams &p, const BrArr &a, const BrOut &o, hipStrea
     launch_route<8>(p, a, o, st);
   else
     launch_route<16>(p, a, o, st);
+}
+
+void br_launch_route_helped(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
+  if (p.Q <= 256)
+    br_launch_helped_one<4, 0>(p, a, o, st);
+  else if (p.Q <= 512)
+    br_launch_helped_one<8, 0>(p, a, o, st);
+  else
+    br_launch_helped_one<16, 0>(p, a, o, st);
 }
 
 void br_launch_assign_br0(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {

@@ -352,7 +352,7 @@ __device__ __forceinline__ void br_advance_cluster(int inst, int lane, int Lcur,
 // the round then appends its admissions behind the survivors, already advanced.  Same final state as the round
 // followed by the decode steps: a list holds its old survivors in order, then the new survivors in admission
 // order; L_g = sum of the kv held; a request whose output is used up within the t steps leaves at once.
-// LDS area of one cluster: [0] flag (helper done), [4..68) per worker: entries its list lost (old length - kept),
+// LDS area of one cluster: [0] flag (lists advanced), [1] flag (a third wave has read what it needs, or there is none), [4..68) per worker: entries its list lost (old length - kept),
 // [68..132) per worker: load change of the old entries.
 #define BR_SPLIT_WORDS 132
 
@@ -371,16 +371,6 @@ __device__ __forceinline__ void br_split_advance(const BrParams &p, int inst, in
   if (lane == 0) split[0] = 1;
 }
 
-// The helper's part for one cluster: snapshot reductions if asked for (they read what the round's epilogue will
-// overwrite, and the epilogue waits for the flag), the decode steps of the old entries, then the flag.
-// UB: (list, chunk) units requested before the first is used
-template <int E, int UB>
-__device__ __forceinline__ void br_split_helper(const BrParams &p, const BrArr &a, const BrOut &o, int inst, int lane,
-                                                int *split, int *lst) {
-  if (o.best_g || o.best_i) br_score_wave_run<E, 0>(p, a, o, inst, lane, lst);
-  br_split_advance<UB>(p, inst, lane, split);
-}
-
 // The epilogue of the wave that ran the round where the decode steps of the old entries are (being) applied apart: by
 // another wave (split kernels), or by this one before the round.  nn0: list lengths at the start of the step.
 // Admitted requests whose output is used up within the t steps leave at once: who they are per worker is collected in
@@ -393,8 +383,9 @@ __device__ __forceinline__ void br_assign_epilogue_split(int inst, int lane, int
   const int G = t.G, tt = t.adv_t;
   BrQueueGroup<E, false> v;
   br_queue_load(t, inst, lane, 0, q0, qn, bound, v, words);
-  // the helper is done with this cluster's lists (it never waits for anything: the flag always comes)
-  while (__atomic_load_n(split, __ATOMIC_RELAXED) == 0) __builtin_amdgcn_s_sleep(4);
+  // the helpers are done with this cluster's lists and queue (they never wait for anything: the flags always come)
+  while (__atomic_load_n(split, __ATOMIC_RELAXED) == 0 || __atomic_load_n(split + 1, __ATOMIC_RELAXED) == 0)
+    __builtin_amdgcn_s_sleep(4);
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // (or this wave's own stores to the lists)
   const int lost = split[4 + lane], dold = split[4 + BR_WAVE + lane];  // lane g: worker g
   const int kept0 = nn0 - lost, a_g = nn - nn0;                        // old survivors, admissions of this round

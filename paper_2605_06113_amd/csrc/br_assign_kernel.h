@@ -857,7 +857,9 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
 // `shared` (BIGR without COOP, one cluster per block of four waves): waves 1-3 serve the subset searches of wave 0
 // (every fourth trip of a mask scan, every fourth run of 64 words of the rows of reachable sums) through the
 // mailbox `svc` and two block barriers per search.
-template <int EM, int HB, bool ADV, bool COOP = false, bool BIGR = false, bool SCORES = false>
+// HELPED: the block's other waves read the cluster's step-start state meanwhile (br_snapshot_helper); the block meets before
+// this wave's epilogue changes it.
+template <int EM, int HB, bool ADV, bool COOP = false, bool BIGR = false, bool SCORES = false, bool HELPED = false>
 __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a, const BrOut &o, int *lds, int inst,
                                                int w = 0, int *split = nullptr,
                                                bool shared = false) {
@@ -981,6 +983,7 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
       __syncthreads();
     }
   }
+  if constexpr (HELPED) __syncthreads();
   if constexpr (COOP) {
     int Lw = st.Lh[0];
     br_assign_epilogue_block4<BRH>(inst, lane, w, q0, qn, cnt, bound, slots, lst, Lw, st.nn, rc, c0, ADV);
@@ -1020,6 +1023,34 @@ __global__ __launch_bounds__(256, (HB > 0 && E == 8 && !BIGR) ? 4 : 1) void br_k
     br_assign_body<E, HB, ADV, false, BIGR>(p, a, o, lds_all, (int)blockIdx.x, w, nullptr, true);
   else
     br_assign_body<E, HB, ADV, false, BIGR>(p, a, o, lds_all + w * WORDS, (int)(blockIdx.x * (blockDim.x >> 6)) + w);
+}
+
+// Small batches without decode steps in the launch: a block per cluster, its first wave runs the round, the others compute
+// what was asked for beside it (the reductions, BR-0 also the matrix) meanwhile.  Two of them: one shares out the requests,
+// one sorts.  1531 clusters, G = 13, queues of 307, matrix and reductions asked for, whole pass: 42.7 us with the reductions on the
+// round's wave and the matrix as a launch before it, 36.5 / 35.6 / 39.1 us with 1 / 2 / 3 such waves.
+#define BR_HELPERS 2
+template <int E, int HB>
+__global__ __launch_bounds__((1 + BR_HELPERS) * BR_WAVE) void br_k_route_helped(BrParams p, BrArr a, BrOut o, unsigned recip_g) {
+  extern __shared__ int lds_all[];
+  const int w = threadIdx.x >> 6, inst = (int)blockIdx.x;
+  if (w == 0) {
+    br_assign_body<E, HB, false, false, false, false, true>(p, a, o, lds_all, inst);
+  } else {
+    br_snapshot_helper<E, HB>(p, a, o, inst, br_lane(), w - 1, BR_HELPERS, recip_g,
+                              lds_all + BR_ROUND_WORDS(E, false) + (w - 1) * (BR_LIST_WORDS(E) + 2 * BR_WAVE));
+    __builtin_amdgcn_s_waitcnt(0);  // every read has returned
+    __syncthreads();
+  }
+}
+
+static inline unsigned br_recip(int G) { return (unsigned)((0x100000000ull + (unsigned)G - 1u) / (unsigned)G); }  // ceil(2^32 / G)
+
+template <int E, int HB>
+static void br_launch_helped_one(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
+  const size_t lds = (BR_ROUND_WORDS(E, false) + (size_t)BR_HELPERS * (BR_LIST_WORDS(E) + 2 * BR_WAVE)) * sizeof(int);
+  hipLaunchKernelGGL((br_k_route_helped<E, HB>), dim3((unsigned)p.N), dim3(BR_WAVE * (1 + BR_HELPERS)), lds, st, p, a, o,
+                     br_recip(p.G));
 }
 
 // Clusters of one wave each per block (one where the queues are long and so the LDS of a cluster is large).

@@ -32,3 +32,16 @@ void br_launch_route_h(const BrParams &p, const BrArr &a, const BrOut &o, hipStr
     launch_route_h<8, BR_HP>(p, a, o, st);
   }
 }
+
+void br_launch_route_h_helped(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
+  if (p.H <= BR_HP / 2) {
+    if (p.Q <= 256)
+      br_launch_helped_one<4, BR_HP / 2>(p, a, o, st);
+    else
+      br_launch_helped_one<8, BR_HP / 2>(p, a, o, st);
+  } else if (p.Q <= 256) {
+    br_launch_helped_one<4, BR_HP>(p, a, o, st);
+  } else {
+    br_launch_helped_one<8, BR_HP>(p, a, o, st);
+  }
+}

@@ -1,41 +1,38 @@
-// Round and decode steps of a BR-0 cluster on two waves (br_route_advance for queues of up to 512 entries,
-// windows of up to 8 requests, small batches): a block holds RPB waves that each run the round of one cluster
-// (Alg. BR-0) and NH helper waves that, meanwhile, compute the snapshot reductions of those clusters (if asked for) and apply the
-// decode steps (Sec. 2.2) to their lists as they stand at the start of the step.  The wave that ran the round
-// appends its admissions behind the old survivors, already advanced (br_assign_epilogue_split).  The decode step
-// streams the lists from HBM while the rounds, dependent chains that leave the memory system idle, are still
-// running: neither waits for the other except at one LDS flag per cluster, which the helper always sets.
+// Round and decode steps of a BR-0 cluster on two or three waves (br_route_advance for queues of up to 512 entries, windows
+// of up to 8 requests, small batches), a block per cluster: the first wave runs the round (Alg. BR-0); meanwhile the second
+// applies the decode steps (Sec. 2.2) to the lists as they stand at the start of the step, and a third, where the snapshot
+// reductions or the score matrix are asked for, computes those (br_snapshot_helper).  The first wave appends its
+// admissions behind the old survivors, already advanced (br_assign_epilogue_split).  The decode step streams the lists
+// from HBM while the round, a dependent chain that leaves the memory system idle, is still running: the first wave waits
+// at one LDS flag for each of the others before its epilogue, and those always come.
 #include "br_assign_kernel.h"
 
-template <int E, int RPB, int NH>
-__global__ __launch_bounds__((RPB + NH) * BR_WAVE) void br_k_route_split(BrParams p, BrArr a, BrOut o) {
+template <int E>
+__global__ __launch_bounds__(3 * BR_WAVE) void br_k_route_split(BrParams p, BrArr a, BrOut o, unsigned recip_g) {
   extern __shared__ int lds_all[];
-  constexpr int WORDS = BR_ROUND_WORDS(E, false) + BR_SPLIT_WORDS;
-  constexpr int HELP = BR_LIST_WORDS(E);  // the helper's list (snapshot reductions), after the clusters' areas
-  constexpr int SPLIT_AT = WORDS - BR_SPLIT_WORDS;
-  const int w = threadIdx.x >> 6, lane = br_lane();
-  const int first = (int)blockIdx.x * RPB;
-  if (w == RPB && lane < RPB) lds_all[lane * WORDS + SPLIT_AT] = 0;  // flags down before any wave looks
+  const int w = threadIdx.x >> 6, lane = br_lane(), inst = (int)blockIdx.x;
+  int *split = lds_all + BR_ROUND_WORDS(E, false);
+  // flags down before any wave looks: the lists, and what a third wave reads of the step-start state
+  if (threadIdx.x == 0) split[0] = 0, split[1] = blockDim.x > 2 * BR_WAVE ? 0 : 1;
   __syncthreads();
-  if (w < RPB) {
-    const int inst = first + w;
-    if (inst >= p.N) return;
-    int *lds = lds_all + w * WORDS;
-    br_assign_body<E, 0, false>(p, a, o, lds, inst, 0, lds + SPLIT_AT);
+  if (w == 0) {
+    br_assign_body<E, 0, false>(p, a, o, lds_all, inst, 0, split);
+  } else if (w == 1) {
+    br_split_advance<8>(p, inst, lane, split);
   } else {
-    for (int c = w - RPB; c < RPB; c += NH) {  // helper h takes clusters h, h + NH, ...
-      const int inst = first + c;
-      if (inst >= p.N) break;
-      br_split_helper<E, 8>(p, a, o, inst, lane, lds_all + c * WORDS + SPLIT_AT, lds_all + RPB * WORDS + (w - RPB) * HELP);
-    }
+    br_snapshot_helper<E, 0>(p, a, o, inst, lane, 0, 1, recip_g, split + BR_SPLIT_WORDS);
+    __builtin_amdgcn_s_waitcnt(0);  // every read has returned before the flag is seen
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    if (lane == 0) split[1] = 1;
   }
 }
 
-template <int E, int RPB, int NH>
+template <int E>
 static void launch_split(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
-  const size_t lds = ((size_t)RPB * (BR_ROUND_WORDS(E, false) + BR_SPLIT_WORDS) + (size_t)NH * BR_LIST_WORDS(E)) * sizeof(int);
-  const dim3 grid((unsigned)((p.N + RPB - 1) / RPB)), block((RPB + NH) * BR_WAVE);
-  hipLaunchKernelGGL((br_k_route_split<E, RPB, NH>), grid, block, lds, st, p, a, o);
+  const bool third = o.F || o.best_g || o.best_i;
+  const size_t lds = (BR_ROUND_WORDS(E, false) + BR_SPLIT_WORDS + (third ? BR_LIST_WORDS(E) + 2 * BR_WAVE : 0)) * sizeof(int);
+  hipLaunchKernelGGL((br_k_route_split<E>), dim3((unsigned)p.N), dim3(BR_WAVE * (third ? 3 : 2)), lds, st, p, a, o, br_recip(p.G));
 }
 
 // For batches below two one-wave clusters per SIMD: one round and one helper per block.  Beyond, with four or more waves
@@ -52,7 +49,7 @@ bool br_split_serves(const BrParams &p) { return p.adv_t > 0 && br_split_shape(p
 
 void br_launch_route_split(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
   if (p.Q <= 256)
-    launch_split<4, 1, 1>(p, a, o, st);
+    launch_split<4>(p, a, o, st);
   else
-    launch_split<8, 1, 1>(p, a, o, st);
+    launch_split<8>(p, a, o, st);
 }

@@ -987,7 +987,7 @@ __global__ __launch_bounds__(256) void br_k_score_wave(BrParams p, BrArr a, BrOu
   extern __shared__ int lds[];
   const int w = threadIdx.x >> 6, inst = (int)(blockIdx.x * (blockDim.x >> 6)) + w;
   if (inst >= p.N) return;
-  br_score_wave_run<EM, HB>(p, a, o, inst, br_lane(), lds + w * BR_LIST_WORDS(EM));
+  br_snapshot_helper<EM, HB>(p, a, o, inst, br_lane(), 0, 1, 0u, lds + w * (BR_LIST_WORDS(EM) + 2 * BR_WAVE));
 }
 
 // ------------------------------------------------------------------ launchers
@@ -1157,11 +1157,11 @@ static void launch_score_wave(const BrParams &p, const BrArr &a, const BrOut &o,
   const int wpb = br_waves_per_block(p.N);
   const dim3 grid((unsigned)((p.N + wpb - 1) / wpb)), block(BR_WAVE * wpb);
   if (p.Q <= 256)
-    hipLaunchKernelGGL((br_k_score_wave<4, HB>), grid, block, wpb * BR_LIST_WORDS(4) * sizeof(int), st, p, a, o);
+    hipLaunchKernelGGL((br_k_score_wave<4, HB>), grid, block, wpb * (BR_LIST_WORDS(4) + 2 * BR_WAVE) * sizeof(int), st, p, a, o);
   else if (p.Q <= 512)
-    hipLaunchKernelGGL((br_k_score_wave<8, HB>), grid, block, wpb * BR_LIST_WORDS(8) * sizeof(int), st, p, a, o);
+    hipLaunchKernelGGL((br_k_score_wave<8, HB>), grid, block, wpb * (BR_LIST_WORDS(8) + 2 * BR_WAVE) * sizeof(int), st, p, a, o);
   else
-    hipLaunchKernelGGL((br_k_score_wave<16, HB>), grid, block, wpb * BR_LIST_WORDS(16) * sizeof(int), st, p, a, o);
+    hipLaunchKernelGGL((br_k_score_wave<16, HB>), grid, block, wpb * (BR_LIST_WORDS(16) + 2 * BR_WAVE) * sizeof(int), st, p, a, o);
 }
 
 // What best_g costs one wave that scores every (waiting request, worker with a free slot) pair of a BR-H cluster, every

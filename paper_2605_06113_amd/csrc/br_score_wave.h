@@ -15,6 +15,8 @@
 // 1531 clusters, G = 13, queues of 307, BR-0: 17.7 us in a block per cluster that scored all pairs twice, 8.8 so.
 #pragma once
 
+#include <type_traits>
+
 #include "br_device.h"
 #include "br_list.h"
 
@@ -52,9 +54,9 @@ __device__ __forceinline__ bool br_penalty_shows(const BrParams &p) {
   return p.beta * d_H >= 0.004f * p.aD;
 }
 
-// x: keys in arrival order (position j * 64 + lane)
+// x: keys in arrival order (position first + j * 64 + lane)
 template <int E, int HB>
-__device__ __forceinline__ void br_snapshot_best_g(const BrParams &p, const BrOut &o, int inst, int lane, int qn,
+__device__ __forceinline__ void br_snapshot_best_g(const BrParams &p, const BrOut &o, int inst, int lane, int first, int qn,
                                                    const unsigned (&x)[E], const BrRoundState<HB> &st) {
   const int G = p.G;
   const int64_t qrow = (int64_t)inst * p.Q;
@@ -103,7 +105,7 @@ __device__ __forceinline__ void br_snapshot_best_g(const BrParams &p, const BrOu
 #pragma unroll
     for (int j = 0; j < E; ++j) {
       many[j] = false;
-      if (j * BR_WAVE >= qn) continue;
+      if (first + j * BR_WAVE >= qn) continue;
       const int s = (int)(x[j] >> BR_IDX_BITS);
       unsigned long long left = br_ballot(bg[j] < 0 && x[j] != 0u);
       many[j] = !exact || 2 * __builtin_popcountll(left) > n_free;
@@ -142,10 +144,14 @@ __device__ __forceinline__ void br_snapshot_best_g(const BrParams &p, const BrOu
   }
 #pragma unroll
   for (int j = 0; j < E; ++j) {
-    const int i = j * BR_WAVE + lane;
+    const int i = first + j * BR_WAVE + lane;
     if (i < p.Q) o.best_g[qrow + i] = i < qn ? bg[j] : -1;
   }
-  for (int i = E * BR_WAVE + lane; i < p.Q; i += BR_WAVE) o.best_g[qrow + i] = -1;
+}
+
+// positions from `first` on that hold no request
+__device__ __forceinline__ void br_snapshot_rest(const BrParams &p, const BrOut &o, int inst, int lane, int first) {
+  for (int i = first + lane; i < p.Q; i += BR_WAVE) o.best_g[(int64_t)inst * p.Q + i] = -1;
 }
 
 // first position of the LDS list (n entries) whose key lies below T
@@ -320,7 +326,10 @@ __device__ __forceinline__ void br_list_build(const BrParams &p, const BrArr &a,
                                               int qn, int *lst, const BrRoundState<HB> &st, unsigned (&x)[E]) {
   br_keys_load<E>(p, a, inst, q0, qn, 0, lane, x);
   if constexpr (SCORES) {
-    if (o.best_g) br_snapshot_best_g<E, HB>(p, o, inst, lane, qn, x, st);
+    if (o.best_g) {
+      br_snapshot_best_g<E, HB>(p, o, inst, lane, 0, qn, x, st);
+      br_snapshot_rest(p, o, inst, lane, E * BR_WAVE);
+    }
   }
   br_list_sort<E>(x, lane);
   if constexpr (SCORES) {
@@ -333,24 +342,85 @@ __device__ __forceinline__ void br_list_build(const BrParams &p, const BrArr &a,
   }
 }
 
-// The snapshot reductions of one cluster alone, on one wave; `lst`: BR_LIST_WORDS(EM) words of LDS.
+// BR-0 scores of 64 requests (from position i0 on, n of them) against every worker, as a wave writes them into the matrix:
+// four neighbours per lane and store (element e of the cluster's rows is request e / G, worker e % G; recip_g: the
+// rounded-up reciprocal of G, exact for e < 2^17).  s, m: length of the request, margin of the worker this lane holds;
+// t: 128 words of LDS.
+__device__ __forceinline__ void br_matrix_rows(const BrParams &p, const BrOut &o, int inst, int lane, int i0, int n, int s, int m,
+                                               unsigned recip_g, int *t) {
+  const int G = p.G, total = n * G;
+  int *F = (int *)o.F + ((int64_t)inst * p.Q + i0) * G;
+  t[lane] = s, t[BR_WAVE + lane] = m;
+  br_wave_sync();
+  auto score = [&](int e) -> int {
+    const int i = G == 1 ? e : (int)__umulhi((unsigned)e, recip_g);
+    return br_score0(G, t[BR_WAVE + (e - i * G)], t[i & 63]);
+  };
+  if (((uintptr_t)F & 15u) == 0) {  // (64 rows are whole 16-byte units: so for all of a cluster's or none)
+    for (int e = 4 * lane; e < total; e += 4 * BR_WAVE) {
+      if (e + 3 < total) {
+        *reinterpret_cast<int4 *>(F + e) = make_int4(score(e), score(e + 1), score(e + 2), score(e + 3));
+      } else {
+        for (int k = e; k < total; ++k) F[k] = score(k);
+      }
+    }
+  } else {
+    for (int e = lane; e < total; e += BR_WAVE) F[e] = score(e);
+  }
+  br_wave_sync();
+}
+
+// What a round's caller asked for beside it (matrix, best_g, best_i), on wave h of the nh that a cluster's block has for it
+// while another wave runs the round: none of it is on the round's path, and nothing here is read after the return.
+// lst: BR_LIST_WORDS(EM) + 128 words of LDS of this wave's.
 template <int EM, int HB>
-__device__ __forceinline__ void br_score_wave_run(const BrParams &p, const BrArr &a, const BrOut &o, int inst, int lane, int *lst) {
+__device__ __forceinline__ void br_snapshot_helper(const BrParams &p, const BrArr &a, const BrOut &o, int inst, int lane, int h,
+                                                   int nh, unsigned recip_g, int *lst) {
   BrClusterIn<HB> in;
   br_cluster_load<HB>(p, a, inst, lane, in);
   BrRoundState<HB> st;
   br_round_state<HB>(p, lane, in.n, in.L, st);
   const int qn = in.q0 + min(in.cnt, p.Q - in.q0);
-  if (st.S_tot == 0 || qn == 0) {
-    br_snapshot_none(p, o, inst, lane);
-  } else if (qn <= BR_WAVE) {
-    unsigned x[1];
-    br_list_build<1, HB, true>(p, a, o, inst, lane, in.q0, qn, lst, st, x);
-  } else if (EM == 4 || qn <= 4 * BR_WAVE) {
-    unsigned x[4];
-    br_list_build<4, HB, true>(p, a, o, inst, lane, in.q0, qn, lst, st, x);
-  } else if constexpr (EM > 4) {
-    unsigned x[EM];
-    br_list_build<EM, HB, true>(p, a, o, inst, lane, in.q0, qn, lst, st, x);
+  const bool none = st.S_tot == 0 || qn == 0;
+  if constexpr (HB == 0) {
+    if (o.F) {
+      const int m = st.Mh[0] - st.Lh[0];
+      for (int i0 = h * BR_WAVE; i0 < qn; i0 += nh * BR_WAVE) {
+        unsigned x[1];
+        br_keys_load<1>(p, a, inst, in.q0, qn, i0, lane, x);
+        br_matrix_rows(p, o, inst, lane, i0, min(qn - i0, BR_WAVE), (int)(x[0] >> BR_IDX_BITS), m, recip_g, lst + BR_LIST_WORDS(EM));
+      }
+    }
   }
+  if (none) {
+    if (h == 0) br_snapshot_none(p, o, inst, lane);
+    return;
+  }
+  // one wave: both reductions off one list; more: the last one sorts, the others share out the requests
+  BrOut mine = o;
+  if (nh > 1) {
+    if (h < nh - 1) {
+      if (o.best_g) {
+        for (int i0 = h * 2 * BR_WAVE; i0 < p.Q; i0 += (nh - 1) * 2 * BR_WAVE) {
+          unsigned x[2];
+          br_keys_load<2>(p, a, inst, in.q0, qn, i0, lane, x);
+          br_snapshot_best_g<2, HB>(p, o, inst, lane, i0, qn, x, st);
+        }
+      }
+      return;
+    }
+    mine.best_g = nullptr;
+  }
+  if (!mine.best_g && !mine.best_i) return;
+  auto with = [&](auto e) {
+    constexpr int E = decltype(e)::value;
+    unsigned x[E];
+    br_list_build<E, HB, true>(p, a, mine, inst, lane, in.q0, qn, lst, st, x);
+  };
+  if (qn <= BR_WAVE)
+    with(std::integral_constant<int, 1>{});
+  else if (EM == 4 || qn <= 4 * BR_WAVE)
+    with(std::integral_constant<int, 4>{});
+  else if constexpr (EM > 4)
+    with(std::integral_constant<int, EM>{});
 }

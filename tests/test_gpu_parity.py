@@ -904,6 +904,40 @@ def test_narrow_windows(G, Q, R_max, H):
         r.close()
 
 
+@pytest.mark.parametrize("N,G,H,Q", [(3, 13, 0, 307), (2, 16, 0, 256), (9, 1, 0, 63), (5, 7, 0, 1000), (3, 64, 0, 512),
+                                     (3, 33, 4, 300), (2, 40, 8, 64), (40, 12, 7, 512)])
+@pytest.mark.parametrize("steps", [0, 1])
+def test_outputs_beside_the_round(N, G, H, Q, steps):
+    """Any of the matrix and the two reductions, on the waves beside the round and with the decode steps in the same call;
+    the step-start state is what they show, whatever the round has changed by then."""
+    import torch
+    for k, names in enumerate((("F",), ("best_g",), ("best_i",), ("F", "best_i"), ("F", "best_g", "best_i"))):
+        cfg, init, arr = wl.random_case(680 + G + H + k, N=N, G=G, B=5, max_wait=Q, H=H, fill=0.7, gate_pfin=0.0)
+        init.n[0], arr.count[-1] = cfg.B * (k % 2), Q
+        init.kv[:], init.rem[:] = np.maximum(init.kv, 1), np.maximum(init.rem, 1)
+        _say(f"beside the round N={N} G={G} H={H} Q={Q} steps={steps} {names}")
+        oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
+        out = r.alloc_outputs()
+        for name in ("F", "best_g", "best_i"):
+            if name not in names:
+                del out[name]
+        if "F" in out and k == 3:  # a matrix that starts between 16-byte boundaries
+            out["F"] = torch.zeros(N * Q * G + 1, dtype=out["F"].dtype, device=out["F"].device)[1:].view(N, Q, G)
+        for rnd in range(2):
+            darr = binding.DeviceArrivals(arr, r.device, r.layout.Pq)
+            if steps:
+                r.route_advance_device(darr, out, steps)
+            else:
+                r.route_step_device(darr, out)
+            ref = oc.route_step(arr)
+            oc.advance(steps)
+            torch.cuda.synchronize()
+            compare_outputs(ref, {key: v.cpu().numpy() for key, v in out.items()} | {key: ref[key] for key in ("best_g", "best_i") if key not in out},
+                            cfg, f"beside the round r{rnd}")
+            compare_state(oc, r.state(), cfg, f"beside the round r{rnd}")
+        r.close()
+
+
 @pytest.mark.parametrize("steps", [1, 2, 8, 9, 40])
 @pytest.mark.parametrize("G,Q", [(5, 200), (3, 512), (3, 700)])
 def test_large_batches_decode_orders(G, Q, steps):
