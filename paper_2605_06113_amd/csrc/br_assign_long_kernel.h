@@ -19,8 +19,10 @@
 //     the worker in hand in registers, so that the update after an admission needs no LDS read);
 //   - a score walks the offsets in order with margins and discounts broadcast from LDS, four per load, and
 //     skips the groups of offsets whose margins no value in question reaches (exact zeros);
-//   - the single best request argmax_i F_g({i}) is found by bracketing, not by scoring the whole waiting set
-//     (pick_single: the score is concave in the length, the waiting set is sorted by length);
+//   - the single best request argmax_i F_g({i}) is read off the requests around the peak of the score (pick_quick), where
+//     rounding could reorder those found by bracketing (pick_single: the score is concave in the length, the waiting set
+//     is sorted by length), never by scoring the whole waiting set.  2048 clusters, G = 8, H = 80, overloaded, with the
+//     register sort and margins kept while the envelope stands: whole pass 75.1 -> 71.2 us, one cluster 27.3 -> 26.0;
 //   - Stage 2 goes straight to the starvation guard when the window's smallest entry scores clearly below
 //     zero (then every subset does).
 // Waiting set, sticky binding and epilogue are those of the short-horizon
@@ -226,9 +228,23 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
     who[i] = -1;
   }
   if (run) {
-    int N2 = BR_WAVE;
-    while (N2 < qn) N2 <<= 1;
-    br_sort_desc<E>(xk, lane, N2);
+    if constexpr (E <= 8) {  // (256 keys: 1800 cycles, where the network of br_sort.h takes 8000)
+      if (qn <= BR_WAVE) {
+        unsigned x1[1] = {xk[0]};
+        br_list_sort<1>(x1, lane);
+        xk[0] = x1[0];
+      } else {
+        br_list_sort<E>(xk, lane);
+        br_list_store<E>(xk, skey, lane);
+        br_wave_sync();
+#pragma unroll
+        for (int j = 0; j < E; ++j) xk[j] = (unsigned)skey[j * BR_WAVE + lane];
+      }
+    } else {
+      int N2 = BR_WAVE;
+      while (N2 < qn) N2 <<= 1;
+      br_sort_desc<E>(xk, lane, N2);
+    }
   }
   int sv[E];
   unsigned alive = 0;
@@ -265,7 +281,11 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
   // two, C = 64 / GP), the partial minima meet in LDS.  Padded offsets: envelope 0 against "no worker".
   const int GP = G <= 8 ? 8 : G <= 16 ? 16 : G <= 32 ? 32 : 64;
   const int C = BR_WAVE / GP;
+  // Formed again only after an admission that raised the envelope somewhere.
+  bool grew = true;  // (on any lane)
+  int mn_kept = 0;
   auto lane_minm = [&]() {
+    if (br_ballot(grew) == 0ull) return max(mn_kept - add, 0);
     const int g = lane & (GP - 1), c = lane / GP;
     int mn = INT32_MAX;
     const int *row = sL + min(g, LS - 1);  // lanes that stand for no worker read the last column (their result is never used)
@@ -281,6 +301,7 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
       for (int cc = 0; cc < C; ++cc) mn = min(mn, pm[cc * GP + g]);
       br_wave_sync();
     }
+    mn_kept = mn, grew = false;
     return max(mn - add, 0);  // min_h (M_h - sL_h) - add, clamped once: the same as clamping every offset
   };
 
@@ -409,6 +430,106 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
     return true;
   };
 
+  // The same decided from four requests where that is certain: 1 (pos, swin set), 0 (no request is admissible), -1 (not
+  // certain: pick_single).  Eq. (brh-Fscore) rises with the length while beta sum_{h: m_h < s} d_h stays below alpha D and
+  // falls beyond, so with b the first sorted position on the rising side the best request is the first one in question at
+  // or behind b or the last one before it (the first of its length).  b is searched with the lanes mapped to offsets, three
+  // probes a step.  Those two and the next ones of other lengths beyond them are scored the same way (at most 12
+  // roundings): the best of the four stands if it leads by more than 4 err_unit times the longest of them, what the two
+  // evaluations of two requests can differ by; by concavity everything farther out is lower still.
+  auto pick_quick = [&](int room, int &pos, int &swin) -> int {
+    int b = 0;
+#pragma unroll
+    for (int step = E == 4 ? 64 : 256; step > 0; step >>= 2) {
+      int e[3];
+      float w[3];  // sum of the discounts whose margin the probe exceeds
+#pragma unroll
+      for (int k = 0; k < 3; ++k) e[k] = skey[min(b + (k + 1) * step, NP) - 1];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const float fs = (float)(e[k] >> BR_IDX_BITS);
+        w[k] = (mr[0] < fs ? dr[0] : 0.0f) + (mr[1] < fs ? dr[1] : 0.0f) + (mr[2] < fs ? dr[2] : 0.0f);
+      }
+      br_wave_fsums(w);
+      int up = 0;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) up += ((b + (k + 1) * step <= qn) & (p.beta * w[k] > p.aD)) ? step : 0;
+      b += up;
+    }
+    b = br_uniform(b);
+    // the requests in question as bits; neighbours are found on the scalar side
+    unsigned long long qm[E];
+#pragma unroll
+    for (int j = 0; j < E; ++j) qm[j] = br_ballot(((alive >> j) & 1u) && sv[j] <= room);
+    auto from_on = [&](int at) -> int {  // first one at or behind `at` / last one before it, or -1
+      int r = -1;
+#pragma unroll
+      for (int j = E - 1; j >= 0; --j) {
+        const int d = at - j * BR_WAVE;
+        const unsigned long long m = d >= BR_WAVE ? 0ull : d > 0 ? qm[j] & (~0ull << d) : qm[j];
+        r = m != 0ull ? j * BR_WAVE + (int)__builtin_ctzll(m) : r;
+      }
+      return r;
+    };
+    auto before = [&](int at) -> int {
+      int r = -1;
+#pragma unroll
+      for (int j = 0; j < E; ++j) {
+        const int d = at - j * BR_WAVE;
+        const unsigned long long m = d <= 0 ? 0ull : d < BR_WAVE ? qm[j] & ~(~0ull << d) : qm[j];
+        r = m != 0ull ? j * BR_WAVE + 63 - (int)__builtin_clzll(m) : r;
+      }
+      return r;
+    };
+    auto length = [&](int at) -> int { return at >= 0 ? br_uniform(skey[at] >> BR_IDX_BITS) : 0; };
+    const int lo = from_on(b);
+    int hi = before(b);
+    if (lo < 0 && hi < 0) return 0;
+    const int s_lo = length(lo), s_hi = length(hi);
+    int lo2 = -1, hi2 = -1;  // the next ones of other lengths; hi becomes the first of its length
+    {
+      int h1 = -1;
+#pragma unroll
+      for (int j = E - 1; j >= 0; --j) {
+        const unsigned long long ml = qm[j] & br_ballot(sv[j] < s_lo), mh = qm[j] & br_ballot(sv[j] > s_hi);
+        const unsigned long long me = qm[j] & br_ballot(sv[j] == s_hi);
+        lo2 = ml != 0ull ? j * BR_WAVE + (int)__builtin_ctzll(ml) : lo2;
+        hi2 = mh != 0ull && hi2 < 0 ? j * BR_WAVE + 63 - (int)__builtin_clzll(mh) : hi2;
+        h1 = me != 0ull ? j * BR_WAVE + (int)__builtin_ctzll(me) : h1;
+      }
+      hi2 = hi >= 0 ? hi2 : -1;
+      hi = hi >= 0 ? h1 : -1;
+    }
+    const int s_lo2 = length(lo2), s_hi2 = length(hi2);
+    const int s[4] = {s_hi, s_lo, s_hi2, s_lo2};
+    float F[4], pen[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      pen[v] = 0.0f;
+#pragma unroll
+      for (int u = 0; u < 3; ++u) pen[v] = __fmaf_rn(dr[u], fmaxf(__fsub_rn((float)s[v], mr[u]), 0.0f), pen[v]);
+    }
+    br_wave_fsums(pen);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) F[v] = s[v] > 0 ? br_scoreh_long_from(p.aD, p.beta, s[v], pen[v]) : -INFINITY;
+    const float e4 = 4.0f * err_unit * (float)max(max(s[0], s[1]), max(s[2], s[3]));
+    const bool useh = br_ballot(F[0] > F[1]) != 0ull;
+    const float lead = fmaxf(F[0], F[1]), other = fmaxf(fminf(F[0], F[1]), fmaxf(F[2], F[3]));
+    if (br_ballot(lead - other > e4) != 0ull) {
+      swin = useh ? s_hi : s_lo;
+      pos = useh ? hi : lo;
+      return 1;
+    }
+    return -1;
+  };
+  auto pick = [&](int room, int &pos, int &swin) -> bool {
+    if constexpr (E <= 8) {
+      const int r = pick_quick(room, pos, swin);
+      if (r >= 0) return r != 0;
+    }
+    return pick_single(room, pos, swin);
+  };
+
   // sticky binding of the request at sorted position pos to worker g
   auto bind = [&](int pos, int g, int slot) {
     adm[pos] = (g << 16) | slot;  // every lane stores the same word
@@ -427,6 +548,7 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
     for (int u = 0; u < 3; ++u) {
       const int h = u * BR_WAVE + lane;
       if (h < H1) {
+        grew |= Lg[u] + ag > Mr[u];
         Mr[u] = max(Mr[u], Lg[u] + ag);
         sM[h] = Mr[u];
       }
@@ -511,7 +633,7 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
         margins_of(g);
         const int room = p.W > 0 ? p.W - __builtin_amdgcn_readlane(Lcur, g) : INT32_MAX;
         int pos = 0, swin = 0;
-        if (!pick_single(room, pos, swin)) {
+        if (!pick(room, pos, swin)) {
           drop_worker(g, capmax);
           continue;
         }
@@ -572,8 +694,10 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
         float pen = 0.0f;
 #pragma unroll
         for (int u = 0; u < 3; ++u) pen = __fmaf_rn(dr[u], fmaxf(__fsub_rn(fs, mr[u]), 0.0f), pen);  // (no discount beyond H)
-        pen = br_wave_fsum(pen);
-        guard_sure = br_scoreh_long_from(p.aD, p.beta, s_last, pen) <= -3.0f * err_unit * fs;
+        float pens[1] = {pen};
+        br_wave_fsums(pens);
+        pen = pens[0];
+        guard_sure = br_ballot(br_scoreh_long_from(p.aD, p.beta, s_last, pen) <= -3.0f * err_unit * fs) != 0ull;
       }
       if (guard_sure) {
         br_wave_sync();  // the window has been read before a later pop rewrites it
@@ -706,7 +830,7 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
       if (bestmask == 0 || bestkey <= 0) {  // starvation guard: the single best request anyway
         ++guard;
         int pos = 0, swin = 0;
-        if (!pick_single(room, pos, swin)) {
+        if (!pick(room, pos, swin)) {
           drop_worker(g, capmax);
           continue;
         }

@@ -155,15 +155,28 @@ __device__ __forceinline__ int br_scan_sum(int x) {
   return x;
 }
 
-// sum over the wave, on every lane (uniform); the order of the additions is fixed
-__device__ __forceinline__ float br_wave_fsum(float x) {
-  x = __fadd_rn(x, __int_as_float(br_dpp<0x111>(0, __float_as_int(x))));
-  x = __fadd_rn(x, __int_as_float(br_dpp<0x112>(0, __float_as_int(x))));
-  x = __fadd_rn(x, __int_as_float(br_dpp<0x114>(0, __float_as_int(x))));
-  x = __fadd_rn(x, __int_as_float(br_dpp<0x118>(0, __float_as_int(x))));
-  x = __fadd_rn(x, __int_as_float(br_dpp<0x142, 0xA>(0, __float_as_int(x))));
-  x = __fadd_rn(x, __int_as_float(br_dpp<0x143, 0xC>(0, __float_as_int(x))));
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), BR_WAVE - 1));
+// sums over the wave, on every lane, N of them side by side; the order of the additions is fixed (a butterfly, each step one
+// instruction that reads another lane or a swap of rows: nothing passes through a scalar register)
+template <int N>
+__device__ __forceinline__ void br_wave_fsums(float (&x)[N]) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = __fadd_rn(x[k], __int_as_float(br_dpp<0xB1, 0xF, true>(0, __float_as_int(x[k]))));   // quad_perm [1,0,3,2]
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = __fadd_rn(x[k], __int_as_float(br_dpp<0x4E, 0xF, true>(0, __float_as_int(x[k]))));   // quad_perm [2,3,0,1]
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = __fadd_rn(x[k], __int_as_float(br_dpp<0x141, 0xF, true>(0, __float_as_int(x[k]))));  // row_half_mirror
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = __fadd_rn(x[k], __int_as_float(br_dpp<0x140, 0xF, true>(0, __float_as_int(x[k]))));  // row_mirror
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const auto r = __builtin_amdgcn_permlane16_swap((unsigned)__float_as_int(x[k]), (unsigned)__float_as_int(x[k]), false, false);
+    x[k] = __fadd_rn(__int_as_float((int)r[0]), __int_as_float((int)r[1]));
+  }
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const auto r = __builtin_amdgcn_permlane32_swap((unsigned)__float_as_int(x[k]), (unsigned)__float_as_int(x[k]), false, false);
+    x[k] = __fadd_rn(__int_as_float((int)r[0]), __int_as_float((int)r[1]));
+  }
 }
 
 // For lanes with `in` set and distinct positions `at` in 0..63: lane k receives the number of the lane whose `at` is k

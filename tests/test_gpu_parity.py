@@ -938,6 +938,27 @@ def test_outputs_beside_the_round(N, G, H, Q, steps):
         r.close()
 
 
+@pytest.mark.parametrize("H", [9, 80, 128])
+@pytest.mark.parametrize("Q", [3, 64, 65, 256, 512])
+@pytest.mark.parametrize("wm", [0, 9000])
+def test_long_horizon_single_picks(H, Q, wm):
+    """The best single request from its neighbours around the peak: few requests, runs of equal lengths on both sides of
+    it, everything longer or shorter than the margins, scores that rounding can reorder (a tiny and a zero beta)."""
+    for k, (beta, greedy) in enumerate(((-1.0, 0), (-1.0, 100), (0.3, 100), (1e-3, 0), (0.0, 100))):
+        cfg, init, arr = wl.random_case(700 + H + Q + k, N=10, G=6, B=7, max_wait=Q, H=H, pred_mode=1, fill=0.8, beta=beta,
+                                        S_greedy=greedy, token_watermark=wm, gate_pfin=0.0)
+        arr.count[:] = Q
+        arr.count[:2] = (1, 2)
+        arr.s[2] = 700                                # one length
+        arr.s[3] = np.where(arr.s[3] % 2 == 0, 32768, 40)
+        arr.s[4] = 30000 + arr.s[4] % 4
+        arr.s[5] = 1 + arr.s[5] % 5
+        arr.s[6] = 1000 + arr.s[6] % 40               # neighbours a token or two apart
+        _say(f"single picks H={H} Q={Q} W={wm} beta={beta} greedy={greedy}")
+        oc, r = run_pair(cfg, init, arr, matrix=False, tag="single picks")
+        r.close()
+
+
 @pytest.mark.parametrize("steps", [1, 2, 8, 9, 40])
 @pytest.mark.parametrize("G,Q", [(5, 200), (3, 512), (3, 700)])
 def test_large_batches_decode_orders(G, Q, steps):
