@@ -321,13 +321,14 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
   const bool split = br_split_serves(p);
   const bool together = best && p.R_max <= 8 &&
                         (p.H == 0 ? p.Q <= 1024 : (p.H <= BR_HP && p.Q <= 512 && !br_score_in_tiles(p)));
+  const bool coop = best && p.H <= BR_HP && p.Q > 1024;  // (on the waves of the round's block that wait for its epilogue)
   // Batches that leave waves to spare: other waves of the cluster's block take what is asked for beside the round, for BR-0
   // the matrix as well (br_k_route_helped, the third wave of br_k_route_split).
   const bool spare = p.N < BR_FULL_BATCH_N && p.R_max <= 8 && p.Q <= (p.H == 0 ? 1024 : 512) && p.H <= BR_HP;
   const bool matrix_too = o.F && p.H == 0 && (split || spare);
   const bool helped = !split && spare && (together || matrix_too);
   BrOut first = o;  // what the score kernels write
-  if (split || together) first.best_g = nullptr, first.best_i = nullptr;
+  if (split || together || coop) first.best_g = nullptr, first.best_i = nullptr;
   if (matrix_too) first.F = nullptr;
   if (rc == BR_OK && (first.F || first.best_g || first.best_i))
     rc = enqueue(ctx, BR_K_SCORE, [&] { br_launch_score(p, a, first, partials, ctx->st); }, br);

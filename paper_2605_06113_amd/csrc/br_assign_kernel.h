@@ -850,7 +850,8 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
 
 // One cluster's round on one wave.  EM: the queue holds up to EM * 64 entries; the list is made for 64 or 256 where no
 // more are waiting.  COOP (EM = 32): the block has four waves; all of them sort a long waiting set together
-// (br_sort_desc_block4) and share the epilogue and the decode step, wave 0 runs the round.
+// (br_sort_desc_block4) and share the epilogue and the decode step, wave 0 runs the round; the others compute the snapshot
+// reductions meanwhile (one cluster, G = 64, H = 8, a queue of 2048: whole pass 49.1 -> 43.0 us against a launch of tiles and one that folds them).
 // SCORES: the snapshot reductions (best_g / best_i where asked for) are taken on the way (br_score_wave.h).
 // `split`: the cluster's BR_SPLIT_WORDS of LDS where the decode steps of the old list entries are applied apart (by
 // another wave meanwhile, or by this one before the round), or null.
@@ -875,6 +876,8 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
   int *hitab = win + 32;                         // BIGR: [BR_SEARCH_WORDS] subset-sum tables
   int *svc = hitab + BR_SEARCH_WORDS;            // BIGR, shared: [32] mailbox
   int *dprows = svc + (shared ? 32 : 0);         // BIGR, R_max > 16: bit rows of the subset search
+  // COOP: [BR_LIST_WORDS(32)] the sorted list as it was at the start
+  int *lst2 = lds + BR_ROUND_WORDS(EM, BIGR) + (BIGR && p.R_max > 16 ? BR_DP_LDS_WORDS : 0);
 
   const int lane = br_lane();
   if constexpr (BIGR && !COOP) {
@@ -945,9 +948,14 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
       br_sort_desc_block4(x8, lst, w, lane);
       // (every wave is past its last read of the exchange buffer: the block meets inside the sort after that)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) lst[br_list_at<32>(w * 512 + j * BR_WAVE + lane)] = (int)x8[j];
+      for (int j = 0; j < 8; ++j) {
+        const int at = br_list_at<32>(w * 512 + j * BR_WAVE + lane);
+        lst[at] = (int)x8[j], lst2[at] = (int)x8[j];
+      }
     }
     __syncthreads();
+    // the snapshot reductions on the waves that have nothing to do until the epilogue (which starts with a block barrier)
+    if (w != 0 && (o.best_g || o.best_i)) br_snapshot_coop<HB>(p, a, o, inst, lane, w - 1, q0, qn, run, lst2, st);
   } else {
 #pragma unroll
     for (int j = 0; j < EM; ++j)
@@ -1060,7 +1068,7 @@ template <int E, int HB, bool BIGR = false>
 static void br_launch_assign_one(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
   const bool dp = BIGR && p.R_max > 16;   // windows beyond 16 requests: one cluster per block, with LDS for the bit rows
   const int wpb = dp ? 1 : br_clusters_per_block(p.N, E);
-  const size_t lds = ((size_t)wpb * BR_ROUND_WORDS(E, BIGR) + (dp ? BR_DP_LDS_WORDS : 0)) * sizeof(int);
+  const size_t lds = ((size_t)wpb * BR_ROUND_WORDS(E, BIGR) + (dp ? BR_DP_LDS_WORDS : 0) + (E == 32 ? BR_LIST_WORDS(32) : 0)) * sizeof(int);
   const dim3 grid((unsigned)((p.N + wpb - 1) / wpb)), block(E == 32 ? 4 * BR_WAVE : BR_WAVE * wpb);
   // (decode steps ride along for BR-0 with windows of up to 8 requests only; elsewhere the caller launches the decode kernel)
   if constexpr (BIGR) {

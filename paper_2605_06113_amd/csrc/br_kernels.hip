@@ -523,15 +523,14 @@ __device__ __forceinline__ void br_margins_to_lds(const BrParams &p, int inst, i
 }
 
 // ------------------------------------------------------------------ F-score matrix + reductions
-// Scores every (waiting request, worker) pair on the step-start snapshot: eq. (br0-Fscore) in
-// int32 or eq. (brh-Fscore) in fp32.  Pass A maps lanes to requests (coalesced request-major
+// Scores every (waiting request, worker) pair on the step-start snapshot, eq. (brh-Fscore) in fp32.  Pass A maps lanes to requests (coalesced request-major
 // reads, worker margins broadcast from LDS) and reduces over workers in registers (best worker per
 // request).  Pass B maps lanes to (request sub-slot, worker) and keeps a running best
 // request per worker, combined across lanes and waves at the end.
 // LONG (horizons beyond BR_HP): the margins keep BR_HS(H) entries per worker, the discounts sit in LDS next
 // to them and a score loops over the offsets (br_scoreh_long), skipping the four-offset groups whose margins no
 // request of the tile reaches (clusters too large for br_k_score_long).
-template <bool BRH, bool LONG = false>
+template <bool LONG>
 __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o) {
   extern __shared__ int lds[];
   const int G = p.G;
@@ -562,7 +561,7 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o) 
       const int g = e / HS, h = e - g * HS;
       sm[e] = __float_as_int(h <= p.H ? (float)p.mh[((int64_t)inst * G + g) * (p.H + 1) + h] : 0.0f);
     }
-  } else if constexpr (BRH) {
+  } else {
     if (wave == 0) br_margins_to_lds(p, inst, lane, 0, G, sm, HS);
   }
   if constexpr (LONG)
@@ -572,15 +571,6 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o) 
     ss[i] = min(max(s, 1), BR_MAX_S_DEV);
   }
   __syncthreads();
-  if (!BRH) {  // M(k) = max_g L_g, m_g = M - L_g
-    if (tid < G) {
-      int M = sL[0];
-      for (int g = 1; g < G; ++g) M = max(M, sL[g]);
-      sm[tid * HS] = M - sL[tid];
-    }
-    __syncthreads();
-  }
-
   // pass A: one request per lane, loop over workers
   for (int t0 = (split * nw + wave) * BR_WAVE; t0 < qn; t0 += nsplit * nw * BR_WAVE) {
     const int i = t0 + lane;
@@ -600,8 +590,8 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o) 
       } else {
         int m[BR_HP + 1];
 #pragma unroll
-        for (int h = 0; h <= BR_HP; ++h) m[h] = (BRH || h == 0) ? sm[g * (BR_HP + 1) + h] : 0;
-        key = br_score_key<BRH>(p, m, s);
+        for (int h = 0; h <= BR_HP; ++h) m[h] = sm[g * (BR_HP + 1) + h];
+        key = br_score_key<true>(p, m, s);
       }
       const bool ok = p.W <= 0 || sL[g] + s <= p.W;
       if (ok && key > bk) {
@@ -624,7 +614,7 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o) 
     const bool act = gl < Gs && g < G;
     int m[BR_HP + 1];
 #pragma unroll
-    for (int h = 0; h <= BR_HP; ++h) m[h] = (!LONG && act && (BRH || h == 0)) ? sm[g * (BR_HP + 1) + h] : 0;
+    for (int h = 0; h <= BR_HP; ++h) m[h] = (!LONG && act) ? sm[g * (BR_HP + 1) + h] : 0;
     const int Lg = act ? sL[g] : 0;
     const bool free_slot = act && scap[g] > 0;
     int bk = BR_KEY_NONE, bs = 0, bi = -1;
@@ -637,7 +627,7 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o) 
         br_scoreh_long<1>(p.aD, p.beta, (const float *)(sm + (act ? g : 0) * HS), sd, HS, dv, Fv);
         key = br_ord(Fv[0]);
       } else {
-        key = br_score_key<BRH>(p, m, s);
+        key = br_score_key<true>(p, m, s);
       }
       const bool ok = free_slot && (p.W <= 0 || Lg + s <= p.W);
       if (ok && (key > bk || (key == bk && s > bs))) {
@@ -850,7 +840,7 @@ __host__ __device__ inline size_t br_score_scratch_words(int Q, int G) {
   return 2 * BR_TILE_GROUPS * (size_t)Q + 3 * T * (size_t)G;
 }
 
-template <bool BRH, bool LONG>
+template <bool LONG>
 __global__ __launch_bounds__(64) void br_k_score_tiles(BrParams p, BrArr a, int *partials, int wpg) {
   extern __shared__ int lds[];
   const int tile = blockIdx.x, wg = blockIdx.y, inst = blockIdx.z;
@@ -871,25 +861,17 @@ __global__ __launch_bounds__(64) void br_k_score_tiles(BrParams p, BrArr a, int 
   cnt = min(max(cnt, 0), a.arr_cap);
   const int qn = q0 + min(cnt, p.Q - q0);
 
-  // worker state of the group; BR-0 margins need the envelope over all workers
-  const int Lall = lane < G ? p.L[(int64_t)inst * G + lane] : BR_LOW;
-  const int M = br_wave_max(Lall);
+  // worker state of the group
   if (lane < gn) {
     sL[lane] = p.L[(int64_t)inst * G + g0 + lane];
     scap[lane] = p.B - p.n[(int64_t)inst * G + g0 + lane];
   }
-  if constexpr (BRH && !LONG) {
+  if constexpr (!LONG) {
     br_margins_to_lds(p, inst, lane, g0, gn, sm, HS);
   } else {
     for (int e = lane; e < gn * HS; e += BR_WAVE) {
       const int gl = e / HS, h = e - gl * HS;
-      int m = 0;
-      if (LONG) {
-        if (h <= p.H) m = p.mh[((int64_t)inst * G + g0 + gl) * (p.H + 1) + h];
-      } else if (h == 0) {
-        m = M - p.L[(int64_t)inst * G + g0 + gl];
-      }
-      sm[e] = LONG ? __float_as_int((float)m) : m;
+      sm[e] = __float_as_int(h <= p.H ? (float)p.mh[((int64_t)inst * G + g0 + gl) * (p.H + 1) + h] : 0.0f);
     }
   }
   if constexpr (LONG)
@@ -917,8 +899,8 @@ __global__ __launch_bounds__(64) void br_k_score_tiles(BrParams p, BrArr a, int 
     } else {
       int m[BR_HP + 1];
 #pragma unroll
-      for (int h = 0; h <= BR_HP; ++h) m[h] = (BRH || h == 0) ? sm[gl * HS + h] : 0;
-      key = br_score_key<BRH>(p, m, s);
+      for (int h = 0; h <= BR_HP; ++h) m[h] = sm[gl * HS + h];
+      key = br_score_key<true>(p, m, s);
     }
     const bool ok = valid && (p.W <= 0 || sL[gl] + s <= p.W);
     if (ok && key > bk) {  // workers in ascending order: the first best stays
@@ -1196,8 +1178,8 @@ static int br_pair_units(const BrParams &p) {
 bool br_score_in_tiles(const BrParams &p) {
   const int T = (p.Q + BR_WAVE - 1) / BR_WAVE, wpg = (p.G + BR_TILE_GROUPS - 1) / BR_TILE_GROUPS, WGN = (p.G + wpg - 1) / wpg;
   if (p.N > BR_SCORE_TILES_MAX_N || T * WGN < 8) return false;
-  if (p.H == 0) return p.Q > 512;
-  // (windows beyond 8 requests: no round's launch to ride in)
+  if (p.H == 0) return false;
+  // (windows beyond 8 requests: no round's launch to ride in; queues beyond 1024 ride in the round's block)
   return p.H > BR_HP || p.Q > 512 || p.R_max > 8 || br_pair_units(p) >= BR_UNITS_ONE_WAVE;
 }
 
@@ -1213,11 +1195,9 @@ static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut 
       const int HS = longh ? BR_HS(p.H) : BR_HP + 1;
       const size_t lds = ((size_t)BR_TILE_WORKERS * HS + (longh ? HS + 4 : 0) + 2 * BR_TILE_WORKERS) * sizeof(int);
       if (longh)
-        hipLaunchKernelGGL((br_k_score_tiles<true, true>), grid, block, lds, st, p, a, partials, wpg);
-      else if (p.H > 0)
-        hipLaunchKernelGGL((br_k_score_tiles<true, false>), grid, block, lds, st, p, a, partials, wpg);
+        hipLaunchKernelGGL((br_k_score_tiles<true>), grid, block, lds, st, p, a, partials, wpg);
       else
-        hipLaunchKernelGGL((br_k_score_tiles<false, false>), grid, block, lds, st, p, a, partials, wpg);
+        hipLaunchKernelGGL((br_k_score_tiles<false>), grid, block, lds, st, p, a, partials, wpg);
       const int QB = (p.Q + 255) / 256;
       hipLaunchKernelGGL(br_k_score_combine, dim3((unsigned)(QB + (p.G + 3) / 4), (unsigned)p.N), dim3(256), 0, st, p, o,
                          (const int *)partials, T, WGN, QB);
@@ -1225,7 +1205,7 @@ static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut 
     }
   }
   const bool block = p.H > 0 && p.Q > 512 && p.N <= BR_BLOCK_MAX_N && br_pair_units(p) >= BR_UNITS_ONE_WAVE;
-  if (!longh && p.Q <= 1024 && !block) {  // one wave per cluster
+  if (!longh && !block) {  // one wave per cluster (queues of up to 1024: longer ones do not come here)
     if (p.H == 0)
       launch_score_wave<0>(p, a, o, st);
     else if (p.H <= BR_HP / 2)
@@ -1251,8 +1231,6 @@ static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut 
     }
   }
   if (longh)
-    hipLaunchKernelGGL((br_k_score<true, true>), grid, dim3(64 * waves), lds, st, p, a, o);
-  else if (p.H > 0)
     hipLaunchKernelGGL(br_k_score<true>, grid, dim3(64 * waves), lds, st, p, a, o);
   else
     hipLaunchKernelGGL(br_k_score<false>, grid, dim3(64 * waves), lds, st, p, a, o);

@@ -424,3 +424,33 @@ __device__ __forceinline__ void br_snapshot_helper(const BrParams &p, const BrAr
   else if constexpr (EM > 4)
     with(std::integral_constant<int, EM>{});
 }
+
+// The snapshot reductions of a cluster with a queue beyond 1024 on the three waves of its block that do not run the round
+// (h = 0..2): requests shared out 128 at a time, best_i on the last one.  lst: the sorted list where more than 256 wait, else
+// room for it.
+template <int HB>
+__device__ __forceinline__ void br_snapshot_coop(const BrParams &p, const BrArr &a, const BrOut &o, int inst, int lane, int h,
+                                                 int q0, int qn, bool run, int *lst, const BrRoundState<HB> &st) {
+  if (!run) {
+    if (h == 0) br_snapshot_none(p, o, inst, lane);
+    return;
+  }
+  if (o.best_g) {
+    for (int i0 = h * 2 * BR_WAVE; i0 < p.Q; i0 += 3 * 2 * BR_WAVE) {
+      unsigned x[2];
+      br_keys_load<2>(p, a, inst, q0, qn, i0, lane, x);
+      br_snapshot_best_g<2, HB>(p, o, inst, lane, i0, qn, x, st);
+    }
+  }
+  if (!o.best_i || h != 2) return;
+  if (qn > 4 * BR_WAVE) {
+    unsigned x[32];
+    br_list_load<32>(x, lst, lane, 0, qn);
+    br_snapshot_best_i<32, HB>(p, o, inst, lane, qn, x, lst, st);
+  } else {
+    BrOut mine = o;
+    mine.best_g = nullptr;
+    unsigned x[4];
+    br_list_build<4, HB, true>(p, a, mine, inst, lane, q0, qn, lst, st, x);
+  }
+}

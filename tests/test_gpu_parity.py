@@ -959,6 +959,24 @@ def test_long_horizon_single_picks(H, Q, wm):
         r.close()
 
 
+@pytest.mark.parametrize("G,H,Q,R_max", [(5, 0, 1025, 4), (64, 0, 2048, 4), (7, 3, 1500, 4), (64, 8, 2048, 4), (3, 8, 1100, 12),
+                                         (4, 0, 2048, 24), (1, 2, 1025, 1)])
+@pytest.mark.parametrize("wm", [0, 12000])
+def test_reductions_of_queues_beyond_1024(G, H, Q, R_max, wm):
+    """On the waves of the round's block that wait for its epilogue: nothing waiting, one register, four, the sorted list of
+    the block; workers all full; any one of the two asked for; batches of one and of many."""
+    for N in (1, 9, 40):
+        cfg, init, arr = wl.random_case(720 + G + H + Q + N + wm, N=N, G=G, B=5, max_wait=Q, H=H, R_max=R_max, fill=0.7,
+                                        token_watermark=wm, gate_pfin=0.0)
+        arr.count[:] = np.resize([Q, 0, 1, 64, 65, 256, 257, Q - 1, Q], N)
+        if N > 8:
+            init.n[8] = cfg.B
+            init.kv[:], init.rem[:] = np.maximum(init.kv, 1), np.maximum(init.rem, 1)
+        _say(f"beyond 1024 N={N} G={G} H={H} Q={Q} R_max={R_max} W={wm}")
+        oc, r = run_pair(cfg, init, arr, matrix=False, tag="beyond 1024")
+        r.close()
+
+
 @pytest.mark.parametrize("steps", [1, 2, 8, 9, 40])
 @pytest.mark.parametrize("G,Q", [(5, 200), (3, 512), (3, 700)])
 def test_large_batches_decode_orders(G, Q, steps):
