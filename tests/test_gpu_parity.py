@@ -977,6 +977,30 @@ def test_reductions_of_queues_beyond_1024(G, H, Q, R_max, wm):
         r.close()
 
 
+@pytest.mark.parametrize("H", [4, 8])
+def test_prediction_rows_at_any_address(H):
+    """Arrivals whose prediction rows do not start on 16-byte boundaries, admitted and deferred."""
+    import torch
+    cfg, init, arr = wl.random_case(740 + H, N=6, G=4, B=6, max_wait=70, H=H, gate_pfin=0.5, fill=0.7)
+    for shift in (0, 1, 2):
+        oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
+        darr = binding.DeviceArrivals(arr, r.device, r.layout.Pq)
+        room = torch.zeros(darr.pred.numel() + shift, dtype=torch.float32, device=r.device)
+        room[shift:] = darr.pred.reshape(-1)
+        darr.pred = room[shift:].view(darr.pred.shape)
+        _say(f"rows H={H} shift={shift}")
+        out = r.alloc_outputs(matrix=False)
+        for rnd in range(2):
+            r.route_step_device(darr, out)
+            ref = oc.route_step(arr)
+            torch.cuda.synchronize()
+            compare_outputs(ref, {k: v.cpu().numpy() for k, v in out.items()}, cfg, f"rows r{rnd}")
+            compare_state(oc, r.state(), cfg, f"rows r{rnd}")
+            oc.advance(3)
+            r.advance(3)
+        r.close()
+
+
 @pytest.mark.parametrize("steps", [1, 2, 8, 9, 40])
 @pytest.mark.parametrize("G,Q", [(5, 200), (3, 512), (3, 700)])
 def test_large_batches_decode_orders(G, Q, steps):
