@@ -137,15 +137,17 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
     while (capmax_cur > 0 && br_ballot(cap == capmax_cur) == 0ull) --capmax_cur;
     return capmax_cur;
   };
-  auto workers_max = [&](int v) -> int { return small ? br_row0_max(v) : br_wave_max(v); };
-  auto workers_min = [&](int v) -> int { return small ? br_row0_min(v) : br_wave_min(v); };
+  auto workers_max = [&](int v) -> int { return br_wave_max(v); };  // (a branch to the row's form costs more than its two steps)
+  auto workers_min = [&](int v) -> int { return br_wave_min(v); };
   // rank of each member among the members by (load, index): lanes that are no members hold INT32_MAX
   auto rank_of = [&](int wkey) -> int {
     if (small) return br_row_rank(wkey);
     int rank = 0;
-    for (int g0 = 0; g0 < G; g0 += 4) {  // lanes beyond G hold INT32_MAX and never count
 #pragma unroll
-      for (int u = 0; u < 4; ++u) rank += (__builtin_amdgcn_readlane(wkey, g0 + u) < wkey) ? 1 : 0;
+    for (int u = 0; u < 32; ++u) rank += (__builtin_amdgcn_readlane(wkey, u) < wkey) ? 1 : 0;
+    if (G > 32) {  // lanes beyond G hold INT32_MAX and never count
+#pragma unroll
+      for (int u = 32; u < 64; ++u) rank += (__builtin_amdgcn_readlane(wkey, u) < wkey) ? 1 : 0;
     }
     return rank;
   };
@@ -348,7 +350,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
     if (smax >= 0) K = min(K, (int)__builtin_popcountll(br_ballot(T < K && st_ <= smax)));  // lengths rise with T
     if (K <= 0) return 0;
     // a run cut by the edge of the 64 requests at hand has an unknown order here
-    if (n_alive > BR_WAVE && __builtin_amdgcn_readlane(ga, BR_WAVE - 1) < K) return 0;
+    if (__builtin_expect(n_alive > BR_WAVE && __builtin_amdgcn_readlane(ga, BR_WAVE - 1) < K, 0)) return 0;
     if (T < K) slots[T] = e;
     br_wave_sync();
     if constexpr (BRH) {
@@ -357,12 +359,16 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
       const int src = br_ranks_to_lanes(rel >= 0 && rel < K, rel, lane);
       const int s_k = slots[min(lane, K - 1)] >> BR_IDX_BITS;
       int mn = INT32_MAX, mo = INT32_MAX;
+      int Lk[NH], Mk[NH];
+#pragma unroll
+      for (int h = 0; h < NH; ++h) Lk[h] = __builtin_amdgcn_ds_bpermute(src << 2, Lh[h]);
+      // envelope before the k-th admission: running maximum over the lanes below
+#pragma unroll
+      for (int h = 0; h < NH; ++h) Mk[h] = lane < K ? Lk[h] + s_k : BR_LOW;
+      br_scan_maxs(Mk);
 #pragma unroll
       for (int h = 0; h < NH; ++h) {
-        const int Lk = __builtin_amdgcn_ds_bpermute(src << 2, Lh[h]);
-        // envelope before the k-th admission: running maximum over the lanes below
-        const int Mk = br_scan_max(lane < K ? Lk + s_k : BR_LOW);
-        const int m = max(max(Mh[h], br_dpp<0x138>(BR_LOW, Mk)) - Lk, 0);  // wave_shr:1
+        const int m = max(max(Mh[h], br_dpp<0x138>(BR_LOW, Mk[h])) - Lk[h], 0);  // wave_shr:1
         mn = min(mn, m);
         mo = h <= ho ? min(mo, m) : mo;
       }
@@ -396,12 +402,9 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
       x[j] = pos < newend ? v : 0u;
     }
     stale |= part;
-    if constexpr (BRH) {
 #pragma unroll
-      for (int h = 0; h < NH; ++h) Mh[h] = workers_max(Lh[h]);
-    } else {
-      Mh[0] = workers_max(Lh[0]);
-    }
+    for (int h = 0; h < NH; ++h) Mh[h] = Lh[h];
+    br_wave_maxs(Mh);
     S_tot -= K;
     n_alive -= K;
     admitted += K;
@@ -460,7 +463,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
       const int room = p.W > 0 ? p.W - Lg[0] : INT32_MAX;
       unsigned key = 0u;
       bool none_below = false;
-      if (!pick(mg, room, key, none_below)) {
+      if (__builtin_expect(!pick(mg, room, key, none_below), 0)) {
         drop_worker(g, capmax);
         ++r;
         continue;

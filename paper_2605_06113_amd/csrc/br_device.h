@@ -144,6 +144,40 @@ __device__ __forceinline__ int br_scan_max(int x) {
   return x;
 }
 
+// N maxima over the wave / N running maxima side by side: one alone waits out the cross-lane hazard of each step.
+template <int N>
+__device__ __forceinline__ void br_wave_maxs(int (&x)[N]) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = max(x[k], br_dpp<0xB1, 0xF, true>(0, x[k]));
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = max(x[k], br_dpp<0x4E, 0xF, true>(0, x[k]));
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = max(x[k], br_dpp<0x141, 0xF, true>(0, x[k]));
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = max(x[k], br_dpp<0x140, 0xF, true>(0, x[k]));
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = max(x[k], br_dpp<0x142, 0xA>(INT32_MIN, x[k]));
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = max(x[k], br_dpp<0x143, 0xC>(INT32_MIN, x[k]));
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = __builtin_amdgcn_readlane(x[k], 63);
+}
+template <int N>
+__device__ __forceinline__ void br_scan_maxs(int (&x)[N]) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = max(x[k], br_dpp<0x111>(INT32_MIN, x[k]));
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = max(x[k], br_dpp<0x112>(INT32_MIN, x[k]));
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = max(x[k], br_dpp<0x114>(INT32_MIN, x[k]));
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = max(x[k], br_dpp<0x118>(INT32_MIN, x[k]));
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = max(x[k], br_dpp<0x142, 0xA>(INT32_MIN, x[k]));
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = max(x[k], br_dpp<0x143, 0xC>(INT32_MIN, x[k]));
+}
+
 // Sum over the lane and all lanes below it.
 __device__ __forceinline__ int br_scan_sum(int x) {
   x += br_dpp<0x111>(0, x);

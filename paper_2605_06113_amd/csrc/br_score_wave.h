@@ -252,7 +252,8 @@ __device__ __forceinline__ void br_round_state(const BrParams &p, int lane, int 
 #pragma unroll
   for (int h = 0; h <= HB; ++h) st.Lh[h] = act ? L_raw[h] : BR_LOW;
 #pragma unroll
-  for (int h = 0; h <= HB; ++h) st.Mh[h] = br_wave_max(st.Lh[h]);
+  for (int h = 0; h <= HB; ++h) st.Mh[h] = st.Lh[h];
+  br_wave_maxs(st.Mh);
   st.S_tot = br_wave_sum(st.cap);
 }
 
