@@ -4,10 +4,14 @@
 // The score does not fall with the margin, and every worker whose margin the request does not exceed gives it the same
 // score, its length: the best worker is the lowest index among the eligible ones with L_g <= M - s (a compare and a
 // ballot), and only if there is none the lightest eligible one (a reduction).  A dependent chain bound by its
-// instructions; lengths come from a register by readlane and decisions are kept in one, 64 arrivals at a time.
-// 4096 clusters, G = 16, 60 arrivals each: 27 us with a score and a reduction per arrival and a second pass to commit, 21 us so.
+// instructions: lengths come from a register by readlane, decisions are kept in one, 64 arrivals at a time, and the chosen
+// worker's words are changed by writelane, so that the arithmetic is scalar.  4096 clusters, G = 16, 60 arrivals each: 27 us
+// with a score and a reduction per arrival and a second pass to commit, 21.7 with vector updates (whole pass 52.9), 17.5 so (48.9).
 #include "br_device.h"
 #include "br_launch.h"
+
+// lane `lane` of old replaced by value (both uniform)
+extern "C" __device__ int br_writelane(int value, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
 
 #define BR_STATB(o, inst, k) (o).stats[(int64_t)(inst) * 16 + (k)]
 
@@ -34,9 +38,10 @@ __global__ __launch_bounds__(256) void br_k_bypass(BrParams p, BrArr a, BrOut o)
   const long long I_before = o.stats ? (long long)G * M - sum_loads() : 0;
 
   int admitted = 0;
-  const bool small = G <= 16;
   const int top = p.W > 0 ? p.W : INT32_MAX;  // (loads stay below 2^25)
   int dropped = 0;
+  // loads as the choice sees them: a worker without a free slot is beyond every bound
+  int Lk = cap > 0 ? L : INT32_MAX;
   int s_next = 1, o_next = 1, id_next = 0;  // the next 64 arrivals, requested while the ones in hand are placed
   auto fetch = [&](int c) {
     const int i = c + lane;
@@ -50,28 +55,27 @@ __global__ __launch_bounds__(256) void br_k_bypass(BrParams p, BrArr a, BrOut o)
   for (int c = 0; c < cnt; c += BR_WAVE) {
     const int s64 = min(max(s_next, 1), BR_MAX_S_DEV), o64 = max(o_next, 1), id64 = id_next;
     fetch(c + BR_WAVE);
-    const int nc = min(BR_WAVE, cnt - c);
+    const int nc = br_uniform(min(BR_WAVE, cnt - c));
     int d64 = -1;
     for (int i = 0; i < nc; ++i) {
       const int s = __builtin_amdgcn_readlane(s64, i);
-      const unsigned long long freem = br_ballot(cap > 0);
-      unsigned long long pickm = freem & br_ballot(L <= min(M, top) - s);
-      if (pickm == 0ull) {  // no worker takes it within its margin: the lightest eligible one
-        const unsigned long long elig = p.W > 0 ? freem & br_ballot(L <= p.W - s) : freem;
-        if (elig == 0ull) continue;
-        const int Le = ((elig >> lane) & 1ull) ? L : INT32_MAX;
-        const int Lmin = small ? br_row0_min(Le) : br_wave_min(Le);
-        pickm = br_ballot(Le == Lmin);
+      unsigned long long pickm = br_ballot(Lk <= min(M, top) - s);
+      if (__builtin_expect(pickm == 0ull, 0)) {  // no worker takes it within its margin: the lightest eligible one
+        const int Le = Lk <= top - s ? Lk : INT32_MAX;  // (top - s stays below what marks a full worker)
+        const int Lmin = br_wave_min(Le);
+        pickm = Lmin == INT32_MAX ? 0ull : br_ballot(Le == Lmin);
       }
-      const int g = (int)__builtin_ctzll(pickm);
-      const bool me = lane == g;
-      M = max(M, __builtin_amdgcn_readlane(L, g) + s);
-      d64 = lane == i ? (g << 16) | __builtin_amdgcn_readlane(nn, g) : d64;
-      L += me ? s : 0;
-      cap -= me ? 1 : 0;
-      nn += me ? 1 : 0;
-      ++admitted;
+      if (__builtin_expect(pickm != 0ull, 1)) {
+        const int g = (int)__builtin_ctzll(pickm);
+        const int Lg = __builtin_amdgcn_readlane(Lk, g) + s, slot = __builtin_amdgcn_readlane(nn, g);
+        M = max(M, Lg);
+        d64 = br_writelane((g << 16) | slot, i, d64);
+        L = br_writelane(Lg, g, L);
+        Lk = br_writelane(slot + 1 < p.B ? Lg : INT32_MAX, g, Lk);
+        nn = br_writelane(slot + 1, g, nn);
+      }
     }
+    admitted += __builtin_popcountll(br_ballot(d64 >= 0));
     // commit: placed arrivals go to their workers' lists; the rest join the waiting queue in order
     const int i = c + lane;
     const bool in = lane < nc, left = in && d64 < 0;
