@@ -665,7 +665,7 @@ __global__ __launch_bounds__(512) void br_k_score(BrParams p, BrArr a, BrOut o) 
 // worker (the tie rules of br_k_score).  Groups of four offsets whose margins no request of the tile reaches are skipped.
 // Overloaded clusters are nearly full most of the time: 2048 clusters, G = 8, H = 80, 135 waiting, 1.2 free slots each:
 // whole pass 89.6 us with every worker scored, 75.1 so.
-__global__ __launch_bounds__(512) void br_k_score_long(BrParams p, BrArr a, BrOut o) {
+__global__ __launch_bounds__(1024) void br_k_score_long(BrParams p, BrArr a, BrOut o) {
   extern __shared__ int lds[];
   const int G = p.G, HS = BR_HS(p.H), KS = G | 1;
   float *sm = (float *)lds;              // [G][HS] margins
@@ -1175,10 +1175,29 @@ static int br_pair_units(const BrParams &p) {
 #define BR_UNITS_ONE_WAVE 2048
 #define BR_BLOCK_MAX_N 256
 
+// Long horizons, up to 16 clusters: one launch of a block per cluster (br_k_score_long) or the tiles and their combine.  The
+// block scores the pairs of workers with a free slot only, and without a watermark a long queue leaves few of those; under a
+// watermark all pairs may be scored.  By (tile of 64 requests, worker) pairs; whole pass, us, block / tiles:
+//   overloaded     G = 8, Q = 256 (32 pairs) 21.1 / 24.5   G = 8, Q = 512 (64) 23.0 / 26.3   G = 16, Q = 256 (64) 25.1 / 32.6
+//                  G = 8, Q = 1024 (128) 29.2 / 34.0       G = 32, Q = 256 (128) 36.2 / 43.9
+//   watermark that keeps slots free everywhere, queue full
+//                  G = 8, Q = 256 40.5 / 39.6              G = 8, Q = 512 54.4 / 47.7        G = 16, Q = 256 59.5 / 59.4
+//                  G = 8, Q = 1024 94 / 66                 G = 32, Q = 256 102 / 96
+static size_t br_long_block_bytes(const BrParams &p) {  // LDS of br_k_score_long
+  const size_t HS = BR_HS(p.H), Qp = ((size_t)p.Q + 63) & ~(size_t)63;
+  return (((size_t)p.G + 1) * HS + 2 * (size_t)p.G + Qp + Qp * (size_t)(p.G | 1)) * sizeof(int);
+}
+#define BR_LONG_BLOCK_LDS (60 * 1024)
+
+static bool br_long_in_block(const BrParams &p, int T) {
+  return br_long_block_bytes(p) <= BR_LONG_BLOCK_LDS && T * p.G <= (p.W <= 0 ? 128 : T <= 4 ? 64 : 0);
+}
+
 bool br_score_in_tiles(const BrParams &p) {
   const int T = (p.Q + BR_WAVE - 1) / BR_WAVE, wpg = (p.G + BR_TILE_GROUPS - 1) / BR_TILE_GROUPS, WGN = (p.G + wpg - 1) / wpg;
   if (p.N > BR_SCORE_TILES_MAX_N || T * WGN < 8) return false;
   if (p.H == 0) return false;
+  if (p.H > BR_HP && br_long_in_block(p, T)) return false;
   // (windows beyond 8 requests: no round's launch to ride in; queues beyond 1024 ride in the round's block)
   return p.H > BR_HP || p.Q > 512 || p.R_max > 8 || br_pair_units(p) >= BR_UNITS_ONE_WAVE;
 }
@@ -1221,14 +1240,11 @@ static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut 
   int nsplit = 1;
   while (nsplit < 8 && nsplit * 2 <= p.G && (int64_t)p.N * nsplit * 2 <= 512 && p.Q > 64 * waves * nsplit) nsplit *= 2;
   const dim3 grid((unsigned)p.N, (unsigned)nsplit);
-  if (longh && p.N > BR_SCORE_TILES_MAX_N) {  // room for all keys of a cluster: every pair is scored once
-    const size_t Qp = ((size_t)p.Q + 63) & ~(size_t)63;
-    const size_t words = ((size_t)p.G + 1) * HS + 2 * (size_t)p.G + Qp + Qp * (size_t)(p.G | 1);
-    if (words * 4 <= 60 * 1024) {
-      // eight waves per cluster while that leaves the batch resident at once
-      hipLaunchKernelGGL(br_k_score_long, dim3((unsigned)p.N), dim3(p.N <= 1024 ? 512 : 256), words * 4, st, p, a, o);
-      return;
-    }
+  if (longh && br_long_block_bytes(p) <= BR_LONG_BLOCK_LDS) {  // room for all keys of a cluster: every pair is scored once
+    // sixteen waves per cluster for a few of them, eight while that leaves the batch resident at once
+    const int threads = p.N <= BR_SCORE_TILES_MAX_N ? 1024 : p.N <= 1024 ? 512 : 256;
+    hipLaunchKernelGGL(br_k_score_long, dim3((unsigned)p.N), dim3(threads), br_long_block_bytes(p), st, p, a, o);
+    return;
   }
   if (longh)
     hipLaunchKernelGGL(br_k_score<true>, grid, dim3(64 * waves), lds, st, p, a, o);

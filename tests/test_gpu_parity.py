@@ -850,12 +850,15 @@ def test_snapshot_reductions_by_their_work(N, G, H, Q, R_max, own):
         r.close()
 
 
-@pytest.mark.parametrize("G,H,Q,wm", [(3, 40, 70, 0), (8, 80, 256, 0), (13, 9, 130, 9000), (64, 17, 65, 0)])
-def test_long_horizon_reductions_by_free_workers(G, H, Q, wm):
+@pytest.mark.parametrize("N,G,H,Q,wm", [
+    (20, 3, 40, 70, 0), (20, 8, 80, 256, 0), (20, 13, 9, 130, 9000), (20, 64, 17, 65, 0),
+    # up to 16 clusters: a block each up to 128 pairs (a watermark: 64, queues of up to 256), tiles beyond
+    (16, 16, 80, 512, 0), (9, 17, 80, 512, 0), (9, 16, 30, 256, 9000), (9, 17, 30, 256, 9000), (9, 4, 20, 320, 9000), (9, 64, 128, 128, 0)])
+def test_long_horizon_reductions_by_free_workers(N, G, H, Q, wm):
     """Only workers with a free slot are scored: none, one, some, all of them free; nothing waiting."""
-    cfg, init, arr = wl.random_case(640 + G + H, N=20, G=G, B=5, max_wait=Q, H=H, pred_mode=1, token_watermark=wm)
+    cfg, init, arr = wl.random_case(640 + G + H, N=N, G=G, B=5, max_wait=Q, H=H, pred_mode=1, token_watermark=wm)
     init.kv[:], init.rem[:] = np.maximum(init.kv, 1), np.maximum(init.rem, 1)  # (slots that the next lines take)
-    for i in range(20):
+    for i in range(N):
         init.n[i, :max(G - i, 0)] = cfg.B   # worker g is full in the clusters below G - g
     arr.count[5] = 0
     arr.count[7] = Q
