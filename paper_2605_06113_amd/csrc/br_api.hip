@@ -327,11 +327,13 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
   const bool spare = p.N < BR_FULL_BATCH_N && p.R_max <= 8 && p.Q <= (p.H == 0 ? 1024 : 512) && p.H <= BR_HP;
   const bool matrix_too = o.F && p.H == 0 && (split || spare);
   const bool helped = !split && spare && (together || matrix_too);
+  const bool long_helped = best && p.H > BR_HP && br_long_helped(p);  // (on the helper waves of the long-horizon round)
   BrOut first = o;  // what the score kernels write
-  if (split || together || coop) first.best_g = nullptr, first.best_i = nullptr;
+  if (split || together || coop || long_helped) first.best_g = nullptr, first.best_i = nullptr;
   if (matrix_too) first.F = nullptr;
   if (rc == BR_OK && (first.F || first.best_g || first.best_i))
     rc = enqueue(ctx, BR_K_SCORE, [&] { br_launch_score(p, a, first, partials, ctx->st); }, br);
+  if (p.H > BR_HP && !long_helped) o.best_g = nullptr, o.best_i = nullptr;  // (done)
   if (rc == BR_OK) {
     rc = enqueue(ctx, BR_K_ASSIGN, [&] {
       if (split)

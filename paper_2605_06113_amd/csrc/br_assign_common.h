@@ -314,6 +314,17 @@ __device__ __forceinline__ BrParams br_late_params() {
   return p;
 }
 
+// Likewise the outputs.
+__device__ __forceinline__ BrOut br_late_out() {
+  typedef __attribute__((address_space(4))) const char kchar_t;
+  typedef __attribute__((address_space(4))) const BrOut kout_t;
+  kchar_t *ka = (kchar_t *)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(ka));
+  BrOut o;
+  __builtin_memcpy(&o, (kout_t *)(ka + sizeof(BrParams) + sizeof(BrArr)), sizeof(BrOut));
+  return o;
+}
+
 // Decode advance of one BR-0 cluster by the wave that has just routed it: br_adv_apply (the arithmetic of
 // the stand-alone advance kernel) over the cluster's G lists in (list, 256-slot chunk) units, UB units
 // requested before the first is used.  `Lcur`, `nn`: load and list length of worker `lane` after the round.

@@ -83,6 +83,68 @@ __device__ __forceinline__ void br_long_slice_best(const BrParams &p, const floa
   }
 }
 
+// LDS of a helper wave for the snapshot reductions: margins of a worker, then the best request it has seen for every worker
+#define BR_LONG_RED_WORDS(HS, G) ((HS) + 4 + ((3 * (G) + 3) & ~3))
+
+// The snapshot reductions of a cluster (K2 + K3) on its nh helper waves while wave 0 runs the round: wave h takes every nh-th
+// tile of 64 requests against every worker with a free slot; a worker's step-start margins are on their way from memory while
+// the one before it is scored.  best_g is written here; what is best for a worker among these requests (score, then the longer
+// request, then the earlier arrival) goes to `red`, where wave 0 finds it at the end of the round.
+__device__ __forceinline__ void br_long_reductions(const BrParams &p, const BrArr &a, const BrOut &o, int inst, int lane, int h,
+                                                   int nh, int q0, int qn, const float *sd, float *red) {
+  const int G = p.G, H1 = p.H + 1, HS = BR_HS(p.H);
+  const int64_t wrow = (int64_t)inst * G, qrow = (int64_t)inst * p.Q;
+  int *part = (int *)(red + HS + 4);
+  const int n_raw = p.n[wrow + min(lane, G - 1)], L = p.L[wrow + min(lane, G - 1)];
+  const unsigned long long freem = br_ballot(lane < G && n_raw < p.B);
+  int ik = BR_KEY_NONE, is = 0, ii = -1;  // lane g: of worker g
+  int mh[3] = {0, 0, 0};
+  auto fetch = [&](int g) {
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+      const int e = u * BR_WAVE + lane;
+      if (u * BR_WAVE < HS) mh[u] = p.mh[(wrow + g) * H1 + min(e, H1 - 1)];
+    }
+  };
+  for (int t = h; t * BR_WAVE < p.Q; t += nh) {
+    const int i = t * BR_WAVE + lane;
+    int bk = BR_KEY_NONE, bg = -1;
+    if (t * BR_WAVE < qn && freem != 0ull) {
+      unsigned x[1];
+      br_keys_load<1>(p, a, inst, q0, qn, t * BR_WAVE, lane, x);
+      fetch((int)__builtin_ctzll(freem));
+      const int s[1] = {(int)(x[0] >> BR_IDX_BITS)};
+      const int top[1] = {br_wave_max(s[0])};
+      for (unsigned long long f = freem; f != 0ull;) {
+        const int g = (int)__builtin_ctzll(f);
+        f &= f - 1ull;
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+          const int e = u * BR_WAVE + lane;
+          if (e < HS) red[e] = e < H1 ? (float)mh[u] : 0.0f;
+        }
+        br_wave_sync();
+        if (f != 0ull) fetch((int)__builtin_ctzll(f));
+        float F[1];
+        br_scoreh_long_sel<1>(p.aD, p.beta, red, sd, HS, lane, top, s, F);
+        br_wave_sync();
+        const int room = p.W > 0 ? p.W - __builtin_amdgcn_readlane(L, g) : INT32_MAX;
+        const int key = x[0] != 0u && s[0] <= room ? br_ord(F[0]) : BR_KEY_NONE;
+        if (key > bk) bk = key, bg = g;  // workers in ascending order: the first best stays
+        const int km = br_wave_max(key);
+        if (km != BR_KEY_NONE) {
+          const int sb = br_wave_max(key == km ? s[0] : -1);
+          const int ib = br_wave_min(key == km && s[0] == sb ? i : INT32_MAX);
+          const bool better = lane == g && (km > ik || (km == ik && (sb > is || (sb == is && ib < ii))));
+          ik = better ? km : ik, is = better ? sb : is, ii = better ? ib : ii;
+        }
+      }
+    }
+    if (o.best_g && i < p.Q) o.best_g[qrow + i] = bg;
+  }
+  if (lane < G) part[lane] = ik, part[G + lane] = is, part[2 * G + lane] = ii;
+}
+
 template <int E, int NW>
 // (queues of up to 256: four waves per SIMD are asked for, which is what br_long_waves counts on)
 __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrParams p, BrArr a, BrOut o) {
@@ -150,6 +212,11 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
 #pragma unroll
       for (int j = 0; j < EW; ++j) svh[j] = skey[(w * EW + j) * BR_WAVE + lane] >> BR_IDX_BITS;
       const int sprobe = skey[lane * E] >> BR_IDX_BITS;  // the probe of this lane in a bracketing search
+      if (o.best_g || o.best_i) {
+        br_long_reductions(p, a, o, inst, lane, w - 1, NW - 1, q0, qn, sd,
+                           (float *)(mbox + 16) + (w - 1) * BR_LONG_RED_WORDS(HS, G));
+        __builtin_amdgcn_s_waitcnt(0);  // every read has returned before the block meets for the last time
+      }
       for (;;) {
         __syncthreads();
         const int cmd = mbox[0];
@@ -876,6 +943,18 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
   if constexpr (NW > 1) {
     mbox[0] = 0;  // the round is over: the helper waves leave
     __syncthreads();
+    int32_t *best_i = br_late_out().best_i;
+    if (best_i && lane < p.G) {  // lane g: the best of what the helpers found for worker g
+      int bk = BR_KEY_NONE, bs = 0, bi = -1;
+#pragma unroll
+      for (int u = 0; u < NW - 1; ++u) {
+        const int *part = mbox + 16 + u * BR_LONG_RED_WORDS(HS, G) + HS + 4;
+        const int k = part[lane], s = part[G + lane], i = part[2 * G + lane];
+        const bool better = i >= 0 && (bi < 0 || k > bk || (k == bk && (s > bs || (s == bs && i < bi))));
+        bk = better ? k : bk, bs = better ? s : bs, bi = better ? i : bi;
+      }
+      best_i[(int64_t)inst * p.G + lane] = bi;
+    }
 #pragma unroll
     for (int u = 1; u < NW; ++u) who[u * BR_WAVE + lane] = -1;  // (held the helpers' partial sums)
     br_wave_sync();
@@ -902,7 +981,8 @@ void br_launch_assign_long_one(const BrParams &p, const BrArr &a, const BrOut &o
   const int HS = BR_HS(p.H);
   const int nw = br_long_waves(p);
   const size_t lds = ((size_t)3 * E * BR_WAVE + 2 * BR_WAVE + 3 * (size_t)HS + (((size_t)HS * BR_LSTRIDE(p.G) + 3) & ~(size_t)3) +
-                      (p.R_max > 8 ? 1024 : 0) + (nw > 1 ? 16 : 0)) * sizeof(int);
+                      (p.R_max > 8 ? 1024 : 0) + (nw > 1 ? 16 : 0) +
+                      (o.best_g || o.best_i ? (nw - 1) * BR_LONG_RED_WORDS(HS, p.G) : 0)) * sizeof(int);
   const dim3 grid((unsigned)p.N), block(BR_WAVE * nw);
   if (nw == 4)
     hipLaunchKernelGGL((br_k_assign_long<E, 4>), grid, block, lds, st, p, a, o);
