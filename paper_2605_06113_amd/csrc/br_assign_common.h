@@ -5,6 +5,8 @@
 // list or stays in the queue: one memory round trip per group of four blocks of 64 entries.
 #pragma once
 
+#include <type_traits>
+
 #include "br_device.h"
 #include "br_score_wave.h"
 
@@ -54,18 +56,34 @@ __device__ __forceinline__ BrTailArgs br_tail_args() {
 
 // ---- pieces of the epilogue, each over GR blocks of 64 arrival positions starting at block j0 ----
 
-// What those positions hold and where they went.  PRED: prediction rows travel with the requests.
-template <int GR, bool PRED>
+// How prediction rows travel with the requests: not at all, by single floats, or as 16-byte words where rows are whole ones
+// and lie on such boundaries (the workspace's always do, the caller's arrivals may not).  One cluster, rows of eight, a queue of
+// 2048: whole pass 43.0 us by single floats, 37.0 so.  Decided once per cluster: decided per row, the two forms share
+// registers and every row is waited for (whole pass of two clusters, rows of
+// five, a queue of 723 55.7 us so, 54.7 without; of the one cluster with a queue of 2048 34.1 and 33.0).
+#define BR_ROWS_NONE 0
+#define BR_ROWS_FLOAT 1
+#define BR_ROWS_WIDE 2
+template <bool PRED, typename F>
+__device__ __forceinline__ void br_with_rows(const BrTailArgs &t, F &&body) {
+  if constexpr (!PRED)
+    body(std::integral_constant<int, BR_ROWS_NONE>{});
+  else if ((t.Pq & 3) == 0 && ((uintptr_t)t.apred & 15u) == 0)
+    body(std::integral_constant<int, BR_ROWS_WIDE>{});
+  else
+    body(std::integral_constant<int, BR_ROWS_FLOAT>{});
+}
+
+// What those positions hold and where they went.
+template <int GR, int ROWS>
 struct BrQueueGroup {
   int bound[GR], id[GR], sq[GR], oq[GR];
-  float pr[PRED ? GR : 1][BR_HP];
+  float pr[ROWS != BR_ROWS_NONE ? GR : 1][BR_HP];
 };
 
-// A request's prediction row, read and written as 16-byte words where rows are whole ones and lie on such boundaries
-// (`wide`: the workspace's always do, the caller's arrivals may not).  One cluster, rows of eight, a queue of 2048: whole pass
-// 43.0 us by single floats, 37.0 so.
-__device__ __forceinline__ void br_row_load(const float *src, int Pq, bool wide, float (&r)[BR_HP]) {
-  if (wide) {
+template <int ROWS>
+__device__ __forceinline__ void br_row_load(const float *src, int Pq, float (&r)[BR_HP]) {
+  if constexpr (ROWS == BR_ROWS_WIDE) {
 #pragma unroll
     for (int q = 0; q < BR_HP; q += 4)
       if (q < Pq) {
@@ -78,8 +96,9 @@ __device__ __forceinline__ void br_row_load(const float *src, int Pq, bool wide,
       if (q < Pq) r[q] = src[q];
   }
 }
+template <int ROWS>
 __device__ __forceinline__ void br_row_store(float *dst, int Pq, const float (&r)[BR_HP]) {
-  if ((Pq & 3) == 0) {
+  if constexpr (ROWS == BR_ROWS_WIDE) {
 #pragma unroll
     for (int q = 0; q < BR_HP; q += 4)
       if (q < Pq) *reinterpret_cast<float4 *>(dst + q) = make_float4(r[q], r[q + 1], r[q + 2], r[q + 3]);
@@ -117,11 +136,10 @@ __device__ __forceinline__ void br_queue_words(const int32_t *qs, const int32_t 
 }
 
 // Where they went (from LDS) and their prediction rows; `words` as read before, or null: read here.
-template <int GR, bool PRED>
+template <int GR, int ROWS>
 __device__ __forceinline__ void br_queue_load(const BrTailArgs &t, int inst, int lane, int j0, int q0, int qn, const int *bound,
-                                              BrQueueGroup<GR, PRED> &v, const BrQueueWords<GR> *words = nullptr) {
+                                              BrQueueGroup<GR, ROWS> &v, const BrQueueWords<GR> *words = nullptr) {
   const int64_t qrow = (int64_t)inst * t.Q, arow = (int64_t)inst * t.arr_cap;
-  const bool wide = PRED && (t.Pq & 3) == 0 && ((uintptr_t)t.apred & 15u) == 0;
   BrQueueWords<GR> w;
   if (words)
     w = *words;
@@ -133,18 +151,18 @@ __device__ __forceinline__ void br_queue_load(const BrTailArgs &t, int inst, int
     v.bound[u] = -1, v.id[u] = w.id[u], v.sq[u] = w.sq[u], v.oq[u] = w.oq[u];
     if (i < qn) {
       v.bound[u] = bound[i];
-      if constexpr (PRED) {
+      if constexpr (ROWS != BR_ROWS_NONE) {
         const bool old = i < q0;
         const float *src = old ? t.qpred + (qrow + i) * t.Pq : t.apred + (arow + (i - q0)) * t.Pq;
-        br_row_load(src, t.Pq, wide, v.pr[u]);
+        br_row_load<ROWS>(src, t.Pq, v.pr[u]);
       }
     }
   }
 }
 
 // List entries of the requests that were bound.
-template <int GR, bool PRED>
-__device__ __forceinline__ void br_commit_store(const BrTailArgs &t, int inst, const BrQueueGroup<GR, PRED> &v, float c0) {
+template <int GR, int ROWS>
+__device__ __forceinline__ void br_commit_store(const BrTailArgs &t, int inst, const BrQueueGroup<GR, ROWS> &v, float c0) {
 #pragma unroll
   for (int u = 0; u < GR; ++u) {
     const int g = v.bound[u] >> 16, slot = v.bound[u] & 0xffff;
@@ -152,8 +170,8 @@ __device__ __forceinline__ void br_commit_store(const BrTailArgs &t, int inst, c
       const int64_t row = ((int64_t)inst * t.G + g) * t.Bs + slot;
       t.kv[row] = min(max(v.sq[u], 1), BR_MAX_S_DEV);
       t.rem[row] = max(v.oq[u], 1);
-      if constexpr (PRED) {
-        br_row_store(t.pred + row * t.P, t.Pq, v.pr[u]);
+      if constexpr (ROWS != BR_ROWS_NONE) {
+        br_row_store<ROWS>(t.pred + row * t.P, t.Pq, v.pr[u]);
         if (t.P == 3 && t.Pq == 0) {  // maintained estimate: first query at age 0, nothing generated yet
           t.pred[row * 3] = c0;
           t.pred[row * 3 + 1] = 0.0f;
@@ -166,9 +184,9 @@ __device__ __forceinline__ void br_commit_store(const BrTailArgs &t, int inst, c
 
 // Outputs of those positions in arrival order, and their deferred requests to queue positions `kept`
 // onwards (order preserved); `kept` moves on by the number stored.
-template <int GR, bool PRED>
+template <int GR, int ROWS>
 __device__ __forceinline__ void br_queue_store(const BrTailArgs &t, int inst, int lane, int j0, int q0, int qn,
-                                               const BrQueueGroup<GR, PRED> &v, int &kept) {
+                                               const BrQueueGroup<GR, ROWS> &v, int &kept) {
   const int64_t qrow = (int64_t)inst * t.Q;
 #pragma unroll
   for (int u = 0; u < GR; ++u) {
@@ -185,7 +203,7 @@ __device__ __forceinline__ void br_queue_store(const BrTailArgs &t, int inst, in
         t.qs[qrow + ni] = min(max(v.sq[u], 1), BR_MAX_S_DEV);
         t.qo[qrow + ni] = max(v.oq[u], 1);
         t.qid[qrow + ni] = v.id[u];
-        if constexpr (PRED) br_row_store(t.qpred + (qrow + ni) * t.Pq, t.Pq, v.pr[u]);
+        if constexpr (ROWS != BR_ROWS_NONE) br_row_store<ROWS>(t.qpred + (qrow + ni) * t.Pq, t.Pq, v.pr[u]);
       }
       kept += __builtin_popcountll(bal);
     }
@@ -241,22 +259,24 @@ __device__ __forceinline__ void br_assign_epilogue(int inst, int lane, int q0, i
   const BrTailArgs t = br_tail_args();
   constexpr int GR = E < 4 ? E : 4;
   int kept = 0;
+  br_with_rows<PRED>(t, [&](auto rows) {
 #pragma unroll
-  for (int j0 = 0; j0 < E; j0 += GR) {
-    if (j0 * BR_WAVE < t.Q) {
-      BrQueueGroup<GR, PRED> v;
-      if (words) {
-        BrQueueWords<GR> w;
+    for (int j0 = 0; j0 < E; j0 += GR) {
+      if (j0 * BR_WAVE < t.Q) {
+        BrQueueGroup<GR, decltype(rows)::value> v;
+        if (words) {
+          BrQueueWords<GR> w;
 #pragma unroll
-        for (int u = 0; u < GR; ++u) w.id[u] = words->id[j0 + u], w.sq[u] = words->sq[j0 + u], w.oq[u] = words->oq[j0 + u];
-        br_queue_load(t, inst, lane, j0, q0, qn, bound, v, &w);
-      } else {
-        br_queue_load(t, inst, lane, j0, q0, qn, bound, v);
+          for (int u = 0; u < GR; ++u) w.id[u] = words->id[j0 + u], w.sq[u] = words->sq[j0 + u], w.oq[u] = words->oq[j0 + u];
+          br_queue_load(t, inst, lane, j0, q0, qn, bound, v, &w);
+        } else {
+          br_queue_load(t, inst, lane, j0, q0, qn, bound, v);
+        }
+        br_commit_store(t, inst, v, c0);
+        br_queue_store(t, inst, lane, j0, q0, qn, v, kept);
       }
-      br_commit_store(t, inst, v, c0);
-      br_queue_store(t, inst, lane, j0, q0, qn, v, kept);
     }
-  }
+  });
   br_write_state(t, inst, lane, q0, qn, cnt, kept, Lcur, nn, rc);
 }
 
@@ -273,32 +293,35 @@ __device__ __forceinline__ void br_assign_epilogue_block4(int inst, int lane, in
   if (share_workers && w == 0) wk[lane] = Lcur, wk[BR_WAVE + lane] = nn;
   __syncthreads();  // the round is over: bound[] is complete
   if (share_workers) Lcur = wk[lane], nn = wk[BR_WAVE + lane];
-  BrQueueGroup<4, PRED> va, vb;
-  br_queue_load(t, inst, lane, w * 8, q0, qn, bound, va);
-  br_queue_load(t, inst, lane, w * 8 + 4, q0, qn, bound, vb);
-  int mine = 0;
+  int total = 0;
+  br_with_rows<PRED>(t, [&](auto rows) {
+    BrQueueGroup<4, decltype(rows)::value> va, vb;
+    br_queue_load(t, inst, lane, w * 8, q0, qn, bound, va);
+    br_queue_load(t, inst, lane, w * 8 + 4, q0, qn, bound, vb);
+    int mine = 0;
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
-    mine += __builtin_popcountll(br_ballot((w * 8 + u) * BR_WAVE + lane < qn && va.bound[u] < 0)) +
-            __builtin_popcountll(br_ballot((w * 8 + 4 + u) * BR_WAVE + lane < qn && vb.bound[u] < 0));
-  // the loaded values must have arrived before any wave stores
-  asm volatile("" ::"v"(va.sq[0]), "v"(va.sq[1]), "v"(va.sq[2]), "v"(va.sq[3]), "v"(vb.sq[0]), "v"(vb.sq[1]), "v"(vb.sq[2]),
-               "v"(vb.sq[3])
-               : "memory");
-  __builtin_amdgcn_s_waitcnt(0);
-  if (lane == 0) sh[w] = mine;
-  __syncthreads();
-  int kept = 0, total = 0;
+    for (int u = 0; u < 4; ++u)
+      mine += __builtin_popcountll(br_ballot((w * 8 + u) * BR_WAVE + lane < qn && va.bound[u] < 0)) +
+              __builtin_popcountll(br_ballot((w * 8 + 4 + u) * BR_WAVE + lane < qn && vb.bound[u] < 0));
+    // the loaded values must have arrived before any wave stores
+    asm volatile("" ::"v"(va.sq[0]), "v"(va.sq[1]), "v"(va.sq[2]), "v"(va.sq[3]), "v"(vb.sq[0]), "v"(vb.sq[1]), "v"(vb.sq[2]),
+                 "v"(vb.sq[3])
+                 : "memory");
+    __builtin_amdgcn_s_waitcnt(0);
+    if (lane == 0) sh[w] = mine;
+    __syncthreads();
+    int kept = 0;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int c = sh[k];
-    kept += k < w ? c : 0;
-    total += c;
-  }
-  br_commit_store(t, inst, va, c0);
-  br_commit_store(t, inst, vb, c0);
-  br_queue_store(t, inst, lane, w * 8, q0, qn, va, kept);
-  br_queue_store(t, inst, lane, w * 8 + 4, q0, qn, vb, kept);
+    for (int k = 0; k < 4; ++k) {
+      const int c = sh[k];
+      kept += k < w ? c : 0;
+      total += c;
+    }
+    br_commit_store(t, inst, va, c0);
+    br_commit_store(t, inst, vb, c0);
+    br_queue_store(t, inst, lane, w * 8, q0, qn, va, kept);
+    br_queue_store(t, inst, lane, w * 8 + 4, q0, qn, vb, kept);
+  });
   if (w == 0) br_write_state(t, inst, lane, q0, qn, cnt, total, Lcur, nn, rc, !share_workers);
   if (share_workers) __syncthreads();  // the lists that a wave goes on to hold entries stored by the others
 }
@@ -414,7 +437,7 @@ __device__ __forceinline__ void br_assign_epilogue_split(int inst, int lane, int
                                                          const BrQueueWords<E> *words) {
   const BrTailArgs t = br_tail_args();
   const int G = t.G, tt = t.adv_t;
-  BrQueueGroup<E, false> v;
+  BrQueueGroup<E, BR_ROWS_NONE> v;
   br_queue_load(t, inst, lane, 0, q0, qn, bound, v, words);
   // the helpers are done with this cluster's lists and queue (they never wait for anything: the flags always come)
   while (__atomic_load_n(split, __ATOMIC_RELAXED) == 0 || __atomic_load_n(split + 1, __ATOMIC_RELAXED) == 0)
