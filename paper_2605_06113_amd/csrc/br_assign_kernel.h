@@ -863,7 +863,11 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
 // mailbox `svc` and two block barriers per search.
 // HELPED: the block's other waves read the cluster's step-start state meanwhile (br_snapshot_helper); the block meets before
 // this wave's epilogue changes it.
-template <int EM, int HB, bool ADV, bool COOP = false, bool BIGR = false, bool SCORES = false, bool HELPED = false>
+// SPLIT: the decode steps of the old entries are applied by another wave in every call, so the other epilogue is left out: with both
+// in the kernel the words requested ahead of a queue of 257..512 went through 100 bytes of scratch memory per lane (2000 clusters,
+// G = 16, queues of 500: whole pass 31.0 us, 26.1 without; one cluster 12.5 and 11.8).
+template <int EM, int HB, bool ADV, bool COOP = false, bool BIGR = false, bool SCORES = false, bool HELPED = false,
+          bool SPLIT = false>
 __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a, const BrOut &o, int *lds, int inst,
                                                int w = 0, int *split = nullptr,
                                                bool shared = false) {
@@ -1004,7 +1008,10 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
     }
   } else {
     bool done = false;
-    if constexpr (!BRH && !BIGR && EM <= 8) {
+    if constexpr (SPLIT) {
+      br_assign_epilogue_split<EM>(inst, lane, q0, qn, cnt, bound, st.Lh[0], st.nn, nn_start, rc, split, lst, &words);
+      return;
+    } else if constexpr (!BRH && !BIGR && EM <= 8) {
       if (split != nullptr) {
         br_assign_epilogue_split<EM>(inst, lane, q0, qn, cnt, bound, st.Lh[0], st.nn, nn_start, rc, split, lst, AHEAD ? &words : nullptr);
         done = true;

@@ -16,7 +16,7 @@ __global__ __launch_bounds__(3 * BR_WAVE) void br_k_route_split(BrParams p, BrAr
   if (threadIdx.x == 0) split[0] = 0, split[1] = blockDim.x > 2 * BR_WAVE ? 0 : 1;
   __syncthreads();
   if (w == 0) {
-    br_assign_body<E, 0, false>(p, a, o, lds_all, inst, 0, split);
+    br_assign_body<E, 0, false, false, false, false, false, true>(p, a, o, lds_all, inst, 0, split);
   } else if (w == 1) {
     br_split_advance<8>(p, inst, lane, split);
   } else {
