@@ -9,9 +9,9 @@ int br_long_waves(const BrParams &p) {
   return (long long)p.N * 4 <= room ? 4 : (long long)p.N * 2 <= room ? 2 : 1;
 }
 
-// The reductions on the round's helper waves: a pair (tile of 64 requests, worker with a free slot) is about 1200 cycles, up to
-// 32 of them per helper hide behind the round.  Whole pass, a launch of their own / so: one cluster, G = 8, H = 80 21.8 / 19.5
-// us; 2048 clusters, overloaded 70.1 / 69.3.
+// The reductions on the round's helper waves, up to 32 pairs (tile of 64 requests, worker) per helper; a pair whose worker has a free
+// slot is about 1200 cycles, and few of them hide behind the round (BR_LONG_ALONE: many).  Whole pass, a launch of their own / so, G = 8,
+// H = 80: one cluster 21.8 / 19.5 us; 2048 clusters, overloaded 62 / 54, all slots free and 128 admissions each 524 / 517.
 bool br_long_helped(const BrParams &p) {
   const int nw = br_long_waves(p), T = (p.Q + BR_WAVE - 1) / BR_WAVE;
   return nw > 1 && T * p.G <= 32 * (nw - 1);

@@ -83,8 +83,13 @@ __device__ __forceinline__ void br_long_slice_best(const BrParams &p, const floa
   }
 }
 
-// LDS of a helper wave for the snapshot reductions: margins of a worker, then the best request it has seen for every worker
+// LDS of a wave for the snapshot reductions: margins of a worker, then the best request it has seen for every worker
 #define BR_LONG_RED_WORDS(HS, G) ((HS) + 4 + ((3 * (G) + 3) & ~3))
+
+// Pairs (tile of 64 requests, worker with a free slot) that the helper waves take alone, per wave.  More (slots free nearly
+// everywhere): wave 0 takes a share before its round, since its first shared search would wait for the helpers anyway
+// (2048 clusters, all slots free, 256 waiting: whole pass 533 us with the helpers alone, 517 so, 524 with a launch of their own).
+#define BR_LONG_ALONE 16
 
 // The snapshot reductions of a cluster (K2 + K3) on its nh helper waves while wave 0 runs the round: wave h takes every nh-th
 // tile of 64 requests against every worker with a free slot; a worker's step-start margins are on their way from memory while
@@ -213,8 +218,10 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
       for (int j = 0; j < EW; ++j) svh[j] = skey[(w * EW + j) * BR_WAVE + lane] >> BR_IDX_BITS;
       const int sprobe = skey[lane * E] >> BR_IDX_BITS;  // the probe of this lane in a bracketing search
       if (o.best_g || o.best_i) {
-        br_long_reductions(p, a, o, inst, lane, w - 1, NW - 1, q0, qn, sd,
-                           (float *)(mbox + 16) + (w - 1) * BR_LONG_RED_WORDS(HS, G));
+        const int free = (int)__builtin_popcountll(br_ballot(lane < G && p.n[(int64_t)inst * G + min(lane, G - 1)] < p.B));
+        const bool all = ((qn + BR_WAVE - 1) / BR_WAVE) * free > BR_LONG_ALONE * (NW - 1);
+        br_long_reductions(p, a, o, inst, lane, all ? w : w - 1, all ? NW : NW - 1, q0, qn, sd,
+                           (float *)(mbox + 16) + w * BR_LONG_RED_WORDS(HS, G));
         __builtin_amdgcn_s_waitcnt(0);  // every read has returned before the block meets for the last time
       }
       for (;;) {
@@ -323,7 +330,18 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
     if (pos < qn) alive |= 1u << j;
   }
   br_wave_sync();
-  if constexpr (NW > 1) __syncthreads();  // the helper waves read their share of the sorted keys
+  if constexpr (NW > 1) {
+    __syncthreads();  // the helper waves read their share of the sorted keys
+    if (o.best_g || o.best_i) {
+      float *red = (float *)(mbox + 16);
+      if (((qn + BR_WAVE - 1) / BR_WAVE) * (int)__builtin_popcountll(br_ballot(cap > 0)) > BR_LONG_ALONE * (NW - 1)) {
+        br_long_reductions(p, a, o, inst, lane, 0, NW, q0, qn, sd, red);
+      } else if (lane < G) {
+        int *part = (int *)(red + HS + 4);
+        part[lane] = BR_KEY_NONE, part[G + lane] = 0, part[2 * G + lane] = -1;
+      }
+    }
+  }
 
   int n_alive = qn;
   int stage1 = 0, pops = 0, guard = 0, wdrop = 0, admitted = 0;
@@ -507,7 +525,7 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
   auto pick_quick = [&](int room, int &pos, int &swin) -> int {
     int b = 0;
 #pragma unroll
-    for (int step = E == 4 ? 64 : 256; step > 0; step >>= 2) {
+    for (int step = 64; step > 0; step >>= 2) {  // (queues of up to 256)
       int e[3];
       float w[3];  // sum of the discounts whose margin the probe exceeds
 #pragma unroll
@@ -589,10 +607,21 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
     }
     return -1;
   };
+  // Queues of up to 256 only, and while it decides at least two picks in three: among many waiting requests of nearly the same
+  // length the leads are within the bounds pick after pick.  Whole pass, us, always bracketed / so, G = 8, H = 80: 2048 clusters,
+  // overloaded 70 / 58; one cluster 114 / 105 and 1000 clusters 320 / 306 in bursts of 60 and 200 arrivals; 2048 clusters, 128
+  // admissions each from a full queue 517 / 531.  300 clusters, G = 16, queues of 500 in bursts: 279 / 352.
+  int credit = 3;
   auto pick = [&](int room, int &pos, int &swin) -> bool {
-    if constexpr (E <= 8) {
-      const int r = pick_quick(room, pos, swin);
-      if (r >= 0) return r != 0;
+    if constexpr (E == 4) {
+      if (credit > 0) {
+        const int r = pick_quick(room, pos, swin);
+        if (r >= 0) {
+          credit = min(credit + 1, 4);
+          return r != 0;
+        }
+        credit -= 2;
+      }
     }
     return pick_single(room, pos, swin);
   };
@@ -700,7 +729,12 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
         margins_of(g);
         const int room = p.W > 0 ? p.W - __builtin_amdgcn_readlane(Lcur, g) : INT32_MAX;
         int pos = 0, swin = 0;
-        if (!pick(room, pos, swin)) {
+        bool got;  // (2048 clusters in bursts of 200 arrivals: 800 us with pick here, 784 so; 1000 clusters 306 and 322)
+        if constexpr (NW == 4)
+          got = pick(room, pos, swin);
+        else
+          got = pick_single(room, pos, swin);
+        if (!got) {
           drop_worker(g, capmax);
           continue;
         }
@@ -944,10 +978,10 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
     mbox[0] = 0;  // the round is over: the helper waves leave
     __syncthreads();
     int32_t *best_i = br_late_out().best_i;
-    if (best_i && lane < p.G) {  // lane g: the best of what the helpers found for worker g
+    if (best_i && lane < p.G) {  // lane g: the best of what the waves found for worker g
       int bk = BR_KEY_NONE, bs = 0, bi = -1;
 #pragma unroll
-      for (int u = 0; u < NW - 1; ++u) {
+      for (int u = 0; u < NW; ++u) {
         const int *part = mbox + 16 + u * BR_LONG_RED_WORDS(HS, G) + HS + 4;
         const int k = part[lane], s = part[G + lane], i = part[2 * G + lane];
         const bool better = i >= 0 && (bi < 0 || k > bk || (k == bk && (s > bs || (s == bs && i < bi))));
@@ -982,7 +1016,7 @@ void br_launch_assign_long_one(const BrParams &p, const BrArr &a, const BrOut &o
   const int nw = br_long_waves(p);
   const size_t lds = ((size_t)3 * E * BR_WAVE + 2 * BR_WAVE + 3 * (size_t)HS + (((size_t)HS * BR_LSTRIDE(p.G) + 3) & ~(size_t)3) +
                       (p.R_max > 8 ? 1024 : 0) + (nw > 1 ? 16 : 0) +
-                      (o.best_g || o.best_i ? (nw - 1) * BR_LONG_RED_WORDS(HS, p.G) : 0)) * sizeof(int);
+                      (nw > 1 && (o.best_g || o.best_i) ? nw * BR_LONG_RED_WORDS(HS, p.G) : 0)) * sizeof(int);
   const dim3 grid((unsigned)p.N), block(BR_WAVE * nw);
   if (nw == 4)
     hipLaunchKernelGGL((br_k_assign_long<E, 4>), grid, block, lds, st, p, a, o);

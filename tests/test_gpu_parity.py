@@ -852,8 +852,8 @@ def test_snapshot_reductions_by_their_work(N, G, H, Q, R_max, own):
 
 @pytest.mark.parametrize("N,G,H,Q,wm", [
     (20, 3, 40, 70, 0), (20, 8, 80, 256, 0), (20, 13, 9, 130, 9000), (20, 64, 17, 65, 0),
-    # on the round's helper waves: one, three of them, up to 32 pairs of (tile, worker) each
-    (1100, 8, 20, 256, 0), (1100, 9, 20, 256, 0), (40, 12, 80, 512, 9000), (40, 13, 80, 512, 0), (8, 24, 128, 256, 9000), (8, 3, 9, 2048, 0),
+    # on the round's helper waves: one, three of them, up to 32 pairs of (tile, worker) each; beyond 16 each with the round's wave
+    (20, 16, 80, 250, 0), (1100, 8, 20, 256, 0), (1100, 9, 20, 256, 0), (40, 12, 80, 512, 9000), (40, 13, 80, 512, 0), (8, 24, 128, 256, 9000), (8, 3, 9, 2048, 0),
     # up to 16 clusters: a block each up to 128 pairs (a watermark: 64, queues of up to 256), tiles beyond
     (16, 16, 80, 512, 0), (9, 17, 80, 512, 0), (9, 16, 30, 256, 9000), (9, 17, 30, 256, 9000), (9, 4, 20, 320, 9000), (9, 64, 128, 128, 0)])
 def test_long_horizon_reductions_by_free_workers(N, G, H, Q, wm):
