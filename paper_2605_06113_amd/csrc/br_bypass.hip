@@ -10,8 +10,14 @@
 #include "br_device.h"
 #include "br_launch.h"
 
-// lane `lane` of old replaced by value (both uniform)
-extern "C" __device__ int br_writelane(int value, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
+// lane `lane` of old replaced by value (both uniform).  The compiler's builtin where it has one; else the intrinsic by its
+// base name, without a type suffix: the compiler completes that for the type at hand, so it does not depend on how a version
+// spells the overloads, and a compiler that does not know the name leaves a symbol that the device link refuses.
+#if __has_builtin(__builtin_amdgcn_writelane)
+__device__ __forceinline__ int br_writelane(int value, int lane, int old) { return __builtin_amdgcn_writelane(value, lane, old); }
+#else
+extern "C" __device__ int br_writelane(int value, int lane, int old) __asm("llvm.amdgcn.writelane");
+#endif
 
 #define BR_STATB(o, inst, k) (o).stats[(int64_t)(inst) * 16 + (k)]
 
