@@ -7,19 +7,19 @@
 // at one LDS flag for each of the others before its epilogue, and those always come.
 #include "br_assign_kernel.h"
 
-template <int E>
-__global__ __launch_bounds__(3 * BR_WAVE) void br_k_route_split(BrParams p, BrArr a, BrOut o, unsigned recip_g) {
+template <int E, bool THIRD>
+__global__ __launch_bounds__((THIRD ? 3 : 2) * BR_WAVE) void br_k_route_split(BrParams p, BrArr a, BrOut o, unsigned recip_g) {
   extern __shared__ int lds_all[];
   const int w = threadIdx.x >> 6, lane = br_lane(), inst = (int)blockIdx.x;
   int *split = lds_all + BR_ROUND_WORDS(E, false);
   // flags down before any wave looks: the lists, and what a third wave reads of the step-start state
-  if (threadIdx.x == 0) split[0] = 0, split[1] = blockDim.x > 2 * BR_WAVE ? 0 : 1;
+  if (threadIdx.x == 0) split[0] = 0, split[1] = THIRD ? 0 : 1;
   __syncthreads();
   if (w == 0) {
     br_assign_body<E, 0, false, false, false, false, false, true>(p, a, o, lds_all, inst, 0, split);
-  } else if (w == 1) {
+  } else if (!THIRD || w == 1) {
     br_split_advance<8>(p, inst, lane, split);
-  } else {
+  } else if constexpr (THIRD) {
     br_snapshot_helper<E, 0>(p, a, o, inst, lane, 0, 1, recip_g, split + BR_SPLIT_WORDS);
     __builtin_amdgcn_s_waitcnt(0);  // every read has returned before the flag is seen
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -28,11 +28,18 @@ __global__ __launch_bounds__(3 * BR_WAVE) void br_k_route_split(BrParams p, BrAr
   }
 }
 
+template <int E, bool THIRD>
+static void launch_split_waves(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
+  const size_t lds = (BR_ROUND_WORDS(E, false) + BR_SPLIT_WORDS + (THIRD ? BR_LIST_WORDS(E) + 2 * BR_WAVE : 0)) * sizeof(int);
+  hipLaunchKernelGGL((br_k_route_split<E, THIRD>), dim3((unsigned)p.N), dim3(BR_WAVE * (THIRD ? 3 : 2)), lds, st, p, a, o, br_recip(p.G));
+}
+
 template <int E>
 static void launch_split(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
-  const bool third = o.F || o.best_g || o.best_i;
-  const size_t lds = (BR_ROUND_WORDS(E, false) + BR_SPLIT_WORDS + (third ? BR_LIST_WORDS(E) + 2 * BR_WAVE : 0)) * sizeof(int);
-  hipLaunchKernelGGL((br_k_route_split<E>), dim3((unsigned)p.N), dim3(BR_WAVE * (third ? 3 : 2)), lds, st, p, a, o, br_recip(p.G));
+  if (o.F || o.best_g || o.best_i)
+    launch_split_waves<E, true>(p, a, o, st);
+  else
+    launch_split_waves<E, false>(p, a, o, st);
 }
 
 // For batches below two one-wave clusters per SIMD: one round and one helper per block.  Beyond, with four or more waves
