@@ -840,7 +840,7 @@ __host__ __device__ inline size_t br_score_scratch_words(int Q, int G) {
   return 2 * BR_TILE_GROUPS * (size_t)Q + 3 * T * (size_t)G;
 }
 
-template <bool LONG>
+template <bool BRH, bool LONG>
 __global__ __launch_bounds__(64) void br_k_score_tiles(BrParams p, BrArr a, int *partials, int wpg) {
   extern __shared__ int lds[];
   const int tile = blockIdx.x, wg = blockIdx.y, inst = blockIdx.z;
@@ -866,7 +866,10 @@ __global__ __launch_bounds__(64) void br_k_score_tiles(BrParams p, BrArr a, int 
     sL[lane] = p.L[(int64_t)inst * G + g0 + lane];
     scap[lane] = p.B - p.n[(int64_t)inst * G + g0 + lane];
   }
-  if constexpr (!LONG) {
+  if constexpr (!BRH) {  // (a score reads the first margin only)
+    const int L = p.L[(int64_t)inst * G + min(lane, G - 1)], m = br_wave_max(L) - L;
+    if (lane >= g0 && lane < g0 + gn) sm[(lane - g0) * HS] = m;
+  } else if constexpr (!LONG) {
     br_margins_to_lds(p, inst, lane, g0, gn, sm, HS);
   } else {
     for (int e = lane; e < gn * HS; e += BR_WAVE) {
@@ -899,8 +902,8 @@ __global__ __launch_bounds__(64) void br_k_score_tiles(BrParams p, BrArr a, int 
     } else {
       int m[BR_HP + 1];
 #pragma unroll
-      for (int h = 0; h <= BR_HP; ++h) m[h] = sm[gl * HS + h];
-      key = br_score_key<true>(p, m, s);
+      for (int h = 0; h <= BR_HP; ++h) m[h] = BRH || h == 0 ? sm[gl * HS + h] : 0;
+      key = br_score_key<BRH>(p, m, s);
     }
     const bool ok = valid && (p.W <= 0 || sL[gl] + s <= p.W);
     if (ok && key > bk) {  // workers in ascending order: the first best stays
@@ -1152,8 +1155,10 @@ static int br_pair_units(const BrParams &p) {
   return ((p.Q + BR_WAVE - 1) / BR_WAVE) * p.G * ((p.H <= BR_HP / 2 ? BR_HP / 2 : BR_HP) + 2);
 }
 
-// Which kernel takes the reductions.  BR-0 needs no score per pair (br_score_wave.h): one wave up to queues of 1024.  For
-// BR-H one wave is bound by the pairs and more waves per cluster cost launches of their own, so what is faster depends on
+// Which kernel takes the reductions.  BR-0 needs no score per pair (br_score_wave.h): one wave up to queues of 1024, except
+// where few clusters with queues of 513..1024 have windows beyond 8 and so a launch of their own (whole pass, us, one wave / tiles,
+// Q = 1024: one cluster, G = 4 21.8 / 21.1, G = 16 29.4 / 26.8, G = 64 46.0 / 44.0; 16 clusters 30.5 / 26.6, 36.4 / 32.8, 55.2 / 53.7).
+// For BR-H one wave is bound by the pairs and more waves per cluster cost launches of their own, so what is faster depends on
 // how many workers have a free slot and how many requests wait, which is not known here.  Whole pass (round and one decode
 // step), us: workers full / queue nearly empty / a token watermark that keeps slots free everywhere and the queue full.
 //   few clusters, Q <= 512             one wave          tiles
@@ -1196,7 +1201,7 @@ static bool br_long_in_block(const BrParams &p, int T) {
 bool br_score_in_tiles(const BrParams &p) {
   const int T = (p.Q + BR_WAVE - 1) / BR_WAVE, wpg = (p.G + BR_TILE_GROUPS - 1) / BR_TILE_GROUPS, WGN = (p.G + wpg - 1) / wpg;
   if (p.N > BR_SCORE_TILES_MAX_N || T * WGN < 8) return false;
-  if (p.H == 0) return false;
+  if (p.H == 0) return p.R_max > 8 && p.Q > 512;  // (narrower windows: in the round's launch)
   if (p.H > BR_HP && br_long_in_block(p, T)) return false;
   // (windows beyond 8 requests: no round's launch to ride in; queues beyond 1024 ride in the round's block)
   return p.H > BR_HP || p.Q > 512 || p.R_max > 8 || br_pair_units(p) >= BR_UNITS_ONE_WAVE;
@@ -1214,9 +1219,11 @@ static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut 
       const int HS = longh ? BR_HS(p.H) : BR_HP + 1;
       const size_t lds = ((size_t)BR_TILE_WORKERS * HS + (longh ? HS + 4 : 0) + 2 * BR_TILE_WORKERS) * sizeof(int);
       if (longh)
-        hipLaunchKernelGGL((br_k_score_tiles<true>), grid, block, lds, st, p, a, partials, wpg);
+        hipLaunchKernelGGL((br_k_score_tiles<true, true>), grid, block, lds, st, p, a, partials, wpg);
+      else if (p.H > 0)
+        hipLaunchKernelGGL((br_k_score_tiles<true, false>), grid, block, lds, st, p, a, partials, wpg);
       else
-        hipLaunchKernelGGL((br_k_score_tiles<false>), grid, block, lds, st, p, a, partials, wpg);
+        hipLaunchKernelGGL((br_k_score_tiles<false, false>), grid, block, lds, st, p, a, partials, wpg);
       const int QB = (p.Q + 255) / 256;
       hipLaunchKernelGGL(br_k_score_combine, dim3((unsigned)(QB + (p.G + 3) / 4), (unsigned)p.N), dim3(256), 0, st, p, o,
                          (const int *)partials, T, WGN, QB);

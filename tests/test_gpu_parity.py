@@ -826,6 +826,8 @@ def _score_launches(r, arr):
     (257, 16, 8, 1024, 4, True), (40, 5, 3, 700, 4, True),
     # windows beyond 8 requests, and BR-0 with them: one wave over queues of up to 1024
     (20, 9, 6, 400, 12, True), (40, 6, 0, 700, 12, True), (18, 7, 0, 1024, 9, True),
+    # BR-0 with them, up to 16 clusters and queues of 513..1024: tiles
+    (16, 7, 0, 513, 12, True), (1, 64, 0, 1024, 9, True), (2, 1, 0, 700, 24, True), (3, 5, 0, 512, 12, True),
 ])
 def test_snapshot_reductions_by_their_work(N, G, H, Q, R_max, own):
     """The kernels that share out the snapshot reductions, on both sides of the lines between them: workers all full, some
