@@ -83,8 +83,11 @@ __device__ __forceinline__ void br_long_slice_best(const BrParams &p, const floa
   }
 }
 
-// LDS of a wave for the snapshot reductions: margins of a worker, then the best request it has seen for every worker
-#define BR_LONG_RED_WORDS(HS, G) ((HS) + 4 + ((3 * (G) + 3) & ~3))
+// LDS of a wave for the snapshot reductions: margins of a worker, the best request it has seen for every worker, then the best
+// worker it has seen for each request of a tile that waves share
+#define BR_LONG_PART_AT(HS) ((HS) + 4)
+#define BR_LONG_BEST_AT(HS, G) (BR_LONG_PART_AT(HS) + ((3 * (G) + 3) & ~3))
+#define BR_LONG_RED_WORDS(HS, G) (BR_LONG_BEST_AT(HS, G) + 2 * BR_WAVE)
 
 // Pairs (tile of 64 requests, worker with a free slot) that the helper waves take alone, per wave.  More (slots free nearly
 // everywhere): wave 0 takes a share before its round, since its first shared search would wait for the helpers anyway
@@ -92,16 +95,24 @@ __device__ __forceinline__ void br_long_slice_best(const BrParams &p, const floa
 #define BR_LONG_ALONE 16
 
 // The snapshot reductions of a cluster (K2 + K3) on its nh helper waves while wave 0 runs the round: wave h takes every nh-th
-// tile of 64 requests against every worker with a free slot; a worker's step-start margins are on their way from memory while
-// the one before it is scored.  best_g is written here; what is best for a worker among these requests (score, then the longer
-// request, then the earlier arrival) goes to `red`, where wave 0 finds it at the end of the round.
+// tile of 64 requests against every worker with a free slot, or, of fewer tiles, one with `share` - 1 other waves, every
+// so many-th of those workers; a worker's step-start margins are on their way from memory while the one before it is scored.
+// best_g is written here, for shared tiles when the round is over (br_long_shared_best); what is best for a worker among these
+// requests (score, then the longer request, then the earlier arrival) goes to `red`, where wave 0 finds it then.
 __device__ __forceinline__ void br_long_reductions(const BrParams &p, const BrArr &a, const BrOut &o, int inst, int lane, int h,
-                                                   int nh, int q0, int qn, const float *sd, float *red) {
+                                                   int nh, int share, int q0, int qn, const float *sd, float *red) {
   const int G = p.G, H1 = p.H + 1, HS = BR_HS(p.H);
   const int64_t wrow = (int64_t)inst * G, qrow = (int64_t)inst * p.Q;
-  int *part = (int *)(red + HS + 4);
+  int *part = (int *)red + BR_LONG_PART_AT(HS), *best = (int *)red + BR_LONG_BEST_AT(HS, G);
   const int n_raw = p.n[wrow + min(lane, G - 1)], L = p.L[wrow + min(lane, G - 1)];
-  const unsigned long long freem = br_ballot(lane < G && n_raw < p.B);
+  const int tiles = (qn + BR_WAVE - 1) / BR_WAVE;
+  unsigned long long freem = br_ballot(lane < G && n_raw < p.B);
+  int first = h, step = nh;  // tiles of this wave
+  if (share > 1) {           // (at most one)
+    const int r = br_rank_below(freem), of = share == 2 ? h & 1 : h;
+    first = tiles <= 1 ? 0 : h >> 1, step = tiles;
+    freem = br_ballot(((freem >> lane) & 1ull) && (share == 3 ? r % 3 : r & (share - 1)) == of);
+  }
   int ik = BR_KEY_NONE, is = 0, ii = -1;  // lane g: of worker g
   int mh[3] = {0, 0, 0};
   auto fetch = [&](int g) {
@@ -111,10 +122,10 @@ __device__ __forceinline__ void br_long_reductions(const BrParams &p, const BrAr
       if (u * BR_WAVE < HS) mh[u] = p.mh[(wrow + g) * H1 + min(e, H1 - 1)];
     }
   };
-  for (int t = h; t * BR_WAVE < p.Q; t += nh) {
+  for (int t = first; t < tiles; t += step) {
     const int i = t * BR_WAVE + lane;
     int bk = BR_KEY_NONE, bg = -1;
-    if (t * BR_WAVE < qn && freem != 0ull) {
+    if (freem != 0ull) {
       unsigned x[1];
       br_keys_load<1>(p, a, inst, q0, qn, t * BR_WAVE, lane, x);
       fetch((int)__builtin_ctzll(freem));
@@ -145,9 +156,34 @@ __device__ __forceinline__ void br_long_reductions(const BrParams &p, const BrAr
         }
       }
     }
-    if (o.best_g && i < p.Q) o.best_g[qrow + i] = bg;
+    if (share > 1)
+      best[lane] = bk, best[BR_WAVE + lane] = bg;
+    else if (o.best_g && i < p.Q)
+      o.best_g[qrow + i] = bg;
   }
+  if (o.best_g)
+    for (int i = (tiles + h) * BR_WAVE + lane; i < p.Q; i += nh * BR_WAVE) o.best_g[qrow + i] = -1;
   if (lane < G) part[lane] = ik, part[G + lane] = is, part[2 * G + lane] = ii;
+}
+
+// Waves that share a tile: with fewer tiles than waves (nh: two to four) and enough workers with a free slot to be worth it.
+// 229 clusters, G = 22, H = 73, at most 44 waiting, half of the slots free, whole pass: 44.1 us with a launch of its own, 55.2
+// with a tile to a wave, 35.1 so.
+__device__ __forceinline__ int br_long_sharers(int nh, int qn, int free) {
+  return free < 2 * nh ? 1 : qn <= BR_WAVE ? nh : nh == 4 && qn <= 2 * BR_WAVE ? 2 : 1;
+}
+
+// best_g of shared tiles from what their waves have left, in the areas from `reds` on: score, then the first worker
+__device__ __forceinline__ void br_long_shared_best(int32_t *best_g, int Q, int inst, int lane, int qn, int share, const int *reds, int words) {
+  for (int i = lane; i < ((qn + BR_WAVE - 1) & ~(BR_WAVE - 1)); i += BR_WAVE) {
+    int bk = BR_KEY_NONE, bg = -1;
+    for (int u = 0; u < share; ++u, reds += words) {
+      const int k = reds[lane], g = reds[BR_WAVE + lane];
+      const bool better = g >= 0 && (bg < 0 || k > bk || (k == bk && g < bg));
+      bk = better ? k : bk, bg = better ? g : bg;
+    }
+    if (i < Q) best_g[(int64_t)inst * Q + i] = bg;
+  }
 }
 
 template <int E, int NW>
@@ -176,7 +212,7 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
   const int LS = BR_LSTRIDE(p.G);
   int *sL = sM + 3 * HS;            // [HS][LS] step-start projections (rows beyond H: "no worker")
   int *hitab = sL + ((HS * LS + 3) & ~3);  // R_max > 8: [1024] sums of window entries 6.. by upper mask bits
-  int *mbox = hitab + (p.R_max > 8 ? 1024 : 0);  // NW > 1: [16] search mailbox: command, admissible length; results from word 4
+  int *mbox = hitab + (p.R_max > 8 ? 1024 : 0);  // NW > 1: [16] search mailbox: command, admissible length; results from word 4; [12] how the reductions were shared out
   int *salive = pm;                 // alive words of the lanes of wave 0 during a search (pm is idle then)
 
   const int lane = br_lane();
@@ -220,8 +256,11 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
       if (o.best_g || o.best_i) {
         const int free = (int)__builtin_popcountll(br_ballot(lane < G && p.n[(int64_t)inst * G + min(lane, G - 1)] < p.B));
         const bool all = ((qn + BR_WAVE - 1) / BR_WAVE) * free > BR_LONG_ALONE * (NW - 1);
-        br_long_reductions(p, a, o, inst, lane, all ? w : w - 1, all ? NW : NW - 1, q0, qn, sd,
+        const int skip = all ? 0 : 1;
+        const int share = br_long_sharers(NW - skip, qn, free);
+        br_long_reductions(p, a, o, inst, lane, w - skip, NW - skip, share, q0, qn, sd,
                            (float *)(mbox + 16) + w * BR_LONG_RED_WORDS(HS, G));
+        if (w == NW - 1) mbox[12] = 2 * share + skip;  // (for this wave, when the round is over)
         __builtin_amdgcn_s_waitcnt(0);  // every read has returned before the block meets for the last time
       }
       for (;;) {
@@ -241,6 +280,10 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
         }
         __syncthreads();
       }
+      int32_t *best_g = br_late_out().best_g;
+      if (w == NW - 1 && best_g && br_uniform(mbox[12]) > 3)
+        br_long_shared_best(best_g, p.Q, inst, lane, qn, br_uniform(mbox[12]) >> 1,
+                            mbox + 16 + (br_uniform(mbox[12]) & 1) * BR_LONG_RED_WORDS(HS, G) + BR_LONG_BEST_AT(HS, G), BR_LONG_RED_WORDS(HS, G));
       return;
     }
   }
@@ -334,10 +377,11 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
     __syncthreads();  // the helper waves read their share of the sorted keys
     if (o.best_g || o.best_i) {
       float *red = (float *)(mbox + 16);
-      if (((qn + BR_WAVE - 1) / BR_WAVE) * (int)__builtin_popcountll(br_ballot(cap > 0)) > BR_LONG_ALONE * (NW - 1)) {
-        br_long_reductions(p, a, o, inst, lane, 0, NW, q0, qn, sd, red);
+      const int free = (int)__builtin_popcountll(br_ballot(cap > 0));
+      if (((qn + BR_WAVE - 1) / BR_WAVE) * free > BR_LONG_ALONE * (NW - 1)) {
+        br_long_reductions(p, a, o, inst, lane, 0, NW, br_long_sharers(NW, qn, free), q0, qn, sd, red);
       } else if (lane < G) {
-        int *part = (int *)(red + HS + 4);
+        int *part = (int *)red + BR_LONG_PART_AT(HS);
         part[lane] = BR_KEY_NONE, part[G + lane] = 0, part[2 * G + lane] = -1;
       }
     }
@@ -982,7 +1026,7 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
       int bk = BR_KEY_NONE, bs = 0, bi = -1;
 #pragma unroll
       for (int u = 0; u < NW; ++u) {
-        const int *part = mbox + 16 + u * BR_LONG_RED_WORDS(HS, G) + HS + 4;
+        const int *part = mbox + 16 + u * BR_LONG_RED_WORDS(HS, G) + BR_LONG_PART_AT(HS);
         const int k = part[lane], s = part[G + lane], i = part[2 * G + lane];
         const bool better = i >= 0 && (bi < 0 || k > bk || (k == bk && (s > bs || (s == bs && i < bi))));
         bk = better ? k : bk, bs = better ? s : bs, bi = better ? i : bi;

@@ -1,6 +1,7 @@
 """Parity of the HIP path (called through the C ABI) against the CPU oracle, element by element
 on the same seeded inputs.  Integer results (assignments, loads, slot tables, queue, BR-0 scores,
 statistics) must be bit-exact; fp32 horizon scores within 1e-5 relative."""
+import dataclasses
 import sys
 
 import numpy as np
@@ -856,7 +857,8 @@ def test_snapshot_reductions_by_their_work(N, G, H, Q, R_max, own):
     (20, 3, 40, 70, 0), (20, 8, 80, 256, 0), (20, 13, 9, 130, 9000), (20, 64, 17, 65, 0),
     # on the round's helper waves: one, three of them, up to 32 pairs of (tile, worker) each; beyond 16 each with the round's wave
     (20, 16, 80, 250, 0), (1100, 8, 20, 256, 0), (1100, 9, 20, 256, 0), (40, 12, 80, 512, 9000), (40, 13, 80, 512, 0), (8, 24, 128, 256, 9000), (8, 3, 9, 2048, 0),
-    # up to 16 clusters: a block each up to 128 pairs (a watermark: 64, queues of up to 256), tiles beyond
+    # up to 16 clusters: a block each up to 128 pairs without a watermark (16 x 8), tiles beyond; the next three and others with a
+    # watermark are on the helper waves (test_long_horizon_reductions_beyond_the_helpers has those that are not)
     (16, 16, 80, 512, 0), (9, 17, 80, 512, 0), (9, 16, 30, 256, 9000), (9, 17, 30, 256, 9000), (9, 4, 20, 320, 9000), (9, 64, 128, 128, 0)])
 def test_long_horizon_reductions_by_free_workers(N, G, H, Q, wm):
     """Only workers with a free slot are scored: none, one, some, all of them free; nothing waiting."""
@@ -868,6 +870,61 @@ def test_long_horizon_reductions_by_free_workers(N, G, H, Q, wm):
     arr.count[7] = Q
     _say(f"long reductions G={G} H={H} Q={Q} W={wm}")
     oc, r = run_pair(cfg, init, arr, matrix=False, tag="long reductions")
+    r.close()
+
+
+@pytest.mark.parametrize("N,G,H,Q,wm,own", [
+    (9, 24, 30, 256, 9000, False), (40, 12, 80, 512, 9000, False),                         # 96 pairs: on the round's helper waves
+    (9, 25, 30, 256, 9000, True), (16, 32, 17, 256, 9000, True), (9, 7, 80, 900, 9000, True),  # 97..128 under a watermark: tiles
+    (9, 25, 30, 256, 0, True), (16, 16, 80, 512, 0, True), (9, 7, 80, 900, 0, True),       # without one: a block per cluster
+    (9, 43, 30, 150, 0, True), (9, 17, 80, 512, 9000, True),                               # beyond 128: tiles
+    (40, 13, 80, 512, 9000, True), (17, 33, 12, 200, 9000, True), (17, 33, 12, 200, 0, True),  # more than 16 clusters: a block
+])
+def test_long_horizon_reductions_beyond_the_helpers(N, G, H, Q, wm, own):
+    """The kernels of their own that take the reductions of a long horizon, with and without a watermark: workers full, some
+    free, all free, nothing waiting; `own`: they come as a launch of their own."""
+    cfg, init, arr = wl.random_case(690 + G + H, N=N, G=G, B=5, max_wait=Q, H=H, pred_mode=1, token_watermark=wm)
+    init.kv[:], init.rem[:] = np.maximum(init.kv, 1), np.maximum(init.rem, 1)
+    init.n[0], init.n[1, ::2], init.n[2] = cfg.B, cfg.B, 0
+    arr.count[3], arr.count[4:6], arr.count[-1] = 0, Q, Q
+    _say(f"beyond the helpers N={N} G={G} H={H} Q={Q} W={wm}")
+    oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
+    for rnd in range(2):
+        ref = oc.route_step(arr if rnd == 0 else wl.Arrivals(np.zeros_like(arr.count), arr.s, arr.o, arr.id, arr.pred))
+        launches, out = _score_launches(r, arr if rnd == 0 else None)
+        assert launches == (1 if own else 0), (launches, own)
+        compare_outputs(ref, out, cfg, f"beyond the helpers r{rnd}")
+        oc.advance(2)
+        r.advance(2)
+    compare_state(oc, r.state(), cfg, "beyond the helpers")
+    r.close()
+
+
+@pytest.mark.parametrize("N", [5, 1100])  # three helper waves, one
+@pytest.mark.parametrize("G", [1, 3, 22, 32])
+@pytest.mark.parametrize("H,Q,wm", [(73, 44, 0), (9, 64, 9000), (128, 130, 0), (20, 300, 9000)])
+def test_long_horizon_reductions_of_short_queues(N, G, H, Q, wm):
+    """Fewer tiles of 64 requests than waves: the waves share a tile's workers.  Nothing, one, 64, 65, 128, 129 or all
+    waiting, no worker free, one, all; equal workers, so that the first of them is the best."""
+    n_all = N
+    N = min(N, 40)
+    cfg, init, arr = wl.random_case(680 + G + H, N=N, G=G, B=5, max_wait=Q, H=H, pred_mode=1, token_watermark=wm)
+    init.kv[:], init.rem[:] = np.maximum(init.kv, 1), np.maximum(init.rem, 1)
+    init.n[:] = 3
+    init.n[0] = cfg.B
+    init.n[1, :-1] = cfg.B
+    init.kv[2:4], init.rem[2:4], init.pred[2:4] = 700, 20, 5
+    counts = [c for c in (0, 1, 2, 63, 64, 65, 128, 129, Q) if c <= Q]
+    arr.count[:] = np.resize(counts, N)
+    arr.count[:4] = min(Q, 64)
+    if n_all > N:  # more copies of the same clusters
+        rows = np.arange(n_all) % N
+        pick = lambda x: None if x is None else np.ascontiguousarray(x[rows])
+        cfg = dataclasses.replace(cfg, n_inst=n_all)
+        init = wl.InitState(*(pick(x) for x in (init.n, init.kv, init.rem, init.pred)))
+        arr = wl.Arrivals(*(pick(x) for x in (arr.count, arr.s, arr.o, arr.id, arr.pred)))
+    _say(f"short queues N={n_all} G={G} H={H} Q={Q} W={wm}")
+    oc, r = run_pair(cfg, init, arr, matrix=False, tag="short queues")
     r.close()
 
 
