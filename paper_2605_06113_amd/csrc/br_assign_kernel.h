@@ -137,8 +137,6 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
     while (capmax_cur > 0 && br_ballot(cap == capmax_cur) == 0ull) --capmax_cur;
     return capmax_cur;
   };
-  auto workers_max = [&](int v) -> int { return br_wave_max(v); };  // (a branch to the row's form costs more than its two steps)
-  auto workers_min = [&](int v) -> int { return br_wave_min(v); };
   // rank of each member among the members by (load, index): lanes that are no members hold INT32_MAX
   auto rank_of = [&](int wkey) -> int {
     if (small) return br_row_rank(wkey);
@@ -435,7 +433,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
     const int s_k = mine >> BR_IDX_BITS;
     int lim = lane_minm();
     if (p.W > 0) lim = min(lim, p.W - Lh[0]);
-    const int k0 = workers_min((cand && s_k > lim) ? rank : kmaxp);
+    const int k0 = br_wave_min((cand && s_k > lim) ? rank : kmaxp);
     if (k0 > 0) {  // ranks 0..k0-1 are in the safe regime: k-th lightest worker takes k-th largest request
       const bool take = cand && rank < k0;
       if (take) bound[IDX_MASK - (mine & IDX_MASK)] = (lane << 16) | nn;
@@ -620,7 +618,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
       // comes before the first other one's go together (nothing is admitted in between)
       const int shortest = tail_len();  // (looked up by the whole wave)
       const bool none = kc >= 0 && p.W - Lh[0] < shortest;
-      const int kfirst = workers_max(none ? -1 : kc);
+      const int kfirst = br_wave_max(none ? -1 : kc);
       const bool out = none && kc > kfirst;
       const int n_out = __builtin_popcountll(br_ballot(out));
       if (n_out > 0) {
@@ -633,7 +631,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
         kc = out ? -1 : kc;
       }
     }
-    const int g = 63 - (workers_max(kc) & 63);
+    const int g = 63 - (br_wave_max(kc) & 63);
     ++pops;
     int Lg[NH], mg[NH];
     margins_of(g, Lg, mg);
@@ -789,12 +787,8 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
       const bool found = pick(mg, room, key, none_below);
       if constexpr (!BRH) {
         if (guard_sure && none_below && tail_bulk_ok) {
-          // This worker takes the shortest waiting request through the guard and the envelope becomes
-          // its new load.  The next pop goes to the next lightest worker that still has this many free
-          // slots; its margin is at most the length just admitted.  While the lengths admitted stay
-          // at or below (G-1)/G of the window's smallest entry, the window is untouched, that entry
-          // still scores <= 0 for every such margin (so the guard fires again) and no waiting request
-          // is below the margin: the pops of this free-slot count follow in one step.
+          // the pops of this free-slot count in one step, as argued for narrow windows above (one function for both: the batch
+          // of 4096 clusters with 250 admissions each takes 114.7 us instead of 112.2)
           const bool member = cap == capmax;
           const int level = __builtin_popcountll(br_ballot(member));
           const int K = min(level, n_alive - w);

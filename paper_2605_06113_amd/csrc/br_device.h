@@ -102,22 +102,13 @@ __device__ __forceinline__ int br_wave_sum(int x) {
   return __builtin_amdgcn_readlane(x, 63);
 }
 
-// Reductions over one row of 16 lanes (lanes 0..15 of the wave: clusters of up to 16 workers keep all of them
-// there): four butterfly steps leave the row's result in each of its lanes, two DPP steps and a bubble less than
-// the wave-wide forms.  What the other rows hold does not matter.
+// Maximum over the wave's first row of 16 lanes (the masks of a window of up to four requests): four butterfly steps, two
+// DPP steps and a bubble less than the wave-wide form.  What the other rows hold does not matter.
 __device__ __forceinline__ int br_row0_max(int x) {
   x = max(x, br_dpp<0xB1, 0xF, true>(0, x));
   x = max(x, br_dpp<0x4E, 0xF, true>(0, x));
   x = max(x, br_dpp<0x141, 0xF, true>(0, x));
   x = max(x, br_dpp<0x140, 0xF, true>(0, x));
-  return __builtin_amdgcn_readlane(x, 0);
-}
-
-__device__ __forceinline__ int br_row0_min(int x) {
-  x = min(x, br_dpp<0xB1, 0xF, true>(0, x));
-  x = min(x, br_dpp<0x4E, 0xF, true>(0, x));
-  x = min(x, br_dpp<0x141, 0xF, true>(0, x));
-  x = min(x, br_dpp<0x140, 0xF, true>(0, x));
   return __builtin_amdgcn_readlane(x, 0);
 }
 
