@@ -1195,7 +1195,7 @@ static size_t br_long_block_bytes(const BrParams &p) {  // LDS of br_k_score_lon
 #define BR_LONG_BLOCK_LDS (60 * 1024)
 
 static bool br_long_in_block(const BrParams &p, int T) {
-  return br_long_block_bytes(p) <= BR_LONG_BLOCK_LDS && T * p.G <= (p.W <= 0 ? 128 : T <= 4 ? 64 : 0);
+  return br_long_block_bytes(p) <= BR_LONG_BLOCK_LDS && p.W <= 0 && T * p.G <= 128;
 }
 
 bool br_score_in_tiles(const BrParams &p) {
@@ -1203,8 +1203,7 @@ bool br_score_in_tiles(const BrParams &p) {
   if (p.N > BR_SCORE_TILES_MAX_N || T * WGN < 8) return false;
   if (p.H == 0) return p.R_max > 8 && p.Q > 512;  // (narrower windows: in the round's launch)
   if (p.H > BR_HP && br_long_in_block(p, T)) return false;
-  // (windows beyond 8 requests: no round's launch to ride in; queues beyond 1024 ride in the round's block)
-  return p.H > BR_HP || p.Q > 512 || p.R_max > 8 || br_pair_units(p) >= BR_UNITS_ONE_WAVE;
+  return p.H > BR_HP || p.Q > 512 || p.R_max > 8;  // (elsewhere in the round's launch)
 }
 
 static void br_launch_reductions(const BrParams &p, const BrArr &a, const BrOut &o, int *partials, hipStream_t st) {
