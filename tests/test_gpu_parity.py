@@ -819,9 +819,11 @@ def _score_launches(r, arr):
 
 
 @pytest.mark.parametrize("N,G,H,Q,R_max,own", [
-    # up to 16 clusters, queues of up to 512: tiles from 2048 units (tiles x workers x offsets) on, one wave below
-    (16, 42, 4, 512, 4, False), (16, 43, 4, 512, 4, True), (17, 64, 8, 512, 4, False), (1, 64, 8, 192, 4, False),
-    (1, 64, 8, 193, 4, True), (2, 25, 8, 512, 4, False), (2, 26, 8, 512, 4, True), (3, 64, 5, 512, 8, True), (16, 64, 8, 512, 1, True),
+    # queues of up to 512: on other waves of the round's block
+    (16, 42, 4, 512, 4, False), (16, 43, 4, 512, 4, False), (17, 64, 8, 512, 4, False), (1, 64, 8, 192, 4, False),
+    (1, 64, 8, 193, 4, False), (2, 25, 8, 512, 4, False), (2, 26, 8, 512, 4, False), (3, 64, 5, 512, 8, False), (16, 64, 8, 512, 1, False),
+    # up to 16 clusters with windows beyond 8: tiles
+    (16, 43, 4, 512, 12, True), (1, 64, 8, 193, 9, True), (2, 26, 8, 512, 16, True), (16, 64, 8, 512, 12, True),
     # queues of 513..1024 (never in the round's launch): tiles, blocks of eight waves from 2048 units on, one wave
     (16, 8, 4, 513, 4, True), (17, 38, 4, 513, 4, True), (17, 37, 4, 513, 4, True), (256, 16, 8, 1024, 4, True),
     (257, 16, 8, 1024, 4, True), (40, 5, 3, 700, 4, True),
