@@ -19,9 +19,10 @@
 //     the worker in hand in registers, so that the update after an admission needs no LDS read);
 //   - a score walks the offsets in order with margins and discounts broadcast from LDS, four per load, and
 //     skips the groups of offsets whose margins no value in question reaches (exact zeros);
-//   - the single best request argmax_i F_g({i}) is read off the requests around the peak of the score (pick_quick), where
-//     rounding could reorder those found by bracketing (pick_single: the score is concave in the length, the waiting set
-//     is sorted by length), never by scoring the whole waiting set.  2048 clusters, G = 8, H = 80, overloaded, with the
+//   - the single best request argmax_i F_g({i}): in queues of up to 256 first read off the requests around the peak of the
+//     score (pick_quick); where rounding could reorder those, and in longer queues, found by bracketing (pick_single: the
+//     score is concave in the length, the waiting set is sorted by length); only where more than 64 requests are left
+//     between the brackets is the whole waiting set scored.  2048 clusters, G = 8, H = 80, overloaded, with the
 //     register sort and margins kept while the envelope stands: whole pass 75.1 -> 71.2 us, one cluster 27.3 -> 26.0;
 //   - Stage 2 goes straight to the starvation guard when the window's smallest entry scores clearly below
 //     zero (then every subset does).
@@ -651,10 +652,12 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
     }
     return -1;
   };
-  // Queues of up to 256 only, and while it decides at least two picks in three: among many waiting requests of nearly the same
-  // length the leads are within the bounds pick after pick.  Whole pass, us, always bracketed / so, G = 8, H = 80: 2048 clusters,
-  // overloaded 70 / 58; one cluster 114 / 105 and 1000 clusters 320 / 306 in bursts of 60 and 200 arrivals; 2048 clusters, 128
-  // admissions each from a full queue 517 / 531.  300 clusters, G = 16, queues of 500 in bursts: 279 / 352.
+  // Queues of up to 256 only (300 clusters, G = 16, queues of 500 in bursts, always bracketed / so: 279 / 352 us), and by what the
+  // picks of the round have shown so far.
+  // Starvation guard: while it decides at least two picks in three; among many waiting requests of nearly the same length the
+  // leads are within the bounds pick after pick.  Whole pass, us, always bracketed / so, G = 8, H = 80, 2048 clusters,
+  // overloaded, a decode step per call 78 / 67, 16 of them 208 / 191, 48: 424 / 400, 100: 748 / 705; a token watermark 82 / 84;
+  // 128 admissions from a full queue 517 / 526 (a bracketing search skips the offsets that no request reaches, most of them there).
   int credit = 3;
   auto pick = [&](int room, int &pos, int &swin) -> bool {
     if constexpr (E == 4) {
@@ -665,6 +668,32 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
           return r != 0;
         }
         credit -= 2;
+      }
+    }
+    return pick_single(room, pos, swin);
+  };
+
+  // Stage 1, four waves a cluster (two: 2048 clusters in bursts of 200 arrivals 784 us bracketed, 800 so): many picks, at first with
+  // wide margins, where bracketing skips most offsets and costs less than the quick pick's fixed work.  So a pick that reaches
+  // the margins of fewer than eight offsets counts against it, and once out of credit it is tried again at every twelfth pick.
+  // Whole pass, us, always bracketed / always tried / so: 8 clusters, G = 13, H = 56, 116 admissions (5 offsets a pick) 274 / 296 / 282;
+  // the same with estimates (17 offsets) 372 / 351 / 363; G = 8, H = 80, one cluster in bursts of 60 169 / 152 / 155, 1000 in bursts of 200
+  // (51 offsets) 695 / 656 / 556.
+  int credit1 = 3, passed = 0;
+  auto pick1 = [&](int room, int &pos, int &swin) -> bool {
+    if constexpr (E == 4 && NW == 4) {
+      if (credit1 > 0 || ++passed == 12) {
+        passed = 0;
+        const int r = pick_quick(room, pos, swin);
+        if (r == 0) return false;
+        if (r > 0) {
+          int reach = 0;
+#pragma unroll
+          for (int u = 0; u < 3; ++u) reach += __builtin_popcountll(br_ballot(u * BR_WAVE + lane < H1 && mr[u] < (float)swin));
+          credit1 = reach >= 8 ? min(credit1 + 1, 4) : max(credit1 - 1, 0);
+          return true;
+        }
+        credit1 = max(credit1 - 2, 0);
       }
     }
     return pick_single(room, pos, swin);
@@ -773,12 +802,7 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
         margins_of(g);
         const int room = p.W > 0 ? p.W - __builtin_amdgcn_readlane(Lcur, g) : INT32_MAX;
         int pos = 0, swin = 0;
-        bool got;  // (2048 clusters in bursts of 200 arrivals: 800 us with pick here, 784 so; 1000 clusters 306 and 322)
-        if constexpr (NW == 4)
-          got = pick(room, pos, swin);
-        else
-          got = pick_single(room, pos, swin);
-        if (!got) {
+        if (!pick1(room, pos, swin)) {
           drop_worker(g, capmax);
           continue;
         }
