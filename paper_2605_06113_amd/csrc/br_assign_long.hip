@@ -9,9 +9,11 @@ int br_long_waves(const BrParams &p) {
   return (long long)p.N * 4 <= room ? 4 : (long long)p.N * 2 <= room ? 2 : 1;
 }
 
-// The reductions on the round's helper waves, up to 32 pairs (tile of 64 requests, worker) per helper; a pair whose worker has a free
-// slot is about 1200 cycles, and few of them hide behind the round (BR_LONG_ALONE: many).  Whole pass, a launch of their own / so, G = 8,
-// H = 80: one cluster 21.8 / 19.5 us; 2048 clusters, overloaded 62 / 54, all slots free and 128 admissions each 524 / 517.
+// The reductions on the round's helper waves, up to 32 pairs (tile of 64 requests, worker) per wave that serves its searches; a pair
+// whose worker has a free slot is about 1200 cycles, and few of them hide behind the round (BR_LONG_ALONE: many).  Up to 256 clusters
+// have more waves for them (br_launch_assign_long_one).  Whole pass, us, a launch of their own / so, H = 80: one cluster, G = 8 21.8 / 19.4;
+// overloaded / lightly loaded / under a watermark that keeps slots free everywhere, 1000 clusters, G = 24, Q = 256 84 / 74, 73 / 59, 175 / 167;
+// 700, G = 12, Q = 512 72 / 73, 54 / 49, 125 / 123; 2048, G = 8, Q = 256 73 / 73, 61 / 60, 123 / 114, and with 128 admissions each 533 / 526.
 bool br_long_helped(const BrParams &p) {
   const int nw = br_long_waves(p), T = (p.Q + BR_WAVE - 1) / BR_WAVE;
   return nw > 1 && T * p.G <= 32 * (nw - 1);

@@ -100,6 +100,7 @@ __device__ __forceinline__ void br_long_slice_best(const BrParams &p, const floa
 // so many-th of those workers; a worker's step-start margins are on their way from memory while the one before it is scored.
 // best_g is written here, for shared tiles when the round is over (br_long_shared_best); what is best for a worker among these
 // requests (score, then the longer request, then the earlier arrival) goes to `red`, where wave 0 finds it then.
+template <bool MANY>
 __device__ __forceinline__ void br_long_reductions(const BrParams &p, const BrArr &a, const BrOut &o, int inst, int lane, int h,
                                                    int nh, int share, int q0, int qn, const float *sd, float *red) {
   const int G = p.G, H1 = p.H + 1, HS = BR_HS(p.H);
@@ -110,9 +111,15 @@ __device__ __forceinline__ void br_long_reductions(const BrParams &p, const BrAr
   unsigned long long freem = br_ballot(lane < G && n_raw < p.B);
   int first = h, step = nh;  // tiles of this wave
   if (share > 1) {           // (at most one)
-    const int r = br_rank_below(freem), of = share == 2 ? h & 1 : h;
-    first = tiles <= 1 ? 0 : h >> 1, step = tiles;
-    freem = br_ballot(((freem >> lane) & 1ull) && (share == 3 ? r % 3 : r & (share - 1)) == of);
+    const int r = br_rank_below(freem);
+    step = tiles;
+    if constexpr (MANY) {
+      first = h / share;
+      freem = br_ballot(((freem >> lane) & 1ull) && r % share == h - first * share);
+    } else {
+      first = tiles <= 1 ? 0 : h >> 1;
+      freem = br_ballot(((freem >> lane) & 1ull) && (share == 3 ? r % 3 : r & (share - 1)) == (share == 2 ? h & 1 : h));
+    }
   }
   int ik = BR_KEY_NONE, is = 0, ii = -1;  // lane g: of worker g
   int mh[3] = {0, 0, 0};
@@ -167,10 +174,15 @@ __device__ __forceinline__ void br_long_reductions(const BrParams &p, const BrAr
   if (lane < G) part[lane] = ik, part[G + lane] = is, part[2 * G + lane] = ii;
 }
 
-// Waves that share a tile: with fewer tiles than waves (nh: two to four) and enough workers with a free slot to be worth it.
+// Waves that share a tile: with fewer tiles than waves (nh), two workers with a free slot or more to each.
 // 229 clusters, G = 22, H = 73, at most 44 waiting, half of the slots free, whole pass: 44.1 us with a launch of its own, 55.2
 // with a tile to a wave, 35.1 so.
+template <bool MANY>  // more than four waves
 __device__ __forceinline__ int br_long_sharers(int nh, int qn, int free) {
+  if constexpr (MANY) {
+    const int tiles = (qn + BR_WAVE - 1) / BR_WAVE;
+    return 2 * tiles > nh ? 1 : max(min(nh / max(tiles, 1), free >> 1), 1);
+  }
   return free < 2 * nh ? 1 : qn <= BR_WAVE ? nh : nh == 4 && qn <= 2 * BR_WAVE ? 2 : 1;
 }
 
@@ -187,9 +199,12 @@ __device__ __forceinline__ void br_long_shared_best(int32_t *best_g, int Q, int 
   }
 }
 
-template <int E, int NW>
+#define BR_LONG_EXTRA_MAX_N 256
+// XW: waves beyond those that serve the searches, for the reductions only (few clusters).
+template <int E, int NW, int XW = 0>
 // (queues of up to 256: four waves per SIMD are asked for, which is what br_long_waves counts on)
-__global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrParams p, BrArr a, BrOut o) {
+__global__ __launch_bounds__(64 * (NW + XW), E == 4 && XW == 0 ? 4 : 1) void br_k_assign_long(BrParams p, BrArr a, BrOut o) {
+  constexpr int RW = NW - 1 + XW;  // waves that have the reductions while wave 0 runs the round
   static_assert(E % NW == 0, "every wave takes whole blocks of 64 sorted positions");
   constexpr int EW = E / NW;  // blocks of 64 sorted positions per wave in a shared search
   // four-offset groups of wave 0 when the probes of a bracketing search are shared: every NW-th, wave w takes the
@@ -227,7 +242,7 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
   // the step-start projections, as contiguous memory: all waves of the block, four words per thread in flight
   {
     const int32_t *src = p.Lh + (int64_t)inst * G * H1;
-    const int words = G * H1, nt = 64 * NW;
+    const int words = G * H1, nt = 64 * (NW + XW);
     const unsigned inv = 0xffffffffu / (unsigned)H1 + 1u;  // e / H1 by a multiply-high (e < 2^14)
     for (int e0 = (int)threadIdx.x; e0 < words; e0 += 4 * nt) {
       int v[4];
@@ -252,23 +267,24 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
       __syncthreads();  // the sorted keys and the discounts are in LDS
       int svh[EW];
 #pragma unroll
-      for (int j = 0; j < EW; ++j) svh[j] = skey[(w * EW + j) * BR_WAVE + lane] >> BR_IDX_BITS;
+      for (int j = 0; j < EW; ++j) svh[j] = skey[(min(w, NW - 1) * EW + j) * BR_WAVE + lane] >> BR_IDX_BITS;
       const int sprobe = skey[lane * E] >> BR_IDX_BITS;  // the probe of this lane in a bracketing search
       if (o.best_g || o.best_i) {
         const int free = (int)__builtin_popcountll(br_ballot(lane < G && p.n[(int64_t)inst * G + min(lane, G - 1)] < p.B));
-        const bool all = ((qn + BR_WAVE - 1) / BR_WAVE) * free > BR_LONG_ALONE * (NW - 1);
+        const bool all = ((qn + BR_WAVE - 1) / BR_WAVE) * free > BR_LONG_ALONE * RW;
         const int skip = all ? 0 : 1;
-        const int share = br_long_sharers(NW - skip, qn, free);
-        br_long_reductions(p, a, o, inst, lane, w - skip, NW - skip, share, q0, qn, sd,
+        const int share = br_long_sharers<(XW > 0)>(RW + 1 - skip, qn, free);
+        br_long_reductions<(XW > 0)>(p, a, o, inst, lane, w - skip, RW + 1 - skip, share, q0, qn, sd,
                            (float *)(mbox + 16) + w * BR_LONG_RED_WORDS(HS, G));
-        if (w == NW - 1) mbox[12] = 2 * share + skip;  // (for this wave, when the round is over)
+        if (w == RW) mbox[12] = 2 * share + skip;  // (for this wave, when the round is over)
         __builtin_amdgcn_s_waitcnt(0);  // every read has returned before the block meets for the last time
       }
       for (;;) {
         __syncthreads();
         const int cmd = mbox[0];
         if (cmd == 0) break;
-        if (cmd == 2) {  // this wave's share of the probes' penalty sums
+        if (XW > 0 && w >= NW) {  // (has no part in searches)
+        } else if (cmd == 2) {  // this wave's share of the probes' penalty sums
           who[w * BR_WAVE + lane] = __float_as_int(br_long_penalty_part(smg, sd, HS, lane, mbox[2], sprobe, SHARE << w));
         } else {         // this wave's share of a full scan
           const int roomq = mbox[1];
@@ -282,7 +298,7 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
         __syncthreads();
       }
       int32_t *best_g = br_late_out().best_g;
-      if (w == NW - 1 && best_g && br_uniform(mbox[12]) > 3)
+      if (w == RW && best_g && br_uniform(mbox[12]) > 3)
         br_long_shared_best(best_g, p.Q, inst, lane, qn, br_uniform(mbox[12]) >> 1,
                             mbox + 16 + (br_uniform(mbox[12]) & 1) * BR_LONG_RED_WORDS(HS, G) + BR_LONG_BEST_AT(HS, G), BR_LONG_RED_WORDS(HS, G));
       return;
@@ -379,8 +395,8 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
     if (o.best_g || o.best_i) {
       float *red = (float *)(mbox + 16);
       const int free = (int)__builtin_popcountll(br_ballot(cap > 0));
-      if (((qn + BR_WAVE - 1) / BR_WAVE) * free > BR_LONG_ALONE * (NW - 1)) {
-        br_long_reductions(p, a, o, inst, lane, 0, NW, br_long_sharers(NW, qn, free), q0, qn, sd, red);
+      if (((qn + BR_WAVE - 1) / BR_WAVE) * free > BR_LONG_ALONE * RW) {
+        br_long_reductions<(XW > 0)>(p, a, o, inst, lane, 0, RW + 1, br_long_sharers<(XW > 0)>(RW + 1, qn, free), q0, qn, sd, red);
       } else if (lane < G) {
         int *part = (int *)red + BR_LONG_PART_AT(HS);
         part[lane] = BR_KEY_NONE, part[G + lane] = 0, part[2 * G + lane] = -1;
@@ -1049,7 +1065,7 @@ __global__ __launch_bounds__(64 * NW, E == 4 ? 4 : 1) void br_k_assign_long(BrPa
     if (best_i && lane < p.G) {  // lane g: the best of what the waves found for worker g
       int bk = BR_KEY_NONE, bs = 0, bi = -1;
 #pragma unroll
-      for (int u = 0; u < NW; ++u) {
+      for (int u = 0; u <= RW; ++u) {
         const int *part = mbox + 16 + u * BR_LONG_RED_WORDS(HS, G) + BR_LONG_PART_AT(HS);
         const int k = part[lane], s = part[G + lane], i = part[2 * G + lane];
         const bool better = i >= 0 && (bi < 0 || k > bk || (k == bk && (s > bs || (s == bs && i < bi))));
@@ -1082,14 +1098,24 @@ template <int E>
 void br_launch_assign_long_one(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
   const int HS = BR_HS(p.H);
   const int nw = br_long_waves(p);
-  const size_t lds = ((size_t)3 * E * BR_WAVE + 2 * BR_WAVE + 3 * (size_t)HS + (((size_t)HS * BR_LSTRIDE(p.G) + 3) & ~(size_t)3) +
-                      (p.R_max > 8 ? 1024 : 0) + (nw > 1 ? 16 : 0) +
-                      (nw > 1 && (o.best_g || o.best_i) ? nw * BR_LONG_RED_WORDS(HS, p.G) : 0)) * sizeof(int);
+  const bool best = o.best_g || o.best_i;
+  const size_t words = (size_t)3 * E * BR_WAVE + 2 * BR_WAVE + 3 * (size_t)HS + (((size_t)HS * BR_LSTRIDE(p.G) + 3) & ~(size_t)3) +
+                       (p.R_max > 8 ? 1024 : 0) + (nw > 1 ? 16 : 0);
+  auto lds = [&](int waves) { return (words + (nw > 1 && best ? waves * BR_LONG_RED_WORDS(HS, p.G) : 0)) * sizeof(int); };
   const dim3 grid((unsigned)p.N), block(BR_WAVE * nw);
-  if (nw == 4)
-    hipLaunchKernelGGL((br_k_assign_long<E, 4>), grid, block, lds, st, p, a, o);
+  // A CU to each cluster: more waves for the reductions, where 60 KB of LDS hold them.  Three alone take up to 96 pairs of 1200
+  // cycles where a token watermark keeps slots free everywhere, and the round waits for them.  One cluster, whole pass, us, a launch
+  // of their own / three helper waves / so: such a watermark, H = 80: G = 8, Q = 256 43.9 / 44.6 / 36.7, G = 16, Q = 256 66 / 84 / 57, G = 4,
+  // Q = 512 34 / 43 / 33, G = 12, Q = 512 50 / 83 / 56; H = 128: G = 8, Q = 256 46 / 56 / 41, G = 12, Q = 512 55 / 99 / 64; workers nearly
+  // full, H = 80: 28.1 / 21.6 / 22.0, 36.0 / 27.3 / 26.5, 28.4 / 22.8 / 22.8, 35.7 / 28.1 / 28.9.  (Q = 256: twelve more 36.6 / 55.4 under the
+  // watermark, and 3 % slower on a lightly loaded cluster.)
+  constexpr int XW = E == 8 ? 8 : E <= 16 ? 4 : 0;
+  if (XW > 0 && best && p.N <= BR_LONG_EXTRA_MAX_N && lds(4 + XW) <= 60 * 1024)
+    hipLaunchKernelGGL((br_k_assign_long<E, 4, XW>), grid, dim3(BR_WAVE * (4 + XW)), lds(4 + XW), st, p, a, o);
+  else if (nw == 4)
+    hipLaunchKernelGGL((br_k_assign_long<E, 4>), grid, block, lds(4), st, p, a, o);
   else if (nw == 2)
-    hipLaunchKernelGGL((br_k_assign_long<E, 2>), grid, block, lds, st, p, a, o);
+    hipLaunchKernelGGL((br_k_assign_long<E, 2>), grid, block, lds(2), st, p, a, o);
   else
-    hipLaunchKernelGGL((br_k_assign_long<E, 1>), grid, block, lds, st, p, a, o);
+    hipLaunchKernelGGL((br_k_assign_long<E, 1>), grid, block, lds(1), st, p, a, o);
 }

@@ -902,7 +902,7 @@ def test_long_horizon_reductions_beyond_the_helpers(N, G, H, Q, wm, own):
     r.close()
 
 
-@pytest.mark.parametrize("N", [5, 1100])  # three helper waves, one
+@pytest.mark.parametrize("N", [5, 300, 1100])  # waves for the reductions: three and others, three, one
 @pytest.mark.parametrize("G", [1, 3, 22, 32])
 @pytest.mark.parametrize("H,Q,wm", [(73, 44, 0), (9, 64, 9000), (128, 130, 0), (20, 300, 9000)])
 def test_long_horizon_reductions_of_short_queues(N, G, H, Q, wm):
