@@ -314,9 +314,9 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
   p.adv_t = split_adv ? 0 : adv_t;
   int32_t rc = BR_OK;
   if (p.H > 0) rc = enqueue(ctx, BR_K_PROJECT, [&] { br_launch_project(p, ctx->st); }, br);
-  // The reductions ride along in the assignment launch (or on the helper wave of the split kernel) where one wave can do
-  // both: their sorted list is the round's, and a launch of their own would wait in line before it.  Not for a few BR-H
-  // clusters whose pairs are too many for one wave (br_score_in_tiles).
+  // The reductions ride along in the assignment launch where its waves can take them, since a launch of their own would wait
+  // in line before it: full batches on the round's wave, which goes on with the sorted list; smaller ones on other waves of the
+  // cluster's block, which load (and sort) for themselves.  Not where few clusters have more work than that hides (br_score_in_tiles).
   const bool best = o.best_g || o.best_i;
   const bool split = br_split_serves(p);
   const bool together = best && p.R_max <= 8 &&

@@ -1149,8 +1149,7 @@ static void launch_score_wave(const BrParams &p, const BrArr &a, const BrOut &o,
     hipLaunchKernelGGL((br_k_score_wave<16, HB>), grid, block, wpb * (BR_LIST_WORDS(16) + 2 * BR_WAVE) * sizeof(int), st, p, a, o);
 }
 
-// What best_g costs one wave that scores every (waiting request, worker with a free slot) pair of a BR-H cluster, every
-// worker having one: units of 64 requests x worker x offset (and two more for the score's frame), about a dozen cycles.
+// The size of a BR-H cluster's reductions: units of 64 requests x worker x offset (and two more for a score's frame).
 static int br_pair_units(const BrParams &p) {
   return ((p.Q + BR_WAVE - 1) / BR_WAVE) * p.G * ((p.H <= BR_HP / 2 ? BR_HP / 2 : BR_HP) + 2);
 }
@@ -1158,36 +1157,41 @@ static int br_pair_units(const BrParams &p) {
 // Which kernel takes the reductions.  BR-0 needs no score per pair (br_score_wave.h): one wave up to queues of 1024, except
 // where few clusters with queues of 513..1024 have windows beyond 8 and so a launch of their own (whole pass, us, one wave / tiles,
 // Q = 1024: one cluster, G = 4 21.8 / 21.1, G = 16 29.4 / 26.8, G = 64 46.0 / 44.0; 16 clusters 30.5 / 26.6, 36.4 / 32.8, 55.2 / 53.7).
-// For BR-H one wave is bound by the pairs and more waves per cluster cost launches of their own, so what is faster depends on
-// how many workers have a free slot and how many requests wait, which is not known here.  Whole pass (round and one decode
-// step), us: workers full / queue nearly empty / a token watermark that keeps slots free everywhere and the queue full.
-//   few clusters, Q <= 512             one wave          tiles
-//     N =  1  G = 16  H = 8  Q = 512   25 / 25 / 53      30 / 26 / 44    (1280 units)
-//     N = 16  G = 32  H = 4  Q = 512   32 / 27 / 62      36 / 30 / 54    (1536)
-//     N =  1  G = 64  H = 8  Q = 256   30 / 36 / 89      34 / 35 / 73    (2560)
-//     N = 16  G = 32  H = 8  Q = 512   40 / 34 / 79      40 / 35 / 61    (2560)
-//     N =  1  G = 64  H = 8  Q = 512   36 / 40 / 121     38 / 36 / 79    (5120)
-//   hence tiles from 2048 units on.  Queues of 513..1024: the tiles at any width (N = 1, G = 8, H = 4: 30 / - / 46 and 28 / - / 37).
-//   more clusters, Q = 1024            one wave          block of eight waves
-//     N =  64  G =  8  H = 4           45 / - / 55       56 / - / 62     (768)
-//     N = 256  G = 16  H = 4           49 / - / 67       55 / - / 65     (1536)
-//     N = 256  G = 16  H = 8           58 / - / 119      62 / - / 94     (2560)
-//     N =  64  G = 64  H = 8           74 / 50 / 185     74 / 54 / 123   (10240)
-//     N = 256  G = 64  H = 8           85 / 56 / 193     90 / 61 / 138
-//     N = 512  G = 64  H = 8           89 / - / 149      115 / - / 141
-//   hence the block from 2048 units on, for up to a block per CU.  Queues of up to 512 stay on one wave there (N = 64, G = 64,
-//   H = 8, Q = 512: 50 / 47 / 129 and, in blocks, 63 / 52 / 109).
+// BR-H, queues of up to 512 and windows of up to 8: on other waves of the round's block (br_k_route_h_helped) or its own.  Else more
+// waves per cluster cost launches of their own, so what is faster depends on how many workers have a free slot and how many
+// requests wait, which is not known here.  Whole pass (round and one decode step), us: workers full / a token watermark that
+// keeps slots free everywhere and the queue full (between them: a queue nearly empty).
+//   few clusters, Q <= 512             round's block       tiles
+//     N =  1  G = 16  H = 8  Q = 512   21.5 / 21.1 / 41.1  27.8 / 27.5 / 48.2
+//     N = 16  G = 32  H = 4  Q = 512   24.5 / 24.2 / 48.0  32.8 / 33.2 / 56.5
+//     N =  1  G = 64  H = 8  Q = 256   26.3 / 25.8 / 73.6  35.1 / 34.6 / 85.5
+//     N = 16  G = 64  H = 8  Q = 512   35.5 / 35.1 / 86.8  45.5 / 47.7 / 94.8
+//   windows beyond 8                   one wave            tiles
+//     N =  1  G = 16  H = 8  Q = 256   26.9 / 47.7         28.7 / 39.4
+//     N =  1  G = 64  H = 8  Q = 512   52.8 / 90.3         54.3 / 81.3
+//     N = 16  G = 64  H = 4  Q = 256   55.1 / 96.4         58.7 / 80.6
+//   few clusters, Q = 1024             one wave            tiles
+//     N =  1  G =  8  H = 4            30.7 / 48.4         28.9 / 37.8
+//     N = 16  G = 16  H = 8            45.0 / 126          40.9 / 81
+//     N =  1  G = 64  H = 8            50.7 / 112          48.6 / 98
+//   more clusters, Q = 1024            one wave            block of eight waves
+//     N =  64  G =  8  H = 4           40 / 57             55 / 64        (768 units)
+//     N = 256  G = 16  H = 4           49 / 80             57 / 74        (1536)
+//     N = 256  G = 16  H = 8           58 / 142            65 / 111       (2560)
+//     N =  64  G = 64  H = 8           66 / 172            80 / 139       (10240)
+//     N = 256  G = 64  H = 8           82 / 226            101 / 161
+//     N = 512  G = 64  H = 8           109 / 246           151 / 214
+//   hence the block from 2048 units on, where the watermark's side is the larger one, for up to a block per CU.
 #define BR_UNITS_ONE_WAVE 2048
 #define BR_BLOCK_MAX_N 256
 
-// Long horizons, up to 16 clusters: one launch of a block per cluster (br_k_score_long) or the tiles and their combine.  The
-// block scores the pairs of workers with a free slot only, and without a watermark a long queue leaves few of those; under a
-// watermark all pairs may be scored.  By (tile of 64 requests, worker) pairs; whole pass, us, block / tiles:
-//   overloaded     G = 8, Q = 256 (32 pairs) 21.1 / 24.5   G = 8, Q = 512 (64) 23.0 / 26.3   G = 16, Q = 256 (64) 25.1 / 32.6
-//                  G = 8, Q = 1024 (128) 29.2 / 34.0       G = 32, Q = 256 (128) 36.2 / 43.9
-//   watermark that keeps slots free everywhere, queue full
-//                  G = 8, Q = 256 40.5 / 39.6              G = 8, Q = 512 54.4 / 47.7        G = 16, Q = 256 59.5 / 59.4
-//                  G = 8, Q = 1024 94 / 66                 G = 32, Q = 256 102 / 96
+// Long horizons, up to 16 clusters, more pairs of (tile of 64 requests, worker) than the round's waves take (96): one launch of
+// a block per cluster (br_k_score_long) or the tiles and their combine.  The block scores the pairs of workers with a free slot
+// only, and without a watermark a long queue leaves few of those; under a watermark all pairs may be scored.  97 to 128 pairs,
+// whole pass, us, block / tiles:
+//   overloaded     G = 13, H = 80, Q = 512 32.7 / 37.4 (16 clusters 45.4 / 49.2)   G = 32, H = 80, Q = 256 41.1 / 48.6
+//                  G = 25, H = 30, Q = 256 34.7 / 38.8 (44.8 / 48.7)               G = 7, H = 80, Q = 1024, 16 clusters 68.6 / 67.3
+//   watermark that keeps slots free everywhere, queue full: 64 / 55 (76 / 66), 121 / 113, 89 / 86 (102 / 98), 96 / 81
 static size_t br_long_block_bytes(const BrParams &p) {  // LDS of br_k_score_long
   const size_t HS = BR_HS(p.H), Qp = ((size_t)p.Q + 63) & ~(size_t)63;
   return (((size_t)p.G + 1) * HS + 2 * (size_t)p.G + Qp + Qp * (size_t)(p.G | 1)) * sizeof(int);

@@ -51,7 +51,7 @@ void br_launch_bypass(const BrParams &p, const BrArr &a, const BrOut &o, hipStre
 void br_launch_baseline(const BrParams &p, const BrArr &a, const BrOut &o, int *pol, int policy, unsigned long long seed,
                         hipStream_t st);
 // BR-0 with decode steps, queues of up to 512, windows of up to 8: round and decode steps on two waves per cluster;
-// the snapshot reductions (best_g / best_i, where asked for) ride on the helper wave
+// the snapshot reductions and the matrix, where asked for, on a third
 bool br_split_shape(const BrParams &p);   // a shape it serves (when there are decode steps)
 bool br_split_serves(const BrParams &p);
 void br_launch_route_split(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
