@@ -3,6 +3,7 @@
 // F-score matrix with its stage-one reductions.
 #include "br.h"
 #include "br_device.h"
+#include "br_advance_seg.h"
 #include "br_launch.h"
 #include "br_score_wave.h"
 
@@ -53,71 +54,6 @@ __global__ __launch_bounds__(256) void br_k_load_init(BrParams p, const int32_t 
 // leaves (net load change -kv), the others gain t tokens.  Dense lists are compacted
 // in place, order preserved (writes never run ahead of reads).  PK as for br_adv_apply.
 
-// A wave's share of a list: LPL lanes, four consecutive slots each; 64 / LPL lists side by side.  Bits of a ballot that
-// belong to the lane's list, counted in all and below the lane.
-template <int LPL>
-__device__ __forceinline__ unsigned br_seg_bits(unsigned long long m, int lane) {
-  const unsigned w = lane < 32 ? (unsigned)m : (unsigned)(m >> 32);
-  return LPL == 32 ? w : (w >> (lane & 16)) & 0xffffu;
-}
-template <int LPL>
-__device__ __forceinline__ int br_seg_count(unsigned long long m, int lane) {
-  return LPL == 64 ? (int)__builtin_popcountll(m) : __builtin_popcount(br_seg_bits<LPL == 64 ? 32 : LPL>(m, lane));
-}
-template <int LPL>
-__device__ __forceinline__ int br_seg_below(unsigned long long m, int lane) {
-  if constexpr (LPL == 64) return br_rank_below(m);
-  else return __builtin_popcount(br_seg_bits<LPL>(m, lane) & ((1u << (lane & (LPL - 1))) - 1u));
-}
-// sum over the lanes of the lane's list, on each of them
-template <int LPL>
-__device__ __forceinline__ int br_seg_sum(int x) {
-  x += br_dpp<0xB1, 0xF, true>(0, x);
-  x += br_dpp<0x4E, 0xF, true>(0, x);
-  x += br_dpp<0x141, 0xF, true>(0, x);
-  x += br_dpp<0x140, 0xF, true>(0, x);
-  if constexpr (LPL >= 32) {
-    const auto r = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)x, false, false);
-    x = (int)(r[0] + r[1]);
-  }
-  if constexpr (LPL == 64) {
-    const auto r = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)x, false, false);
-    x = (int)(r[0] + r[1]);
-  }
-  return x;
-}
-
-// Prediction rows of the lists of a wave, from slot `from` of each on (from >= n: nothing moves), to slots map[]
-// (by lane * 4 + k as the slots are held): the lanes of a list walk its rows as contiguous memory, V at a time, four
-// requested before the first is stored.
-template <class V, int LPL>
-__device__ __forceinline__ void br_seg_rows_move(float *pw, int P, const short *map, int from, int n, int lane) {
-  const int upr = P / (int)(sizeof(V) / sizeof(float));  // units per row, 1..8
-  const unsigned inv = 65536u / (unsigned)upr + 1u;      // x / upr for x < 2048 by multiplication
-  const short *mine = map + (lane & ~(LPL - 1)) * 4;
-  V *rows = reinterpret_cast<V *>(pw);
-  const int end = n * upr;
-  auto dest = [&](int x) -> int {
-    const int j = (int)(((unsigned)x * inv) >> 16);
-    const int to = mine[j];
-    return to >= 0 && to != j ? to * upr + (x - j * upr) : -1;
-  };
-  for (int x = from * upr + (lane & (LPL - 1)); br_ballot(x < end) != 0ull; x += 4 * LPL) {
-    const int xb = x + LPL, xc = x + 2 * LPL, xd = x + 3 * LPL;
-    V va, vb, vc, vd;
-    if (x < end) va = rows[x];
-    if (xb < end) vb = rows[xb];
-    if (xc < end) vc = rows[xc];
-    if (xd < end) vd = rows[xd];
-    const int da = x < end ? dest(x) : -1, db = xb < end ? dest(xb) : -1;
-    const int dc = xc < end ? dest(xc) : -1, dd = xd < end ? dest(xd) : -1;
-    if (da >= 0) rows[da] = va;
-    if (db >= 0) rows[db] = vb;
-    if (dc >= 0) rows[dc] = vc;
-    if (dd >= 0) rows[dd] = vd;
-  }
-}
-
 // Lists of up to 4 * LPL slots (LPL = 16, 32, 64): RW x 64 / LPL lists per wave, everything requested before the first
 // result is needed.  Short lists side by side keep the lanes busy and their chains (the list, the rows that move, the
 // estimator's look-ups) in step: lists of 64 slots with maintained estimates (2048 clusters, G = 8) 36 -> 14.5 us, of
@@ -125,112 +61,43 @@ __device__ __forceinline__ void br_seg_rows_move(float *pw, int P, const short *
 template <int LPL, int RW, int PK>
 __global__ __launch_bounds__(256) void br_k_advance_seg(BrParams p, int t) {
   constexpr int LPW = BR_WAVE / LPL;  // lists of a wave side by side
-  const int64_t row0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * (RW * LPW);
+  const int wave = br_uniform((int)(threadIdx.x >> 6));
+  const int64_t row0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + wave) * (RW * LPW);
   const int64_t rows = (int64_t)p.N * p.G;
   if (row0 >= rows) return;
-  const int lane = br_lane(), lseg = lane & (LPL - 1), seg = lane / LPL, e0 = 4 * lseg;
-  __shared__ __align__(16) int lds_all[PK > 0 ? 4 * 256 : 4];
-  int *lds = PK > 0 ? lds_all + (threadIdx.x >> 6) * 256 : nullptr;
+  const int lane = br_lane(), lists = (int)min(rows - row0, (int64_t)(RW * LPW));
+  const BrSegBase b = br_seg_base(p, row0);
+  __shared__ __align__(16) int lds_all[4 * BR_SEG_WORDS(PK)];
+  int *lds = lds_all + wave * BR_SEG_WORDS(PK);
   int n_g[RW], L_g[RW];
-  int4 kv4[RW], rem4[RW];
-  float ch[RW][4], age[RW][4], since[RW][4];  // PK 2
+  BrSegSlots<PK> v[RW];
 #pragma unroll
   for (int r = 0; r < RW; ++r) {
-    const int64_t row = row0 + r * LPW + seg;
-    const bool ok = row < rows;
-    n_g[r] = ok ? p.n[row] : 0;
-    L_g[r] = ok ? p.L[row] : 0;
-    br_adv_load(p.kv + row * p.Bs, p.rem + row * p.Bs, e0, ok ? p.Bs : 0, kv4[r], rem4[r]);
-    if constexpr (PK == 2) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) ch[r][k] = 0.0f, age[r][k] = 0.0f, since[r][k] = 0.0f;
-      if (ok && e0 < p.Bs) br_rows3_load(p.pred + (row * p.Bs + e0) * 3, ch[r], age[r], since[r]);
-    }
+    const int at = r * LPW + lane / LPL, list = min(at, lists - 1);
+    const bool ok = at < lists;
+    n_g[r] = ok ? br_seg_at<int>(b.n, 4u * (unsigned)list) : 0;
+    L_g[r] = ok ? br_seg_at<int>(b.L, 4u * (unsigned)list) : 0;
+    br_seg_load<LPL, PK>(b, p.Bs, list, ok ? p.Bs : 0, lane, v[r]);
   }
 #pragma unroll
   for (int r = 0; r < RW; ++r) {
-    const int64_t row = row0 + r * LPW + seg;
-    const bool ok = row < rows;
-    const int n = n_g[r];
-    int32_t *kw = p.kv + row * p.Bs, *rw = p.rem + row * p.Bs;
-    const int kv[4] = {kv4[r].x, kv4[r].y, kv4[r].z, kv4[r].w}, rem[4] = {rem4[r].x, rem4[r].y, rem4[r].z, rem4[r].w};
-    bool stay[4];
-    unsigned long long bs[4];
-    bool any_leave = false;
-    int kept = 0, lost = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const bool used = e0 + k < n;
-      stay[k] = used && rem[k] > t;
-      any_leave |= used && !stay[k];
-      lost += used && !stay[k] ? kv[k] : 0;
-      bs[k] = br_ballot(stay[k]);
-      kept += br_seg_count<LPL>(bs[k], lane);
-    }
-    if constexpr (PK == 2) br_refresh_update4(p, t, stay, ch[r], age[r], since[r], lds, lane);
-    const unsigned long long bl = br_ballot(any_leave);
-    int gone = 0;
-    if (bl == 0ull || br_seg_count<LPL>(bl, lane) == 0) {  // nothing leaves the lane's list: same positions, 16-byte stores
-      if (e0 < n) {
-        *reinterpret_cast<int4 *>(kw + e0) = make_int4(kv[0] + (stay[0] ? t : 0), kv[1] + (stay[1] ? t : 0),
-                                                        kv[2] + (stay[2] ? t : 0), kv[3] + (stay[3] ? t : 0));
-        *reinterpret_cast<int4 *>(rw + e0) = make_int4(rem[0] - (stay[0] ? t : 0), rem[1] - (stay[1] ? t : 0),
-                                                        rem[2] - (stay[2] ? t : 0), rem[3] - (stay[3] ? t : 0));
-        if constexpr (PK == 2) {  // rows beyond the list go back as they came
-          float *q = p.pred + (row * p.Bs + e0) * 3;
-          *reinterpret_cast<float4 *>(q) = make_float4(ch[r][0], age[r][0], since[r][0], ch[r][1]);
-          *reinterpret_cast<float4 *>(q + 4) = make_float4(age[r][1], since[r][1], ch[r][2], age[r][2]);
-          *reinterpret_cast<float4 *>(q + 8) = make_float4(since[r][2], ch[r][3], age[r][3], since[r][3]);
-        }
-      }
+    const int at = r * LPW + lane / LPL, list = min(at, lists - 1);
+    const bool ok = at < lists;
+    short *map = reinterpret_cast<short *>(lds + BR_SEG_LIST_WORDS);
+    BrSegPlan d;
+    br_seg_decide<LPL, PK>(p, t, n_g[r], lane, v[r], lds, map, d);
+    if (PK == 1 && d.any) {
+      br_with_row_unit(p.P, [&](auto unit, auto upr) {  // the rows are requested before anything is stored
+        using V = decltype(unit);
+        V q[4];
+        br_seg_rows_ask<LPL, decltype(upr)::value, V>(b.pred, p.Bs, p.P, list, d.from, n_g[r], lane, q);
+        br_seg_store<LPL, PK>(b, p.Bs, t, list, ok, L_g[r], lane, v[r], d, lds);
+        br_seg_rows_place<LPL, decltype(upr)::value, V>(b.pred, p.Bs, p.P, list, d.from, n_g[r], map, lane, q);
+      });
     } else {
-      int pos = 0;  // survivors in lower lanes, then the lane's own in order
-#pragma unroll
-      for (int k = 0; k < 4; ++k) pos += br_seg_below<LPL>(bs[k], lane);
-      int to[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        to[k] = stay[k] ? pos : -1;
-        pos += stay[k] ? 1 : 0;
-        if (stay[k]) {
-          kw[to[k]] = kv[k] + t;
-          rw[to[k]] = rem[k] - t;
-          if constexpr (PK == 2) {
-            float *q = p.pred + (row * p.Bs + to[k]) * 3;
-            q[0] = ch[r][k], q[1] = age[r][k], q[2] = since[r][k];
-          }
-        }
-      }
-      if constexpr (PK == 1)
-        *reinterpret_cast<short4 *>(reinterpret_cast<short *>(lds) + 4 * lane) =
-            make_short4((short)to[0], (short)to[1], (short)to[2], (short)to[3]);
+      br_seg_store<LPL, PK>(b, p.Bs, t, list, ok, L_g[r], lane, v[r], d, lds);
     }
-    if (bl != 0ull) {
-      gone = br_seg_sum<LPL>(lost);
-      if constexpr (PK == 1) {
-        br_wave_sync();
-        const short *map = reinterpret_cast<const short *>(lds);
-        int from = n;  // first slot whose row may move: the first leaver's group
-        if constexpr (LPL == 64) {
-          from = 4 * (int)__builtin_ctzll(bl);
-        } else {
-          const unsigned sl = br_seg_bits<LPL>(bl, lane);
-          if (sl != 0u) from = 4 * __builtin_ctz(sl);
-        }
-        float *pw = p.pred + row * p.Bs * p.P;
-        if ((p.P & 3) == 0)
-          br_seg_rows_move<float4, LPL>(pw, p.P, map, from, n, lane);
-        else if ((p.P & 1) == 0)
-          br_seg_rows_move<float2, LPL>(pw, p.P, map, from, n, lane);
-        else
-          br_seg_rows_move<float, LPL>(pw, p.P, map, from, n, lane);
-        br_wave_sync();  // the map is rewritten by the next lists
-      }
-    }
-    if (ok && lseg == 0) {
-      p.L[row] = L_g[r] + kept * t - gone;  // survivors gain t tokens each
-      p.n[row] = kept;
-    }
+    br_wave_sync();  // the words are rewritten by the next lists
   }
 }
 
