@@ -304,12 +304,13 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
     o.best_i = out->best_i;
   }
   BrParams p = ctx->p;
-  // Decode steps in the round's launch: BR-0 only, on the two waves per cluster of the split kernel where it serves, and on
+  // Decode steps in the round's launch: BR-0 on the two waves per cluster of the split kernel where it serves, and on
   // the wave that has routed the cluster for batches that fill the chip (4096 clusters, G = 16, B = 144: a step 42 us
-  // against 50 as two launches, 48 steps 111 against 122).  Everywhere else they follow as a launch of their own, which streams the lists with more loads in
-  // flight than the round's waves can hold (BR-H, H = 4, G = 16: 512 clusters 38 us against 46, 4096 clusters 78 against
-  // 76; one cluster, H = 8: 26 against 33; BR-0, 512 clusters with queues of 1024: 40 against 44).
-  const bool fused_adv = p.H == 0 && p.R_max <= 8 && (br_split_shape(p) || p.N >= BR_FULL_BATCH_N);
+  // against 50 as two launches, 48 steps 111 against 122); BR-H likewise (br_route_h_advances).  Everywhere else they follow
+  // as a launch of their own, which streams the lists with more loads in flight than the round's waves can hold (BR-H, H = 4,
+  // G = 16: 512 clusters 38 us against 46; one cluster, H = 8: 26 against 33; BR-0, 512 clusters with queues of 1024: 40
+  // against 44).
+  const bool fused_adv = p.H == 0 ? p.R_max <= 8 && (br_split_shape(p) || p.N >= BR_FULL_BATCH_N) : br_route_h_advances(p);
   const bool split_adv = adv_t > 0 && !fused_adv;
   p.adv_t = split_adv ? 0 : adv_t;
   int32_t rc = BR_OK;
@@ -342,7 +343,7 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
         br_launch_route_h_helped(p, a, o, ctx->st);
       else if (helped)
         br_launch_route_helped(p, a, o, ctx->st);
-      else if (together && p.H > 0)
+      else if (p.H > 0 && (together || p.adv_t > 0))
         br_launch_route_h(p, a, o, ctx->st);
       else if (together)
         br_launch_route(p, a, o, ctx->st);

@@ -866,7 +866,6 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
                                                int w = 0, int *split = nullptr,
                                                bool shared = false) {
   static_assert(!COOP || EM == 32, "the four-wave sort covers 4 x 512 keys");
-  static_assert(!ADV || HB == 0, "decode steps ride along with BR-0 rounds only");
   constexpr bool BRH = HB > 0;
   constexpr int NH = HB + 1;
   if (inst >= p.N) return;
@@ -1013,7 +1012,10 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
     }
     if (!done) {
       br_assign_epilogue<EM, BRH>(inst, lane, q0, qn, cnt, bound, st.Lh[0], st.nn, rc, c0, AHEAD ? &words : nullptr);
-      if constexpr (ADV) br_advance_cluster<8>(inst, lane, st.Lh[0], st.nn);
+      if constexpr (ADV && BRH)
+        br_advance_cluster_rows(inst, lane, st.Lh[0], st.nn, bound);
+      else if constexpr (ADV)
+        br_advance_cluster<8>(inst, lane, st.Lh[0], st.nn);
     }
   }
 }

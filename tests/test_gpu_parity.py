@@ -1091,6 +1091,38 @@ def test_large_batches_decode_orders(G, Q, steps):
     r.close()
 
 
+@pytest.mark.parametrize("G,B,Q,H,pred_mode,steps", [
+    (5, 60, 200, 4, 0, 1), (5, 64, 40, 8, 0, 7), (3, 65, 512, 4, 0, 40), (3, 128, 300, 3, 0, 9), (2, 129, 100, 8, 0, 12),
+    (2, 256, 256, 4, 0, 3), (9, 12, 64, 5, 1, 2), (3, 100, 256, 2, 0, 20), (4, 33, 300, 7, 3, 5), (2, 131, 60, 6, 0, 30),
+    (1, 50, 100, 4, 0, 2),
+])
+def test_large_batches_decode_with_prediction_rows(G, B, Q, H, pred_mode, steps):
+    """Batches beyond 2048 BR-H clusters with decode steps in the round's launch: every width of list and of prediction row
+    (whole 16-byte words or not), workers that lose nothing, something and everything, a last group of lists that is not full."""
+    N = 2051
+    cfg, init, arr = wl.random_case(1400 + B + H, N=N, G=G, B=B, max_wait=Q, H=H, fill=0.7, n_wait=Q // 3, pred_mode=pred_mode,
+                                    gate_pfin=0.3)
+    rng = np.random.default_rng(B + H)
+    arr.count[::7] = np.arange(len(arr.count[::7])) % 9
+    arr.o[:, ::3] = 1 + arr.o[:, ::3] % (2 * steps)
+    init.n[0, 0], init.n[1, G - 1] = 0, B
+    init.rem[1, G - 1] = 500
+    keep = rng.random((N, G, 1)) < 0.4                # lists that lose nothing for a while
+    init.rem[:] = np.where(keep & (init.rem > 0), init.rem + 3 * steps, init.rem)
+    init.kv[1, G - 1] = np.maximum(init.kv[1, G - 1], 1)
+    _say(f"decode with rows G={G} B={B} Q={Q} H={H} mode={pred_mode} steps={steps}")
+    oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
+    for rnd in range(3):
+        ref = oc.route_step(arr)
+        out = r.route_step(arr, matrix=False, scores=rnd != 1, advance=steps)
+        if rnd == 1:
+            ref = {k: v for k, v in ref.items() if k in out}
+        compare_outputs(ref, out, cfg, f"decode with rows r{rnd}")
+        oc.advance(steps)
+        compare_state(oc, r.state(), cfg, f"decode with rows r{rnd}")
+    r.close()
+
+
 def test_large_batch_appends_beyond_the_masks():
     """The same with workers that take more than 64 requests in a round (empty workers, short requests), some of which end
     within the steps: the append's bit masks do not hold them."""
