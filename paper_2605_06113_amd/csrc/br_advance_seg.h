@@ -133,10 +133,10 @@ __device__ __forceinline__ void br_seg_decide(const BrParams &p, int t, int n, i
   }
 }
 
-// The list as the plan leaves it, its load and its length.  lds: BR_SEG_WORDS(PK) less the map.
+// The list as the plan leaves it.  lds: BR_SEG_WORDS(PK) less the map.
 template <int LPL, int PK>
-__device__ __forceinline__ void br_seg_store(const BrSegBase &b, int Bs, int t, int list, bool ok, int L, int lane,
-                                             const BrSegSlots<PK> &v, const BrSegPlan &d, int *lds) {
+__device__ __forceinline__ void br_seg_store(const BrSegBase &b, int Bs, int list, int lane, const BrSegSlots<PK> &v,
+                                             const BrSegPlan &d, int *lds) {
   const int lseg = lane & (LPL - 1), e0 = 4 * lseg;
   const int kv[4] = {v.kv4.x, v.kv4.y, v.kv4.z, v.kv4.w}, rem[4] = {v.rem4.x, v.rem4.y, v.rem4.z, v.rem4.w};
   int *mine = lds + 4 * (lane - lseg);
@@ -160,7 +160,12 @@ __device__ __forceinline__ void br_seg_store(const BrSegBase &b, int Bs, int t, 
         br_seg_at<float4>(b.pred, 3u * at + 16u * c) = *reinterpret_cast<const float4 *>(rows + 12 * lane + 4 * c);
     }
   }
-  if (ok && lseg == LPL - 1) {
+}
+
+// Its load and its length.
+template <int LPL>
+__device__ __forceinline__ void br_seg_worker(const BrSegBase &b, int t, int list, bool ok, int L, int lane, const BrSegPlan &d) {
+  if (ok && (lane & (LPL - 1)) == LPL - 1) {
     br_seg_at<int>(b.L, 4u * (unsigned)list) = L + d.kept * t - d.gone;  // survivors gain t tokens each
     br_seg_at<int>(b.n, 4u * (unsigned)list) = d.kept;
   }
@@ -269,7 +274,8 @@ __device__ __forceinline__ void br_advance_lists(const BrParams &p, int t, int i
 #pragma unroll
     for (int r = 0; r < RW; ++r) {
       const int L = __builtin_amdgcn_ds_bpermute(list[r] << 2, Lcur);
-      br_seg_store<LPL, 1>(b, p.Bs, t, list[r], ok[r], L, lane, v[r], d[r], lds + r * BR_SEG_WORDS(1));
+      br_seg_store<LPL, 1>(b, p.Bs, list[r], lane, v[r], d[r], lds + r * BR_SEG_WORDS(1));
+      br_seg_worker<LPL>(b, t, list[r], ok[r], L, lane, d[r]);
     }
 #pragma unroll
     for (int r = 0; r < RW; ++r)
@@ -281,4 +287,44 @@ __device__ __forceinline__ void br_advance_lists(const BrParams &p, int t, int i
   bool ahead = false;
   for (int g0 = 0; g0 < p.G; g0 += RW * LPW)
     ahead = ahead ? batch(g0, std::true_type{}) : batch(g0, std::false_type{});
+}
+
+// The same for lists without prediction rows (BR-0; 4096 clusters, G = 16, B = 144, overloaded, a step per call: whole pass 46.9 us
+// with lists one by one through masked single-word stores, 41.5 so; 48 steps and 250 admissions 111.5 and 105.9), workers [g0, g1): `done` gets each list's worker, plan and the lane that
+// holds both whole.  lds: two turns of BR_SEG_WORDS(0) of the wave's.
+template <int LPL, int RW, class F>
+__device__ __forceinline__ void br_advance_lists_plain(const BrParams &p, int t, const BrSegBase &b, int lane, int g0, int g1,
+                                                       int nn, int *lds, F &&done) {
+  constexpr int LPW = BR_WAVE / LPL;
+  for (; g0 < g1; g0 += RW * LPW) {
+    BrSegSlots<0> v[RW];
+    int n[RW], list[RW];
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+      const int g = g0 + r * LPW + lane / LPL;
+      list[r] = min(g, g1 - 1);
+      n[r] = __builtin_amdgcn_ds_bpermute(list[r] << 2, nn);
+      n[r] = g < g1 ? n[r] : 0;
+      br_seg_load<LPL, 0>(b, p.Bs, list[r], n[r], lane, v[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+      int *words = lds + (r & 1) * BR_SEG_WORDS(0);
+      BrSegPlan d;
+      br_seg_decide<LPL, 0>(p, t, n[r], lane, v[r], words, nullptr, d);
+      br_seg_store<LPL, 0>(b, p.Bs, list[r], lane, v[r], d, words);
+      done(list[r], d, g0 + r * LPW + lane / LPL < g1 && (lane & (LPL - 1)) == LPL - 1);
+    }
+    br_wave_sync();
+  }
+}
+template <class F>
+__device__ __forceinline__ void br_advance_lists_any(const BrParams &p, int t, const BrSegBase &b, int lane, int g0, int g1, int nn,
+                                                     int *lds, F &&done) {
+  if (p.Bs <= 64)
+    br_advance_lists_plain<16, 2>(p, t, b, lane, g0, g1, nn, lds, done);
+  else if (p.Bs <= 128)
+    br_advance_lists_plain<32, 4>(p, t, b, lane, g0, g1, nn, lds, done);
+  else
+    br_advance_lists_plain<64, 8>(p, t, b, lane, g0, g1, nn, lds, done);
 }

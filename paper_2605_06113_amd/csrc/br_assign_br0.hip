@@ -19,13 +19,13 @@ template <int E, bool ADV>
 __global__ __launch_bounds__(256) void br_k_route(BrParams p, BrArr a, BrOut o) {
   extern __shared__ int lds_all[];
   constexpr bool MIX = ADV && E <= 8;
-  constexpr int WORDS = BR_ROUND_WORDS(E, false) + (MIX ? BR_SPLIT_WORDS : 0);
+  constexpr int ROUND = ADV ? BR_ROUND_ADV_WORDS(E) : BR_ROUND_WORDS(E, false), WORDS = ROUND + (MIX ? BR_SPLIT_WORDS : 0);
   const int w = threadIdx.x >> 6, b = (int)blockIdx.x, inst = b * (int)(blockDim.x >> 6) + w;
   int *lds = lds_all + w * WORDS, *split = nullptr;
   if (MIX && p.adv_t <= 8 && ((b + (b >> 8) + w) & 1) && inst < p.N) {  // (blocks 256 apart share a CU: both orders on every SIMD)
-    split = lds + BR_ROUND_WORDS(E, false);
+    split = lds + ROUND;
     if (br_lane() == 0) split[1] = 1;  // (no other wave reads this cluster)
-    br_split_advance<8>(p, inst, br_lane(), split);
+    br_split_advance<8>(p, inst, br_lane(), split, lds);
   }
   br_assign_body<E, 0, ADV, false, false, true>(p, a, o, lds, inst, 0, split);
 }
@@ -34,7 +34,7 @@ template <int E>
 static void launch_route(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
   const int wpb = br_clusters_per_block(p.N, E);
   const bool adv = p.adv_t > 0;
-  const size_t lds = (size_t)wpb * (BR_ROUND_WORDS(E, false) + (adv && E <= 8 ? BR_SPLIT_WORDS : 0)) * sizeof(int);
+  const size_t lds = (size_t)wpb * (adv ? BR_ROUND_ADV_WORDS(E) + (E <= 8 ? BR_SPLIT_WORDS : 0) : BR_ROUND_WORDS(E, false)) * sizeof(int);
   const dim3 grid((unsigned)((p.N + wpb - 1) / wpb)), block(BR_WAVE * wpb);
   if (adv)
     hipLaunchKernelGGL((br_k_route<E, true>), grid, block, lds, st, p, a, o);

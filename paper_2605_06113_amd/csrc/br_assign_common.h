@@ -349,19 +349,37 @@ __device__ __forceinline__ BrOut br_late_out() {
   return o;
 }
 
-// Decode advance of one BR-0 cluster by the wave that has just routed it: br_adv_apply (the arithmetic of
-// the stand-alone advance kernel) over the cluster's G lists in (list, 256-slot chunk) units, UB units
-// requested before the first is used.  `Lcur`, `nn`: load and list length of worker `lane` after the round.
-// STORE = false: loads and counts are not stored; lane g returns its list's load change in `dL_out` and its new
-// length in `n_out` instead (the split kernels, where another wave owns the workers' final state).
+// Decode steps of one BR-0 cluster by the wave that has just routed it.  `Lcur`, `nn`: load and list length of worker `lane`
+// after the round; lists [g0, g1) are this wave's; lds: BR_PLAIN_WORDS of the wave's.
+// STORE = false: loads and counts are not stored; what list g loses and its load change go to split[4 + g] and
+// split[4 + 64 + g] instead (the split kernels, where another wave owns the workers' final state).
+#define BR_PLAIN_WORDS (2 * BR_SEG_WORDS(0))
 template <int UB, bool STORE = true>
-__device__ __forceinline__ void br_advance_cluster(int inst, int lane, int Lcur, int nn, int g0 = 0, int g1 = 64,
-                                                   int *dL_out = nullptr, int *n_out = nullptr) {
+__device__ __forceinline__ void br_advance_cluster(int inst, int lane, int Lcur, int nn, int *lds, int g0 = 0, int g1 = 64,
+                                                   int *split = nullptr) {
   const BrParams p = br_late_params();
   const int t = p.adv_t;
   br_wave_sync();  // the round's own writes into the lists are read back below
-  const int G = min(p.G, g1), NC = (p.Bs + 255) >> 8, U = max(G - g0, 0) * NC;  // lists [g0, G) are this wave's
+  const int G = min(p.G, g1);
   const int64_t row0 = (int64_t)__builtin_amdgcn_readfirstlane(inst) * p.G;  // scalar: list bases stay in SGPRs
+  if (p.Bs <= 256) {
+    const BrSegBase b = br_seg_base(p, row0);
+    br_advance_lists_any(p, t, b, lane, g0, G, nn, lds, [&](int g, const BrSegPlan &d, bool whole) {
+      if constexpr (STORE) {
+        const int L = __builtin_amdgcn_ds_bpermute(g << 2, Lcur);
+        if (whole) {
+          br_seg_at<int>(b.L, 4u * (unsigned)g) = L + d.kept * t - d.gone;
+          br_seg_at<int>(b.n, 4u * (unsigned)g) = d.kept;
+        }
+      } else {
+        const int n = __builtin_amdgcn_ds_bpermute(g << 2, nn);
+        if (whole) split[4 + g] = n - d.kept, split[4 + BR_WAVE + g] = d.kept * t - d.gone;
+      }
+    });
+    return;
+  }
+  // longer lists: br_adv_apply over (list, 256-slot chunk) units, UB units requested before the first is used
+  const int NC = (p.Bs + 255) >> 8, U = max(G - g0, 0) * NC;
   const int64_t rowa = row0 + g0;
   int dLw = 0, nw = nn;     // lane g: load change and new length of worker g
   int kept = 0, gone = 0;   // running state of the list in progress: survivors, kv that left
@@ -398,8 +416,8 @@ __device__ __forceinline__ void br_advance_cluster(int inst, int lane, int Lcur,
       p.n[row0 + lane] = nw;
     }
   } else {
-    *dL_out = dLw;
-    *n_out = nw;
+    split[4 + lane] = nn - nw;
+    split[4 + BR_WAVE + lane] = dLw;
   }
 }
 
@@ -432,15 +450,13 @@ __device__ __forceinline__ void br_advance_cluster_rows(int inst, int lane, int 
 #define BR_SPLIT_WORDS 132
 
 // The decode steps of a cluster's lists as they stand, what they lost and by how much their loads change, then the flag.
+// lds: BR_PLAIN_WORDS of the wave's.
 template <int UB>
-__device__ __forceinline__ void br_split_advance(const BrParams &p, int inst, int lane, int *split) {
+__device__ __forceinline__ void br_split_advance(const BrParams &p, int inst, int lane, int *split, int *lds) {
   const bool act = lane < p.G;
   const int n_raw = p.n[(int64_t)inst * p.G + (act ? lane : 0)];
   const int n0 = act ? min(max(n_raw, 0), p.B) : 0;
-  int dL = 0, kept = n0;
-  br_advance_cluster<UB, false>(inst, lane, 0, n0, 0, 64, &dL, &kept);
-  split[4 + lane] = n0 - kept;
-  split[4 + BR_WAVE + lane] = dL;
+  br_advance_cluster<UB, false>(inst, lane, 0, n0, lds, 0, 64, split);
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // the lists are in place before the flag is seen
   __builtin_amdgcn_wave_barrier();
   if (lane == 0) split[0] = 1;

@@ -54,6 +54,9 @@
 // table (BIGR), then the mailbox of shared subset searches and the bit rows of br_subset_dp.h where they are used
 #define BR_SEARCH_WORDS 1344
 #define BR_ROUND_WORDS(EM, BIGR) ((EM) * BR_WAVE + BR_LIST_WORDS(EM) + BR_WAVE + ((BIGR) ? 32 + BR_SEARCH_WORDS : 0))
+// the same where the wave goes on to apply decode steps to its cluster's lists
+#define BR_ROUND_ADV_WORDS(EM) (BR_ROUND_WORDS(EM, false) > BR_PLAIN_WORDS ? BR_ROUND_WORDS(EM, false) : BR_PLAIN_WORDS)
+static_assert(BR_ROUND_WORDS(32, false) + BR_LIST_WORDS(32) >= 4 * BR_PLAIN_WORDS, "four waves share the lists' LDS");
 static_assert(BR_SEARCH_WORDS >= BR_HALVES_WORDS && BR_SEARCH_WORDS >= 1024, "LDS of a subset search");
 
 // Trips of 256 masks from which a block's four waves share a search: fewer are not worth two barriers.
@@ -997,7 +1000,7 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
     br_assign_epilogue_block4<BRH>(inst, lane, w, q0, qn, cnt, bound, slots, lst, Lw, st.nn, rc, c0, ADV);
     if constexpr (ADV) {
       const int per = (G + 3) >> 2;
-      br_advance_cluster<8>(inst, lane, Lw, st.nn, min(w * per, G), min(w * per + per, G));
+      br_advance_cluster<8>(inst, lane, Lw, st.nn, lds + w * BR_PLAIN_WORDS, min(w * per, G), min(w * per + per, G));
     }
   } else {
     bool done = false;
@@ -1015,7 +1018,7 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
       if constexpr (ADV && BRH)
         br_advance_cluster_rows(inst, lane, st.Lh[0], st.nn, bound);
       else if constexpr (ADV)
-        br_advance_cluster<8>(inst, lane, st.Lh[0], st.nn);
+        br_advance_cluster<8>(inst, lane, st.Lh[0], st.nn, lds);
     }
   }
 }
@@ -1029,7 +1032,7 @@ template <int E, int HB, bool ADV, bool BIGR = false>
 // `share` (BIGR, queues of up to 1024): one cluster per block, its four waves share the subset scans
 __global__ __launch_bounds__(256, (HB > 0 && E == 8 && !BIGR) ? 4 : 1) void br_k_assign(BrParams p, BrArr a, BrOut o, int share) {
   extern __shared__ int lds_all[];
-  constexpr int WORDS = BR_ROUND_WORDS(E, BIGR);
+  constexpr int WORDS = ADV ? BR_ROUND_ADV_WORDS(E) : BR_ROUND_WORDS(E, BIGR);
   const int w = threadIdx.x >> 6;
   if constexpr (E == 32)  // one cluster per block, four waves for the sort
     br_assign_body<E, HB, ADV, true, BIGR>(p, a, o, lds_all, (int)blockIdx.x, w);
@@ -1074,7 +1077,9 @@ template <int E, int HB, bool BIGR = false>
 static void br_launch_assign_one(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
   const bool dp = BIGR && p.R_max > 16;   // windows beyond 16 requests: one cluster per block, with LDS for the bit rows
   const int wpb = dp ? 1 : br_clusters_per_block(p.N, E);
-  const size_t lds = ((size_t)wpb * BR_ROUND_WORDS(E, BIGR) + (dp ? BR_DP_LDS_WORDS : 0) + (E == 32 ? BR_LIST_WORDS(32) : 0)) * sizeof(int);
+  const bool adv = HB == 0 && !BIGR && p.adv_t > 0;
+  const size_t lds = ((size_t)wpb * (adv ? BR_ROUND_ADV_WORDS(E) : BR_ROUND_WORDS(E, BIGR)) + (dp ? BR_DP_LDS_WORDS : 0) +
+                      (E == 32 ? BR_LIST_WORDS(32) : 0)) * sizeof(int);
   const dim3 grid((unsigned)((p.N + wpb - 1) / wpb)), block(E == 32 ? 4 * BR_WAVE : BR_WAVE * wpb);
   // (decode steps ride along for BR-0 with windows of up to 8 requests only; elsewhere the caller launches the decode kernel)
   if constexpr (BIGR) {
@@ -1096,7 +1101,7 @@ static void br_launch_assign_one(const BrParams &p, const BrArr &a, const BrOut 
   } else if constexpr (HB > 0) {
     hipLaunchKernelGGL((br_k_assign<E, HB, false>), grid, block, lds, st, p, a, o, 0);
   } else {
-    if (p.adv_t > 0)
+    if (adv)
       hipLaunchKernelGGL((br_k_assign<E, HB, true>), grid, block, lds, st, p, a, o, 0);
     else
       hipLaunchKernelGGL((br_k_assign<E, HB, false>), grid, block, lds, st, p, a, o, 0);

@@ -18,9 +18,9 @@ __global__ __launch_bounds__((THIRD ? 3 : 2) * BR_WAVE) void br_k_route_split(Br
   if (w == 0) {
     br_assign_body<E, 0, false, false, false, false, false, true>(p, a, o, lds_all, inst, 0, split);
   } else if (!THIRD || w == 1) {
-    br_split_advance<8>(p, inst, lane, split);
+    br_split_advance<8>(p, inst, lane, split, split + BR_SPLIT_WORDS);
   } else if constexpr (THIRD) {
-    br_snapshot_helper<E, 0>(p, a, o, inst, lane, 0, 1, recip_g, split + BR_SPLIT_WORDS);
+    br_snapshot_helper<E, 0>(p, a, o, inst, lane, 0, 1, recip_g, split + BR_SPLIT_WORDS + BR_PLAIN_WORDS);
     __builtin_amdgcn_s_waitcnt(0);  // every read has returned before the flag is seen
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_wave_barrier();
@@ -30,7 +30,7 @@ __global__ __launch_bounds__((THIRD ? 3 : 2) * BR_WAVE) void br_k_route_split(Br
 
 template <int E, bool THIRD>
 static void launch_split_waves(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
-  const size_t lds = (BR_ROUND_WORDS(E, false) + BR_SPLIT_WORDS + (THIRD ? BR_LIST_WORDS(E) + 2 * BR_WAVE : 0)) * sizeof(int);
+  const size_t lds = (BR_ROUND_WORDS(E, false) + BR_SPLIT_WORDS + BR_PLAIN_WORDS + (THIRD ? BR_LIST_WORDS(E) + 2 * BR_WAVE : 0)) * sizeof(int);
   hipLaunchKernelGGL((br_k_route_split<E, THIRD>), dim3((unsigned)p.N), dim3(BR_WAVE * (THIRD ? 3 : 2)), lds, st, p, a, o, br_recip(p.G));
 }
 

@@ -91,12 +91,13 @@ __global__ __launch_bounds__(256) void br_k_advance_seg(BrParams p, int t) {
         using V = decltype(unit);
         V q[4];
         br_seg_rows_ask<LPL, decltype(upr)::value, V>(b.pred, p.Bs, p.P, list, d.from, n_g[r], lane, q);
-        br_seg_store<LPL, PK>(b, p.Bs, t, list, ok, L_g[r], lane, v[r], d, lds);
+        br_seg_store<LPL, PK>(b, p.Bs, list, lane, v[r], d, lds);
         br_seg_rows_place<LPL, decltype(upr)::value, V>(b.pred, p.Bs, p.P, list, d.from, n_g[r], map, lane, q);
       });
     } else {
-      br_seg_store<LPL, PK>(b, p.Bs, t, list, ok, L_g[r], lane, v[r], d, lds);
+      br_seg_store<LPL, PK>(b, p.Bs, list, lane, v[r], d, lds);
     }
+    br_seg_worker<LPL>(b, t, list, ok, L_g[r], lane, d);
     br_wave_sync();  // the words are rewritten by the next lists
   }
 }
