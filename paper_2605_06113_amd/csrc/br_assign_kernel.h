@@ -46,6 +46,7 @@
 #include "br_sort.h"
 #include "br_assign_common.h"
 #include "br_subset_dp.h"
+#include "br_subset_few.h"
 #include "br_subset_halves.h"
 #include "br_subset_list.h"
 #include "br_score_wave.h"
@@ -57,12 +58,12 @@
 // the same where the wave goes on to apply decode steps to its cluster's lists
 #define BR_ROUND_ADV_WORDS(EM) (BR_ROUND_WORDS(EM, false) > BR_PLAIN_WORDS ? BR_ROUND_WORDS(EM, false) : BR_PLAIN_WORDS)
 static_assert(BR_ROUND_WORDS(32, false) + BR_LIST_WORDS(32) >= 4 * BR_PLAIN_WORDS, "four waves share the lists' LDS");
-static_assert(BR_SEARCH_WORDS >= BR_HALVES_WORDS && BR_SEARCH_WORDS >= 1024, "LDS of a subset search");
+static_assert(BR_SEARCH_WORDS >= BR_HALVES_WORDS && BR_SEARCH_WORDS >= BR_FEW_WORDS && BR_SEARCH_WORDS >= 1024, "LDS of a subset search");
 
 // Trips of 256 masks from which a block's four waves share a search: fewer are not worth two barriers.
 #define BR_SHARE_TRIPS 4
-// BR-0: trips from which the sums of the window's halves decide instead (br_subset_halves.h: about 5800 cycles at kmax = 4
-// and 200 more per request beyond; a trip is 350 to 600 cycles on one wave).
+// BR-0, limits beyond BR_FEW_MAX: trips from which the sums of the window's halves decide instead (br_subset_halves.h: about
+// 6300 cycles at kmax = 6 and 200 more per request beyond; a trip is 350 to 600 cycles on one wave).
 #define BR_HALVES_TRIPS 6
 
 // Subset search of a window of up to 16 requests (Stage 2, BIGR), this wave's share of it: the best key and its lowest
@@ -706,10 +707,12 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
           const bool listed = br_list_serves(w, kmax);
           const int trips = ((listed ? br_list_size(w, kmax) : 1 << w) + 255) >> 8;  // of 256 masks each
           const bool halves = !BRH && trips >= BR_HALVES_TRIPS;
-          if (kmax <= 3) {
+          if (!BRH && br_few_serves(w, kmax)) {
+            br_subset_few(G, mg[0], win, w, kmax, room, lane, hitab, bestkey, bestmask);
+          } else if (kmax <= 3) {
             int mbest;
             br_wave_sync();
-            br_small_search(win, w, kmax, room, lane, score4, bestkey, mbest);
+            br_small_search<BRH>(win, w, kmax, room, lane, score4, bestkey, mbest);
             bestmask = bestkey == BR_KEY_NONE ? 0u : (unsigned)mbest;
           } else if (halves) {
             br_subset_halves(G, mg[0], win, w, kmax, room, lane, hitab, bestkey, bestmask);

@@ -6,9 +6,10 @@
 // takes four of the 256 subsets of the others and looks up, in the list of what the limit leaves, the neighbours of
 // what the margin leaves: 9 steps of one LDS read each, all four side by side.  The mask is the lowest one that has
 // the chosen sum: lowest upper byte, then lowest lower byte.
-// About 600 instructions on one wave at any limit, no memory beyond LDS: 5800 cycles at kmax = 4 and 6300 at 6, a chain of
-// LDS and DPP latencies (sort 1700, lists 900, search 1300).  The list of masks (br_subset_list.h) has 2516 of them at
-// kmax = 4 (5200 cycles on four waves), 14892 at 6 (15000) and needs the scan of all 65536 beyond half of the window.
+// About 600 instructions on one wave at any limit, no memory beyond LDS: 6300 cycles at kmax = 6, a chain of
+// LDS and DPP latencies (sort 1700, lists 900, search 1300).  The list of masks (br_subset_list.h) has 14892 of them at
+// kmax = 6 (15000 cycles on four waves) and needs the scan of all 65536 beyond half of the window.  Limits of 3 to 5 form every
+// sum (br_subset_few.h).
 #pragma once
 
 #include "br_list.h"

@@ -3,8 +3,8 @@
 //
 // Stage 2 runs where free slots are scarce, so the limit kmax = min(free slots of the worker, R_max) is usually a few:
 // of the 65535 masks of a window of 16, 696 have at most three bits.  Those need neither masks nor tables
-// (br_small_search); beyond, BR-0 decides by the sums of the window's halves (br_subset_halves.h) and the list serves
-// BR-H and short walks.  Within one bit count the masks below 2^w are the
+// (br_small_search); BR-0 forms every sum at limits of 3 to 5 (br_subset_few.h) and decides by the sums of the window's
+// halves beyond (br_subset_halves.h), so the list serves BR-H and short walks.  Within one bit count the masks below 2^w are the
 // first C(w, c) of their section, so any window width reads a dense piece of the list.  A mask's sum is two reads of
 // tables over its lower and upper byte that the wave builds per pop (256 words each, in LDS).  About 16 instructions
 // per 64 masks against 11 of the scan over all masks (br_bigr_scan), which therefore stays for kmax > w / 2 (at 8 of 16
@@ -153,11 +153,11 @@ static __device__ constexpr BrTriples br_triples = br_make_triples();
 
 // The search at kmax <= 3, windows of up to 16: single requests, pairs and triples read the window itself, without tables.
 // Lane (g, i) of 4 x 16 takes the pairs of i with 4g .. 4g + 3 (i with itself: the single request); triples come from
-// a list, on its way meanwhile.  A search of up to 136 / 696 subsets took 2300 / 3500 cycles by tables
+// a list, on its way meanwhile (TRIPLES: BR-H).  A search of up to 136 / 696 subsets took 2300 / 3500 cycles by tables
 // and mask list.
-template <class Score>
+template <bool TRIPLES, class Score>
 __device__ __forceinline__ void br_small_search(const int *win, int w, int kmax, int room, int lane, Score score, int &bk, int &bm) {
-  const int n3 = kmax >= 3 ? br_mask_counts.at[w][3] : 0;
+  const int n3 = TRIPLES && kmax >= 3 ? br_mask_counts.at[w][3] : 0;
   unsigned e[3][4];
   if (n3 > 0) {
 #pragma unroll

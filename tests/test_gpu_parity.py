@@ -645,6 +645,20 @@ def test_window_halves(R_max, free, wm):
         r.close()
 
 
+@pytest.mark.parametrize("R_max,free,G,wm", [(9, 3, 1, 0), (9, 4, 5, 0), (10, 5, 64, 0), (12, 5, 5, 20000), (16, 3, 5, 0), (16, 4, 2, 30000),
+                                             (16, 5, 16, 0), (16, 6, 5, 0), (20, 5, 5, 0)])
+def test_window_every_sum(R_max, free, G, wm):
+    """BR-0 windows at limits of 3 to 5 requests, where every sum is formed: windows down to the last requests, one worker and
+    64, watermarks on either side of the margin, ties between sums below and above it, the longest lengths."""
+    for tie, s_hi in [(False, 4096), (True, 4096), (False, 3), (False, 32768)]:
+        cfg, init, arr = wl.random_case(970 + R_max + free, N=4, G=G, B=24, max_wait=260, s_hi=s_hi, tie_heavy=tie, n_wait=min(4 * G * free, 250),
+                                        R_max=R_max, S_greedy=10 ** 6, fill=1.0, token_watermark=wm)
+        init.n[:] = cfg.B - free
+        _say(f"every sum: window {R_max}, free slots {free}, G {G}, watermark {wm}, ties {tie}, lengths to {s_hi}")
+        oc, r = run_pair(cfg, init, arr, tag=f"every sum {R_max} {free} {G}")
+        r.close()
+
+
 def test_wide_window_long_requests_reach_the_row_bound():
     """Windows of 32 requests with lengths up to 32768 and room for many per pop: subset sums beyond the length of
     the bit rows (131071) exist and are not candidates on either side; rows too long for LDS go to the workspace."""
