@@ -951,11 +951,11 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
     if (run && qn > 256) {  // same for every wave of the block
       unsigned x8[8];
       br_keys_load<8>(p, a, inst, q0, qn, w * 512, lane, x8);
-      br_sort_desc_block4(x8, lst, w, lane);
+      br_sort_desc_block4(x8, lst, w, lane, qn);
       // (every wave is past its last read of the exchange buffer: the block meets inside the sort after that)
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const int at = br_list_at<32>(w * 512 + j * BR_WAVE + lane);
+        const int at = br_list_at<32>(w * 512 + lane * 8 + j);
         lst[at] = (int)x8[j], lst2[at] = (int)x8[j];
       }
     }

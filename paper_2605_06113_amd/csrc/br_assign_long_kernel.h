@@ -361,25 +361,7 @@ __global__ __launch_bounds__(64 * (NW + XW), E == 4 && XW == 0 ? 4 : 1) void br_
     adm[i] = -1;
     who[i] = -1;
   }
-  if (run) {
-    if constexpr (E <= 8) {  // (256 keys: 1800 cycles, where the network of br_sort.h takes 8000)
-      if (qn <= BR_WAVE) {
-        unsigned x1[1] = {xk[0]};
-        br_list_sort<1>(x1, lane);
-        xk[0] = x1[0];
-      } else {
-        br_list_sort<E>(xk, lane);
-        br_list_store<E>(xk, skey, lane);
-        br_wave_sync();
-#pragma unroll
-        for (int j = 0; j < E; ++j) xk[j] = (unsigned)skey[j * BR_WAVE + lane];
-      }
-    } else {
-      int N2 = BR_WAVE;
-      while (N2 < qn) N2 <<= 1;
-      br_sort_desc<E>(xk, lane, N2);
-    }
-  }
+  if (run) br_sort_across<E>(xk, skey, lane, qn);
   int sv[E];
   unsigned alive = 0;
 #pragma unroll

@@ -1,118 +1,82 @@
-// In-register bitonic sort of one wavefront's E*64 keys, descending by position
-// pos = j*64 + lane (x[j] of lane l holds position j*64 + l).
+// Sorts of a waiting set beyond one list in registers (br_list.h): by the four waves of a block, and on one wave with the
+// result across the lanes.
 //
-// Compare-exchange partners that differ in a bit >= 64 sit in the same lane (two registers of
-// one lane: a min and a max, no data movement).  Partners 1 or 2 lanes apart come through a DPP
-// quad permute, 4 or 8 lanes apart through a pair of bank-masked DPP row shifts, 16 apart
-// through ds_swizzle and 32 apart through ds_bpermute; none of these touches LDS memory.
+// Both are the bitonic sort of br_list.h, whose positions lie lane * E + j: partners up to E positions apart are two registers
+// of one lane (a min and a max, or two med3), the others one DPP or permlane move and a med3.  With positions j * 64 + lane nearly
+// every stage is a move between lanes, some of them through LDS.  Whole pass, us, so laid out / as lists of no more registers than
+// hold the waiting set: one cluster, G = 64, H = 8, a queue of 2048 42.5 / 39.4, H = 0, 1500 27.0 / 24.4; H = 80 on one wave: a queue of
+// 2048 70.2 / 50.7, of 1024 40.2 / 32.5; 300 clusters, 1000 64.5 / 54.6; 100 clusters, 2048, 30 admissions each 168 / 131.
 #pragma once
 
-#include "br_device.h"
+#include <type_traits>
 
-template <int S>
-__device__ __forceinline__ unsigned br_xor_lane(unsigned x, int bperm_addr) {
-  if constexpr (S == 1) {
-    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, true);  // quad_perm [1,0,3,2]
-  } else if constexpr (S == 2) {
-    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, true);  // quad_perm [2,3,0,1]
-  } else if constexpr (S == 4) {
-    // lanes with bit 2 clear (banks 0,2) read lane+4, the others (banks 1,3) read lane-4
-    int y = __builtin_amdgcn_update_dpp(0, (int)x, 0x104, 0xF, 0x5, false);  // row_shl:4
-    y = __builtin_amdgcn_update_dpp(y, (int)x, 0x114, 0xF, 0xA, false);      // row_shr:4
-    return (unsigned)y;
-  } else if constexpr (S == 8) {
-    int y = __builtin_amdgcn_update_dpp(0, (int)x, 0x108, 0xF, 0x3, false);  // row_shl:8
-    y = __builtin_amdgcn_update_dpp(y, (int)x, 0x118, 0xF, 0xC, false);      // row_shr:8
-    return (unsigned)y;
-  } else if constexpr (S == 16) {
-    return (unsigned)__builtin_amdgcn_ds_swizzle((int)x, 0x401F);  // and 0x1f, or 0, xor 0x10
-  } else {
-    return (unsigned)__builtin_amdgcn_ds_bpermute(bperm_addr, (int)x);
-  }
-}
+#include "br_list.h"
 
-// One cross-lane stage (partner distance S < 64) of the merge of blocks of size K.
-template <int E, int K, int S>
-__device__ __forceinline__ void br_sort_lane_stage(unsigned (&x)[E], int lane, int n2) {
-  const int addr32 = (lane ^ 32) << 2;
-  const bool lower = (lane & S) == 0;
-  bool keep_max_lane = lower;  // K >= 64: direction is a per-register constant
-  if constexpr (K < 64) keep_max_lane = ((lane & K) == 0) == lower;
-#pragma unroll
-  for (int j = 0; j < E; ++j) {
-    if (j * 64 < n2) {
-      const unsigned y = br_xor_lane<S>(x[j], addr32);
-      const unsigned hi = max(x[j], y), lo = min(x[j], y);
-      bool keep_max = keep_max_lane;
-      if constexpr (K >= 64) keep_max = (((j * 64) & K) == 0) ? lower : !lower;
-      x[j] = keep_max ? hi : lo;
-    }
-  }
-}
-
-// One in-lane stage (partner distance S >= 64): registers j and j + S/64 of the same lane.
-template <int E, int K, int S>
-__device__ __forceinline__ void br_sort_reg_stage(unsigned (&x)[E], int n2) {
-  constexpr int JS = S / 64;
-#pragma unroll
-  for (int j = 0; j < E; ++j) {
-    if ((j & JS) == 0 && j + JS < E && (j + JS) * 64 < n2) {
-      const bool desc = ((j * 64) & K) == 0;
-      const unsigned hi = max(x[j], x[j + JS]), lo = min(x[j], x[j + JS]);
-      x[j] = desc ? hi : lo;
-      x[j + JS] = desc ? lo : hi;
-    }
-  }
-}
-
-template <int E, int K, int S>
-__device__ __forceinline__ void br_sort_merge(unsigned (&x)[E], int lane, int n2) {
-  if constexpr (S >= 64)
-    br_sort_reg_stage<E, K, S>(x, n2);
-  else
-    br_sort_lane_stage<E, K, S>(x, lane, n2);
-  if constexpr (S > 1) br_sort_merge<E, K, S / 2>(x, lane, n2);
-}
-
-template <int E, int K>
-__device__ __forceinline__ void br_sort_levels(unsigned (&x)[E], int lane, int n2) {
-  if constexpr (K > 2) br_sort_levels<E, K / 2>(x, lane, n2);
-  if (K <= n2) br_sort_merge<E, K, K / 2>(x, lane, n2);
-}
-
-// Sort the first n2 positions (n2 a power of two, 64 <= n2 <= E*64) in descending order.
-// Positions >= n2 must hold keys no larger than any key below n2 (they are left alone).
-template <int E>
-__device__ __forceinline__ void br_sort_desc(unsigned (&x)[E], int lane, int n2) {
-  br_sort_levels<E, E * 64>(x, lane, n2);
-}
-
-// Sort of up to 2048 keys by the four waves of a block, 512 per wave (8 registers per lane):
-// position = w*512 + j*64 + lane, descending over the whole block.  Each wave sorts its own 512, then
-// two merge levels follow.  A level starts by comparing the two sorted halves mirrored (element i of
-// the first with element n-1-i of the second, through `buf` in LDS); after that every element of the
-// first half is at least every element of the second and each half is bitonic, so halves are finished
-// by plain half-cleaners: across waves at distance 512 (same position in the partner wave), inside a
-// wave by the register and lane stages above.  Every wave of the block must call this (block barriers).
+// Sort of up to 2048 keys (the first qn; the others are zero) by the four waves of a block, 512 per wave (8 registers per lane):
+// position = w * 512 + lane * 8 + j, descending over the whole block.  Each wave sorts its own 512, then two merge levels follow
+// (none where fewer wait).  A level starts by comparing the two sorted halves mirrored (element i of the first with element
+// n-1-i of the second, through `buf` in LDS); after that every element of the first half is at least every element of the second
+// and each half is bitonic, so halves are finished by plain half-cleaners: across waves at distance 512 (same position in the
+// partner wave), inside a wave by the stages of a list.  Every wave of the block must call this with the same qn (block barriers).
 __device__ __forceinline__ void br_sort_block4_exchange(unsigned (&x)[8], int *buf, int w, int lane, int partner,
                                                         bool mirrored, bool keep_max) {
-#pragma unroll
-  for (int j = 0; j < 8; ++j) buf[w * 512 + j * 64 + lane] = (int)x[j];
+  int4 *mine = reinterpret_cast<int4 *>(buf + w * 512 + lane * 8);
+  mine[0] = make_int4((int)x[0], (int)x[1], (int)x[2], (int)x[3]);
+  mine[1] = make_int4((int)x[4], (int)x[5], (int)x[6], (int)x[7]);
   __syncthreads();
-  unsigned y[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j)
-    y[j] = (unsigned)(mirrored ? buf[partner * 512 + (7 - j) * 64 + (63 - lane)] : buf[partner * 512 + j * 64 + lane]);
+  const int4 *other = reinterpret_cast<const int4 *>(buf + partner * 512 + (mirrored ? 63 - lane : lane) * 8);
+  const int4 a = other[0], b = other[1];
   __syncthreads();
+  const int z[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
-  for (int j = 0; j < 8; ++j) x[j] = keep_max ? max(x[j], y[j]) : min(x[j], y[j]);
+  for (int j = 0; j < 8; ++j) {
+    const unsigned y = (unsigned)(mirrored ? z[7 - j] : z[j]);
+    x[j] = keep_max ? max(x[j], y) : min(x[j], y);
+  }
 }
 
-__device__ __forceinline__ void br_sort_desc_block4(unsigned (&x)[8], int *buf, int w, int lane) {
-  br_sort_desc<8>(x, lane, 512);
-  br_sort_block4_exchange(x, buf, w, lane, w ^ 1, true, (w & 1) == 0);   // pairs of waves: 1024 keys each
-  br_sort_merge<8, 512, 256>(x, lane, 512);
-  br_sort_block4_exchange(x, buf, w, lane, 3 - w, true, w < 2);          // all four: 2048 keys
-  br_sort_block4_exchange(x, buf, w, lane, w ^ 1, false, (w & 1) == 0);
-  br_sort_merge<8, 512, 256>(x, lane, 512);
+__device__ __forceinline__ void br_sort_desc_block4(unsigned (&x)[8], int *buf, int w, int lane, int qn) {
+  br_list_sort<8>(x, lane);
+  if (qn > 512) {
+    br_sort_block4_exchange(x, buf, w, lane, w ^ 1, true, (w & 1) == 0);   // pairs of waves: 1024 keys each
+    br_list_stage<8, 512, 256>(x, lane);
+  }
+  if (qn > 1024) {
+    br_sort_block4_exchange(x, buf, w, lane, 3 - w, true, w < 2);          // all four: 2048 keys
+    br_sort_block4_exchange(x, buf, w, lane, w ^ 1, false, (w & 1) == 0);
+    br_list_stage<8, 512, 256>(x, lane);
+  }
+}
+
+// Sort of E * 64 keys on one wave, the first qn of them not zero, descending by position j * 64 + lane: as a list of as many
+// registers as hold them, then through buf (E * 64 words of LDS).
+template <int E>
+__device__ __forceinline__ void br_sort_across(unsigned (&x)[E], int *buf, int lane, int qn) {
+  auto as_list = [&](auto n) {
+    constexpr int N = decltype(n)::value;
+    unsigned y[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) y[j] = x[j];
+    br_list_sort<N>(y, lane);
+    if constexpr (N == 1) {
+      x[0] = y[0];
+    } else {
+#pragma unroll
+      for (int j = 0; j < N; j += 4)
+        *reinterpret_cast<int4 *>(buf + lane * N + j) = make_int4((int)y[j], (int)y[j + 1], (int)y[j + 2], (int)y[j + 3]);
+      br_wave_sync();
+#pragma unroll
+      for (int j = 0; j < N; ++j) x[j] = (unsigned)buf[j * BR_WAVE + lane];
+    }
+  };
+  if (qn <= BR_WAVE)
+    as_list(std::integral_constant<int, 1>{});
+  else if (E == 4 || qn <= 4 * BR_WAVE)
+    as_list(std::integral_constant<int, 4>{});
+  else if (E == 8 || qn <= 8 * BR_WAVE)
+    as_list(std::integral_constant<int, E < 8 ? E : 8>{});
+  else if (E == 16 || qn <= 16 * BR_WAVE)
+    as_list(std::integral_constant<int, E < 16 ? E : 16>{});
+  else
+    as_list(std::integral_constant<int, E>{});
 }

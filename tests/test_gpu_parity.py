@@ -659,6 +659,20 @@ def test_window_every_sum(R_max, free, G, wm):
         r.close()
 
 
+@pytest.mark.parametrize("H,max_wait", [(0, 2048), (8, 2048), (40, 2048), (40, 1024), (40, 512)])
+def test_sorts_at_the_edges_of_their_sizes(H, max_wait):
+    """Waiting sets around the sizes from which a sort takes more registers or more waves of the block; equal lengths among them."""
+    for n_wait in (1, 64, 65, 256, 257, 512, 513, 1024, 1025, 1537, 2048):
+        if n_wait > max_wait:
+            break
+        for tie in (False, True):
+            kw = dict(pred_mode=1) if H else {}
+            cfg, init, arr = wl.random_case(990 + n_wait, N=2, G=5, B=12, max_wait=max_wait, H=H, tie_heavy=tie, n_wait=n_wait, fill=0.7, **kw)
+            _say(f"sort: H={H}, queue of {max_wait}, {n_wait} waiting, ties {tie}")
+            oc, r = run_pair(cfg, init, arr, tag=f"sort {H} {max_wait} {n_wait}")
+            r.close()
+
+
 def test_wide_window_long_requests_reach_the_row_bound():
     """Windows of 32 requests with lengths up to 32768 and room for many per pop: subset sums beyond the length of
     the bit rows (131071) exist and are not candidates on either side; rows too long for LDS go to the workspace."""
