@@ -974,8 +974,8 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
     auto with = [&](auto e) {
       constexpr int E = decltype(e)::value;
       unsigned x[E];
-      if constexpr (COOP && E == 32) {
-        br_list_load<32>(x, lst, lane, 0, qn);
+      if constexpr (COOP && E >= 16) {
+        br_list_load<E>(x, lst, lane, 0, qn);
       } else {
         br_list_build<E, HB, SCORES>(p, a, o, inst, lane, q0, qn, lst, st, x);
       }
@@ -986,6 +986,8 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
       with(std::integral_constant<int, 1>{});
     else if (EM == 4 || qn <= 4 * BR_WAVE)
       with(std::integral_constant<int, 4>{});
+    else if (COOP && qn <= 16 * BR_WAVE)
+      with(std::integral_constant<int, COOP ? 16 : EM>{});
     else if constexpr (EM > 4)
       with(std::integral_constant<int, EM>{});
   }
@@ -1117,7 +1119,7 @@ static void br_launch_assign_sized(const BrParams &p, const BrArr &a, const BrOu
     br_launch_assign_one<4, HB, BIGR>(p, a, o, st);
   else if (p.Q <= 512)
     br_launch_assign_one<8, HB, BIGR>(p, a, o, st);
-  else if (p.Q <= 1024)
+  else if (p.Q <= 1024 && (BIGR || !br_block_serves(p)))
     br_launch_assign_one<16, HB, BIGR>(p, a, o, st);
   else
     br_launch_assign_one<32, HB, BIGR>(p, a, o, st);

@@ -38,6 +38,18 @@ void br_launch_assign_bigr(const BrParams &p, const BrArr &a, const BrOut &o, hi
 void br_launch_assign_br0(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
 // BR-H, H <= 4
 void br_launch_assign_brh4(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
+// Queues of 513..1024, windows of up to 8: the round on a block of four waves per cluster, as beyond 1024 (sort and epilogue
+// shared; BR-0 reductions on the waves that wait), while every block is resident at once: registers leave three of these waves per
+// SIMD for BR-0, two for H > 4.  Whole pass, us, one wave and its helpers / so, G = 16, a queue of 1000, reductions asked for,
+// overloaded / under a watermark that keeps slots free everywhere / lightly loaded:
+//   H = 0   one cluster 17.7 / 11.5, 27.2 / 20.9    256: 25.6 / 19.0, 30.4 / 24.6    600: - , - , 22.3 / 15.1    768: 32.6 / 25.7, 38.7 / 31.0
+//           1024: 34.8 / 32.6, 41.9 / 48.0          2047: 47.4 / 51.0, 59.5 / 72.3
+//   H = 4   16 clusters 36.5 / 29.4, 45.2 / 39.0, 25.7 / 22.2    768: 59.3 / 51.9, 77.8 / 74.7, 30.5 / 27.1, with 700 arrivals 209 / 211
+//   H = 8   one cluster 33.4 / 28.1, 48.7 / 41.9, 24.0 / 22.1    512: 65.7 / 57.5, 128 / 118, 35.4 / 32.4, with 700 arrivals 394 / 363
+//           1024 without reductions: 62.2 / 66.4
+inline bool br_block_serves(const BrParams &p) {
+  return p.Q > 512 && p.Q <= 1024 && p.R_max <= 8 && p.H <= BR_HP && p.N <= (p.H > 0 ? 512 : 768);
+}
 // BR-0, Q <= 1024: snapshot reductions and assignment in one launch
 void br_launch_route(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
 // BR-H (H <= BR_HP), Q <= 512: the same in one launch

@@ -673,6 +673,20 @@ def test_sorts_at_the_edges_of_their_sizes(H, max_wait):
             r.close()
 
 
+@pytest.mark.parametrize("H,N", [(0, 2), (0, 768), (0, 769), (3, 2), (8, 512), (8, 513)])
+def test_queues_of_513_to_1024_on_both_sides_of_the_line(H, N):
+    """Up to a number of clusters a block of four waves runs the round: nothing, a few, just over half of it and all of the queue
+    waiting, one worker and several, matrix and reductions asked for, a watermark that leaves requests behind."""
+    for Q, G, R_max, wm in [(513, 3, 4, 0), (1024, 5, 8, 9000), (700, 1, 1, 0)]:
+        kw = dict(gate_pfin=0.3) if H else {}
+        cfg, init, arr = wl.random_case(930 + Q + H, N=N, G=G, B=6, max_wait=Q, H=H, R_max=R_max, fill=0.6, token_watermark=wm, **kw)
+        counts = [c for c in (0, 1, 64, 65, 256, 257, 512, 513, Q) if c <= Q]
+        arr.count[:] = np.resize(counts[::-1], N)
+        _say(f"queue of {Q}, N={N} G={G} H={H} R_max={R_max} W={wm}")
+        oc, r = run_pair(cfg, init, arr, tag=f"queue {Q} N={N} H={H}")
+        r.close()
+
+
 def test_wide_window_long_requests_reach_the_row_bound():
     """Windows of 32 requests with lengths up to 32768 and room for many per pop: subset sums beyond the length of
     the bit rows (131071) exist and are not candidates on either side; rows too long for LDS go to the workspace."""
