@@ -325,6 +325,8 @@ __device__ __forceinline__ void br_advance_lists_any(const BrParams &p, int t, c
     br_advance_lists_plain<16, 2>(p, t, b, lane, g0, g1, nn, lds, done);
   else if (p.Bs <= 128)
     br_advance_lists_plain<32, 4>(p, t, b, lane, g0, g1, nn, lds, done);
+  else if (g1 - g0 <= 4)
+    br_advance_lists_plain<64, 4>(p, t, b, lane, g0, g1, nn, lds, done);
   else
     br_advance_lists_plain<64, 8>(p, t, b, lane, g0, g1, nn, lds, done);
 }

@@ -120,7 +120,9 @@ __device__ __forceinline__ void br_bigr_scan(const BrParams &p, const int (&mg)[
 // The two stages on one wave.  x: the qn waiting requests as a sorted list.  bound [arrival position]: worker << 16 | slot
 // of the requests admitted (the others keep what is there).  lst, slots, win, hitab: LDS (see BR_ROUND_WORDS).
 // svc (BIGR, shared): mailbox of the block's other three waves, which serve the subset searches.
-template <int E, int HB, bool BIGR>
+// DP (BIGR, BR-0): windows of 17 to 32 as well, by reachable sums; a kernel of its own, which the searches of every sum stay out
+// of (3 clusters, G = 7, window 24, whole pass: 367 us, 376 with both in one).
+template <int E, int HB, bool BIGR, bool DP = false>
 __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, int qn, unsigned (&x)[E], int *bound, int *lst,
                                          int *slots, int *win, int *hitab, int *svc, int *dprows, bool shared,
                                          BrRoundState<HB> &st, BrRoundCounts &rc) {
@@ -694,7 +696,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
           }
           kmax = br_useful_count(sum, F, slack, w > 16 ? min(room, BR_DP_MAX_SUM) : room, kmax, lane);
         }
-        if (w > 16) {
+        if ((BRH || DP) && w > 16) {
           // windows of 17..32 requests: reachable sums instead of masks (br_subset_dp.h)
           br_subset_dp<BRH>(p, mg, win, w, kmax, room, lane, dprows,
                             p.dp + (size_t)inst * br_dp_cluster_words(min(p.B, p.R_max)), bestmask, bestkey,
@@ -707,15 +709,15 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
           const bool listed = br_list_serves(w, kmax);
           const int trips = ((listed ? br_list_size(w, kmax) : 1 << w) + 255) >> 8;  // of 256 masks each
           const bool halves = !BRH && trips >= BR_HALVES_TRIPS;
-          if (!BRH && br_few_serves(w, kmax)) {
+          if (!BRH && !DP && br_few_serves(w, kmax)) {
             br_subset_few(G, mg[0], win, w, kmax, room, lane, hitab, bestkey, bestmask);
           } else if (kmax <= 3) {
             int mbest;
             br_wave_sync();
-            br_small_search<BRH>(win, w, kmax, room, lane, score4, bestkey, mbest);
+            br_small_search<BRH || DP>(win, w, kmax, room, lane, score4, bestkey, mbest);
             bestmask = bestkey == BR_KEY_NONE ? 0u : (unsigned)mbest;
           } else if (halves) {
-            br_subset_halves(G, mg[0], win, w, kmax, room, lane, hitab, bestkey, bestmask);
+            br_subset_halves<!DP>(G, mg[0], win, w, kmax, room, lane, hitab, bestkey, bestmask);
           } else {
             if (!listed) {
               const int nhi = w > 6 ? 1 << (w - 6) : 1;
@@ -867,7 +869,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
 // in the kernel the words requested ahead of a queue of 257..512 went through 100 bytes of scratch memory per lane (2000 clusters,
 // G = 16, queues of 500: whole pass 31.0 us, 26.1 without; one cluster 12.5 and 11.8).
 template <int EM, int HB, bool ADV, bool COOP = false, bool BIGR = false, bool SCORES = false, bool HELPED = false,
-          bool SPLIT = false>
+          bool SPLIT = false, bool DP = false>
 __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a, const BrOut &o, int *lds, int inst,
                                                int w = 0, int *split = nullptr,
                                                bool shared = false) {
@@ -980,7 +982,7 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
         br_list_build<E, HB, SCORES>(p, a, o, inst, lane, q0, qn, lst, st, x);
       }
       br_wave_sync();
-      br_round<E, HB, BIGR>(p, inst, lane, qn, x, bound, lst, slots, win, hitab, svc, dprows, shared, st, rc);
+      br_round<E, HB, BIGR, DP>(p, inst, lane, qn, x, bound, lst, slots, win, hitab, svc, dprows, shared, st, rc);
     };
     if (qn <= BR_WAVE)
       with(std::integral_constant<int, 1>{});
@@ -1033,18 +1035,18 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
 // (a batch of 4096 clusters is four waves per SIMD): it is asked to fit.
 // BIGR: candidate windows of 9..16 requests (R_max > 8); a separate instantiation so that the kernels for
 // the deployed window sizes keep their registers and code size.
-template <int E, int HB, bool ADV, bool BIGR = false>
+template <int E, int HB, bool ADV, bool BIGR = false, bool DP = false>
 // `share` (BIGR, queues of up to 1024): one cluster per block, its four waves share the subset scans
 __global__ __launch_bounds__(256, (HB > 0 && E == 8 && !BIGR) ? 4 : 1) void br_k_assign(BrParams p, BrArr a, BrOut o, int share) {
   extern __shared__ int lds_all[];
   constexpr int WORDS = ADV ? BR_ROUND_ADV_WORDS(E) : BR_ROUND_WORDS(E, BIGR);
   const int w = threadIdx.x >> 6;
   if constexpr (E == 32)  // one cluster per block, four waves for the sort
-    br_assign_body<E, HB, ADV, true, BIGR>(p, a, o, lds_all, (int)blockIdx.x, w);
+    br_assign_body<E, HB, ADV, true, BIGR, false, false, false, DP>(p, a, o, lds_all, (int)blockIdx.x, w);
   else if (BIGR && share)
-    br_assign_body<E, HB, ADV, false, BIGR>(p, a, o, lds_all, (int)blockIdx.x, w, nullptr, true);
+    br_assign_body<E, HB, ADV, false, BIGR, false, false, false, DP>(p, a, o, lds_all, (int)blockIdx.x, w, nullptr, true);
   else
-    br_assign_body<E, HB, ADV, false, BIGR>(p, a, o, lds_all + w * WORDS, (int)(blockIdx.x * (blockDim.x >> 6)) + w);
+    br_assign_body<E, HB, ADV, false, BIGR, false, false, false, DP>(p, a, o, lds_all + w * WORDS, (int)(blockIdx.x * (blockDim.x >> 6)) + w);
 }
 
 // Small batches without decode steps in the launch: a block per cluster, its first wave runs the round, the others compute
@@ -1099,7 +1101,12 @@ static void br_launch_assign_one(const BrParams &p, const BrArr &a, const BrOut 
     const long long room = 1024ll * max(1, (E == 4 ? 4 : E == 8 ? 3 : 2) - (HB > 0 ? 1 : 0));
     if ((HB > 0 || dp) && E <= 16 && (long long)p.N * 4 <= room) {
       const size_t lds1 = ((size_t)BR_ROUND_WORDS(E, true) + 32 + (dp ? BR_DP_LDS_WORDS : 0)) * sizeof(int);
-      hipLaunchKernelGGL((br_k_assign<E, HB, false, true>), dim3((unsigned)p.N), dim3(4 * BR_WAVE), lds1, st, p, a, o, 1);
+      if (HB == 0)  // (reachable sums)
+        hipLaunchKernelGGL((br_k_assign<E, HB, false, true, HB == 0>), dim3((unsigned)p.N), dim3(4 * BR_WAVE), lds1, st, p, a, o, 1);
+      else
+        hipLaunchKernelGGL((br_k_assign<E, HB, false, true>), dim3((unsigned)p.N), dim3(4 * BR_WAVE), lds1, st, p, a, o, 1);
+    } else if (HB == 0 && dp) {
+      hipLaunchKernelGGL((br_k_assign<E, HB, false, true, HB == 0>), grid, block, lds, st, p, a, o, 0);
     } else {
       hipLaunchKernelGGL((br_k_assign<E, HB, false, true>), grid, block, lds, st, p, a, o, 0);
     }

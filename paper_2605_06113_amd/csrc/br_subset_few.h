@@ -11,7 +11,7 @@
 // requests leaves.  Where that leaves one request, seven upper subsets share a wave (9 lanes each), where it leaves none, 64.
 // 15 wave-wide sums at kmax = 3, 57 at 4 and 151 at 5 (696, 2516 and 6884 subsets).  Loops with few sums a turn wait for LDS at
 // every turn and are slower than what they replace, so this is straight code, one piece per kmax.
-// 1024 clusters, G = 16, 46 admissions in 18 pops each (limits of 1 to 7), whole pass: window 16 71 -> 64 us (before: triples
+// 1024 clusters, G = 16, 46 admissions in 18 pops each (limits of 1 to 7), whole pass: window 16 71 -> 60 us (before: triples
 // by a list at 3, the sums of the halves beyond), window 12 72 -> 64, window 9 (the list of masks) 69 -> 63.
 #pragma once
 
@@ -119,6 +119,7 @@ __device__ __forceinline__ void br_subset_few(int G, int m, const int *win, int 
                                               int &bestkey, unsigned &bestmask) {
   bestkey = BR_KEY_NONE, bestmask = 0u;
   if (room < 0) return;
+  br_stay(lane);
   const unsigned place = br_few_places.v[lane];
   int lo[4], hi[4];
   br_half_sums(win, w, BR_FEW_ABSENT, lane, lo, hi);

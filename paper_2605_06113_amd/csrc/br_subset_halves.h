@@ -37,8 +37,10 @@ constexpr BrHalvesLists br_make_halves_lists() {
 }
 static __device__ constexpr BrHalvesLists br_halves_lists = br_make_halves_lists();
 
+template <bool STAY>
 __device__ __forceinline__ void br_subset_halves(int G, int m, const int *win, int w, int kmax, int room, int lane, int *tab,
                                                  int &bestkey, unsigned &bestmask) {
+  if constexpr (STAY) br_stay(lane);
   const int lists = br_halves_lists.v[lane & 15];
   int lo[4], hi[4];
   br_half_sums(win, w, BR_HALVES_ABSENT, lane, lo, hi);

@@ -73,6 +73,11 @@ __device__ __forceinline__ bool br_list_serves(int w, int kmax) { return w > 8 &
 // number of non-empty subsets of w requests with at most kmax of them (kmax <= 8)
 __device__ __forceinline__ int br_list_size(int w, int kmax) { return br_mask_counts.upto[w][kmax]; }
 
+// What a search computes from the lane alone (its tables' loads among it) stays in the search: taken out of the loop over the
+// pops it holds registers throughout the round (BR-0, windows of up to 16, queues of up to 256: 220 of them, 154 so and with wider windows
+// in a kernel of their own: three waves per SIMD instead of two; 3000 clusters, window 16, whole pass 143 -> 89 us).
+__device__ __forceinline__ void br_stay(int &lane) { asm volatile("" : "+v"(lane)); }
+
 // Sum of the lane + 1 smallest entries of a window of up to 32 requests (sorted, longest first), for lanes below w.
 __device__ __forceinline__ int br_min_sums(const int *win, int w, int lane) {
   int x = lane < w ? win[max(w - 1 - lane, 0)] >> BR_IDX_BITS : 0;
@@ -157,6 +162,7 @@ static __device__ constexpr BrTriples br_triples = br_make_triples();
 // and mask list.
 template <bool TRIPLES, class Score>
 __device__ __forceinline__ void br_small_search(const int *win, int w, int kmax, int room, int lane, Score score, int &bk, int &bm) {
+  if constexpr (!TRIPLES) br_stay(lane);
   const int n3 = TRIPLES && kmax >= 3 ? br_mask_counts.at[w][3] : 0;
   unsigned e[3][4];
   if (n3 > 0) {
