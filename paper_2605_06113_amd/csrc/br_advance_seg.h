@@ -296,14 +296,18 @@ template <int LPL, int RW, class F>
 __device__ __forceinline__ void br_advance_lists_plain(const BrParams &p, int t, const BrSegBase &b, int lane, int g0, int g1,
                                                        int nn, int *lds, F &&done) {
   constexpr int LPW = BR_WAVE / LPL;
+  // a list per wave, four at a time: number and length of the list are the wave's, not the lanes' (one cluster, G = 64, lists of 144
+  // slots: whole pass 28.3 us, 29.0 without; eight at a time the kernel would get by with five waves per SIMD instead of four,
+  // which batches of several times that size are slower with: 8192 clusters 94.1 us, 91.8 without)
+  constexpr bool WHOLE = LPL == BR_WAVE && RW <= 4;
   for (; g0 < g1; g0 += RW * LPW) {
     BrSegSlots<0> v[RW];
     int n[RW], list[RW];
 #pragma unroll
     for (int r = 0; r < RW; ++r) {
-      const int g = g0 + r * LPW + lane / LPL;
+      const int g = g0 + r * LPW + (WHOLE ? 0 : lane / LPL);
       list[r] = min(g, g1 - 1);
-      n[r] = __builtin_amdgcn_ds_bpermute(list[r] << 2, nn);
+      n[r] = WHOLE ? __builtin_amdgcn_readlane(nn, list[r]) : __builtin_amdgcn_ds_bpermute(list[r] << 2, nn);
       n[r] = g < g1 ? n[r] : 0;
       br_seg_load<LPL, 0>(b, p.Bs, list[r], n[r], lane, v[r]);
     }
@@ -318,15 +322,17 @@ __device__ __forceinline__ void br_advance_lists_plain(const BrParams &p, int t,
     br_wave_sync();
   }
 }
-template <class F>
+// LONG: lists beyond 128 slots taken at a time: 8 for what one cluster alone takes, 4 where the registers that eight hold (some
+// 20) would cost waves that a batch needs (br_k_route_split, br_k_route).
+template <int LONG, class F>
 __device__ __forceinline__ void br_advance_lists_any(const BrParams &p, int t, const BrSegBase &b, int lane, int g0, int g1, int nn,
                                                      int *lds, F &&done) {
   if (p.Bs <= 64)
     br_advance_lists_plain<16, 2>(p, t, b, lane, g0, g1, nn, lds, done);
   else if (p.Bs <= 128)
     br_advance_lists_plain<32, 4>(p, t, b, lane, g0, g1, nn, lds, done);
-  else if (g1 - g0 <= 4)
+  else if (LONG <= 4 || g1 - g0 <= 4)
     br_advance_lists_plain<64, 4>(p, t, b, lane, g0, g1, nn, lds, done);
   else
-    br_advance_lists_plain<64, 8>(p, t, b, lane, g0, g1, nn, lds, done);
+    br_advance_lists_plain<64, LONG>(p, t, b, lane, g0, g1, nn, lds, done);
 }

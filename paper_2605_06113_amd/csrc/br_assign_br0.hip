@@ -15,17 +15,25 @@
 //   4096 clusters, G =  8, B = 64     1 step 22 / 23   4: 31 / 32    8: 40 / 40     16: 52 / 53     48: 69 / 68
 //   4096 clusters, G = 32, B = 96     1 step 62 / 64   4: 95 / 95    8: 120 / 121   16: 164 / 164   48: 188 / 188
 // At 0.7 times the load both orders are ahead by up to 1.3 us up to 8 steps (first shape: 44 / 43 at 8 steps).
-template <int E, bool ADV>
-__global__ __launch_bounds__(256) void br_k_route(BrParams p, BrArr a, BrOut o) {
+// Batches of 4097..6144 clusters (5120 with queues beyond 256) are resident at once where the decode steps take four long lists
+// at a time (ADV = 4: 80 and 83 registers, six and five waves per SIMD); with eight, 102 registers leave four.  Batches that fit four,
+// or are several times that, are faster with eight.  Eight / four at a time, us (and with the masked single-word stores before either):
+//   4100 clusters, G = 16, B = 144, one step 52.5 / 45.1 (49.2)    5120: 67.1 / 58.7 (61.4), 48 steps 145 / 121 (126)    6000: 73.4 / 68.6 (86.5)
+//   queues of 500                            5120: 81.7 / 70.3 (72.0), 48 steps 167 / 136 (140)                         6000: 89.0 / 93.0 (99.6)
+//   4096 clusters, one step 43.2 / 44.2, 48 steps 105.8 / 107.5    8192: 91.8 / 96.2    16000: 172 / 176
+template <int E, int ADV>
+__global__ __launch_bounds__(256, ADV == 4 ? (E == 4 ? 6 : 5) : 1) void br_k_route(BrParams p, BrArr a, BrOut o) {
   extern __shared__ int lds_all[];
-  constexpr bool MIX = ADV && E <= 8;
+  constexpr bool MIX = ADV > 0 && E <= 8;
   constexpr int ROUND = ADV ? BR_ROUND_ADV_WORDS(E) : BR_ROUND_WORDS(E, false), WORDS = ROUND + (MIX ? BR_SPLIT_WORDS : 0);
   const int w = threadIdx.x >> 6, b = (int)blockIdx.x, inst = b * (int)(blockDim.x >> 6) + w;
   int *lds = lds_all + w * WORDS, *split = nullptr;
-  if (MIX && p.adv_t <= 8 && ((b + (b >> 8) + w) & 1) && inst < p.N) {  // (blocks 256 apart share a CU: both orders on every SIMD)
-    split = lds + ROUND;
-    if (br_lane() == 0) split[1] = 1;  // (no other wave reads this cluster)
-    br_split_advance<8>(p, inst, br_lane(), split, lds);
+  if constexpr (MIX) {
+    if (p.adv_t <= 8 && ((b + (b >> 8) + w) & 1) && inst < p.N) {  // (blocks 256 apart share a CU: both orders on every SIMD)
+      split = lds + ROUND;
+      if (br_lane() == 0) split[1] = 1;  // (no other wave reads this cluster)
+      br_split_advance<ADV>(p, inst, br_lane(), split, lds);
+    }
   }
   br_assign_body<E, 0, ADV, false, false, true>(p, a, o, lds, inst, 0, split);
 }
@@ -36,10 +44,12 @@ static void launch_route(const BrParams &p, const BrArr &a, const BrOut &o, hipS
   const bool adv = p.adv_t > 0;
   const size_t lds = (size_t)wpb * (adv ? BR_ROUND_ADV_WORDS(E) + (E <= 8 ? BR_SPLIT_WORDS : 0) : BR_ROUND_WORDS(E, false)) * sizeof(int);
   const dim3 grid((unsigned)((p.N + wpb - 1) / wpb)), block(BR_WAVE * wpb);
-  if (adv)
-    hipLaunchKernelGGL((br_k_route<E, true>), grid, block, lds, st, p, a, o);
+  if (adv && E <= 8 && p.N > 4 * 1024 && p.N <= (E == 4 ? 6 : 5) * 1024)
+    hipLaunchKernelGGL((br_k_route<E, E <= 8 ? 4 : 8>), grid, block, lds, st, p, a, o);
+  else if (adv)
+    hipLaunchKernelGGL((br_k_route<E, 8>), grid, block, lds, st, p, a, o);
   else
-    hipLaunchKernelGGL((br_k_route<E, false>), grid, block, lds, st, p, a, o);
+    hipLaunchKernelGGL((br_k_route<E, 0>), grid, block, lds, st, p, a, o);
 }
 
 void br_launch_route(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {

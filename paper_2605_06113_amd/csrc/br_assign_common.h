@@ -351,10 +351,11 @@ __device__ __forceinline__ BrOut br_late_out() {
 
 // Decode steps of one BR-0 cluster by the wave that has just routed it.  `Lcur`, `nn`: load and list length of worker `lane`
 // after the round; lists [g0, g1) are this wave's; lds: BR_PLAIN_WORDS of the wave's.
+// LONG as for br_advance_lists_any.
 // STORE = false: loads and counts are not stored; what list g loses and its load change go to split[4 + g] and
 // split[4 + 64 + g] instead (the split kernels, where another wave owns the workers' final state).
 #define BR_PLAIN_WORDS (2 * BR_SEG_WORDS(0))
-template <int UB, bool STORE = true>
+template <int LONG, bool STORE = true>
 __device__ __forceinline__ void br_advance_cluster(int inst, int lane, int Lcur, int nn, int *lds, int g0 = 0, int g1 = 64,
                                                    int *split = nullptr) {
   const BrParams p = br_late_params();
@@ -364,7 +365,7 @@ __device__ __forceinline__ void br_advance_cluster(int inst, int lane, int Lcur,
   const int64_t row0 = (int64_t)__builtin_amdgcn_readfirstlane(inst) * p.G;  // scalar: list bases stay in SGPRs
   if (p.Bs <= 256) {
     const BrSegBase b = br_seg_base(p, row0);
-    br_advance_lists_any(p, t, b, lane, g0, G, nn, lds, [&](int g, const BrSegPlan &d, bool whole) {
+    br_advance_lists_any<LONG>(p, t, b, lane, g0, G, nn, lds, [&](int g, const BrSegPlan &d, bool whole) {
       if constexpr (STORE) {
         const int L = __builtin_amdgcn_ds_bpermute(g << 2, Lcur);
         if (whole) {
@@ -379,6 +380,7 @@ __device__ __forceinline__ void br_advance_cluster(int inst, int lane, int Lcur,
     return;
   }
   // longer lists: br_adv_apply over (list, 256-slot chunk) units, UB units requested before the first is used
+  constexpr int UB = 8;
   const int NC = (p.Bs + 255) >> 8, U = max(G - g0, 0) * NC;
   const int64_t rowa = row0 + g0;
   int dLw = 0, nw = nn;     // lane g: load change and new length of worker g
@@ -451,12 +453,12 @@ __device__ __forceinline__ void br_advance_cluster_rows(int inst, int lane, int 
 
 // The decode steps of a cluster's lists as they stand, what they lost and by how much their loads change, then the flag.
 // lds: BR_PLAIN_WORDS of the wave's.
-template <int UB>
+template <int LONG>
 __device__ __forceinline__ void br_split_advance(const BrParams &p, int inst, int lane, int *split, int *lds) {
   const bool act = lane < p.G;
   const int n_raw = p.n[(int64_t)inst * p.G + (act ? lane : 0)];
   const int n0 = act ? min(max(n_raw, 0), p.B) : 0;
-  br_advance_cluster<UB, false>(inst, lane, 0, n0, lds, 0, 64, split);
+  br_advance_cluster<LONG, false>(inst, lane, 0, n0, lds, 0, 64, split);
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // the lists are in place before the flag is seen
   __builtin_amdgcn_wave_barrier();
   if (lane == 0) split[0] = 1;

@@ -857,6 +857,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
 // more are waiting.  COOP (EM = 32): the block has four waves; all of them sort a long waiting set together
 // (br_sort_desc_block4) and share the epilogue and the decode step, wave 0 runs the round; the others compute the snapshot
 // reductions meanwhile (one cluster, G = 64, H = 8, a queue of 2048: whole pass 49.1 -> 43.0 us against a launch of tiles and one that folds them).
+// ADV: decode steps after the round (0: none; BR-0: that many long lists at a time, see br_advance_lists_any).
 // SCORES: the snapshot reductions (best_g / best_i where asked for) are taken on the way (br_score_wave.h).
 // `split`: the cluster's BR_SPLIT_WORDS of LDS where the decode steps of the old list entries are applied apart (by
 // another wave meanwhile, or by this one before the round), or null.
@@ -868,7 +869,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
 // SPLIT: the decode steps of the old entries are applied by another wave in every call, so the other epilogue is left out: with both
 // in the kernel the words requested ahead of a queue of 257..512 went through 100 bytes of scratch memory per lane (2000 clusters,
 // G = 16, queues of 500: whole pass 31.0 us, 26.1 without; one cluster 12.5 and 11.8).
-template <int EM, int HB, bool ADV, bool COOP = false, bool BIGR = false, bool SCORES = false, bool HELPED = false,
+template <int EM, int HB, int ADV, bool COOP = false, bool BIGR = false, bool SCORES = false, bool HELPED = false,
           bool SPLIT = false, bool DP = false>
 __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a, const BrOut &o, int *lds, int inst,
                                                int w = 0, int *split = nullptr,
@@ -1004,10 +1005,10 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
   if constexpr (HELPED) __syncthreads();
   if constexpr (COOP) {
     int Lw = st.Lh[0];
-    br_assign_epilogue_block4<BRH>(inst, lane, w, q0, qn, cnt, bound, slots, lst, Lw, st.nn, rc, c0, ADV);
+    br_assign_epilogue_block4<BRH>(inst, lane, w, q0, qn, cnt, bound, slots, lst, Lw, st.nn, rc, c0, ADV > 0);
     if constexpr (ADV) {
       const int per = (G + 3) >> 2;
-      br_advance_cluster<8>(inst, lane, Lw, st.nn, lds + w * BR_PLAIN_WORDS, min(w * per, G), min(w * per + per, G));
+      br_advance_cluster<ADV>(inst, lane, Lw, st.nn, lds + w * BR_PLAIN_WORDS, min(w * per, G), min(w * per + per, G));
     }
   } else {
     bool done = false;
@@ -1025,7 +1026,7 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
       if constexpr (ADV && BRH)
         br_advance_cluster_rows(inst, lane, st.Lh[0], st.nn, bound);
       else if constexpr (ADV)
-        br_advance_cluster<8>(inst, lane, st.Lh[0], st.nn, lds);
+        br_advance_cluster<ADV>(inst, lane, st.Lh[0], st.nn, lds);
     }
   }
 }
@@ -1035,9 +1036,9 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
 // (a batch of 4096 clusters is four waves per SIMD): it is asked to fit.
 // BIGR: candidate windows of 9..16 requests (R_max > 8); a separate instantiation so that the kernels for
 // the deployed window sizes keep their registers and code size.
-template <int E, int HB, bool ADV, bool BIGR = false, bool DP = false>
+template <int E, int HB, int ADV, bool BIGR = false, bool DP = false>
 // `share` (BIGR, queues of up to 1024): one cluster per block, its four waves share the subset scans
-__global__ __launch_bounds__(256, (HB > 0 && E == 8 && !BIGR) ? 4 : 1) void br_k_assign(BrParams p, BrArr a, BrOut o, int share) {
+__global__ __launch_bounds__(256, (HB > 0 && E == 8 && !BIGR) ? 4 : ADV == 4 ? 6 : 1) void br_k_assign(BrParams p, BrArr a, BrOut o, int share) {
   extern __shared__ int lds_all[];
   constexpr int WORDS = ADV ? BR_ROUND_ADV_WORDS(E) : BR_ROUND_WORDS(E, BIGR);
   const int w = threadIdx.x >> 6;
@@ -1059,7 +1060,7 @@ __global__ __launch_bounds__((1 + BR_HELPERS) * BR_WAVE) void br_k_route_helped(
   extern __shared__ int lds_all[];
   const int w = threadIdx.x >> 6, inst = (int)blockIdx.x;
   if (w == 0) {
-    br_assign_body<E, HB, false, false, false, false, true>(p, a, o, lds_all, inst);
+    br_assign_body<E, HB, 0, false, false, false, true>(p, a, o, lds_all, inst);
   } else {
     br_snapshot_helper<E, HB>(p, a, o, inst, br_lane(), w - 1, BR_HELPERS, recip_g,
                               lds_all + BR_ROUND_WORDS(E, false) + (w - 1) * (BR_LIST_WORDS(E) + 2 * BR_WAVE));
@@ -1102,21 +1103,25 @@ static void br_launch_assign_one(const BrParams &p, const BrArr &a, const BrOut 
     if ((HB > 0 || dp) && E <= 16 && (long long)p.N * 4 <= room) {
       const size_t lds1 = ((size_t)BR_ROUND_WORDS(E, true) + 32 + (dp ? BR_DP_LDS_WORDS : 0)) * sizeof(int);
       if (HB == 0)  // (reachable sums)
-        hipLaunchKernelGGL((br_k_assign<E, HB, false, true, HB == 0>), dim3((unsigned)p.N), dim3(4 * BR_WAVE), lds1, st, p, a, o, 1);
+        hipLaunchKernelGGL((br_k_assign<E, HB, 0, true, HB == 0>), dim3((unsigned)p.N), dim3(4 * BR_WAVE), lds1, st, p, a, o, 1);
       else
-        hipLaunchKernelGGL((br_k_assign<E, HB, false, true>), dim3((unsigned)p.N), dim3(4 * BR_WAVE), lds1, st, p, a, o, 1);
+        hipLaunchKernelGGL((br_k_assign<E, HB, 0, true>), dim3((unsigned)p.N), dim3(4 * BR_WAVE), lds1, st, p, a, o, 1);
     } else if (HB == 0 && dp) {
-      hipLaunchKernelGGL((br_k_assign<E, HB, false, true, HB == 0>), grid, block, lds, st, p, a, o, 0);
+      hipLaunchKernelGGL((br_k_assign<E, HB, 0, true, HB == 0>), grid, block, lds, st, p, a, o, 0);
     } else {
-      hipLaunchKernelGGL((br_k_assign<E, HB, false, true>), grid, block, lds, st, p, a, o, 0);
+      hipLaunchKernelGGL((br_k_assign<E, HB, 0, true>), grid, block, lds, st, p, a, o, 0);
     }
   } else if constexpr (HB > 0) {
-    hipLaunchKernelGGL((br_k_assign<E, HB, false>), grid, block, lds, st, p, a, o, 0);
+    hipLaunchKernelGGL((br_k_assign<E, HB, 0>), grid, block, lds, st, p, a, o, 0);
   } else {
-    if (adv)
-      hipLaunchKernelGGL((br_k_assign<E, HB, true>), grid, block, lds, st, p, a, o, 0);
+    // (six waves per SIMD with four long lists at a time, five with eight, 80 and 94 registers: 6000 clusters, G = 16, B = 144, eight /
+    // four, us: one step 75.8 / 70.9, 48 steps 142 / 129; 5120 clusters 58.7 / 60.4)
+    if (adv && E <= 8 && p.N > 5 * 1024 && p.N <= 6 * 1024)
+      hipLaunchKernelGGL((br_k_assign<E, HB, E <= 8 ? 4 : 8>), grid, block, lds, st, p, a, o, 0);
+    else if (adv)
+      hipLaunchKernelGGL((br_k_assign<E, HB, 8>), grid, block, lds, st, p, a, o, 0);
     else
-      hipLaunchKernelGGL((br_k_assign<E, HB, false>), grid, block, lds, st, p, a, o, 0);
+      hipLaunchKernelGGL((br_k_assign<E, HB, 0>), grid, block, lds, st, p, a, o, 0);
   }
 }
 

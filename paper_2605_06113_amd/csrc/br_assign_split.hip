@@ -7,8 +7,15 @@
 // at one LDS flag for each of the others before its epilogue, and those always come.
 #include "br_assign_kernel.h"
 
+// The decode steps take four long lists at a time: with eight the kernel holds 100 registers instead of 79 (queues of up to 256) and 94,
+// and two fifths of the waves that were resident are not.  Whole pass with reductions, us, eight / four at a time (and with the masked
+// single-word stores before either), G = 16, B = 144:
+//   one step              1024 clusters 19.1 / 18.6 (19.2)    1600: 24.3 / 22.4 (23.2)    2047: 27.7 / 23.7 (24.4)    with the matrix 31.1 / 26.7 (27.0)
+//   48 steps              2047 clusters 85.0 / 75.3 (76.9)
+//   queues of 500         2047 clusters 33.1 / 30.9 (32.1)    without reductions 30.5 / 29.1 (29.1)
+// (The bound on the block's size is that of four waves: with the true one the compiler reserves scratch memory that nothing uses.)
 template <int E, bool THIRD>
-__global__ __launch_bounds__((THIRD ? 3 : 2) * BR_WAVE) void br_k_route_split(BrParams p, BrArr a, BrOut o, unsigned recip_g) {
+__global__ __launch_bounds__(256, E == 4 ? 6 : 5) void br_k_route_split(BrParams p, BrArr a, BrOut o, unsigned recip_g) {
   extern __shared__ int lds_all[];
   const int w = threadIdx.x >> 6, lane = br_lane(), inst = (int)blockIdx.x;
   int *split = lds_all + BR_ROUND_WORDS(E, false);
@@ -16,9 +23,9 @@ __global__ __launch_bounds__((THIRD ? 3 : 2) * BR_WAVE) void br_k_route_split(Br
   if (threadIdx.x == 0) split[0] = 0, split[1] = THIRD ? 0 : 1;
   __syncthreads();
   if (w == 0) {
-    br_assign_body<E, 0, false, false, false, false, false, true>(p, a, o, lds_all, inst, 0, split);
+    br_assign_body<E, 0, 0, false, false, false, false, true>(p, a, o, lds_all, inst, 0, split);
   } else if (!THIRD || w == 1) {
-    br_split_advance<8>(p, inst, lane, split, split + BR_SPLIT_WORDS);
+    br_split_advance<4>(p, inst, lane, split, split + BR_SPLIT_WORDS);
   } else if constexpr (THIRD) {
     br_snapshot_helper<E, 0>(p, a, o, inst, lane, 0, 1, recip_g, split + BR_SPLIT_WORDS + BR_PLAIN_WORDS);
     __builtin_amdgcn_s_waitcnt(0);  // every read has returned before the flag is seen

@@ -1133,6 +1133,27 @@ def test_large_batches_decode_orders(G, Q, steps):
     r.close()
 
 
+@pytest.mark.parametrize("N,scores", [(4097, True), (5121, False), (6145, True)])
+@pytest.mark.parametrize("G,B,Q,steps", [(5, 129, 60, 1), (3, 256, 300, 9), (2, 260, 20, 3), (7, 60, 64, 8)])
+def test_batches_of_4097_clusters_and_more_decode(N, scores, G, B, Q, steps):
+    """BR-0 batches around the line from which the decode steps take four long lists at a time (and back to eight): lists of every
+    width, groups of lists that are not full, queues of either size class."""
+    cfg, init, arr = wl.random_case(1500 + N + B, N=N, G=G, B=B, max_wait=Q, fill=0.8, n_wait=Q // 2)
+    init.n[0, 0], init.n[1, G - 1] = 0, B
+    init.kv[1, G - 1], init.rem[1, G - 1] = np.maximum(init.kv[1, G - 1], 1), 500
+    arr.count[::7] = np.arange(len(arr.count[::7])) % 9
+    arr.o[:, ::3] = 1 + arr.o[:, ::3] % (2 * steps)
+    _say(f"beyond 4096 N={N} G={G} B={B} Q={Q} steps={steps}")
+    oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
+    for rnd in range(2):
+        ref = oc.route_step(arr)
+        out = r.route_step(arr, matrix=False, scores=scores, advance=steps)
+        compare_outputs({k: v for k, v in ref.items() if k in out}, out, cfg, f"beyond 4096 r{rnd}")
+        oc.advance(steps)
+        compare_state(oc, r.state(), cfg, f"beyond 4096 r{rnd}")
+    r.close()
+
+
 @pytest.mark.parametrize("G,B,Q,H,pred_mode,steps", [
     (5, 60, 200, 4, 0, 1), (5, 64, 40, 8, 0, 7), (3, 65, 512, 4, 0, 40), (3, 128, 300, 3, 0, 9), (2, 129, 100, 8, 0, 12),
     (2, 256, 256, 4, 0, 3), (9, 12, 64, 5, 1, 2), (3, 100, 256, 2, 0, 20), (4, 33, 300, 7, 3, 5), (2, 131, 60, 6, 0, 30),
