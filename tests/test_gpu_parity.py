@@ -1186,6 +1186,60 @@ def test_large_batches_decode_with_prediction_rows(G, B, Q, H, pred_mode, steps)
     r.close()
 
 
+def _lists_in_every_state(init, B, steps):
+    """Workers whose list is empty, full and losing nothing, full and losing everything; requests that end within the steps."""
+    G = init.n.shape[1]
+    init.kv[:], init.rem[:] = np.maximum(init.kv, 1), 1 + init.rem % (3 * steps)
+    init.n[0, 0] = 0
+    init.n[1, G - 1] = init.n[2, 0] = B
+    init.rem[1, G - 1], init.rem[2, 0] = 500, 1
+
+
+@pytest.mark.parametrize("Q,G,B,steps", [(1025, 1, 64, 1), (2048, 3, 65, 9), (1025, 5, 128, 9), (2048, 5, 129, 1), (1025, 16, 256, 1),
+                                         (2048, 3, 260, 9), (1030, 16, 60, 9), (2048, 1, 200, 1)])
+def test_long_queues_large_batches_decode(Q, G, B, steps):
+    """BR-0 batches beyond 2048 clusters with queues beyond 1024: the four waves that have sorted the queue and shared the epilogue share the
+    decode steps too, a part of the lists each, in LDS that held the sorted list: fewer lists than waves, parts that are not
+    full, nothing waiting, a list of each length class and every entry of the queue taken."""
+    N = 2051
+    cfg, init, arr = wl.random_case(1700 + Q + G + B, N=N, G=G, B=B, max_wait=Q, fill=0.8, n_wait=Q)
+    _lists_in_every_state(init, B, steps)
+    arr.count[:] = np.arange(N) % 20
+    few = slice(5, N, 171)
+    arr.count[few] = np.resize([Q, 0, 64, 257, 513, 1024, 1025, Q - 1], len(arr.count[few]))
+    arr.o[:, ::3] = 1 + arr.o[:, ::3] % (2 * steps)
+    _say(f"long queues decode Q={Q} G={G} B={B} steps={steps}")
+    oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
+    for rnd in range(2):
+        ref = oc.route_step(arr)
+        out = r.route_step(arr, matrix=False, scores=rnd == 0, advance=steps)
+        compare_outputs({k: v for k, v in ref.items() if k in out}, out, cfg, f"long queues decode r{rnd}")
+        oc.advance(steps)
+        compare_state(oc, r.state(), cfg, f"long queues decode r{rnd}")
+    r.close()
+
+
+@pytest.mark.parametrize("N,Q", [(5, 40), (5, 300), (2051, 40), (2051, 600)])
+@pytest.mark.parametrize("B", [64, 65, 128, 131, 256, 260, 515])
+def test_decode_beside_the_round_list_widths(B, N, Q):
+    """BR-0 decode steps in the round's launch at the widths of list where its routines change: on the wave beside the round (few
+    clusters), before the round on half of the waves (up to 8 steps, many clusters) and after it."""
+    for steps in (1, 8, 9):
+        cfg, init, arr = wl.random_case(1800 + B + Q + steps, N=N, G=5, B=B, max_wait=Q, fill=0.8, n_wait=min(Q, 30))
+        _lists_in_every_state(init, B, steps)
+        arr.count[:] = np.arange(N) % 30
+        arr.o[:, ::3] = 1 + arr.o[:, ::3] % (2 * steps)
+        _say(f"decode beside the round B={B} N={N} Q={Q} steps={steps}")
+        oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
+        for rnd in range(2):
+            ref = oc.route_step(arr)
+            out = r.route_step(arr, matrix=False, scores=rnd == 0, advance=steps)
+            compare_outputs({k: v for k, v in ref.items() if k in out}, out, cfg, f"decode beside the round r{rnd}")
+            oc.advance(steps)
+            compare_state(oc, r.state(), cfg, f"decode beside the round r{rnd}")
+        r.close()
+
+
 def test_large_batch_appends_beyond_the_masks():
     """The same with workers that take more than 64 requests in a round (empty workers, short requests), some of which end
     within the steps: the append's bit masks do not hold them."""
