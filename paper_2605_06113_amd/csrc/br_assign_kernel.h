@@ -1037,16 +1037,24 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
 // BIGR: candidate windows of 9..16 requests (R_max > 8); a separate instantiation so that the kernels for
 // the deployed window sizes keep their registers and code size.
 template <int E, int HB, int ADV, bool BIGR = false, bool DP = false>
-// `share` (BIGR, queues of up to 1024): one cluster per block, its four waves share the subset scans
+// `share` (BIGR, queues of up to 1024; BR-0: reachable sums only): one cluster per block, its four waves share the searches
 __global__ __launch_bounds__(256, (HB > 0 && E == 8 && !BIGR) ? 4 : ADV == 4 ? 6 : 1) void br_k_assign(BrParams p, BrArr a, BrOut o, int share) {
   extern __shared__ int lds_all[];
   constexpr int WORDS = ADV ? BR_ROUND_ADV_WORDS(E) : BR_ROUND_WORDS(E, BIGR);
   const int w = threadIdx.x >> 6;
-  if constexpr (E == 32)  // one cluster per block, four waves for the sort
+  if constexpr (E == 32) {  // one cluster per block, four waves for the sort
     br_assign_body<E, HB, ADV, true, BIGR, false, false, false, DP>(p, a, o, lds_all, (int)blockIdx.x, w);
-  else if (BIGR && share)
-    br_assign_body<E, HB, ADV, false, BIGR, false, false, false, DP>(p, a, o, lds_all, (int)blockIdx.x, w, nullptr, true);
-  else
+    return;
+  }
+  // (in the kernel for BR-0 windows of up to 16, which never shares, the second copy of the round cost scalar registers and four vector
+  // ones, with queues of 257..512 the third wave per SIMD: 3000 clusters, window 16, queues of 512, whole pass 102 us, 79 without)
+  if constexpr (BIGR && (HB > 0 || DP)) {
+    if (share) {
+      br_assign_body<E, HB, ADV, false, BIGR, false, false, false, DP>(p, a, o, lds_all, (int)blockIdx.x, w, nullptr, true);
+      return;
+    }
+  }
+  if constexpr (E != 32)
     br_assign_body<E, HB, ADV, false, BIGR, false, false, false, DP>(p, a, o, lds_all + w * WORDS, (int)(blockIdx.x * (blockDim.x >> 6)) + w);
 }
 

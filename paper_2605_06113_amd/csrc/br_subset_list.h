@@ -74,7 +74,7 @@ __device__ __forceinline__ bool br_list_serves(int w, int kmax) { return w > 8 &
 __device__ __forceinline__ int br_list_size(int w, int kmax) { return br_mask_counts.upto[w][kmax]; }
 
 // What a search computes from the lane alone (its tables' loads among it) stays in the search: taken out of the loop over the
-// pops it holds registers throughout the round (BR-0, windows of up to 16, queues of up to 256: 220 of them, 154 so and with wider windows
+// pops it holds registers throughout the round (BR-0, windows of up to 16, queues of up to 256: 220 of them, 153 so and with wider windows
 // in a kernel of their own: three waves per SIMD instead of two; 3000 clusters, window 16, whole pass 143 -> 89 us).
 __device__ __forceinline__ void br_stay(int &lane) { asm volatile("" : "+v"(lane)); }
 

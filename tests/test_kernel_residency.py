@@ -13,6 +13,8 @@ WAVES = {
     "_Z10br_k_routeILi4ELi8EE": 4, "_Z10br_k_routeILi8ELi8EE": 4,
     "_Z11br_k_assignILi4ELi0ELi4E": 6, "_Z11br_k_assignILi8ELi0ELi4E": 6,       # 5121..6144 clusters, no reductions
     "_Z11br_k_assignILi4ELi0ELi8E": 5, "_Z11br_k_assignILi8ELi0ELi8E": 5,
+    "_Z11br_k_assignILi4ELi0ELi0ELb1ELb0E": 3, "_Z11br_k_assignILi8ELi0ELi0ELb1ELb0E": 3,   # BR-0, windows of 9..16
+    "_Z11br_k_assignILi16ELi0ELi0ELb1ELb0E": 3,
 }
 
 
