@@ -310,7 +310,7 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
   // as a launch of their own, which streams the lists with more loads in flight than the round's waves can hold (BR-H, H = 4,
   // G = 16: 512 clusters 38 us against 46; one cluster, H = 8: 26 against 33; BR-0, 512 clusters with queues of 1024: 40
   // against 44).
-  const bool fused_adv = p.H == 0 ? p.R_max <= 8 && (br_split_shape(p) || p.N >= BR_FULL_BATCH_N) : br_route_h_advances(p);
+  const bool fused_adv = p.H == 0 ? p.R_max <= 8 && (br_split_shape(p) || p.N >= BR_FULL_BATCH_N) : br_route_h_advances(p, adv_t);
   const bool split_adv = adv_t > 0 && !fused_adv;
   p.adv_t = split_adv ? 0 : adv_t;
   int32_t rc = BR_OK;

@@ -54,7 +54,7 @@ inline bool br_block_serves(const BrParams &p) {
 void br_launch_route(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
 // BR-H (H <= BR_HP), Q <= 512: the same in one launch
 void br_launch_route_h(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
-bool br_route_h_advances(const BrParams &p);  // its decode steps ride in that launch
+bool br_route_h_advances(const BrParams &p, int t);  // t decode steps ride in that launch
 // batches below BR_FULL_BATCH_N without decode steps in the launch, queues of up to 512 (BR-0: 1024), windows of up to 8: the
 // round with the reductions (BR-0: and the matrix) on other waves of the cluster's block
 void br_launch_route_helped(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);

@@ -1210,6 +1210,28 @@ def test_long_queues_large_batches_decode(Q, G, B, steps):
     arr.o[:, ::3] = 1 + arr.o[:, ::3] % (2 * steps)
     _say(f"long queues decode Q={Q} G={G} B={B} steps={steps}")
     oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
+@pytest.mark.parametrize("N,G,B,Q,H,pred_mode,steps", [
+    (4097, 3, 40, 60, 4, 0, 8), (4097, 3, 40, 60, 4, 0, 9), (5120, 2, 70, 256, 3, 0, 1), (5121, 2, 70, 256, 3, 0, 1), (4097, 3, 40, 60, 5, 0, 1),
+    (2049, 25, 130, 20, 8, 1, 4), (2049, 25, 130, 20, 8, 1, 5), (2049, 24, 130, 20, 8, 1, 1),
+    (2300, 30, 93, 30, 8, 0, 4), (2300, 30, 93, 30, 8, 0, 5),
+])
+def test_decode_with_prediction_rows_on_both_sides_of_the_lines(N, G, B, Q, H, pred_mode, steps):
+    """BR-H batches around the lines between decode steps in the round's launch and in one of their own: by waves per SIMD, by the turns of a
+    wave over its lists, by the bytes of the batch."""
+    cfg, init, arr = wl.random_case(1450 + N + steps, N=N, G=G, B=B, max_wait=Q, H=H, fill=0.7, n_wait=Q // 2, pred_mode=pred_mode, gate_pfin=0.3)
+    arr.o[:, ::3] = 1 + arr.o[:, ::3] % (2 * steps)
+    init.rem[::2] += 2 * steps                        # lists that lose nothing beside those that do
+    _say(f"decode lines N={N} G={G} B={B} Q={Q} H={H} mode={pred_mode} steps={steps}")
+    oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
+    for rnd in range(2):
+        ref = oc.route_step(arr)
+        out = r.route_step(arr, matrix=False, scores=rnd == 0, advance=steps)
+        compare_outputs({k: v for k, v in ref.items() if k in out}, out, cfg, f"decode lines r{rnd}")
+        oc.advance(steps)
+        compare_state(oc, r.state(), cfg, f"decode lines r{rnd}")
+    r.close()
+
+
     for rnd in range(2):
         ref = oc.route_step(arr)
         out = r.route_step(arr, matrix=False, scores=rnd == 0, advance=steps)
