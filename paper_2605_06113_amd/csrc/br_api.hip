@@ -318,15 +318,15 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
   // The reductions ride along in the assignment launch where its waves can take them, since a launch of their own would wait
   // in line before it: full batches on the round's wave, which goes on with the sorted list; smaller ones on other waves of the
   // cluster's block, which load (and sort) for themselves.  Not where few clusters have more work than that hides (br_score_in_tiles).
-  const bool best = o.best_g || o.best_i;
+  const bool best = o.best_g || o.best_i, block = br_block_serves(p, o.F != nullptr);
   const bool split = br_split_serves(p);
   const bool together = best && p.R_max <= 8 &&
-                        (p.H == 0 ? p.Q <= 1024 && !br_block_serves(p) : (p.H <= BR_HP && p.Q <= 512 && !br_score_in_tiles(p)));
+                        (p.H == 0 ? p.Q <= 1024 && !block : (p.H <= BR_HP && p.Q <= 512 && !br_score_in_tiles(p)));
   // on the waves of the round's block that wait for its epilogue (BR-H, queues of 513..1024: a launch of their own, see br_score_in_tiles)
-  const bool coop = best && p.H <= BR_HP && (p.Q > 1024 || (p.H == 0 && br_block_serves(p)));
+  const bool coop = best && p.H <= BR_HP && (p.Q > 1024 || (p.H == 0 && block));
   // Batches that leave waves to spare: other waves of the cluster's block take what is asked for beside the round, for BR-0
   // the matrix as well (br_k_route_helped, the third wave of br_k_route_split).
-  const bool spare = p.N < BR_FULL_BATCH_N && p.R_max <= 8 && p.Q <= (p.H == 0 ? 1024 : 512) && p.H <= BR_HP && !br_block_serves(p);
+  const bool spare = p.N < BR_FULL_BATCH_N && p.R_max <= 8 && p.Q <= (p.H == 0 ? 1024 : 512) && p.H <= BR_HP && !block;
   const bool matrix_too = o.F && p.H == 0 && (split || spare);
   const bool helped = !split && spare && (together || matrix_too);
   const bool long_helped = best && p.H > BR_HP && br_long_helped(p);  // (on the helper waves of the long-horizon round)
@@ -335,7 +335,7 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
   if (matrix_too) first.F = nullptr;
   if (rc == BR_OK && (first.F || first.best_g || first.best_i))
     rc = enqueue(ctx, BR_K_SCORE, [&] { br_launch_score(p, a, first, partials, ctx->st); }, br);
-  if (p.H > BR_HP ? !long_helped : p.H > 0 && br_block_serves(p)) o.best_g = nullptr, o.best_i = nullptr;  // (done)
+  if (p.H > BR_HP ? !long_helped : p.H > 0 && block) o.best_g = nullptr, o.best_i = nullptr;  // (done)
   if (rc == BR_OK) {
     rc = enqueue(ctx, BR_K_ASSIGN, [&] {
       if (split)

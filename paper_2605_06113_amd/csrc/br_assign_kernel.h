@@ -1139,7 +1139,7 @@ static void br_launch_assign_sized(const BrParams &p, const BrArr &a, const BrOu
     br_launch_assign_one<4, HB, BIGR>(p, a, o, st);
   else if (p.Q <= 512)
     br_launch_assign_one<8, HB, BIGR>(p, a, o, st);
-  else if (p.Q <= 1024 && (BIGR || !br_block_serves(p)))
+  else if (p.Q <= 1024 && (BIGR || !br_block_serves(p, o.F != nullptr)))
     br_launch_assign_one<16, HB, BIGR>(p, a, o, st);
   else
     br_launch_assign_one<32, HB, BIGR>(p, a, o, st);

@@ -47,7 +47,18 @@ void br_launch_assign_brh4(const BrParams &p, const BrArr &a, const BrOut &o, hi
 //   H = 4   16 clusters 36.5 / 29.4, 45.2 / 39.0, 25.7 / 22.2    768: 59.3 / 51.9, 77.8 / 74.7, 30.5 / 27.1, with 700 arrivals 209 / 211
 //   H = 8   one cluster 33.4 / 28.1, 48.7 / 41.9, 24.0 / 22.1    512: 65.7 / 57.5, 128 / 118, 35.4 / 32.4, with 700 arrivals 394 / 363
 //           1024 without reductions: 62.2 / 66.4
-inline bool br_block_serves(const BrParams &p) {
+// Neither reductions nor matrix, overloaded, a queue of 520 | 1000, whole pass with a decode step:
+//   H = 0   one cluster 16.0 / 12.7 | 18.8 / 12.9    64: 20.8 / 17.5 | 23.8 / 17.6    768: 26.3 / 25.3 | 31.0 / 27.1
+//   H = 8   one cluster 25.8 / 22.5 | 29.1 / 22.3    512: 43.3 / 40.1 | 50.4 / 43.9
+// `matrix` (BR-0): the helpers of one wave take the score matrix beside the round, with the block it is a launch before it; under 640 the
+// sort that the block shares is worth less than that launch once a few clusters overlap.  Overloaded, lightly loaded, G = 16 (and overloaded G = 64, 64 clusters; G = 48, 300 clusters):
+//   queue of 520     4 clusters 20.4 / 20.3, 14.5 / 13.6    64: 21.6 / 22.6, 14.8 / 14.2 (35.7 / 37.9)    300: 25.5 / 27.2, 16.0 / 15.8 (38.3 / 41.8)
+//                    768: 32.9 / 34.4, 18.2 / 18.5
+//            600     16: 22.1 / 22.0, 14.9 / 13.9           64: 22.6 / 23.0, 15.1 / 14.2                  300: 26.4 / 28.0, 16.2 / 15.8
+//            700     64: 23.6 / 23.4, 16.4 / 15.0 (45.2 / 40.8)    300: 27.8 / 28.3, 17.6 / 16.7 (46.7 / 45.3)    768: 35.4 / 36.4, 20.0 / 19.2
+//           1000     64: 29.4 / 25.0, 20.0 / 15.1 (58.9 / 45.7)    768: 41.2 / 39.8, 24.1 / 20.0
+inline bool br_block_serves(const BrParams &p, bool matrix) {
+  if (matrix && p.H == 0 && p.Q <= 640 && p.N > 16) return false;
   return p.Q > 512 && p.Q <= 1024 && p.R_max <= 8 && p.H <= BR_HP && p.N <= (p.H > 0 ? 512 : 768);
 }
 // BR-0, Q <= 1024: snapshot reductions and assignment in one launch

@@ -426,7 +426,8 @@ __device__ __forceinline__ void br_snapshot_helper(const BrParams &p, const BrAr
     with(std::integral_constant<int, EM>{});
 }
 
-// The snapshot reductions of a cluster with a queue beyond 1024 on the three waves of its block that do not run the round
+// The snapshot reductions of a cluster whose round has a block of four waves (queues beyond 1024, shorter ones where br_block_serves)
+// on the three that do not run it
 // (h = 0..2): requests shared out 128 at a time, best_i on the last one.  lst: the sorted list where more than 256 wait, else
 // room for it.
 template <int HB>

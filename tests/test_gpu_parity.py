@@ -687,6 +687,30 @@ def test_queues_of_513_to_1024_on_both_sides_of_the_line(H, N):
         r.close()
 
 
+@pytest.mark.parametrize("N,Q", [(16, 640), (17, 640), (17, 641), (768, 513), (769, 641)])
+@pytest.mark.parametrize("wm", [0, 9000])
+def test_matrix_of_queues_of_513_to_1024_on_both_sides_of_the_line(N, Q, wm):
+    """The score matrix beside the round (up to a queue of 640, more than a few clusters) or before it, with and without the reductions
+    and with decode steps in the same call."""
+    import torch
+    for k, names in enumerate((("F",), ("F", "best_g", "best_i"))):
+        cfg, init, arr = wl.random_case(960 + N + Q + k, N=N, G=4, B=6, max_wait=Q, fill=0.6, token_watermark=wm)
+        arr.count[:] = np.resize([Q, 513, 512, 257, 64, 1, 0], N)
+        _say(f"matrix: queue of {Q}, N={N} W={wm} {names}")
+        oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
+        out = {name: v for name, v in r.alloc_outputs().items() if name in names or name not in ("F", "best_g", "best_i")}
+        darr = binding.DeviceArrivals(arr, r.device, r.layout.Pq)
+        for rnd in range(2):
+            r.route_advance_device(darr, out, rnd)
+            ref = oc.route_step(arr)
+            oc.advance(rnd)
+            torch.cuda.synchronize()
+            got = {key: v.cpu().numpy() for key, v in out.items()}
+            compare_outputs({key: v for key, v in ref.items() if key in got}, got, cfg, f"matrix r{rnd}")
+            compare_state(oc, r.state(), cfg, f"matrix r{rnd}")
+        r.close()
+
+
 def test_wide_window_long_requests_reach_the_row_bound():
     """Windows of 32 requests with lengths up to 32768 and room for many per pop: subset sums beyond the length of
     the bit rows (131071) exist and are not candidates on either side; rows too long for LDS go to the workspace."""
@@ -1186,6 +1210,28 @@ def test_large_batches_decode_with_prediction_rows(G, B, Q, H, pred_mode, steps)
     r.close()
 
 
+@pytest.mark.parametrize("N,G,B,Q,H,pred_mode,steps", [
+    (4097, 3, 40, 60, 4, 0, 8), (4097, 3, 40, 60, 4, 0, 9), (5120, 2, 70, 256, 3, 0, 1), (5121, 2, 70, 256, 3, 0, 1), (4097, 3, 40, 60, 5, 0, 1),
+    (2049, 25, 130, 20, 8, 1, 4), (2049, 25, 130, 20, 8, 1, 5), (2049, 24, 130, 20, 8, 1, 1),
+    (2300, 30, 93, 30, 8, 0, 4), (2300, 30, 93, 30, 8, 0, 5),
+])
+def test_decode_with_prediction_rows_on_both_sides_of_the_lines(N, G, B, Q, H, pred_mode, steps):
+    """BR-H batches around the lines between decode steps in the round's launch and in one of their own: by waves per SIMD, by the turns of a
+    wave over its lists, by the bytes of the batch."""
+    cfg, init, arr = wl.random_case(1450 + N + steps, N=N, G=G, B=B, max_wait=Q, H=H, fill=0.7, n_wait=Q // 2, pred_mode=pred_mode, gate_pfin=0.3)
+    arr.o[:, ::3] = 1 + arr.o[:, ::3] % (2 * steps)
+    init.rem[::2] += 2 * steps                        # lists that lose nothing beside those that do
+    _say(f"decode lines N={N} G={G} B={B} Q={Q} H={H} mode={pred_mode} steps={steps}")
+    oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
+    for rnd in range(2):
+        ref = oc.route_step(arr)
+        out = r.route_step(arr, matrix=False, scores=rnd == 0, advance=steps)
+        compare_outputs({k: v for k, v in ref.items() if k in out}, out, cfg, f"decode lines r{rnd}")
+        oc.advance(steps)
+        compare_state(oc, r.state(), cfg, f"decode lines r{rnd}")
+    r.close()
+
+
 def _lists_in_every_state(init, B, steps):
     """Workers whose list is empty, full and losing nothing, full and losing everything; requests that end within the steps."""
     G = init.n.shape[1]
@@ -1210,28 +1256,6 @@ def test_long_queues_large_batches_decode(Q, G, B, steps):
     arr.o[:, ::3] = 1 + arr.o[:, ::3] % (2 * steps)
     _say(f"long queues decode Q={Q} G={G} B={B} steps={steps}")
     oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
-@pytest.mark.parametrize("N,G,B,Q,H,pred_mode,steps", [
-    (4097, 3, 40, 60, 4, 0, 8), (4097, 3, 40, 60, 4, 0, 9), (5120, 2, 70, 256, 3, 0, 1), (5121, 2, 70, 256, 3, 0, 1), (4097, 3, 40, 60, 5, 0, 1),
-    (2049, 25, 130, 20, 8, 1, 4), (2049, 25, 130, 20, 8, 1, 5), (2049, 24, 130, 20, 8, 1, 1),
-    (2300, 30, 93, 30, 8, 0, 4), (2300, 30, 93, 30, 8, 0, 5),
-])
-def test_decode_with_prediction_rows_on_both_sides_of_the_lines(N, G, B, Q, H, pred_mode, steps):
-    """BR-H batches around the lines between decode steps in the round's launch and in one of their own: by waves per SIMD, by the turns of a
-    wave over its lists, by the bytes of the batch."""
-    cfg, init, arr = wl.random_case(1450 + N + steps, N=N, G=G, B=B, max_wait=Q, H=H, fill=0.7, n_wait=Q // 2, pred_mode=pred_mode, gate_pfin=0.3)
-    arr.o[:, ::3] = 1 + arr.o[:, ::3] % (2 * steps)
-    init.rem[::2] += 2 * steps                        # lists that lose nothing beside those that do
-    _say(f"decode lines N={N} G={G} B={B} Q={Q} H={H} mode={pred_mode} steps={steps}")
-    oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
-    for rnd in range(2):
-        ref = oc.route_step(arr)
-        out = r.route_step(arr, matrix=False, scores=rnd == 0, advance=steps)
-        compare_outputs({k: v for k, v in ref.items() if k in out}, out, cfg, f"decode lines r{rnd}")
-        oc.advance(steps)
-        compare_state(oc, r.state(), cfg, f"decode lines r{rnd}")
-    r.close()
-
-
     for rnd in range(2):
         ref = oc.route_step(arr)
         out = r.route_step(arr, matrix=False, scores=rnd == 0, advance=steps)
