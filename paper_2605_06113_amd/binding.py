@@ -300,7 +300,7 @@ class Router:
         return int(self.lib.br_route_step_static(self.ctx, C.byref(a) if a is not None else None, C.byref(o)))
 
     def route_advance_device(self, darr: Optional[DeviceArrivals], out, n_steps: int = 1) -> None:
-        """Enqueue one round and n_steps decode steps (one launch for BR-0 where that pays); no synchronisation."""
+        """Enqueue one round and n_steps decode steps (in one launch where that pays); no synchronisation."""
         a = darr.struct() if darr is not None else None
         o = self.out_struct(out)
         _check(self.lib.br_route_advance(self.ctx, C.byref(a) if a is not None else None, C.byref(o), int(n_steps)),

@@ -305,11 +305,11 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
   }
   BrParams p = ctx->p;
   // Decode steps in the round's launch: BR-0 on the two waves per cluster of the split kernel where it serves, and on
-  // the wave that has routed the cluster for batches that fill the chip (4096 clusters, G = 16, B = 144: a step 42 us
-  // against 50 as two launches, 48 steps 111 against 122); BR-H likewise (br_route_h_advances).  Everywhere else they follow
-  // as a launch of their own, which streams the lists with more loads in flight than the round's waves can hold (BR-H, H = 4,
-  // G = 16: 512 clusters 38 us against 46; one cluster, H = 8: 26 against 33; BR-0, 512 clusters with queues of 1024: 40
-  // against 44).
+  // the wave that has routed the cluster for batches that fill the chip (4096 clusters, G = 16, B = 144: a step 39 us
+  // against 47 as two launches, 48 steps 104 against 116); BR-H likewise (br_route_h_advances).  Everywhere else they follow
+  // as a launch of their own, which streams the lists with more loads in flight than the round's waves can hold (BR-H, G = 16,
+  // B = 96, one step: H = 4, 512 clusters 25 us against 31, 1500 clusters 38 against 42; H = 8, one cluster 18 against 24).  BR-0 with queues of
+  // 513..1024 and fewer clusters takes about the same either way (512 clusters 22.1 us, 21.0 in one launch; 8 steps 42.9 and 42.0).
   const bool fused_adv = p.H == 0 ? p.R_max <= 8 && (br_split_shape(p) || p.N >= BR_FULL_BATCH_N) : br_route_h_advances(p, adv_t);
   const bool split_adv = adv_t > 0 && !fused_adv;
   p.adv_t = split_adv ? 0 : adv_t;

@@ -9,18 +9,20 @@
 // ADV: for a few decode steps, half of the waves apply them to their lists as they stand before the round (and append
 // what they admit already advanced), the other half after it.  With one order for all, the memory idles while every wave
 // routes and the issue slots idle while every wave streams.  After many steps rounds are long (many admissions) and the
-// streaming hides in their tail anyway.  Both orders / one order, us, offered load 1.3 times what the workers serve:
-//   4096 clusters, G = 16, B = 144    1 step 43 / 43   4: 62 / 61    8: 82 / 80     16: 98 / 97     48: 119 / 117
-//   2048 clusters, G = 16, B = 144    1 step 33 / 34   4: 49 / 49    8: 63 / 64     16: 76 / 76     48: 93 / 92
-//   4096 clusters, G =  8, B = 64     1 step 22 / 23   4: 31 / 32    8: 40 / 40     16: 52 / 53     48: 69 / 68
-//   4096 clusters, G = 32, B = 96     1 step 62 / 64   4: 95 / 95    8: 120 / 121   16: 164 / 164   48: 188 / 188
-// At 0.7 times the load both orders are ahead by up to 1.3 us up to 8 steps (first shape: 44 / 43 at 8 steps).
+// streaming hides in their tail anyway.  Both orders / one order, us, offered load 0.7 and 1.3 times what the workers serve:
+//   4096 clusters, G = 16, B = 144    1 step 29.2 / 32.3, 38.6 / 40.3    4: 32.9 / 34.8, 51.1 / 50.0    8: 39.3 / 38.5, 66.9 / 65.5    16: - , 84.6 / 83.3
+//   4096 clusters, G = 32, B = 96     1 step 34.2 / 39.9, 44.2 / 49.2    4: 37.0 / 42.0, 55.7 / 59.9    8: 39.5 / 44.6, 72.4 / 71.2    16: - , 101 / 100
+//   4096 clusters, G =  8, B = 64     1 step 14.7 / 14.8, 18.5 / 18.5    4: 18.3 / 18.2, 26.3 / 26.0    8: 21.1 / 21.1, 32.1 / 32.0    16: - , 42.4 / 42.2
+//   2300 clusters, G = 64, B = 60     1 step 29.5 / 37.9, 36.4 / 40.7    4: 33.6 / 39.3, 54.4 / 55.5    8: 37.2 / 41.0, 70.4 / 70.8
+//   8192 clusters, G =  8, B = 96     1 step 28.9 / 28.8, 36.6 / 35.9    4: 34.7 / 34.2, 51.2 / 50.3    8: 40.4 / 39.8, 64.4 / 63.9
+// 48 steps: 112 / 110, 86 / 85 and 60.6 / 60.0 on the first three.
 // Batches of 4097..6144 clusters (5120 with queues beyond 256) are resident at once where the decode steps take four long lists
 // at a time (ADV = 4: 80 and 83 registers, six and five waves per SIMD); with eight, 102 registers leave four.  Batches that fit four,
 // or are several times that, are faster with eight.  Eight / four at a time, us (and with the masked single-word stores before either):
 //   4100 clusters, G = 16, B = 144, one step 52.5 / 45.1 (49.2)    5120: 67.1 / 58.7 (61.4), 48 steps 145 / 121 (126)    6000: 73.4 / 68.6 (86.5)
 //   queues of 500                            5120: 81.7 / 70.3 (72.0), 48 steps 167 / 136 (140)                         6000: 89.0 / 93.0 (99.6)
 //   4096 clusters, one step 43.2 / 44.2, 48 steps 105.8 / 107.5    8192: 91.8 / 96.2    16000: 172 / 176
+// (80 registers leave three words per lane in scratch memory, outside the loops: five instructions in all.)
 template <int E, int ADV>
 __global__ __launch_bounds__(256, ADV == 4 ? (E == 4 ? 6 : 5) : 1) void br_k_route(BrParams p, BrArr a, BrOut o) {
   extern __shared__ int lds_all[];

@@ -955,7 +955,8 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
       unsigned x8[8];
       br_keys_load<8>(p, a, inst, q0, qn, w * 512, lane, x8);
       br_sort_desc_block4(x8, lst, w, lane, qn);
-      // (every wave is past its last read of the exchange buffer: the block meets inside the sort after that)
+      // (every wave is past its last read of the exchange buffer: the block meets inside the sort after that; up to 512 waiting nothing
+      // is exchanged and each wave writes its own part only)
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int at = br_list_at<32>(w * 512 + lane * 8 + j);
@@ -1123,7 +1124,7 @@ static void br_launch_assign_one(const BrParams &p, const BrArr &a, const BrOut 
     hipLaunchKernelGGL((br_k_assign<E, HB, 0>), grid, block, lds, st, p, a, o, 0);
   } else {
     // (six waves per SIMD with four long lists at a time, five with eight, 80 and 94 registers: 6000 clusters, G = 16, B = 144, eight /
-    // four, us: one step 75.8 / 70.9, 48 steps 142 / 129; 5120 clusters 58.7 / 60.4)
+    // four, us: one step 75.8 / 70.9, 48 steps 142 / 129; 5120 clusters 58.7 / 60.4; two words per lane in scratch memory, three instructions)
     if (adv && E <= 8 && p.N > 5 * 1024 && p.N <= 6 * 1024)
       hipLaunchKernelGGL((br_k_assign<E, HB, E <= 8 ? 4 : 8>), grid, block, lds, st, p, a, o, 0);
     else if (adv)

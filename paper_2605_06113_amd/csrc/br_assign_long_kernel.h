@@ -202,7 +202,9 @@ __device__ __forceinline__ void br_long_shared_best(int32_t *best_g, int Q, int 
 #define BR_LONG_EXTRA_MAX_N 256
 // XW: waves beyond those that serve the searches, for the reductions only (few clusters).
 template <int E, int NW, int XW = 0>
-// (queues of up to 256: four waves per SIMD are asked for, which is what br_long_waves counts on)
+// (queues of up to 256: four waves per SIMD are asked for, which is what br_long_waves counts on.  Beyond, the compiler reserves 20 bytes
+// of scratch memory with four waves a cluster that no instruction touches; asking for two waves per SIMD takes them away and is slower:
+// H = 80, G = 8, queues of 1024, 100 clusters 65.0 us, 63.7 so)
 __global__ __launch_bounds__(64 * (NW + XW), E == 4 && XW == 0 ? 4 : 1) void br_k_assign_long(BrParams p, BrArr a, BrOut o) {
   constexpr int RW = NW - 1 + XW;  // waves that have the reductions while wave 0 runs the round
   static_assert(E % NW == 0, "every wave takes whole blocks of 64 sorted positions");

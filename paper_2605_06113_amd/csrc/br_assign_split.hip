@@ -52,9 +52,10 @@ static void launch_split(const BrParams &p, const BrArr &a, const BrOut &o, hipS
 // For batches below two one-wave clusters per SIMD: one round and one helper per block.  Beyond, with four or more waves
 // per SIMD, the decode step overlaps other clusters' rounds on the one-wave kernels as well.  Whole pass with reductions,
 // us, two waves / one wave per cluster (G = 16):
-//   B = 96, 256 waiting, one step      1024 clusters 19 / 27   2047: 24 / 31   3072: 29 / 35   4096: 39 / 38
-//   B = 144, 246 admitted, 48 steps    1024 clusters 66 / 76   2047: 80 / 88   3072: 95 / 98   4096: 116 / 111
-// (two waves are ahead up to about 3500 clusters: the line is on the safe side).
+//   B = 96, overloaded, one step       1024 clusters 15.4 / 20.2   2047: 19.8 / 23.5   3072: 25.4 / 26.1
+//   B = 144, 250 admitted, 48 steps    1024 clusters 60.8 / 67.9   2047: 75.2 / 79.9   3072: 98.7 / 91.2
+//   B = 144, overloaded                2048 clusters, 1 step 24.8 / 30.6   4: 35.0 / 41.0   8: 46.9 / 52.8   16: 59.8 / 64.7   48: 78.8 / 83.3
+// (at 2048 two waves are ahead still: the line is on the safe side).
 bool br_split_shape(const BrParams &p) {
   return p.H == 0 && p.R_max <= 8 && p.Q <= 512 && p.N < BR_FULL_BATCH_N;
 }
