@@ -639,7 +639,7 @@ def main():
     st_a = stats[:, binding.ST["admitted"]].astype(np.float64)
     ops_assign = 4.0 * float((st_a * st_q - st_a * (st_a - 1) / 2).sum())
     counters = profile_counters()
-    kname = {(True, "assign"): "br_k_route<4, true>", (False, "assign"): "br_k_route<4, false>",
+    kname = {(True, "assign"): "br_k_route<4, 8>", (False, "assign"): "br_k_route<4, 0>",
              (True, "advance"): "br_k_advance_seg<64, 2, 0>", (False, "advance"): "br_k_advance_seg<64, 2, 0>"}
 
     def kernel_table(kern, fused):
