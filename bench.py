@@ -291,6 +291,8 @@ def brh_run(device, steps=8, warmup=1, gate=None, deployed=False):
     active = N * G * per_worker
     bytes_k = dict(project=active * (4 + 4 * P) + N * G * 4 + N * (H + 1) * 4 * (2 * G + 1) + N * G * 4,
                    advance=(active + admitted) * 16 + N * G * 16)
+    if kern["advance"][1] == 0:  # the decode steps ride in the projection's pass over the lists: predictions and kv are read once
+        bytes_k["project"] += active * 12 + N * G * 8
     res = dict(workload=f"{N} clusters: BR-H H={H}, G={G}, B={cfg.B}, R_max={cfg.R_max}, {per_worker} active per worker, "
                         f"256 waiting; p_fin gate {cfg.gate_pfin}" + ("; estimate maintained by the library" if deployed else ""),
                ms_per_step=elapsed / steps * 1e3, pairs_per_s=qn * G * steps / elapsed,

@@ -233,11 +233,11 @@ int32_t br_advance_decode(br_ctx *ctx, int32_t n_steps);
  * n_steps decode steps of br_advance_decode (Sec. 2.2; Alg. BR-0 / Alg. BR-H), with exactly their
  * results: same outputs (written as br_route_step writes them, statistics describe the state
  * right after the round) and same workspace contents afterwards as the two calls in sequence.
- * With candidate windows of up to 8 requests the assignment launch itself applies the decode steps where that pays: in
+ * With candidate windows of up to 8 requests other launches of the call apply the decode steps where that pays.  BR-0: in
  * batches of 2048 clusters and more the wave that routes a cluster also applies them to that cluster's lists, so that some
- * clusters stream their lists while others are routing (BR-0; BR-H with H <= 8, queues of up to 512 and supplied predictions,
- * by the number of steps and the size of the batch); in smaller BR-0 batches with queues of up to 512 a second wave per
- * cluster does.  Otherwise the decode kernel follows as a launch of its own on the same stream.
+ * clusters stream their lists while others are routing; in smaller batches with queues of up to 512 a second wave per
+ * cluster does.  BR-H (H <= 8, queues of up to 512, at most 256 slots, supplied predictions): the projection's pass over the lists does.
+ * Otherwise the decode kernel follows as a launch of its own on the same stream.
  * Arguments, ownership and errors as for br_route_step; n_steps >= 0 (0: identical to
  * br_route_step), BR_EINVAL otherwise.
  */

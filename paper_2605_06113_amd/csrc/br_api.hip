@@ -304,17 +304,17 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
     o.best_i = out->best_i;
   }
   BrParams p = ctx->p;
-  // Decode steps in the round's launch: BR-0 on the two waves per cluster of the split kernel where it serves, and on
+  // Decode steps in the call's other launches: BR-0 on the two waves per cluster of the split kernel where it serves, and on
   // the wave that has routed the cluster for batches that fill the chip (4096 clusters, G = 16, B = 144: a step 39 us
-  // against 47 as two launches, 48 steps 104 against 116); BR-H likewise (br_route_h_advances).  Everywhere else they follow
-  // as a launch of their own, which streams the lists with more loads in flight than the round's waves can hold (BR-H, G = 16,
-  // B = 96, one step: H = 4, 512 clusters 25 us against 31, 1500 clusters 38 against 42; H = 8, one cluster 18 against 24).  BR-0 with queues of
+  // against 47 as two launches, 48 steps 104 against 116); BR-H in the projection's pass over the lists (br_project_advances).
+  // Everywhere else they follow as a launch of their own.  BR-0 with queues of
   // 513..1024 and fewer clusters takes about the same either way (512 clusters 22.1 us, 21.0 in one launch; 8 steps 42.9 and 42.0).
-  const bool fused_adv = p.H == 0 ? p.R_max <= 8 && (br_split_shape(p) || p.N >= BR_FULL_BATCH_N) : br_route_h_advances(p, adv_t);
+  const bool fused_adv = p.H == 0 ? p.R_max <= 8 && (br_split_shape(p) || p.N >= BR_FULL_BATCH_N) : br_project_advances(p);
   const bool split_adv = adv_t > 0 && !fused_adv;
   p.adv_t = split_adv ? 0 : adv_t;
   int32_t rc = BR_OK;
-  if (p.H > 0) rc = enqueue(ctx, BR_K_PROJECT, [&] { br_launch_project(p, ctx->st); }, br);
+  if (p.H > 0)
+    rc = enqueue(ctx, BR_K_PROJECT, [&] { p.adv_t > 0 ? br_launch_project_advance(p, ctx->st) : br_launch_project(p, ctx->st); }, br);
   // The reductions ride along in the assignment launch where its waves can take them, since a launch of their own would wait
   // in line before it: full batches on the round's wave, which goes on with the sorted list; smaller ones on other waves of the
   // cluster's block, which load (and sort) for themselves.  Not where few clusters have more work than that hides (br_score_in_tiles).
@@ -344,7 +344,7 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
         br_launch_route_h_helped(p, a, o, ctx->st);
       else if (helped)
         br_launch_route_helped(p, a, o, ctx->st);
-      else if (p.H > 0 && (together || p.adv_t > 0))
+      else if (p.H > 0 && together)
         br_launch_route_h(p, a, o, ctx->st);
       else if (together)
         br_launch_route(p, a, o, ctx->st);

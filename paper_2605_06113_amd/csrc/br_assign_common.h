@@ -76,36 +76,36 @@ __device__ __forceinline__ void br_with_rows(const BrTailArgs &t, F &&body) {
 }
 
 // What those positions hold and where they went.
-template <int GR, int ROWS>
+template <int GR, int ROWS, int NQ = BR_HP>  // NQ: words of a row at most
 struct BrQueueGroup {
   int bound[GR], id[GR], sq[GR], oq[GR];
-  float pr[ROWS != BR_ROWS_NONE ? GR : 1][BR_HP];
+  float pr[ROWS != BR_ROWS_NONE ? GR : 1][NQ];
 };
 
-template <int ROWS>
-__device__ __forceinline__ void br_row_load(const float *src, int Pq, float (&r)[BR_HP]) {
+template <int ROWS, int NQ>
+__device__ __forceinline__ void br_row_load(const float *src, int Pq, float (&r)[NQ]) {
   if constexpr (ROWS == BR_ROWS_WIDE) {
 #pragma unroll
-    for (int q = 0; q < BR_HP; q += 4)
+    for (int q = 0; q < NQ; q += 4)
       if (q < Pq) {
         const float4 v = *reinterpret_cast<const float4 *>(src + q);
         r[q] = v.x, r[q + 1] = v.y, r[q + 2] = v.z, r[q + 3] = v.w;
       }
   } else {
 #pragma unroll
-    for (int q = 0; q < BR_HP; ++q)
+    for (int q = 0; q < NQ; ++q)
       if (q < Pq) r[q] = src[q];
   }
 }
-template <int ROWS>
-__device__ __forceinline__ void br_row_store(float *dst, int Pq, const float (&r)[BR_HP]) {
+template <int ROWS, int NQ>
+__device__ __forceinline__ void br_row_store(float *dst, int Pq, const float (&r)[NQ]) {
   if constexpr (ROWS == BR_ROWS_WIDE) {
 #pragma unroll
-    for (int q = 0; q < BR_HP; q += 4)
+    for (int q = 0; q < NQ; q += 4)
       if (q < Pq) *reinterpret_cast<float4 *>(dst + q) = make_float4(r[q], r[q + 1], r[q + 2], r[q + 3]);
   } else {
 #pragma unroll
-    for (int q = 0; q < BR_HP; ++q)
+    for (int q = 0; q < NQ; ++q)
       if (q < Pq) dst[q] = r[q];
   }
 }
@@ -137,9 +137,9 @@ __device__ __forceinline__ void br_queue_words(const int32_t *qs, const int32_t 
 }
 
 // Where they went (from LDS) and their prediction rows; `words` as read before, or null: read here.
-template <int GR, int ROWS>
+template <int GR, int ROWS, int NQ>
 __device__ __forceinline__ void br_queue_load(const BrTailArgs &t, int inst, int lane, int j0, int q0, int qn, const int *bound,
-                                              BrQueueGroup<GR, ROWS> &v, const BrQueueWords<GR> *words = nullptr) {
+                                              BrQueueGroup<GR, ROWS, NQ> &v, const BrQueueWords<GR> *words = nullptr) {
   const int64_t qrow = (int64_t)inst * t.Q, arow = (int64_t)inst * t.arr_cap;
   BrQueueWords<GR> w;
   if (words)
@@ -161,16 +161,70 @@ __device__ __forceinline__ void br_queue_load(const BrTailArgs &t, int inst, int
   }
 }
 
+// ---- BR-H with decode steps in the call: the projection's pass over the lists has applied them to the old entries
+// (br_k_project_advance), and the round's epilogue appends its admissions behind the survivors, already advanced.  Same final
+// state as the round followed by the decode steps (see the split step below).
+// Admitted requests whose output is used up within the decode steps leave at once.  Who they are is collected in bit masks
+// by order of admission, a worker's from word `at` on, as many words as its admissions take, so that the others go straight to
+// their final slots.  lds: [0..64) `at` per worker, [64..128) kv that leaves, then the masks (64 words and one per 32 entries that wait).
+#define BR_DEAD_WORDS(E) (3 * BR_WAVE + 2 * (E))
+struct BrAhead {
+  const int *lost, *n0;  // null: no decode steps
+  int *dead;             // null: everybody outlives them
+  int t;
+};
+
+__device__ __forceinline__ void br_dead_clear(int lane, int a_g, int words, int *dead) {
+  const int mine = (a_g + 31) >> 5;
+  dead[lane] = br_scan_sum(mine) - mine;
+  dead[BR_WAVE + lane] = 0;
+  for (int k = lane; k < words; k += BR_WAVE) dead[2 * BR_WAVE + k] = 0;
+}
+
+__device__ __forceinline__ void br_dead_mark(const BrAhead &h, int bound, int s, int o) {
+  if (bound >= 0 && max(o, 1) <= h.t) {
+    const int g = (bound >> 16) & 63, k = (bound & 0xffff) - h.n0[g];
+    atomicOr(&h.dead[2 * BR_WAVE + h.dead[g] + (k >> 5)], 1 << (k & 31));
+    atomicAdd(&h.dead[BR_WAVE + g], min(max(s, 1), BR_MAX_S_DEV));
+  }
+}
+
+// the admissions before the k-th of worker g that leave at once
+__device__ __forceinline__ int br_dead_before(const BrAhead &h, int g, int k) {
+  const int *m = h.dead + 2 * BR_WAVE + h.dead[g];
+  int c = __builtin_popcount((unsigned)m[k >> 5] & ((1u << (k & 31)) - 1u));
+  for (int i = 0; i < k >> 5; ++i) c += __builtin_popcount((unsigned)m[i]);
+  return c;
+}
+
+// load and length of worker `lane` after the decode steps: Lcur, nn right after the round
+__device__ __forceinline__ void br_ahead_workers(const BrTailArgs &t, int inst, int lane, int Lcur, int nn, const int *ahead,
+                                                 const BrAhead &h) {
+  int a_g = nn - ahead[2 * BR_WAVE + lane], n = nn - ahead[lane], L = Lcur + ahead[BR_WAVE + lane];
+  if (h.dead) {
+    int gone = 0;
+    for (int k = 0; k < (a_g + 31) >> 5; ++k) gone += __builtin_popcount((unsigned)h.dead[2 * BR_WAVE + h.dead[lane] + k]);
+    a_g -= gone, n -= gone, L -= h.dead[BR_WAVE + lane];
+  }
+  if (lane < t.G) {
+    t.L[(int64_t)inst * t.G + lane] = L + a_g * h.t;
+    t.n[(int64_t)inst * t.G + lane] = n;
+  }
+}
+
 // List entries of the requests that were bound.
-template <int GR, int ROWS>
-__device__ __forceinline__ void br_commit_store(const BrTailArgs &t, int inst, const BrQueueGroup<GR, ROWS> &v, float c0) {
+template <int GR, int ROWS, int NQ>
+__device__ __forceinline__ void br_commit_store(const BrTailArgs &t, int inst, const BrQueueGroup<GR, ROWS, NQ> &v, float c0,
+                                                const BrAhead &h = BrAhead{nullptr, nullptr, nullptr, 0}) {
 #pragma unroll
   for (int u = 0; u < GR; ++u) {
     const int g = v.bound[u] >> 16, slot = v.bound[u] & 0xffff;
-    if (v.bound[u] >= 0 && g < t.G && slot < t.B) {
-      const int64_t row = ((int64_t)inst * t.G + g) * t.Bs + slot;
-      t.kv[row] = min(max(v.sq[u], 1), BR_MAX_S_DEV);
-      t.rem[row] = max(v.oq[u], 1);
+    if (v.bound[u] >= 0 && g < t.G && slot < t.B && max(v.oq[u], 1) > h.t) {
+      int64_t row = ((int64_t)inst * t.G + g) * t.Bs + slot;
+      if (h.lost) row -= h.lost[g];  // behind the old survivors
+      if (h.dead) row -= br_dead_before(h, g, slot - h.n0[g]);
+      t.kv[row] = min(max(v.sq[u], 1), BR_MAX_S_DEV) + h.t;
+      t.rem[row] = max(v.oq[u], 1) - h.t;
       if constexpr (ROWS != BR_ROWS_NONE) {
         br_row_store<ROWS>(t.pred + row * t.P, t.Pq, v.pr[u]);
         if (t.P == 3 && t.Pq == 0) {  // maintained estimate: first query at age 0, nothing generated yet
@@ -185,9 +239,9 @@ __device__ __forceinline__ void br_commit_store(const BrTailArgs &t, int inst, c
 
 // Outputs of those positions in arrival order, and their deferred requests to queue positions `kept`
 // onwards (order preserved); `kept` moves on by the number stored.
-template <int GR, int ROWS>
+template <int GR, int ROWS, int NQ>
 __device__ __forceinline__ void br_queue_store(const BrTailArgs &t, int inst, int lane, int j0, int q0, int qn,
-                                               const BrQueueGroup<GR, ROWS> &v, int &kept) {
+                                               const BrQueueGroup<GR, ROWS, NQ> &v, int &kept) {
   const int64_t qrow = (int64_t)inst * t.Q;
 #pragma unroll
   for (int u = 0; u < GR; ++u) {
@@ -279,6 +333,58 @@ __device__ __forceinline__ void br_assign_epilogue(int inst, int lane, int q0, i
     }
   });
   br_write_state(t, inst, lane, q0, qn, cnt, kept, Lcur, nn, rc);
+}
+
+// The same for BR-H, whose decode steps may have been applied to the old entries ahead of the round.  dead: BR_DEAD_WORDS(E).
+// The first rows are requested with the entries' words: a wait for a load waits for the stores before it too.
+template <int E, int NQ>
+__device__ __forceinline__ void br_assign_epilogue_ahead(int inst, int lane, int q0, int qn, int cnt, const int *bound, int Lcur,
+                                                         int nn, const BrRoundCounts &rc, float c0, const int *ahead, int *dead) {
+  const BrTailArgs t = br_tail_args();
+  constexpr int GR = E < 4 ? E : 4;
+  BrAhead h{nullptr, nullptr, nullptr, t.adv_t};
+  BrQueueWords<E> words;
+  br_queue_words<E>(t.qs, t.qo, t.qid, t.as, t.ao, t.aid, (int64_t)inst * t.Q, (int64_t)inst * t.arr_cap, lane, 0, q0, qn, words);
+  int kept = 0;
+  br_with_rows<true>(t, [&](auto rows) {
+    BrQueueGroup<GR, decltype(rows)::value, NQ> v;
+    auto load = [&](int j0) {
+      BrQueueWords<GR> w;
+#pragma unroll
+      for (int u = 0; u < GR; ++u) w.id[u] = words.id[j0 + u], w.sq[u] = words.sq[j0 + u], w.oq[u] = words.oq[j0 + u];
+      br_queue_load(t, inst, lane, j0, q0, qn, bound, v, &w);
+    };
+    load(0);
+    if (h.t > 0) {
+      h.lost = ahead, h.n0 = ahead + 2 * BR_WAVE;
+      int b[E];
+      bool short_one = false;
+#pragma unroll
+      for (int u = 0; u < E; ++u) {
+        const int i = u * BR_WAVE + lane;
+        b[u] = i < qn ? bound[i] : -1;
+        short_one |= b[u] >= 0 && max(words.oq[u], 1) <= h.t;
+      }
+      if (br_ballot(short_one) != 0ull) {
+        h.dead = dead;
+        br_dead_clear(lane, nn - h.n0[lane], BR_WAVE + 2 * E, dead);
+        br_wave_sync();
+#pragma unroll
+        for (int u = 0; u < E; ++u) br_dead_mark(h, b[u], words.sq[u], words.oq[u]);
+        br_wave_sync();
+      }
+    }
+#pragma unroll
+    for (int j0 = 0; j0 < E; j0 += GR) {
+      if (j0 * BR_WAVE < t.Q) {
+        if (j0 > 0) load(j0);
+        br_commit_store(t, inst, v, c0, h);
+        br_queue_store(t, inst, lane, j0, q0, qn, v, kept);
+      }
+    }
+  });
+  br_write_state(t, inst, lane, q0, qn, cnt, kept, Lcur, nn, rc, h.t == 0);  // statistics: the state right after the round
+  if (h.t > 0) br_ahead_workers(t, inst, lane, Lcur, nn, ahead, h);
 }
 
 // The epilogue on the four waves of a block (queues of up to 2048 entries): wave w owns the arrival positions
@@ -421,24 +527,6 @@ __device__ __forceinline__ void br_advance_cluster(int inst, int lane, int Lcur,
     split[4 + lane] = nn - nw;
     split[4 + BR_WAVE + lane] = dLw;
   }
-}
-
-// Decode steps of a BR-H cluster by the wave that has just routed it (lists of up to 256 slots whose prediction rows move
-// along; a SIMD's waves end their rounds one after the other, so the memory works for some while others route): Lcur, nn: load and list length of worker `lane` after the round; lds: BR_TAIL_WORDS of the wave's.
-#define BR_TAIL_WORDS (2 * BR_SEG_WORDS(1))
-__device__ __forceinline__ void br_advance_cluster_rows(int inst, int lane, int Lcur, int nn, int *lds) {
-  const BrParams p = br_late_params();
-  br_wave_sync();  // the round's own writes into the lists are read back below
-  br_with_row_unit(p.P, [&](auto unit, auto upr) {
-    using V = decltype(unit);
-    constexpr int UPR = decltype(upr)::value;
-    if (p.Bs <= 64)
-      br_advance_lists<16, 2, UPR, V>(p, p.adv_t, inst, lane, Lcur, nn, lds);
-    else if (p.Bs <= 128)
-      br_advance_lists<32, 2, UPR, V>(p, p.adv_t, inst, lane, Lcur, nn, lds);
-    else
-      br_advance_lists<64, 2, UPR, V>(p, p.adv_t, inst, lane, Lcur, nn, lds);
-  });
 }
 
 // ---------------------------------------------------------------- split step: round and decode step on two waves

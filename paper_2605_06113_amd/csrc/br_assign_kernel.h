@@ -51,10 +51,10 @@
 #include "br_subset_list.h"
 #include "br_score_wave.h"
 
-// LDS of a cluster whose queue holds up to EM * 64 entries: bound [EM * 64], list copy, slots [64], Stage-2 window and
+// LDS of a cluster whose queue holds up to EM * 64 entries: bound [EM * 64], list copy, slots [64], what BR-H lists lost ahead of the round, Stage-2 window and
 // table (BIGR), then the mailbox of shared subset searches and the bit rows of br_subset_dp.h where they are used
 #define BR_SEARCH_WORDS 1344
-#define BR_ROUND_WORDS(EM, BIGR) ((EM) * BR_WAVE + BR_LIST_WORDS(EM) + BR_WAVE + ((BIGR) ? 32 + BR_SEARCH_WORDS : 0))
+#define BR_ROUND_WORDS(EM, BIGR) ((EM) * BR_WAVE + BR_LIST_WORDS(EM) + BR_WAVE + ((EM) <= 8 && !(BIGR) ? BR_AHEAD_WORDS : 0) + ((BIGR) ? 32 + BR_SEARCH_WORDS : 0))
 // the same where the wave goes on to apply decode steps to its cluster's lists
 #define BR_ROUND_ADV_WORDS(EM) (BR_ROUND_WORDS(EM, false) > BR_PLAIN_WORDS ? BR_ROUND_WORDS(EM, false) : BR_PLAIN_WORDS)
 static_assert(BR_ROUND_WORDS(32, false) + BR_LIST_WORDS(32) >= 4 * BR_PLAIN_WORDS, "four waves share the lists' LDS");
@@ -877,11 +877,13 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
   static_assert(!COOP || EM == 32, "the four-wave sort covers 4 x 512 keys");
   constexpr bool BRH = HB > 0;
   constexpr int NH = HB + 1;
+  constexpr bool STEPS = BRH && EM <= 8 && !BIGR;  // decode steps may have been applied ahead of the round
   if (inst >= p.N) return;
   int *bound = lds;                              // [EM * 64] by arrival position: worker << 16 | slot, or -1
   int *lst = bound + EM * BR_WAVE;               // copy of the list
   int *slots = lst + BR_LIST_WORDS(EM);          // [64] requests of a bulk step in order of admission
-  int *win = slots + BR_WAVE;                // BIGR: [32] Stage-2 candidate window
+  int *ahead = slots + BR_WAVE;                  // EM <= 8, not BIGR: [BR_AHEAD_WORDS] (br_ahead_keep)
+  int *win = ahead;                              // BIGR: [32] Stage-2 candidate window
   int *hitab = win + 32;                         // BIGR: [BR_SEARCH_WORDS] subset-sum tables
   int *svc = hitab + BR_SEARCH_WORDS;            // BIGR, shared: [32] mailbox
   int *dprows = svc + (shared ? 32 : 0);         // BIGR, R_max > 16: bit rows of the subset search
@@ -935,7 +937,10 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
   br_round_state<HB>(p, lane, in.n, in.L, st);
   const int nn_start = st.nn;
   if constexpr (BRH) {
-    if (w == 0) br_store_margins<HB>(p, inst, lane, st);
+    if (w == 0) {
+      if (STEPS && p.adv_t > 0) br_ahead_keep(p, inst, lane, st.nn, ahead);  // (before the margins replace it)
+      br_store_margins<HB>(p, inst, lane, st);
+    }
   }
 
   BrRoundCounts rc = {};
@@ -1023,23 +1028,24 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
       }
     }
     if (!done) {
-      br_assign_epilogue<EM, BRH>(inst, lane, q0, qn, cnt, bound, st.Lh[0], st.nn, rc, c0, AHEAD ? &words : nullptr);
-      if constexpr (ADV && BRH)
-        br_advance_cluster_rows(inst, lane, st.Lh[0], st.nn, bound);
-      else if constexpr (ADV)
-        br_advance_cluster<ADV>(inst, lane, st.Lh[0], st.nn, lds);
+      if constexpr (STEPS)
+        br_assign_epilogue_ahead<EM, HB>(inst, lane, q0, qn, cnt, bound, st.Lh[0], st.nn, rc, c0, ahead, lst);
+      else
+        br_assign_epilogue<EM, BRH>(inst, lane, q0, qn, cnt, bound, st.Lh[0], st.nn, rc, c0, AHEAD ? &words : nullptr);
+      if constexpr (ADV) br_advance_cluster<ADV>(inst, lane, st.Lh[0], st.nn, lds);
     }
   }
 }
 
 // every wave of the block owns one cluster and its own slice of LDS; waves never meet at a barrier
 // The BR-H kernel for queues of up to 512 needs one register more than lets four waves share a SIMD
-// (a batch of 4096 clusters is four waves per SIMD): it is asked to fit.
+// (a batch of 4096 clusters is four waves per SIMD): it is asked to fit, and so is that for H <= 4 and queues of up to 256 (two
+// registers too many for five).
 // BIGR: candidate windows of 9..16 requests (R_max > 8); a separate instantiation so that the kernels for
 // the deployed window sizes keep their registers and code size.
 template <int E, int HB, int ADV, bool BIGR = false, bool DP = false>
 // `share` (BIGR, queues of up to 1024; BR-0: reachable sums only): one cluster per block, its four waves share the searches
-__global__ __launch_bounds__(256, (HB > 0 && E == 8 && !BIGR) ? 4 : ADV == 4 ? 6 : 1) void br_k_assign(BrParams p, BrArr a, BrOut o, int share) {
+__global__ __launch_bounds__(256, (HB > 0 && E == 8 && !BIGR) ? 4 : (HB == 4 && E == 4 && !BIGR) ? 5 : ADV == 4 ? 6 : 1) void br_k_assign(BrParams p, BrArr a, BrOut o, int share) {
   extern __shared__ int lds_all[];
   constexpr int WORDS = ADV ? BR_ROUND_ADV_WORDS(E) : BR_ROUND_WORDS(E, BIGR);
   const int w = threadIdx.x >> 6;

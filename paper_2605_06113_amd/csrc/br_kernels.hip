@@ -5,6 +5,7 @@
 #include "br_device.h"
 #include "br_advance_seg.h"
 #include "br_launch.h"
+#include "br_project.h"
 #include "br_score_wave.h"
 
 // ------------------------------------------------------------------ initialisation
@@ -146,13 +147,7 @@ __global__ __launch_bounds__(256) void br_k_advance(BrParams p, int t) {
   }
 }
 // The kernel is VALU-bound before it is HBM-bound (rocprofv3: ~500 vector instructions per wave with every
-// loop written for 8 offsets and run-time widths), so the horizon bucket HB (4 or 8 offsets beyond h = 0), EXACT
-// (H == HB: no per-offset conditions) and the kind of prediction row PK (0: a hazard per offset, 1: c_hat
-// itself first in the row, 2: the pair (p_fin, mu_rem)) are compile-time.  c_hat of one active request (Appendix "Short-horizon prediction interface"): the survival sum
-// of the hazards = E[min(r, H)] (eq. (two-stage)/(composite)) in sequential fp32, the p_fin gate and the floor
-// of Appendix "Refresh logic", clip to [1, H]; or eq. (composite) on a supplied (p_fin, mu_rem) with the same gate;
-// or the supplied / maintained value itself; all floored and clipped the same way.  A request counts kv + h at the offsets
-// h <= floor(c_hat) (h is an integer, so that is (float)h <= c_hat; a NaN counts nowhere): per offset the kv
+// loop written for 8 offsets and run-time widths), so HB, EXACT and PK (br_project.h) are compile-time.  Per offset the kv
 // part is summed in a register and over the wave, the count comes from a ballot.
 template <int NC, int RW, int HB, bool EXACT, int PK>
 __global__ __launch_bounds__(256) void br_k_project_rows(BrParams p) {
@@ -171,9 +166,8 @@ __global__ __launch_bounds__(256) void br_k_project_rows(BrParams p) {
   if (row0 >= rows) return;
   const int lane = br_lane();
   const int H1 = p.H + 1;
-  const float Hf = (float)p.H;
   int n_g[RW], kv[RW][NC];
-  float pr[RW][NC][HAZ ? HB : (PK == 2 ? 2 : 1)];
+  float pr[RW][NC][BR_ROW_FLOATS(HB, PK)];
 #pragma unroll
   for (int r = 0; r < RW; ++r) n_g[r] = row0 + r < rows ? p.n[row0 + r] : 0;
 #pragma unroll
@@ -211,29 +205,7 @@ __global__ __launch_bounds__(256) void br_k_project_rows(BrParams p) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const int j = c * BR_WAVE + lane;
-      float ch;
-      if constexpr (HAZ) {
-        float S = 1.0f;
-        ch = 0.0f;
-#pragma unroll
-        for (int q = 0; q < HB; ++q) {
-          if (EXACT || q < p.H) {
-            ch = __fadd_rn(ch, S);
-            S = __fmul_rn(S, __fsub_rn(1.0f, pr[r][c][q]));
-          }
-        }
-        const float pfin = __fsub_rn(1.0f, S);
-        if (p.gate > 0.0f && pfin < p.gate) ch = Hf;
-      } else if constexpr (PK == 2) {
-        const float pf = pr[r][c][0], mu = pr[r][c][1];
-        ch = __fadd_rn(__fmul_rn(__fsub_rn(1.0f, pf), Hf), __fmul_rn(pf, mu));
-        if (p.gate > 0.0f && pf < p.gate) ch = Hf;
-      } else {
-        ch = pr[r][c][0];
-      }
-      ch = ch < 1.0f ? 1.0f : ch;
-      ch = ch > Hf ? Hf : ch;
-      const int hm = (j < n_g[r] && ch >= 1.0f) ? (int)ch : -1;  // last offset the request counts at
+      const int hm = j < n_g[r] ? br_last_offset<HB, EXACT, PK>(p, pr[r][c]) : -1;
 #pragma unroll
       for (int h = 0; h <= HB; ++h) {
         if (EXACT || h <= p.H) {
@@ -251,6 +223,18 @@ __global__ __launch_bounds__(256) void br_k_project_rows(BrParams p) {
       }
     }
   }
+}
+
+// The same with p.adv_t decode steps applied to the lists as they stand, in one pass over them (br_project_lists).
+template <int LPL, int HB, bool EXACT, int PK>
+__global__ __launch_bounds__(256) void br_k_project_advance(BrParams p) {
+  constexpr int LPW = BR_WAVE / LPL;
+  const int wave = br_uniform((int)(threadIdx.x >> 6));
+  const int64_t row0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + wave) * LPW;
+  const int64_t rows = (int64_t)p.N * p.G;
+  if (row0 >= rows) return;
+  __shared__ __align__(16) int lds_all[4 * BR_SEG_WORDS(1)];
+  br_project_lists<LPL, HB, EXACT, PK>(p, row0, (int)min(rows - row0, (int64_t)LPW), br_lane(), lds_all + wave * BR_SEG_WORDS(1));
 }
 
 // Horizons beyond BR_HP (Appendix "Short-horizon prediction interface", eq. (wprofile-new)): a request counts
@@ -917,6 +901,53 @@ static void launch_project_rows(const BrParams &p, hipStream_t st) {
     launch_project_rows_h<NC, RW, 4, false>(p, st);
   else
     launch_project_rows_h<NC, RW, 8, false>(p, st);
+}
+
+template <int LPL, int HB, bool EXACT>
+static void launch_project_advance_h(const BrParams &p, hipStream_t st) {
+  const int64_t rows = (int64_t)p.N * p.G, per = 4 * (BR_WAVE / LPL);
+  const dim3 grid((unsigned)((rows + per - 1) / per)), block(256);
+  if (p.pred_mode == 0)
+    hipLaunchKernelGGL((br_k_project_advance<LPL, HB, EXACT, 0>), grid, block, 0, st, p);
+  else if (p.pred_mode == 3)
+    hipLaunchKernelGGL((br_k_project_advance<LPL, HB, EXACT, 2>), grid, block, 0, st, p);
+  else
+    hipLaunchKernelGGL((br_k_project_advance<LPL, HB, EXACT, 1>), grid, block, 0, st, p);
+}
+
+template <int LPL>
+static void launch_project_advance(const BrParams &p, hipStream_t st) {
+  if (p.H == 4)
+    launch_project_advance_h<LPL, 4, true>(p, st);
+  else if (p.H == 8)
+    launch_project_advance_h<LPL, 8, true>(p, st);
+  else if (p.H < 4)
+    launch_project_advance_h<LPL, 4, false>(p, st);
+  else
+    launch_project_advance_h<LPL, 8, false>(p, st);
+}
+
+// BR-H, H <= 8: decode steps in the projection's pass over the lists, where the rows are supplied (maintained estimates query the
+// history), lists fit br_project_lists and the round's kernel has the epilogue for it (queues of up to 512, windows of up to 8).  Whole pass, us, with the
+// decode steps behind the round (a launch of their own; from 2048 clusters on in the round's, which streamed lists and rows a second time while other
+// clusters were routed) / so, reductions asked for, offered load 0.8 and 1.3 times what the workers serve (one figure: see there):
+//   one step       1 cluster, G = 16, B = 96, H = 4 (0.8) 14.5 / 10.1    H = 8 (1.3) 21.3 / 17.6    256: 18.0 / 13.8, 31.3 / 27.8    1500: 30.7 / 26.4, 63.1 / 57.6
+//                  2400, G = 48, H = 4 (0.7) 103 / 96    4096, G = 16, H = 4 (0.7) 59.2 / 58.2    4096, G = 32, H = 4, pairs (1.3) 121 / 113    4500 (0.9) 147 / 138
+//   8 steps        4096, G = 16, H = 4 (1.3) 118 / 116    G = 32 237 / 213, without the gate 305 / 320    3000, G = 32, B = 144, H = 8 406 / 333
+//   16 to 40       1500, G = 32, H = 4 (0.8) 131 / 120    4096 (lookahead, 0.8) 237 / 228    2048, G = 64, H = 8 (0.9) 401 / 367
+//                  2048, G = 32, H = 8 (0.9) 316 / 327    2500, G = 32, B = 144, H = 4 (1.3) 287 / 291
+// Rounds of hundreds of admissions, above all without the gate, hid more of the second pass than the first one saves.
+bool br_project_advances(const BrParams &p) {
+  return p.H > 0 && p.H <= BR_HP && p.pred_mode != 2 && p.Bs <= 256 && p.Q <= 512 && p.R_max <= 8;
+}
+
+void br_launch_project_advance(const BrParams &p, hipStream_t st) {
+  if (p.Bs <= 64)
+    launch_project_advance<16>(p, st);
+  else if (p.Bs <= 128)
+    launch_project_advance<32>(p, st);
+  else
+    launch_project_advance<64>(p, st);
 }
 
 void br_launch_discounts(const BrParams &p, float gamma, hipStream_t st) {

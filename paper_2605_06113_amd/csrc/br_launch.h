@@ -15,6 +15,9 @@ void br_launch_load_init(const BrParams &p, const int32_t *n, const int32_t *kv,
                          hipStream_t st);
 void br_launch_advance(const BrParams &p, int t, hipStream_t st);
 void br_launch_project(const BrParams &p, hipStream_t st);
+// the same with p.adv_t decode steps applied to the lists as they stand, where br_project_advances
+bool br_project_advances(const BrParams &p);
+void br_launch_project_advance(const BrParams &p, hipStream_t st);
 // horizons beyond BR_HP: fills the discount table p.dl (once per context)
 void br_launch_discounts(const BrParams &p, float gamma, hipStream_t st);
 // `partials`: br_score_scratch_bytes() of device memory for the partial results of the tiled path, or null
@@ -65,7 +68,6 @@ inline bool br_block_serves(const BrParams &p, bool matrix) {
 void br_launch_route(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
 // BR-H (H <= BR_HP), Q <= 512: the same in one launch
 void br_launch_route_h(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
-bool br_route_h_advances(const BrParams &p, int t);  // t decode steps ride in that launch
 // batches below BR_FULL_BATCH_N without decode steps in the launch, queues of up to 512 (BR-0: 1024), windows of up to 8: the
 // round with the reductions (BR-0: and the matrix) on other waves of the cluster's block
 void br_launch_route_helped(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);

@@ -276,6 +276,22 @@ __device__ __forceinline__ void br_store_margins(const BrParams &p, int inst, in
   if (lane < p.G) p.minm[wrow] = mn;
 }
 
+// Decode steps applied ahead of the round (br_k_project_advance): what a worker's list lost and its load change, handed to
+// the round in the words of its margins, which the round is about to write (one offset at least beyond h = 0, so there are two).
+__device__ __forceinline__ void br_ahead_store(const BrParams &p, int64_t row, int lost, int dL) {
+  p.mh[row * (p.H + 1)] = lost;
+  p.mh[row * (p.H + 1) + 1] = dL;
+}
+// LDS of a cluster: [0..64) per worker: entries its list lost ahead of the round, [64..128) load change of the old entries,
+// [128..192) list length at the start of the step.
+#define BR_AHEAD_WORDS 192
+__device__ __forceinline__ void br_ahead_keep(const BrParams &p, int inst, int lane, int nn, int *ahead) {
+  const int64_t wrow = (int64_t)inst * p.G + (lane < p.G ? lane : 0);
+  ahead[lane] = p.mh[wrow * (p.H + 1)];
+  ahead[BR_WAVE + lane] = p.mh[wrow * (p.H + 1) + 1];
+  ahead[2 * BR_WAVE + lane] = nn;
+}
+
 // Loads of a cluster's worker words and queue lengths: everything that does not need the queue length, requested before
 // the first result is used (lanes without a worker read worker 0's words).
 template <int HB>

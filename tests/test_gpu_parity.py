@@ -1232,6 +1232,32 @@ def test_decode_with_prediction_rows_on_both_sides_of_the_lines(N, G, B, Q, H, p
     r.close()
 
 
+@pytest.mark.parametrize("N,G,B,Q,H,pred_mode,steps", [
+    (1, 1, 256, 512, 4, 0, 30), (2, 2, 200, 512, 8, 0, 60), (3, 5, 64, 256, 1, 0, 1), (2, 64, 12, 300, 2, 0, 3), (3, 16, 96, 512, 3, 0, 40),
+    (5, 3, 65, 64, 5, 0, 9), (2, 13, 128, 257, 6, 0, 12), (3, 7, 129, 200, 7, 0, 2), (4, 9, 3, 40, 8, 1, 5), (2, 1, 256, 400, 4, 3, 25),
+    (2, 33, 60, 512, 8, 3, 48), (2049, 2, 33, 60, 4, 1, 4),
+])
+def test_decode_steps_ahead_of_the_round(N, G, B, Q, H, pred_mode, steps):
+    """BR-H decode steps in the projection's pass over the lists: admissions behind the survivors, those that end within the steps among them
+    (more than a mask word's 32 and 64 of a worker where it has the slots), with and without outputs, without arrivals and without free slots."""
+    cfg, init, arr = wl.random_case(1500 + N + B + H, N=N, G=G, B=B, max_wait=Q, H=H, fill=0.5, n_wait=Q, pred_mode=pred_mode, gate_pfin=0.3)
+    arr.o[:, ::2] = 1 + arr.o[:, ::2] % steps         # every other admission leaves at once
+    init.rem[::2] = 1 + init.rem[::2] % (2 * steps)
+    if N > 1:
+        init.n[1, 0], init.rem[1, 0], init.kv[1, 0] = B, 500, np.maximum(init.kv[1, 0], 1)
+    _say(f"decode ahead N={N} G={G} B={B} Q={Q} H={H} mode={pred_mode} steps={steps}")
+    oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
+    for rnd in range(4):
+        a = wl.Arrivals(arr.count * (rnd != 2), arr.s, arr.o, arr.id, arr.pred)
+        ref = oc.route_step(a, want_prep=True)
+        out = r.route_step(a, matrix=rnd == 1, scores=rnd != 3, advance=steps)
+        compare_prep(ref, r.state(), f"decode ahead r{rnd}")
+        compare_outputs({k: v for k, v in ref.items() if k in out}, out, cfg, f"decode ahead r{rnd}")
+        oc.advance(steps)
+        compare_state(oc, r.state(), cfg, f"decode ahead r{rnd}")
+    r.close()
+
+
 def _lists_in_every_state(init, B, steps):
     """Workers whose list is empty, full and losing nothing, full and losing everything; requests that end within the steps."""
     G = init.n.shape[1]
