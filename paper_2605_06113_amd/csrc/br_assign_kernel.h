@@ -159,7 +159,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
   int n_alive = qn;
   int head = 0;        // entries consumed from the front (they read BR_ENTRY_GONE); the list is [head, head + n_alive)
   bool stale = true;   // the LDS copy of the list is out of date (consumed entries aside)
-  int stage1 = 0, pops = 0, guard = 0, wdrop = 0, admitted = 0;
+  int stage1 = 0, pops = 0, guard = 0, wdrop = 0;
 
   auto list_to_lds = [&]() {
     if (stale) {
@@ -311,7 +311,6 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
     nn += dk;
     S_tot -= k;
     n_alive -= k;
-    admitted += k;
   };
 
   auto drop_worker = [&](int g, int capg) {
@@ -411,7 +410,6 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
     br_wave_maxs(Mh);
     S_tot -= K;
     n_alive -= K;
-    admitted += K;
     tail_dirty = true;
     br_wave_sync();
     return K;
@@ -453,7 +451,6 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
       for (int j = 0; j < E; ++j) x[j] = lane * E + j < head ? BR_ENTRY_GONE : x[j];
       S_tot -= k0;
       n_alive -= k0;
-      admitted += k0;
       stage1 += k0;
     }
     br_wave_sync();
@@ -500,7 +497,9 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
   // instructions) and a scalar instruction that reads a vector result waits for four, so what is common goes straight
   // down.  In one loop with the window of eight a pop took 2400 to 3000 cycles alone on its SIMD, so 1250 to 1500 (1500 to 2000
   // through the guard).  Whole pass: 1531 clusters, G = 13, 10 admissions each 46.6 -> 42.7 us; 4096, G = 16, 6 admissions
-  // 48.9 -> 47.1; one, G = 64, a queue of 2048 under a watermark 52.9 -> 49.1.
+  // 48.9 -> 47.1; one, G = 64, a queue of 2048 under a watermark 52.9 -> 49.1.  With the turns' shared state cut down, lane masks formed
+  // by ballots alone and the score in one full-rate multiply-add (below) 1040 to 1330 and 1500 to 1800: 1531 clusters 33.6 -> 32.3, 4096
+  // 41.5 -> 41.2, with 250 admissions each and 48 steps 104.8 -> 103.3.
   if (!BIGR && p.R_max <= 4) {
     // all ones at the length of window entry b on the lanes whose mask holds it (an entry beyond R_max never; one beyond
     // the list reads as zero, so its masks repeat lower ones, which win)
@@ -511,21 +510,30 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
     const int limit = p.W > 0 ? p.W : 1 << 29;           // of a load (none: beyond every load and length)
     // length of the shortest waiting request as last looked up: it only rises, so a worker that cannot take a request of
     // this length is out for good; one that turns out to be too full when its turn comes has it looked up again
-    int shortest = p.W > 0 ? tail_len() : 0;
+    auto shortest_now = [&]() {
+      tail_dirty = true;
+      return tail_len();
+    };
+    int shortest = p.W > 0 ? shortest_now() : 0;
+    // What the turns carry on is kept to what they read, since what differs between their ends is copied at each: free slots in
+    // all, whether the LDS copy stands, which entry is the shortest are formed where they are asked for.
+    auto take = [&](unsigned key, int g, int slot) {  // sticky binding of list entry `key` to worker g
+      bound[IDX_MASK - (int)(key & IDX_MASK)] = (g << 16) | slot;
+      br_list_remove<E>(x, key);
+      if constexpr (BRH && E >= 16) stale = true;  // (pick reads the copy)
+    };
     // (every turn admits a request, sets a worker aside, or goes on to a lower free-slot count after such a turn)
-    for (int it = 0; it < 2 * bound_it && n_alive > 0 && S_tot > 0; ++it) {
+    for (int turns = 2 * bound_it; min(min(n_alive, capmax_cur), turns) > 0; --turns) {
       // priority (free slots, horizon-min margin), lowest index on ties.  Workers for which even the shortest request is
       // too long are set aside when their turn comes; those whose turn comes before the first other one's go together
       // (nothing is admitted in between).
       const int prio = (int)(((unsigned)lane_minm() << 6) | (unsigned)(63 - lane));
-      const bool member = cap == capmax_cur, takes = limit - Lh[0] >= shortest;
-      int top = br_wave_max(member && takes ? prio : -1);
-      const bool out = member && !takes && prio > top;
-      const unsigned long long outm = br_ballot(out);
-      if (__builtin_expect((outm != 0ull) | (top < 0), 0)) {
+      const unsigned long long members = br_ballot(cap == capmax_cur), takes = br_ballot(limit - Lh[0] >= shortest);
+      int top = br_wave_max(__builtin_amdgcn_inverse_ballot_w64(members & takes) ? prio : -1);
+      const unsigned long long outm = members & ~takes & br_ballot(prio > top);
+      if (__builtin_expect((outm | (unsigned long long)(unsigned)(top >> 31)) != 0ull, 0)) {  // (or no member)
         const int n_out = __builtin_popcountll(outm);
-        cap = out ? 0 : cap;
-        S_tot -= capmax_cur * n_out;
+        cap = __builtin_amdgcn_inverse_ballot_w64(outm) ? 0 : cap;
         wdrop += n_out;
         pops += n_out;
         guard += n_out;
@@ -552,7 +560,8 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
       unsigned mask;
       bool found;  // a subset scores above zero (the empty one scores zero: the guard's case like any other)
       if constexpr (!BRH) {
-        const int F = br_score0(G, mg[0], delta);
+        int F;  // br_score0 (the compiler loses sight of the factors' 24 bits in the loop and multiplies in quarter rate)
+        asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(F) : "v"(max(delta - mg[0], 0)), "v"(-G), "v"(delta));
         const int best = br_row0_max(ok ? F * 64 + (63 - lane) : INT32_MIN);
         found = best >= 64;
         mask = 63u - ((unsigned)best & 63u);
@@ -567,7 +576,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
         const int sum = __builtin_amdgcn_readlane(delta, (int)mask);
 #pragma unroll
         for (int b = 0; b < 4; ++b)
-          if (__builtin_expect((mask >> b) & 1u, 1)) bind(wv[b], g, slot++);  // slots follow the order of the window
+          if (__builtin_expect((mask >> b) & 1u, 1)) take(wv[b], g, slot++);  // slots follow the order of the window
         add_load(g, Lg, sum, __builtin_popcount(mask));
       } else {
         // starvation guard: the single best request anyway
@@ -588,9 +597,11 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
             int s_last = (int)(wv[0] >> BR_IDX_BITS);
 #pragma unroll
             for (int b = 1; b < 4; ++b) s_last = b < w ? (int)(wv[b] >> BR_IDX_BITS) : s_last;
-            const int K = min((int)__builtin_popcountll(br_ballot(member)), n_alive - w);
+            const bool member = __builtin_amdgcn_inverse_ballot_w64(members);
+            const int K = min((int)__builtin_popcountll(members), n_alive - w);
             if (K >= 3 && br_score0(G, mg[0], s_last) <= 0) {
               const int rank = rank_of(member ? (int)(((unsigned)Lh[0] << 6) | (unsigned)lane) : INT32_MAX);
+              stale = true;
               done = tail_bulk(member ? rank : BR_WAVE, 0, K, (G - 1) * s_last / G);
               if (done > 0) pops += done - 1, guard += done - 1;
             }
@@ -598,11 +609,11 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
         }
         if (done == 0) {
           if (some) {
-            bind(key, g, slot);
+            take(key, g, slot);
             add_load(g, Lg, (int)(key >> BR_IDX_BITS), 1);
           } else {
             drop_worker(g, capmax_cur);
-            shortest = tail_len();
+            shortest = shortest_now();
           }
         }
       }
@@ -846,7 +857,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
 #pragma unroll
   for (int h = 0; h < NH; ++h) st.Lh[h] = Lh[h];
   st.nn = nn;
-  rc.admitted = admitted;
+  rc.admitted = qn - n_alive;
   rc.stage1 = stage1;
   rc.pops = pops;
   rc.guard = guard;
