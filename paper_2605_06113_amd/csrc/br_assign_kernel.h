@@ -146,20 +146,13 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
   // rank of each member among the members by (load, index): lanes that are no members hold INT32_MAX
   auto rank_of = [&](int wkey) -> int {
     if (small) return br_row_rank(wkey);
-    int rank = 0;
-#pragma unroll
-    for (int u = 0; u < 32; ++u) rank += (__builtin_amdgcn_readlane(wkey, u) < wkey) ? 1 : 0;
-    if (G > 32) {  // lanes beyond G hold INT32_MAX and never count
-#pragma unroll
-      for (int u = 32; u < 64; ++u) rank += (__builtin_amdgcn_readlane(wkey, u) < wkey) ? 1 : 0;
-    }
-    return rank;
+    return G <= 32 ? br_wave_rank<false>(wkey) : br_wave_rank<true>(wkey);
   };
 
   int n_alive = qn;
   int head = 0;        // entries consumed from the front (they read BR_ENTRY_GONE); the list is [head, head + n_alive)
   bool stale = true;   // the LDS copy of the list is out of date (consumed entries aside)
-  int stage1 = 0, pops = 0, guard = 0, wdrop = 0;
+  int pops = 0, guard = 0, wdrop = 0;
 
   auto list_to_lds = [&]() {
     if (stale) {
@@ -291,9 +284,14 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
   };
 
   // sticky binding of list entry `key` to worker g
-  auto bind = [&](unsigned key, int g, int slot) {
+  auto take = [&](unsigned key, int g, int slot) {
     bound[IDX_MASK - (int)(key & IDX_MASK)] = (g << 16) | slot;  // every lane stores the same word: no lane masking needed
     br_list_remove<E>(x, key);
+    if constexpr (BRH && E >= 16) stale = true;  // (pick reads the copy)
+  };
+  // where the copy of the list and its shortest entry are looked at again
+  auto bind = [&](unsigned key, int g, int slot) {
+    take(key, g, slot);
     stale = true;
     tail_dirty |= key == tail_key;
   };
@@ -451,13 +449,10 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
       for (int j = 0; j < E; ++j) x[j] = lane * E + j < head ? BR_ENTRY_GONE : x[j];
       S_tot -= k0;
       n_alive -= k0;
-      stage1 += k0;
     }
     br_wave_sync();
     // the rest of the level in rank order
-    for (int r = k0; r < level;) {
-      if (!(S_tot > p.S_greedy && n_alive > 0)) break;
-      const int left = min(level - r, min(S_tot - p.S_greedy, n_alive));
+    for (int r = k0, end = kmaxp; r < end;) {  // (every admission takes one off what ends the stage and off the level alike)
       const int g = (int)__builtin_ctzll(br_ballot(rank == r));
       int Lg[NH], mg[NH];
       margins_of(g, Lg, mg);
@@ -467,22 +462,24 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
       if (__builtin_expect(!pick(mg, room, key, none_below), 0)) {
         drop_worker(g, capmax);
         ++r;
+        end = r + min(level - r, min(S_tot - p.S_greedy, n_alive));
         continue;
       }
-      if (none_below && tail_bulk_ok && left >= 3) {
-        const int done = tail_bulk(rank, r, left, -1);
+      if (none_below && tail_bulk_ok && end - r >= 3) {
+        const int done = tail_bulk(rank, r, end - r, -1);
         if (done > 0) {
-          stage1 += done;
           r += done;
           continue;
         }
       }
-      bind(key, g, __builtin_amdgcn_readlane(nn, g));
+      take(key, g, __builtin_amdgcn_readlane(nn, g));
+      stale = true;
       add_load(g, Lg, (int)(key >> BR_IDX_BITS), 1);
-      ++stage1;
       ++r;
     }
   }
+  const int stage1 = qn - n_alive;
+  tail_dirty = true;
 
   // ---- Stage 2: refined allocation over the workers that still have free slots
   if (head > 0 && n_alive > 0) {  // the window is read off the front of the list
@@ -517,11 +514,6 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
     int shortest = p.W > 0 ? shortest_now() : 0;
     // What the turns carry on is kept to what they read, since what differs between their ends is copied at each: free slots in
     // all, whether the LDS copy stands, which entry is the shortest are formed where they are asked for.
-    auto take = [&](unsigned key, int g, int slot) {  // sticky binding of list entry `key` to worker g
-      bound[IDX_MASK - (int)(key & IDX_MASK)] = (g << 16) | slot;
-      br_list_remove<E>(x, key);
-      if constexpr (BRH && E >= 16) stale = true;  // (pick reads the copy)
-    };
     // (every turn admits a request, sets a worker aside, or goes on to a lower free-slot count after such a turn)
     for (int turns = 2 * bound_it; min(min(n_alive, capmax_cur), turns) > 0; --turns) {
       // priority (free slots, horizon-min margin), lowest index on ties.  Workers for which even the shortest request is
