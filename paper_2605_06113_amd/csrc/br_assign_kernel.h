@@ -193,20 +193,21 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
       br_list_around<E>(x, T, hi, lo);
       none_below = lo == 0u;
       const int sh = (int)(hi >> BR_IDX_BITS), sl = (int)(lo >> BR_IDX_BITS);
-      const bool okh = (hi != 0u) & (hi != BR_ENTRY_GONE) & (sh < room1), okl = lo != 0u;
-      bool useh;
+      // each below zero where it speaks against the longer one: no such entry (0 or gone), too long; scored below the shorter one (equal: the lower position)
+      int longer = min((int)hi - 1, room1 - 1 - sh);
       if constexpr (BRH) {
         const int F = br_ord(br_scoreh(p, mg, lane == 0 ? sh : sl));
-        useh = okh & (!okl | (__builtin_amdgcn_readlane(F, 0) >= __builtin_amdgcn_readlane(F, 1)));  // (equal: the lower position)
+        longer = (lo == 0u) | (__builtin_amdgcn_readlane(F, 0) >= __builtin_amdgcn_readlane(F, 1)) ? longer : -1;
       } else {
-        useh = okh & (!okl | (sh - G * (sh - m) >= sl));
+        longer = min(longer, sh - G * (sh - m) - (lo != 0u ? sl : -(1 << 30)));
       }
+      const bool useh = longer >= 0;
       key = lo;
       if (useh) {  // the first of its length
         unsigned before;
         br_list_around<E>(x, (unsigned)(sh + 1) << BR_IDX_BITS, before, key);
       }
-      return okh | okl;
+      return key != 0u;
     }
     if constexpr (BRH) {
       none_below = false;
@@ -339,9 +340,8 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
     const int snext = __builtin_amdgcn_update_dpp(0, st_, 0x130, 0xF, 0xF, false);  // lane + 1
     // requests of equal length are contiguous; within such a run the order of admission is by
     // arrival, the reverse of the order of the lanes
-    const bool gs = valid && (lane == 0 || sprev != st_);
-    const bool ge = valid && (lane == nA - 1 || snext != st_);
-    const unsigned long long sm = br_ballot(gs), em = br_ballot(ge);
+    const unsigned long long last = 1ull << (nA - 1), here = last | (last - 1ull);
+    const unsigned long long sm = (br_ballot(sprev != st_) | 1ull) & here, em = (br_ballot(snext != st_) & here) | last;
     int T = BR_WAVE, ga = BR_WAVE;
     if (valid) {
       ga = 63 - (int)__builtin_clzll(sm & ((2ull << lane) - 1ull));
@@ -403,9 +403,13 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
       x[j] = pos < newend ? v : 0u;
     }
     stale |= part;
+    if constexpr (BRH) {
 #pragma unroll
-    for (int h = 0; h < NH; ++h) Mh[h] = Lh[h];
-    br_wave_maxs(Mh);
+      for (int h = 0; h < NH; ++h) Mh[h] = Lh[h];
+      br_wave_maxs(Mh);
+    } else {  // each of them became the envelope
+      Mh[0] = __builtin_amdgcn_readlane(Lh[0], (int)__builtin_ctzll(br_ballot(rank == r0 + K - 1)));
+    }
     S_tot -= K;
     n_alive -= K;
     tail_dirty = true;
@@ -423,11 +427,12 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
     if (capmax <= 0) break;
     // the level: workers sharing the largest free-slot count, ranked by (load, index); each is
     // picked exactly once, in rank order, before any other worker can reach this free-slot count
-    const bool member = cap == capmax;
+    const unsigned long long members = br_ballot(cap == capmax);
+    const bool member = __builtin_amdgcn_inverse_ballot_w64(members);
     const int wkey = member ? (int)(((unsigned)Lh[0] << 6) | (unsigned)lane) : INT32_MAX;
     int rank = rank_of(wkey);
     rank = member ? rank : BR_WAVE;  // (no member has rank 64)
-    const int level = __builtin_popcountll(br_ballot(member));
+    const int level = __builtin_popcountll(members);
     const int kmaxp = min(level, min(S_tot - p.S_greedy, n_alive));
     list_to_lds();
     const bool cand = rank < kmaxp;
