@@ -656,12 +656,15 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
     unsigned wv[8];
     int ws[8];
     int s_last = 0;  // smallest length in the window (its w-th entry)
+    int wl = 0;      // BIGR: the window, entry l on lane l (BR-0 up to 16 requests: on lane l of each row)
+    constexpr bool W16 = !BRH && !DP;
     if constexpr (BIGR) {
 #pragma unroll
       for (int j = 0; j < E; ++j)
         if (lane * E + j < 32) win[lane * E + j] = (int)x[j];
       br_wave_sync();
-      s_last = br_uniform(win[w - 1] >> BR_IDX_BITS);
+      wl = win[lane & (W16 ? 15 : 31)];  // (read once: what a pop looks up of it comes from here)
+      s_last = __builtin_amdgcn_readlane(wl, w - 1) >> BR_IDX_BITS;
     } else {
 #pragma unroll
       for (int b = 0; b < 8; ++b) {
@@ -694,15 +697,15 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
       if constexpr (BIGR) {
         int kmax = min(min(capmax, p.R_max), w);
         {
-          const int sum = br_min_sums(win, w, lane);
+          const int sum = br_rest_sums(wl, w, lane);
           float F, slack;
           if constexpr (BRH) {
             F = br_scoreh(p, mg, sum);
-            slack = 3.2e-6f * dscale * (float)(kmax * (br_uniform(win[0]) >> BR_IDX_BITS));
+            slack = 3.2e-6f * dscale * (float)(kmax * (__builtin_amdgcn_readlane(wl, 0) >> BR_IDX_BITS));
           } else {  // (scores of sums below 2^20 times G <= 64 stay below 2^26: rounded to float they keep their order up
             F = (float)br_score0(G, mg[0], min(sum, 1 << 20)), slack = 32.0f;  // to units of 8, and the slack covers those)
           }
-          kmax = br_useful_count(sum, F, slack, w > 16 ? min(room, BR_DP_MAX_SUM) : room, kmax, lane);
+          kmax = br_useful_rest(sum, F, slack, w > 16 ? min(room, BR_DP_MAX_SUM) : room, kmax, w, lane);
         }
         if ((BRH || DP) && w > 16) {
           // windows of 17..32 requests: reachable sums instead of masks (br_subset_dp.h)
@@ -715,17 +718,17 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
             for (int u = 0; u < 4; ++u) key[u] = br_score_key<BRH>(p, mg, delta[u]);
           };
           const bool listed = br_list_serves(w, kmax);
-          const int trips = ((listed ? br_list_size(w, kmax) : 1 << w) + 255) >> 8;  // of 256 masks each
-          const bool halves = !BRH && trips >= BR_HALVES_TRIPS;
+          // trips of 256 masks each (asked for only beyond the searches of few requests: a load from constant memory)
+          auto trips = [&]() { return ((listed ? br_list_size(w, kmax) : 1 << w) + 255) >> 8; };
           if (!BRH && !DP && br_few_serves(w, kmax)) {
-            br_subset_few(G, mg[0], win, w, kmax, room, lane, hitab, bestkey, bestmask);
+            br_subset_few(G, mg[0], wl, w, kmax, room, lane, hitab, bestkey, bestmask);
           } else if (kmax <= 3) {
             int mbest;
             br_wave_sync();
-            br_small_search<BRH || DP>(win, w, kmax, room, lane, score4, bestkey, mbest);
+            br_small_search<BRH || DP>(W16 ? wl : win[lane & 15], win, w, kmax, room, lane, score4, bestkey, mbest);
             bestmask = bestkey == BR_KEY_NONE ? 0u : (unsigned)mbest;
-          } else if (halves) {
-            br_subset_halves<!DP>(G, mg[0], win, w, kmax, room, lane, hitab, bestkey, bestmask);
+          } else if (!BRH && trips() >= BR_HALVES_TRIPS) {
+            br_subset_halves<!DP>(G, mg[0], wl, w, kmax, room, lane, hitab, bestkey, bestmask);
           } else {
             if (!listed) {
               const int nhi = w > 6 ? 1 << (w - 6) : 1;
@@ -737,7 +740,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
               }
             }
             int mbest;
-            const bool shared_scan = shared && trips >= BR_SHARE_TRIPS;
+            const bool shared_scan = shared && trips() >= BR_SHARE_TRIPS;
             if (shared_scan) {
               if (listed) br_list_tables(win, w, hitab, lane);
 #pragma unroll
@@ -834,7 +837,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
       int delta = 0;
       if constexpr (BIGR) {
         for (unsigned m = bestmask; m != 0u; m &= m - 1u) {
-          const unsigned key = (unsigned)br_uniform(win[__builtin_ctz(m)]);
+          const unsigned key = (unsigned)__builtin_amdgcn_readlane(wl, __builtin_ctz(m));
           bind(key, g, slot++);
           delta += (int)(key >> BR_IDX_BITS);
         }

@@ -115,14 +115,14 @@ __device__ __forceinline__ void br_few_walk(const int *lower, const int *upper, 
   }
 }
 
-__device__ __forceinline__ void br_subset_few(int G, int m, const int *win, int w, int kmax, int room, int lane, int *tab,
+__device__ __forceinline__ void br_subset_few(int G, int m, int wl, int w, int kmax, int room, int lane, int *tab,
                                               int &bestkey, unsigned &bestmask) {
   bestkey = BR_KEY_NONE, bestmask = 0u;
   if (room < 0) return;
   br_stay(lane);
   const unsigned place = br_few_places.v[lane];
   int lo[4], hi[4];
-  br_half_sums(win, w, BR_FEW_ABSENT, lane, lo, hi);
+  br_half_sums(wl, w, BR_FEW_ABSENT, lane, lo, hi);
   int *lower = tab, *upper = tab + 256 + 3;
 #pragma unroll
   for (int u = 0; u < 4; ++u) lower[(place >> (8 * u)) & 255u] = min(lo[u], BR_FEW_ABSENT) << 8;

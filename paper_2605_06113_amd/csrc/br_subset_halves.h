@@ -38,12 +38,12 @@ constexpr BrHalvesLists br_make_halves_lists() {
 static __device__ constexpr BrHalvesLists br_halves_lists = br_make_halves_lists();
 
 template <bool STAY>
-__device__ __forceinline__ void br_subset_halves(int G, int m, const int *win, int w, int kmax, int room, int lane, int *tab,
+__device__ __forceinline__ void br_subset_halves(int G, int m, int wl, int w, int kmax, int room, int lane, int *tab,
                                                  int &bestkey, unsigned &bestmask) {
   if constexpr (STAY) br_stay(lane);
   const int lists = br_halves_lists.v[lane & 15];
   int lo[4], hi[4];
-  br_half_sums(win, w, BR_HALVES_ABSENT, lane, lo, hi);
+  br_half_sums(wl, w, BR_HALVES_ABSENT, lane, lo, hi);
   const int pl = __builtin_popcount(lane);
   constexpr int pu[4] = {0, 1, 1, 2};
 

@@ -10,7 +10,8 @@
 // per 64 masks against 11 of the scan over all masks (br_bigr_scan), which therefore stays for kmax > w / 2 (at 8 of 16
 // the list still holds 39202 masks).
 // 1024 clusters, G = 16, window 16, 46 admissions in 19 pops each, whole pass: 505 us with the scan, 142 with the list
-// alone, 75 with the searches named above.
+// alone, 75 with the searches named above, 60 with sums of three to five requests formed (br_subset_few.h), 57 since a pop reads the
+// window from LDS once: what it looks up of it (smallest entry, sums, the requests it binds) waited for LDS each time.
 #pragma once
 
 #include "br_device.h"
@@ -89,6 +90,18 @@ __device__ __forceinline__ int br_min_sums(const int *win, int w, int lane) {
   return x;
 }
 
+// Sum of a window's entries from the lane's on, the w - lane smallest, for lanes below w; `wl`: the window, entry l on lane l (w <= 32).
+__device__ __forceinline__ int br_rest_sums(int wl, int w, int lane) {
+  const int s = lane < w ? wl >> BR_IDX_BITS : 0;
+  int x = s;
+  x += br_dpp<0x111>(0, x);       // row_shr:1
+  x += br_dpp<0x112>(0, x);       // row_shr:2
+  x += br_dpp<0x114>(0, x);       // row_shr:4
+  x += br_dpp<0x118>(0, x);       // row_shr:8
+  x += br_dpp<0x142, 0x2>(0, x);  // row_bcast:15 into row 1
+  return __builtin_amdgcn_readlane(x, 31) - x + s;
+}
+
 // Most requests a subset of the window can usefully hold, at most kmax.  Lane c - 1 passes the sum of the c smallest
 // entries and its score as computed; `slack` is four times the rounding bound of a score of any subset (0 for exact
 // scores).  The score is concave in the sum: when the c smallest entries score below the c - 1 smallest (by more than
@@ -101,11 +114,17 @@ __device__ __forceinline__ int br_useful_count(int sum, float F, float slack, in
   return bal != 0ull ? min(kmax, (int)__builtin_ctzll(bal)) : kmax;
 }
 
+// The same from br_rest_sums: lane w - c passes the sum of the c smallest entries.
+__device__ __forceinline__ int br_useful_rest(int sum, float F, float slack, int room, int kmax, int w, int lane) {
+  const float fewer = __int_as_float(br_dpp<0x130>(0, __float_as_int(F)));  // wave_shl:1
+  const unsigned long long bal = br_ballot(lane < w - 1 && (F < fewer - slack || sum > room));
+  return bal != 0ull ? min(kmax, w - 64 + (int)__builtin_clzll(bal)) : kmax;
+}
+
 // Sums of the window entries that the 256 values of a mask's lower (lo) and upper byte (hi) select, values lane, 64 +
-// lane, ... per lane; `absent` stands for the entries beyond a window of fewer than 16 (w > 8).
-__device__ __forceinline__ void br_half_sums(const int *win, int w, int absent, int lane, int (&lo)[4], int (&hi)[4]) {
-  const int at = win[lane & 15] >> BR_IDX_BITS;
-  const int mine = lane < w ? at : absent;
+// lane, ... per lane; `absent` stands for the entries beyond a window of fewer than 16 (w > 8).  wl: entry l on lane l < 16.
+__device__ __forceinline__ void br_half_sums(int wl, int w, int absent, int lane, int (&lo)[4], int (&hi)[4]) {
+  const int mine = lane < w ? wl >> BR_IDX_BITS : absent;
   auto length = [&](int b) { return __builtin_amdgcn_readlane(mine, b); };
   lo[0] = 0, hi[0] = 0;
 #pragma unroll
@@ -121,7 +140,7 @@ __device__ __forceinline__ void br_half_sums(const int *win, int w, int absent, 
 // The byte tables of a search: lower byte in tab[0..255], upper byte in tab[256..511].
 __device__ __forceinline__ void br_list_tables(const int *win, int w, int *tab, int lane) {
   int lo[4], hi[4];
-  br_half_sums(win, w, 0, lane, lo, hi);
+  br_half_sums(win[lane & 15], w, 0, lane, lo, hi);
 #pragma unroll
   for (int u = 0; u < 4; ++u) tab[u * BR_WAVE + lane] = lo[u], tab[256 + u * BR_WAVE + lane] = hi[u];
 }
@@ -158,10 +177,10 @@ static __device__ constexpr BrTriples br_triples = br_make_triples();
 
 // The search at kmax <= 3, windows of up to 16: single requests, pairs and triples read the window itself, without tables.
 // Lane (g, i) of 4 x 16 takes the pairs of i with 4g .. 4g + 3 (i with itself: the single request); triples come from
-// a list, on its way meanwhile (TRIPLES: BR-H).  A search of up to 136 / 696 subsets took 2300 / 3500 cycles by tables
+// a list, on its way meanwhile (TRIPLES: BR-H).  wl: entry lane & 15.  A search of up to 136 / 696 subsets took 2300 / 3500 cycles by tables
 // and mask list.
 template <bool TRIPLES, class Score>
-__device__ __forceinline__ void br_small_search(const int *win, int w, int kmax, int room, int lane, Score score, int &bk, int &bm) {
+__device__ __forceinline__ void br_small_search(int wl, const int *win, int w, int kmax, int room, int lane, Score score, int &bk, int &bm) {
   if constexpr (!TRIPLES) br_stay(lane);
   const int n3 = TRIPLES && kmax >= 3 ? br_mask_counts.at[w][3] : 0;
   unsigned e[3][4];
@@ -177,7 +196,7 @@ __device__ __forceinline__ void br_small_search(const int *win, int w, int kmax,
   int delta[4], key[4][4];
   const int i = lane & 15, j0 = (lane >> 4) * 4;
   {
-    const int si = win[i] >> BR_IDX_BITS;
+    const int si = wl >> BR_IDX_BITS;
     int sj[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) sj[u] = win[j0 + u] >> BR_IDX_BITS;
