@@ -225,7 +225,7 @@ int32_t br_init(const br_config *cfg, const br_init_state *init, br_ctx **out) {
   }
   volatile float aD = cfg->alpha * acc;
   p.dsum = acc;
-  p.pad = 0;
+  p.project = 0;
   p.aD = cfg->H > 0 ? (float)aD : 1.0f;
   p.beta = cfg->H > 0 ? cfg->beta : (float)cfg->G;
 
@@ -312,9 +312,6 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
   const bool fused_adv = p.H == 0 ? p.R_max <= 8 && (br_split_shape(p) || p.N >= BR_FULL_BATCH_N) : br_project_advances(p);
   const bool split_adv = adv_t > 0 && !fused_adv;
   p.adv_t = split_adv ? 0 : adv_t;
-  int32_t rc = BR_OK;
-  if (p.H > 0)
-    rc = enqueue(ctx, BR_K_PROJECT, [&] { p.adv_t > 0 ? br_launch_project_advance(p, ctx->st) : br_launch_project(p, ctx->st); }, br);
   // The reductions ride along in the assignment launch where its waves can take them, since a launch of their own would wait
   // in line before it: full batches on the round's wave, which goes on with the sorted list; smaller ones on other waves of the
   // cluster's block, which load (and sort) for themselves.  Not where few clusters have more work than that hides (br_score_in_tiles).
@@ -333,7 +330,12 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
   BrOut first = o;  // what the score kernels write
   if (split || together || coop || long_helped) first.best_g = nullptr, first.best_i = nullptr;
   if (matrix_too) first.F = nullptr;
-  if (rc == BR_OK && (first.F || first.best_g || first.best_i))
+  const bool score = first.F || first.best_g || first.best_i;
+  p.project = p.H > BR_HP && !score && br_long_projects(p);
+  int32_t rc = BR_OK;
+  if (p.H > 0 && !p.project)
+    rc = enqueue(ctx, BR_K_PROJECT, [&] { p.adv_t > 0 ? br_launch_project_advance(p, ctx->st) : br_launch_project(p, ctx->st); }, br);
+  if (rc == BR_OK && score)
     rc = enqueue(ctx, BR_K_SCORE, [&] { br_launch_score(p, a, first, partials, ctx->st); }, br);
   if (p.H > BR_HP ? !long_helped : p.H > 0 && block) o.best_g = nullptr, o.best_i = nullptr;  // (done)
   if (rc == BR_OK) {

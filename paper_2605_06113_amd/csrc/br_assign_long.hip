@@ -9,6 +9,13 @@ int br_long_waves(const BrParams &p) {
   return (long long)p.N * 4 <= room ? 4 : (long long)p.N * 2 <= room ? 2 : 1;
 }
 
+// Queues of up to 256, several waves a cluster: the blocks that route form the projections, where a launch of their own came before.
+// Whole pass, us, so / a launch of their own, H = 80 unless given, decode lists 90 % full: one cluster of 8 workers, H = 40 16.2 / 18.0, library-
+// maintained estimates 18.7 / 20.8; 100 clusters, G = 8 34.0 / 35.3; 256, G = 16 51.7 / 55.8; 1000, G = 24 72.1 / 75.1; 2048, G = 8 65.7 /
+// 69.4; G = 64, H = 48 340.5 / 339.8.  One wave a cluster loses what the more waves of a launch of its own hide (4096, G = 8 91.9 / 89.9; 6000,
+// H = 16 68.1 / 66.7), and with longer queues the round takes far longer than the projection (G = 32, Q = 512, H = 16 59.4 / 59.4).
+bool br_long_projects(const BrParams &p) { return p.Q <= 256 && br_long_waves(p) > 1; }
+
 // The reductions on the round's helper waves, up to 32 pairs (tile of 64 requests, worker) per wave that serves its searches; a pair
 // whose worker has a free slot is about 1200 cycles, and few of them hide behind the round (BR_LONG_ALONE: many).  Up to 256 clusters
 // have more waves for them (br_launch_assign_long_one).  Whole pass, us, a launch of their own / so, H = 80: one cluster, G = 8 21.8 / 19.4;

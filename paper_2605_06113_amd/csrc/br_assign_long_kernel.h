@@ -24,6 +24,8 @@
 //     score is concave in the length, the waiting set is sorted by length); only where more than 64 requests are left
 //     between the brackets is the whole waiting set scored.  2048 clusters, G = 8, H = 80, overloaded, with the
 //     register sort and margins kept while the envelope stands: whole pass 75.1 -> 71.2 us, one cluster 27.3 -> 26.0;
+//   - with queues of up to 256 and several waves a cluster the block forms the projections itself, before the round
+//     (br_long_projects): one cluster, G = 8, H = 80, whole pass 20.6 -> 18.8 us, 2048 clusters 69.4 -> 65.7;
 //   - Stage 2 goes straight to the starvation guard when the window's smallest entry scores clearly below
 //     zero (then every subset does).
 // Waiting set, sticky binding and epilogue are those of the short-horizon
@@ -39,6 +41,7 @@
 
 #include "br_device.h"
 #include "br_launch.h"
+#include "br_project.h"
 #include "br_sort.h"
 #include "br_assign_common.h"
 #include "br_subset_list.h"
@@ -218,6 +221,14 @@ __global__ __launch_bounds__(64 * (NW + XW), E == 4 && XW == 0 ? 4 : 1) void br_
   const int inst = (int)blockIdx.x;
   if (inst >= p.N) return;
   const int H1 = p.H + 1, HS = BR_HS(p.H);
+  constexpr bool PROJECTS = E == 4 && NW > 1;  // (br_long_projects)
+  if constexpr (PROJECTS) {
+    if (p.project) {
+      br_project_long<NW + XW>(p, inst, (int)threadIdx.x, lds);
+      if (p.pred_mode == 2 && threadIdx.x >= 64 * (NW + XW - 1)) lds[p.project] = __float_as_int(br_survival_start(p, br_lane()));
+      __syncthreads();  // what it wrote is in place, and its LDS free
+    }
+  }
   int *skey = lds;                  // [NP] sorted keys (s << 11 | 2047 - arrival position)
   int *adm = lds + NP;              // [NP] by sorted position: worker << 16 | slot, or -1
   int *who = lds + 2 * NP;          // [NP] by arrival position: worker << 16 | slot, or -1 (filled after the round)
@@ -308,7 +319,7 @@ __global__ __launch_bounds__(64 * (NW + XW), E == 4 && XW == 0 ? 4 : 1) void br_
   }
 
   float c0 = 0.0f;  // first estimate of a newly admitted request when the library maintains c_hat
-  if (p.pred_mode == 2) c0 = *p.c0;
+  if (p.pred_mode == 2) c0 = PROJECTS && p.project ? __int_as_float(lds[p.project]) : *p.c0;
 
   // ---- worker state: lane g holds worker g
   const bool act = lane < G;
@@ -1085,7 +1096,10 @@ void br_launch_assign_long_one(const BrParams &p, const BrArr &a, const BrOut &o
   const bool best = o.best_g || o.best_i;
   const size_t words = (size_t)3 * E * BR_WAVE + 2 * BR_WAVE + 3 * (size_t)HS + (((size_t)HS * BR_LSTRIDE(p.G) + 3) & ~(size_t)3) +
                        (p.R_max > 8 ? 1024 : 0) + (nw > 1 ? 16 : 0);
-  auto lds = [&](int waves) { return (words + (nw > 1 && best ? waves * BR_LONG_RED_WORDS(HS, p.G) : 0)) * sizeof(int); };
+  auto lds = [&](int waves) {
+    const size_t round = words + (nw > 1 && best ? waves * BR_LONG_RED_WORDS(HS, p.G) : 0);
+    return (p.project ? max(round, (size_t)BR_PROJECT_LONG_WORDS(p.G, HS, waves)) + 1 : round) * sizeof(int);
+  };
   const dim3 grid((unsigned)p.N), block(BR_WAVE * nw);
   // A CU to each cluster: more waves for the reductions, where 60 KB of LDS hold them.  Three alone take up to 96 pairs of 1200
   // cycles where a token watermark keeps slots free everywhere, and the round waits for them.  One cluster, whole pass, us, a launch
@@ -1093,13 +1107,18 @@ void br_launch_assign_long_one(const BrParams &p, const BrArr &a, const BrOut &o
   // Q = 512 34 / 43 / 33, G = 12, Q = 512 50 / 83 / 56; H = 128: G = 8, Q = 256 46 / 56 / 41, G = 12, Q = 512 55 / 99 / 64; workers nearly
   // full, H = 80: 28.1 / 21.6 / 22.0, 36.0 / 27.3 / 26.5, 28.4 / 22.8 / 22.8, 35.7 / 28.1 / 28.9.  (Q = 256: twelve more 36.6 / 55.4 under the
   // watermark, and 3 % slower on a lightly loaded cluster.)
+  auto with = [&](int waves) {  // the last word holds the estimate at age 0 when the blocks form the projections
+    BrParams q = p;
+    if (q.project) q.project = (int32_t)(lds(waves) / sizeof(int)) - 1;
+    return q;
+  };
   constexpr int XW = E == 8 ? 8 : E <= 16 ? 4 : 0;
   if (XW > 0 && best && p.N <= BR_LONG_EXTRA_MAX_N && lds(4 + XW) <= 60 * 1024)
-    hipLaunchKernelGGL((br_k_assign_long<E, 4, XW>), grid, dim3(BR_WAVE * (4 + XW)), lds(4 + XW), st, p, a, o);
+    hipLaunchKernelGGL((br_k_assign_long<E, 4, XW>), grid, dim3(BR_WAVE * (4 + XW)), lds(4 + XW), st, with(4 + XW), a, o);
   else if (nw == 4)
-    hipLaunchKernelGGL((br_k_assign_long<E, 4>), grid, block, lds(4), st, p, a, o);
+    hipLaunchKernelGGL((br_k_assign_long<E, 4>), grid, block, lds(4), st, with(4), a, o);
   else if (nw == 2)
-    hipLaunchKernelGGL((br_k_assign_long<E, 2>), grid, block, lds(2), st, p, a, o);
+    hipLaunchKernelGGL((br_k_assign_long<E, 2>), grid, block, lds(2), st, with(2), a, o);
   else
-    hipLaunchKernelGGL((br_k_assign_long<E, 1>), grid, block, lds(1), st, p, a, o);
+    hipLaunchKernelGGL((br_k_assign_long<E, 1>), grid, block, lds(1), st, with(1), a, o);
 }

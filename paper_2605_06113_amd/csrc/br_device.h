@@ -33,7 +33,7 @@ struct BrParams {
   int32_t *dp;              // R_max > 16: per-cluster areas for the subset search by reachable sums (br_subset_dp.h)
   float *c0;                // pred_mode 2: estimate at age 0, written by the projection of every round
   float dsum;               // sum of the discounts
-  int32_t pad;
+  int32_t project;          // long horizons: the round's blocks form the projections first
 };
 
 struct BrArr {  // arrivals of one round (device pointers, may be null when none)

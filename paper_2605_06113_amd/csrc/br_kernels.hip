@@ -237,116 +237,16 @@ __global__ __launch_bounds__(256) void br_k_project_advance(BrParams p) {
   br_project_lists<LPL, HB, EXACT, PK>(p, row0, (int)min(rows - row0, (int64_t)LPW), br_lane(), lds_all + wave * BR_SEG_WORDS(1));
 }
 
-// Horizons beyond BR_HP (Appendix "Short-horizon prediction interface", eq. (wprofile-new)): a request counts
-// kv + h at the offsets h <= c_hat, so one histogram of floor(c_hat) per worker (count and kv sum, in LDS) and
-// its suffix sums give L_g(k+h) = sum_{c >= h} kvsum[c] + h * sum_{c >= h} count[c] without a register per
-// offset.  Integer sums, so the order of accumulation does not matter.  One block per cluster: each wave takes
-// every fourth worker list and leaves its row in an LDS tile as well; then, with threads mapped to offsets,
-// the envelope M_h = max_g L_g(k+h) and the margins, and with threads mapped to workers the horizon-min
-// margin (short horizons: by the round's wave, br_store_margins).
-// The lists of a wave are taken in units of 64 slots with the next unit requested before the one in hand is used; suffix
-// sums are wave-wide DPP scans with lanes mapped to offsets in descending order (a walk over all bins on every lane took
-// 750 instructions per list).  2048 clusters, G = 8, B = 64, H = 80: 36 -> 10 us.  A last block writes the
-// estimate at age 0 that newly admitted requests get (pred_mode 2).
-#define BR_BINS 192  // offsets 0..BR_HL in whole waves
 __global__ __launch_bounds__(256) void br_k_project_long(BrParams p) {
   extern __shared__ int lds[];
-  const int wave = threadIdx.x >> 6, lane = br_lane(), tid = threadIdx.x;
-  const int inst = blockIdx.x;
-  if (inst == p.N) {
-    if (wave == 0) {
+  if ((int)blockIdx.x == p.N) {  // the estimate at age 0 that newly admitted requests get (pred_mode 2)
+    if (threadIdx.x < BR_WAVE) {
       const float c = br_survival(p, 0);
-      if (lane == 0) *p.c0 = c;
+      if (threadIdx.x == 0) *p.c0 = c;
     }
     return;
   }
-  const int G = p.G, H = p.H, H1 = H + 1, HS = BR_HS(H);
-  int *tile = lds;                                     // [G][HS] projections
-  int *sM = lds + G * HS;                              // [HS] envelope
-  int *cnt = sM + HS + wave * 2 * BR_BINS;             // this wave's histogram: requests whose last offset is c
-  int *kvs = cnt + BR_BINS;                            // ... and the sum of their kv
-  const float Hf = (float)H;
-  const int64_t row0 = (int64_t)inst * G;
-  const int mine = wave + 4 * lane;                    // lane i: length of this wave's i-th list
-  const int nn = mine < G ? min(max(p.n[row0 + mine], 0), p.B) : 0;
-#pragma unroll
-  for (int u = 0; u < BR_BINS / BR_WAVE; ++u) cnt[u * BR_WAVE + lane] = 0, kvs[u * BR_WAVE + lane] = 0;
-  br_wave_sync();
-  auto fetch = [&](int g, int j0, int &kv, float &c, float &c2) {  // (whole rows: no wait for the length)
-    const int64_t at = (row0 + g) * p.Bs + min(j0 + lane, p.Bs - 1);
-    kv = p.kv[at];
-    c = p.pred[at * p.P];  // pred_mode 1 and 2 keep c_hat first
-    c2 = p.pred_mode == 3 ? p.pred[at * p.P + 1] : 0.0f;
-  };
-  int kv_n = 0;
-  float c_n = 0.0f, c2_n = 0.0f;
-  if (wave < G) fetch(wave, 0, kv_n, c_n, c2_n);
-  for (int g = wave; g < G; g += 4) {
-    const int64_t row = row0 + g;
-    const int n = __builtin_amdgcn_readlane(nn, (g - wave) >> 2);
-    int topc = 0, topk = 0;  // requests that reach the last offset (the gate's anchor: the common case)
-    for (int j0 = 0; j0 < max(n, 1); j0 += BR_WAVE) {
-      const int j = j0 + lane;
-      const int kv = kv_n;
-      float c = c_n;
-      const float mu = c2_n;
-      const int gn = j0 + BR_WAVE < n ? g : g + 4, jn = j0 + BR_WAVE < n ? j0 + BR_WAVE : 0;  // the next unit
-      if (gn < G) fetch(gn, jn, kv_n, c_n, c2_n);
-      if (p.pred_mode == 3) {              // the pair (p_fin, mu_rem): eq. (composite) and the gate
-        const float pf = c;
-        c = __fadd_rn(__fmul_rn(__fsub_rn(1.0f, pf), Hf), __fmul_rn(pf, mu));
-        if (p.gate > 0.0f && pf < p.gate) c = Hf;
-      }
-      c = c < 1.0f ? 1.0f : c;
-      c = c > Hf ? Hf : c;
-      int hm = -1;
-      if (j < n && c >= 0.0f) hm = min((int)c, H);  // offsets h with (float)h <= c_hat are 0..floor(c_hat); a NaN counts nowhere
-      const bool top = hm == H;
-      topc += __builtin_popcountll(br_ballot(top));
-      topk += top ? kv : 0;
-      if (hm >= 0 && !top) {
-        atomicAdd(&cnt[hm], 1);
-        atomicAdd(&kvs[hm], kv);
-      }
-    }
-    topk = br_wave_sum(topk);
-    br_wave_sync();
-    // suffix sums: lane l of chunk u stands for offset 64 u + 63 - l; the chunks above are in the carry
-    int Cc = topc, Kc = topk;
-#pragma unroll
-    for (int u = BR_BINS / BR_WAVE - 1; u >= 0; --u) {
-      if (u * BR_WAVE < H1) {
-        const int h = u * BR_WAVE + 63 - lane;
-        const int C = br_scan_sum(cnt[h]) + Cc, K = br_scan_sum(kvs[h]) + Kc;
-        cnt[h] = 0, kvs[h] = 0;
-        Cc = __builtin_amdgcn_readlane(C, 63), Kc = __builtin_amdgcn_readlane(K, 63);
-        if (h < H1) {
-          const int v = K + h * C;
-          p.Lh[row * H1 + h] = v;
-          tile[g * HS + h] = v;
-        }
-      }
-    }
-    br_wave_sync();  // the histogram is filled again for this wave's next list
-  }
-  __syncthreads();
-  if (tid < H1) {  // thread = offset
-    int M = tile[tid];
-    for (int g = 1; g < G; ++g) M = max(M, tile[g * HS + tid]);
-    p.Mh[(int64_t)inst * H1 + tid] = M;
-    sM[tid] = M;
-  }
-  __syncthreads();
-  for (int g = wave; g < G; g += 4) {  // wave = worker, lane = offset
-    int mn = INT32_MAX;
-    for (int h = lane; h < H1; h += BR_WAVE) {
-      const int m = max(sM[h] - tile[g * HS + h], 0);
-      p.mh[(row0 + g) * H1 + h] = m;
-      mn = min(mn, m);
-    }
-    mn = br_wave_min(mn);
-    if (lane == 0) p.minm[row0 + g] = mn;
-  }
+  br_project_long<4>(p, (int)blockIdx.x, (int)threadIdx.x, lds);
 }
 
 // d = (1, gamma, ..., gamma^H) by repeated fp32 product (Sec. 4.1), zeros up to the padded length
@@ -956,7 +856,7 @@ void br_launch_discounts(const BrParams &p, float gamma, hipStream_t st) {
 
 void br_launch_project(const BrParams &p, hipStream_t st) {
   if (p.H > BR_HP) {  // projection, envelope and margins in one launch
-    const size_t lds = (((size_t)p.G + 1) * BR_HS(p.H) + 8 * BR_BINS) * sizeof(int);
+    const size_t lds = (size_t)BR_PROJECT_LONG_WORDS(p.G, BR_HS(p.H), 4) * sizeof(int);
     hipLaunchKernelGGL(br_k_project_long, dim3((unsigned)p.N + (p.pred_mode == 2 ? 1u : 0u)), dim3(256), lds, st, p);
     return;
   }

@@ -34,6 +34,8 @@ void br_launch_assign(const BrParams &p, const BrArr &a, const BrOut &o, hipStre
 void br_launch_assign_long(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
 // waves per cluster of that kernel (1, 2 or 4)
 int br_long_waves(const BrParams &p);
+// that kernel's blocks form the projections first, where nothing else needs them before it
+bool br_long_projects(const BrParams &p);
 // the snapshot reductions of these shapes ride on that kernel's helper waves (where o.best_g / o.best_i are set)
 bool br_long_helped(const BrParams &p);
 // candidate windows of 9..32 requests (H <= BR_HP); no fused decode steps

@@ -132,3 +132,121 @@ __device__ __forceinline__ void br_project_lists(const BrParams &p, int64_t row0
     }
   }
 }
+
+// Horizons beyond BR_HP (Appendix "Short-horizon prediction interface", eq. (wprofile-new)): a request counts
+// kv + h at the offsets h <= c_hat, so one histogram of floor(c_hat) per worker (count and kv sum, in LDS) and
+// its suffix sums give L_g(k+h) = sum_{c >= h} kvsum[c] + h * sum_{c >= h} count[c] without a register per
+// offset.  Integer sums, so the order of accumulation does not matter.  One block per cluster: each wave takes
+// every fourth worker list and leaves its row in an LDS tile as well; then, with threads mapped to offsets,
+// the envelope M_h = max_g L_g(k+h) and the margins, and with threads mapped to workers the horizon-min
+// margin (short horizons: by the round's wave, br_store_margins).
+// The lists of a wave are taken in units of 64 slots with the next unit requested before the one in hand is used; suffix
+// sums are wave-wide DPP scans with lanes mapped to offsets in descending order (a walk over all bins on every lane took
+// 750 instructions per list).  2048 clusters, G = 8, B = 64, H = 80: 36 -> 10 us.  By NW waves of a block, each in its own part of
+// LDS: in a launch of its own, or by those that go on with the cluster's round (br_k_assign_long).
+#define BR_BINS 192  // offsets 0..BR_HL in whole waves
+#define BR_PROJECT_LONG_WORDS(G, HS, NW) (((G) + 1) * (HS) + 2 * (NW) * BR_BINS)
+template <int NW>
+__device__ __forceinline__ void br_project_long(const BrParams &p, int inst, int tid, int *lds) {
+  const int wave = br_uniform(tid >> 6), lane = br_lane();
+  const int G = p.G, H = p.H, H1 = H + 1, HS = BR_HS(H);
+  int *tile = lds;                                     // [G][HS] projections
+  int *sM = lds + G * HS;                              // [HS] envelope
+  int *cnt = sM + HS + wave * 2 * BR_BINS;             // this wave's histogram: requests whose last offset is c
+  int *kvs = cnt + BR_BINS;                            // ... and the sum of their kv
+  const float Hf = (float)H;
+  const int64_t row0 = (int64_t)inst * G;
+  const int mine = wave + NW * lane;                    // lane i: length of this wave's i-th list
+  const int nn = mine < G ? min(max(p.n[row0 + mine], 0), p.B) : 0;
+#pragma unroll
+  for (int u = 0; u < BR_BINS / BR_WAVE; ++u) cnt[u * BR_WAVE + lane] = 0, kvs[u * BR_WAVE + lane] = 0;
+  br_wave_sync();
+  auto fetch = [&](int g, int j0, int &kv, float &c, float &c2) {  // (whole rows: no wait for the length)
+    const int64_t at = (row0 + g) * p.Bs + min(j0 + lane, p.Bs - 1);
+    kv = p.kv[at];
+    c = p.pred[at * p.P];  // pred_mode 1 and 2 keep c_hat first
+    c2 = p.pred_mode == 3 ? p.pred[at * p.P + 1] : 0.0f;
+  };
+  int kv_n = 0;
+  float c_n = 0.0f, c2_n = 0.0f;
+  if (wave < G) fetch(wave, 0, kv_n, c_n, c2_n);
+  for (int g = wave; g < G; g += NW) {
+    const int64_t row = row0 + g;
+    const int n = __builtin_amdgcn_readlane(nn, (g - wave) / NW);
+    int topc = 0, topk = 0;  // requests that reach the last offset (the gate's anchor: the common case)
+    for (int j0 = 0; j0 < max(n, 1); j0 += BR_WAVE) {
+      const int j = j0 + lane;
+      const int kv = kv_n;
+      float c = c_n;
+      const float mu = c2_n;
+      const int gn = j0 + BR_WAVE < n ? g : g + NW, jn = j0 + BR_WAVE < n ? j0 + BR_WAVE : 0;  // the next unit
+      if (gn < G) fetch(gn, jn, kv_n, c_n, c2_n);
+      if (p.pred_mode == 3) {              // the pair (p_fin, mu_rem): eq. (composite) and the gate
+        const float pf = c;
+        c = __fadd_rn(__fmul_rn(__fsub_rn(1.0f, pf), Hf), __fmul_rn(pf, mu));
+        if (p.gate > 0.0f && pf < p.gate) c = Hf;
+      }
+      c = c < 1.0f ? 1.0f : c;
+      c = c > Hf ? Hf : c;
+      int hm = -1;
+      if (j < n && c >= 0.0f) hm = min((int)c, H);  // offsets h with (float)h <= c_hat are 0..floor(c_hat); a NaN counts nowhere
+      const bool top = hm == H;
+      topc += __builtin_popcountll(br_ballot(top));
+      topk += top ? kv : 0;
+      if (hm >= 0 && !top) {
+        atomicAdd(&cnt[hm], 1);
+        atomicAdd(&kvs[hm], kv);
+      }
+    }
+    topk = br_wave_sum(topk);
+    br_wave_sync();
+    // suffix sums: lane l of chunk u stands for offset 64 u + 63 - l; the chunks above are in the carry
+    int Cc = topc, Kc = topk;
+#pragma unroll
+    for (int u = BR_BINS / BR_WAVE - 1; u >= 0; --u) {
+      if (u * BR_WAVE < H1) {
+        const int h = u * BR_WAVE + 63 - lane;
+        const int C = br_scan_sum(cnt[h]) + Cc, K = br_scan_sum(kvs[h]) + Kc;
+        cnt[h] = 0, kvs[h] = 0;
+        Cc = __builtin_amdgcn_readlane(C, 63), Kc = __builtin_amdgcn_readlane(K, 63);
+        if (h < H1) {
+          const int v = K + h * C;
+          p.Lh[row * H1 + h] = v;
+          tile[g * HS + h] = v;
+        }
+      }
+    }
+    br_wave_sync();  // the histogram is filled again for this wave's next list
+  }
+  __syncthreads();
+  for (int h = tid; h < H1; h += 64 * NW) {  // thread = offset
+    int M = tile[h];
+    for (int g = 1; g < G; ++g) M = max(M, tile[g * HS + h]);
+    p.Mh[(int64_t)inst * H1 + h] = M;
+    sM[h] = M;
+  }
+  __syncthreads();
+  for (int g = wave; g < G; g += NW) {  // wave = worker, lane = offset
+    int mn = INT32_MAX;
+    for (int h = lane; h < H1; h += BR_WAVE) {
+      const int m = max(sM[h] - tile[g * HS + h], 0);
+      p.mh[(row0 + g) * H1 + h] = m;
+      mn = min(mn, m);
+    }
+    mn = br_wave_min(mn);
+    if (lane == 0) p.minm[row0 + g] = mn;
+  }
+}
+
+// br_survival at age 0 by a whole wave: both ranks by 64 pivots a step, where a lane alone halves.
+__device__ __forceinline__ float br_survival_start(const BrParams &p, int lane) {
+  int step = p.hist_n > 0 ? 1 : 0, lo = 0, hi = 0;
+  while (step > 0 && (long long)step * BR_WAVE < p.hist_n) step *= BR_WAVE;
+  for (; step > 0; step /= BR_WAVE) {
+    const int a = lo + (lane + 1) * step, b = hi + (lane + 1) * step;
+    const int va = p.hist[min(a, p.hist_n) - 1], vb = p.hist[min(b, p.hist_n) - 1];
+    lo += step * __builtin_popcountll(br_ballot(a <= p.hist_n && va <= 0));
+    hi += step * __builtin_popcountll(br_ballot(b <= p.hist_n && vb <= p.H));
+  }
+  return br_survival_at(p, 0, lo, hi, p.hsum[lo], p.hsum[hi]);
+}

@@ -996,6 +996,33 @@ def test_long_horizon_reductions_of_short_queues(N, G, H, Q, wm):
     r.close()
 
 
+@pytest.mark.parametrize("N,G,B,Q,H,pred_mode,hist_n", [
+    (1, 8, 64, 256, 80, 2, 1000), (2, 1, 130, 64, 128, 3, 0), (3, 13, 65, 256, 63, 1, 0), (257, 5, 64, 130, 64, 2, 64), (4, 33, 20, 200, 127, 2, 4097),
+    (1025, 3, 70, 100, 128, 2, 1), (1100, 9, 129, 256, 9, 3, 0), (2049, 4, 20, 64, 80, 2, 65), (2, 8, 64, 257, 80, 2, 63),
+])
+def test_long_horizon_projections_by_the_round(N, G, B, Q, H, pred_mode, hist_n):
+    """Projections formed by the blocks that route: more lists than waves and fewer, lists in two and three turns, offsets beyond the block's
+    threads, the estimate at age 0 of histories around the pivots of a step; and the launches of their own they take the place of (the
+    matrix asked for, one wave a cluster, longer queues)."""
+    rng = np.random.default_rng(690 + H)
+    hist = np.sort(rng.integers(0, 3 * H, hist_n)).astype(np.int32) if hist_n else None
+    cfg, init, arr = wl.random_case(690 + N + G, N=N, G=G, B=B, max_wait=Q, H=H, fill=0.8, n_wait=min(Q, 4 * G), pred_mode=pred_mode, gate_pfin=0.3)
+    init.n[0, 0] = 0
+    init.n[N - 1, G - 1] = B
+    init.kv[N - 1, G - 1], init.rem[N - 1, G - 1] = np.maximum(init.kv[N - 1, G - 1], 1), np.maximum(init.rem[N - 1, G - 1], 3)
+    _say(f"long projections N={N} G={G} B={B} Q={Q} H={H} mode={pred_mode} hist={hist_n}")
+    oc, r = br_oracle.OracleCluster(cfg, init, hist=hist), binding.Router(cfg, init, hist=hist)
+    for rnd in range(3):
+        a = wl.Arrivals(arr.count * (rnd != 1), arr.s, arr.o, arr.id, arr.pred)
+        ref = oc.route_step(a, want_prep=True)
+        out = r.route_step(a, matrix=rnd == 2 and N < 100, scores=rnd != 1, advance=2)
+        compare_prep(ref, r.state(), f"long projections r{rnd}")
+        compare_outputs({k: v for k, v in ref.items() if k in out}, out, cfg, f"long projections r{rnd}")
+        oc.advance(2)
+        compare_state(oc, r.state(), cfg, f"long projections r{rnd}")
+    r.close()
+
+
 @pytest.mark.parametrize("beta", [-1.0, 0.05, 1e-4, 0.0])
 @pytest.mark.parametrize("G,H,Q,wm", [(24, 4, 200, 0), (5, 8, 300, 0), (33, 7, 130, 20000)])
 def test_horizon_best_worker_within_and_beyond_margins(G, H, Q, wm, beta):
