@@ -832,11 +832,13 @@ static void launch_project_advance(const BrParams &p, hipStream_t st) {
 // decode steps behind the round (a launch of their own; from 2048 clusters on in the round's, which streamed lists and rows a second time while other
 // clusters were routed) / so, reductions asked for, offered load 0.8 and 1.3 times what the workers serve (one figure: see there):
 //   one step       1 cluster, G = 16, B = 96, H = 4 (0.8) 14.5 / 10.1    H = 8 (1.3) 21.3 / 17.6    256: 18.0 / 13.8, 31.3 / 27.8    1500: 30.7 / 26.4, 63.1 / 57.6
-//                  2400, G = 48, H = 4 (0.7) 103 / 96    4096, G = 16, H = 4 (0.7) 59.2 / 58.2    4096, G = 32, H = 4, pairs (1.3) 121 / 113    4500 (0.9) 147 / 138
-//   8 steps        4096, G = 16, H = 4 (1.3) 118 / 116    G = 32 237 / 213, without the gate 305 / 320    3000, G = 32, B = 144, H = 8 406 / 333
-//   16 to 40       1500, G = 32, H = 4 (0.8) 131 / 120    4096 (lookahead, 0.8) 237 / 228    2048, G = 64, H = 8 (0.9) 401 / 367
-//                  2048, G = 32, H = 8 (0.9) 316 / 327    2500, G = 32, B = 144, H = 4 (1.3) 287 / 291
-// Rounds of hundreds of admissions, above all without the gate, hid more of the second pass than the first one saves.
+//                  2400, G = 48, H = 4 (0.7) 103 / 95    4096, G = 16, H = 4 (0.7) 59.0 / 57.9    4096, G = 32, H = 4, pairs (1.3) 121 / 112    4500 (0.9) 147 / 137
+//   8 steps        4096, G = 16, H = 4 (1.3) 118 / 114    G = 32 237 / 211    3000, G = 32, B = 144, H = 8 406 / 325
+//   16 to 40       1500, G = 32, H = 4 (0.8) 131 / 120    4096 (lookahead, 0.8) 236 / 216    2048, G = 64, H = 8 (0.9) 402 / 354
+//                  2048, G = 32, H = 8 (0.9) 316 / 306    2500, G = 32, B = 144, H = 4 (1.3) 286 / 280
+//   no gate        one step, 4096, G = 32, H = 4 (1.3) 175 / 167    8 steps, 1500 188 / 180; 4096, 70 % full (0.4) 139.9 / 139.1
+//                  8 steps, 4096, overloaded, in the round's launch / so: G = 32 306 / 312, G = 16 148 / 154 (a launch of their own 344, 169)
+// Rounds of hundreds of admissions without the gate differ most in length, and the short ones hid more of the second pass than the first one saves.
 bool br_project_advances(const BrParams &p) {
   return p.H > 0 && p.H <= BR_HP && p.pred_mode != 2 && p.Bs <= 256 && p.Q <= 512 && p.R_max <= 8;
 }
