@@ -114,43 +114,40 @@ __device__ __forceinline__ int br_row0_max(int x) {
 
 // Number of lanes whose key is below the caller's, among the wave's first 16, 32 or 64 (keys pairwise distinct, or INT32_MAX for
 // lanes that do not take part; the caller among them).  A row of 16 keys is turned past the lanes fifteen or sixteen times; a turn is two instructions: a
-// subtraction that reads the other lane, whose borrow the sum takes up (as a comparison, which cannot read another lane, it takes
-// four or five).  Stage 1 ranks the workers of every capacity level.  Whole pass, us, with comparisons (beyond 16 workers against each of 32 or 64 lanes read
-// out one by one) / so: 4096 clusters, G = 16, 250 admissions each 103.3 / 97.2; G = 32, H = 4 229 / 215.
-// One block each: a value has to be two wait states old before another lane's instruction reads it.
-#define BR_BELOW_TURN(K) "v_sub_co_u32_dpp %0, vcc, %2, %3 row_ror:" #K " row_mask:0xf bank_mask:0xf\n\tv_addc_co_u32 %1, vcc, 0, %1, vcc\n\t"
-#define BR_BELOW_TURNS                                                                                              \
-  BR_BELOW_TURN(1) BR_BELOW_TURN(2) BR_BELOW_TURN(3) BR_BELOW_TURN(4) BR_BELOW_TURN(5) BR_BELOW_TURN(6)             \
-  BR_BELOW_TURN(7) BR_BELOW_TURN(8) BR_BELOW_TURN(9) BR_BELOW_TURN(10) BR_BELOW_TURN(11) BR_BELOW_TURN(12)          \
-  BR_BELOW_TURN(13) BR_BELOW_TURN(14) BR_BELOW_TURN(15)
-__device__ __forceinline__ int br_row_rank(int key) {
-  int d, n = 0;
-  key ^= (int)0x80000000;  // (signed keys, an unsigned borrow)
-  asm("s_nop 1\n\t" BR_BELOW_TURNS : "=&v"(d), "+v"(n) : "v"(key), "v"(key) : "vcc");
-  return n;
+// subtraction that reads the other lane, and a shift that takes up its sign, to be counted at the end.  So keys have 31 bits (of a load beyond the stated range
+// the lower 25).  Stage 1 ranks the workers of every capacity level.  (A borrow that the next instruction adds up has to wait two states for it, four issue slots
+// a turn with the wait; a comparison, which cannot read another lane, takes four or five instructions.)
+template <int K>
+__device__ __forceinline__ unsigned br_below_turns(int other, int key, unsigned n) {
+  const int o = __builtin_amdgcn_mov_dpp(other, 0x120 + K, 0xF, 0xF, true);  // row_ror:K
+  n = __builtin_amdgcn_alignbit(n, (unsigned)(o - key), 31);
+  if constexpr (K < 15) return br_below_turns<K + 1>(other, key, n);
+  else return n;
 }
-// `other`: the keys of a row, at the same places; n: what was counted before
-__device__ __forceinline__ int br_row_below(int other, int key, int n) {
-  int d;
-  asm("v_sub_co_u32 %0, vcc, %2, %3\n\tv_addc_co_u32 %1, vcc, 0, %1, vcc\n\t" BR_BELOW_TURNS
-      : "=&v"(d), "+v"(n)
-      : "v"(other), "v"(key)
-      : "vcc");
-  return n;
+__device__ __forceinline__ int br_row_rank(int key) {
+  key &= INT32_MAX;
+  return __builtin_popcount(br_below_turns<1>(key, key, (unsigned)key) & 0x7fffu);
+}
+// two rows of keys, at the same places
+__device__ __forceinline__ int br_rows_below(int a, int b, int key) {
+  unsigned n = __builtin_amdgcn_alignbit((unsigned)key, (unsigned)(a - key), 31);
+  n = br_below_turns<1>(a, key, n);
+  n = __builtin_amdgcn_alignbit(n, (unsigned)(b - key), 31);
+  return __builtin_popcount(br_below_turns<1>(b, key, n));
 }
 template <bool ALL>  // of 64 lanes, else of the first 32
 __device__ __forceinline__ int br_wave_rank(int key) {
-  key ^= (int)0x80000000;
+  key &= INT32_MAX;
   const auto a = __builtin_amdgcn_permlane16_swap((unsigned)key, (unsigned)key, false, false);
   int low = (int)a[0], high = (int)a[1];  // rows 0, 0, 2, 2 and 1, 1, 3, 3
   int rank = 0;
   if constexpr (ALL) {
     const auto l = __builtin_amdgcn_permlane32_swap((unsigned)low, (unsigned)low, false, false);
     const auto h = __builtin_amdgcn_permlane32_swap((unsigned)high, (unsigned)high, false, false);
-    rank = br_row_below((int)h[1], key, br_row_below((int)l[1], key, 0));
+    rank = br_rows_below((int)l[1], (int)h[1], key);
     low = (int)l[0], high = (int)h[0];
   }
-  return br_row_below(high, key, br_row_below(low, key, rank));
+  return rank + br_rows_below(low, high, key);
 }
 
 // Maximum over the lane and all lanes below it.
