@@ -240,6 +240,10 @@ int32_t br_advance_decode(br_ctx *ctx, int32_t n_steps);
  * Otherwise the decode kernel follows as a launch of its own on the same stream.
  * Arguments, ownership and errors as for br_route_step; n_steps >= 0 (0: identical to
  * br_route_step), BR_EINVAL otherwise.
+ * BR_EHIP from a BR-H call whose decode steps ride in the projection's pass can mean that this pass is on the stream and the
+ * round is not.  Lists and lengths in the workspace then disagree until br_route_advance is called again with the same
+ * n_steps, outside a stream capture: it does the round and what is left of the step, on the arrivals that it is given.  Any
+ * other round or decode step on the context returns BR_EHIP until then.
  */
 int32_t br_route_advance(br_ctx *ctx, const br_arrivals *in, const br_step_out *out, int32_t n_steps);
 

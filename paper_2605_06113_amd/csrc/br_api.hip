@@ -103,6 +103,7 @@ struct br_ctx {
   int32_t static_hip;      // why it is null: the hipError_t of the failed look-up
   hipStream_t st;
   int32_t last_hip;
+  int32_t ahead;           // decode steps that a failed br_route_advance has applied to the old list entries without its round (0: none)
   bool prof;
   std::vector<EvPair> pending, spare;
   double ms[BR_NKERNELS];
@@ -116,24 +117,41 @@ int32_t fail_hip(br_ctx *ctx, hipError_t e) {
   return BR_EHIP;
 }
 
-// Enqueue one kernel; with profiling on, bracket it with an event pair on the same stream.
+// With profiling on: event pairs, and room to keep them, for `launches` kernels, so that a call that cannot have them ends before its first one.
+int32_t events_for(br_ctx *ctx, size_t launches) {
+  if (!ctx->prof) return BR_OK;
+  try {  // (`spare` takes what is pending once that is read)
+    const size_t most = ctx->spare.size() + ctx->pending.size() + launches;
+    if (ctx->spare.capacity() < most) ctx->spare.reserve(2 * most);
+    if (ctx->pending.capacity() < most) ctx->pending.reserve(2 * most);
+  } catch (...) {
+    return BR_ENOMEM;
+  }
+  while (ctx->spare.size() < launches) {
+    EvPair ev{};
+    hipError_t e = hipEventCreate(&ev.a);
+    if (e != hipSuccess) return fail_hip(ctx, e);
+    e = hipEventCreate(&ev.b);
+    if (e != hipSuccess) {
+      (void)hipEventDestroy(ev.a);
+      return fail_hip(ctx, e);
+    }
+    ctx->spare.push_back(ev);
+  }
+  return BR_OK;
+}
+
+// Enqueue one kernel; with profiling on, bracket it with an event pair on the same stream (events_for has it).  *launched: the kernel
+// is on the stream, whatever is returned.
 template <class Fn>
-int32_t enqueue(br_ctx *ctx, int kid, Fn &&fn, bool bracket = true) {
+int32_t enqueue(br_ctx *ctx, int kid, Fn &&fn, bool bracket = true, bool *launched = nullptr) {
   EvPair ev{};
   const bool prof = ctx->prof && bracket;
   if (prof) {
-    if (!ctx->spare.empty()) {
-      ev = ctx->spare.back();
-      ctx->spare.pop_back();
-    } else {
-      hipError_t e = hipEventCreate(&ev.a);
-      if (e != hipSuccess) return fail_hip(ctx, e);
-      e = hipEventCreate(&ev.b);
-      if (e != hipSuccess) {
-        (void)hipEventDestroy(ev.a);
-        return fail_hip(ctx, e);
-      }
-    }
+    const int32_t rc = events_for(ctx, 1);
+    if (rc != BR_OK) return rc;
+    ev = ctx->spare.back();
+    ctx->spare.pop_back();
     ev.kid = kid;
     hipError_t e = hipEventRecord(ev.a, ctx->st);
     if (e != hipSuccess) {
@@ -150,6 +168,7 @@ int32_t enqueue(br_ctx *ctx, int kid, Fn &&fn, bool bracket = true) {
     if (prof) ctx->spare.push_back(ev);
     return fail_hip(ctx, e);
   }
+  if (launched) *launched = true;
   if (prof) {
     e = hipEventRecord(ev.b, ctx->st);
     if (e != hipSuccess) {
@@ -159,6 +178,11 @@ int32_t enqueue(br_ctx *ctx, int kid, Fn &&fn, bool bracket = true) {
     ctx->pending.push_back(ev);
   }
   return BR_OK;
+}
+
+bool capturing(br_ctx *ctx) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(ctx->st, &s) == hipSuccess && s != hipStreamCaptureStatusNone;
 }
 
 }  // namespace
@@ -188,6 +212,7 @@ int32_t br_init(const br_config *cfg, const br_init_state *init, br_ctx **out) {
   ctx->lay = l;
   ctx->st = (hipStream_t)cfg->stream;
   ctx->last_hip = 0;
+  ctx->ahead = 0;
   ctx->prof = false;
   for (int k = 0; k < BR_NKERNELS; ++k) {
     ctx->ms[k] = 0.0;
@@ -271,6 +296,9 @@ int32_t br_init(const br_config *cfg, const br_init_state *init, br_ctx **out) {
 // the workspace, and no launch is bracketed by profiling events (creating one allocates)
 static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out, int32_t adv_t, bool fixed_scratch = false) {
   if (!ctx || adv_t < 0) return BR_EINVAL;
+  // a call that failed behind its projection: this one goes on from there, or nothing does (a graph would leave the projection out of every replay)
+  const bool resumed = ctx->ahead != 0;
+  if (resumed && (adv_t != ctx->ahead || capturing(ctx))) return BR_EHIP;
   const bool br = !fixed_scratch;
   int *partials = ctx->score_scratch;
   if (fixed_scratch) {
@@ -332,9 +360,10 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
   if (matrix_too) first.F = nullptr;
   const bool score = first.F || first.best_g || first.best_i;
   p.project = p.H > BR_HP && !score && br_long_projects(p);
-  int32_t rc = BR_OK;
-  if (p.H > 0 && !p.project)
-    rc = enqueue(ctx, BR_K_PROJECT, [&] { p.adv_t > 0 ? br_launch_project_advance(p, ctx->st) : br_launch_project(p, ctx->st); }, br);
+  int32_t rc = br ? events_for(ctx, 4) : BR_OK;
+  bool projected = resumed, routed = false;
+  if (rc == BR_OK && p.H > 0 && !p.project && !resumed)
+    rc = enqueue(ctx, BR_K_PROJECT, [&] { p.adv_t > 0 ? br_launch_project_advance(p, ctx->st) : br_launch_project(p, ctx->st); }, br, &projected);
   if (rc == BR_OK && score)
     rc = enqueue(ctx, BR_K_SCORE, [&] { br_launch_score(p, a, first, partials, ctx->st); }, br);
   if (p.H > BR_HP ? !long_helped : p.H > 0 && block) o.best_g = nullptr, o.best_i = nullptr;  // (done)
@@ -352,8 +381,10 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
         br_launch_route(p, a, o, ctx->st);
       else
         br_launch_assign(p, a, o, ctx->st);
-    }, br);
+    }, br, &routed);
   }
+  // the lists have had their decode steps but not the round that writes loads and lengths (a failed capture has run nothing)
+  if (projected && p.H > 0 && p.adv_t > 0) ctx->ahead = routed || (!resumed && capturing(ctx)) ? 0 : adv_t;
   if (rc == BR_OK && split_adv) rc = enqueue(ctx, BR_K_ADVANCE, [&] { br_launch_advance(p, adv_t, ctx->st); }, br);
   return rc;
 }
@@ -412,6 +443,7 @@ int32_t br_route_baseline(br_ctx *ctx, const br_arrivals *in, const br_step_out 
 int32_t br_advance_decode(br_ctx *ctx, int32_t n_steps) {
   if (!ctx || n_steps < 0) return BR_EINVAL;
   if (n_steps == 0) return BR_OK;
+  if (ctx->ahead != 0) return BR_EHIP;  // (a failed br_route_advance comes first)
   return enqueue(ctx, BR_K_ADVANCE, [&] { br_launch_advance(ctx->p, n_steps, ctx->st); });
 }
 
