@@ -129,6 +129,9 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
   constexpr int NP = E * BR_WAVE;
   constexpr bool BRH = HB > 0;
   constexpr int NH = HB + 1;
+  // (what ends a level's turns is looked up at each: carried along it put the kernels of queues beyond 256 two to four words a lane into scratch memory.  4096
+  // clusters, G = 16, H = 8, queues of 512, 8 steps, whole pass 181.5 -> 180.1 us, without reductions 172.1 -> 171.3; with shorter queues 188 against 179, 2048 clusters, 40 steps)
+  constexpr bool LESS = HB == 8 && E == 8;
   constexpr int IDX_MASK = (1 << BR_IDX_BITS) - 1;
   constexpr int BIAS2 = 1 << 24;               // subset of <= 8 requests: score in (-2^24, 2^18]
   const int G = p.G;
@@ -160,7 +163,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
       return rank;
     }
     if (small) return br_row_rank(wkey);
-    return G <= 32 ? br_wave_rank<false>(wkey) : br_wave_rank<true>(wkey);
+    return br_wave_rank(wkey, G > 32);
   };
 
   int n_alive = qn;
@@ -471,7 +474,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
     }
     br_wave_sync();
     // the rest of the level in rank order
-    for (int r = k0, end = kmaxp; r < end;) {  // (every admission takes one off what ends the stage and off the level alike)
+    for (int r = k0, end = kmaxp; LESS ? r < level && S_tot > p.S_greedy && n_alive > 0 : r < end;) {  // (every admission takes one off what ends the stage and off the level alike)
       const int g = (int)__builtin_ctzll(br_ballot(rank == r));
       int Lg[NH], mg[NH];
       margins_of(g, Lg, mg);
@@ -484,8 +487,9 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
         end = r + min(level - r, min(S_tot - p.S_greedy, n_alive));
         continue;
       }
-      if (none_below && tail_bulk_ok && end - r >= 3) {
-        const int done = tail_bulk(rank, r, end - r, -1);
+      const int left = LESS ? min(level - r, min(S_tot - p.S_greedy, n_alive)) : end - r;
+      if (none_below && tail_bulk_ok && left >= 3) {
+        const int done = tail_bulk(rank, r, left, -1);
         if (done > 0) {
           r += done;
           continue;
@@ -1063,14 +1067,15 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
 }
 
 // every wave of the block owns one cluster and its own slice of LDS; waves never meet at a barrier
-// The BR-H kernel for queues of up to 512 needs one register more than lets four waves share a SIMD
-// (a batch of 4096 clusters is four waves per SIMD): it is asked to fit, and so is that for H <= 4 and queues of up to 256 (two
-// registers too many for five).
+// The BR-H kernels need one or two registers more than let four waves share a SIMD
+// (a batch of 4096 clusters is four waves per SIMD): they are asked to fit, and so is that for H <= 4 and queues of up to 256 (two
+// registers too many for five).  H = 5..8, queues of up to 256, no reductions, 130 registers and three waves / 128 and four, whole pass, us: 4096 clusters, G = 16,
+// overloaded, H = 8, one step 107.3 / 99.7, H = 6, 16 steps 183.8 / 174.4; 3500, G = 40 142.4 / 134.6.
 // BIGR: candidate windows of 9..16 requests (R_max > 8); a separate instantiation so that the kernels for
 // the deployed window sizes keep their registers and code size.
 template <int E, int HB, int ADV, bool BIGR = false, bool DP = false>
 // `share` (BIGR, queues of up to 1024; BR-0: reachable sums only): one cluster per block, its four waves share the searches
-__global__ __launch_bounds__(256, (HB > 0 && E == 8 && !BIGR) ? 4 : (HB == 4 && E == 4 && !BIGR) ? 5 : ADV == 4 ? 6 : 1) void br_k_assign(BrParams p, BrArr a, BrOut o, int share) {
+__global__ __launch_bounds__(256, (HB > 0 && E == 8 && !BIGR) ? 4 : (HB > 0 && E == 4 && !BIGR) ? (HB == 4 ? 5 : 4) : ADV == 4 ? 6 : 1) void br_k_assign(BrParams p, BrArr a, BrOut o, int share) {
   extern __shared__ int lds_all[];
   constexpr int WORDS = ADV ? BR_ROUND_ADV_WORDS(E) : BR_ROUND_WORDS(E, BIGR);
   const int w = threadIdx.x >> 6;

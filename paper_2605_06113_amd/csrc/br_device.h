@@ -135,13 +135,12 @@ __device__ __forceinline__ int br_rows_below(int a, int b, int key) {
   n = __builtin_amdgcn_alignbit(n, (unsigned)(b - key), 31);
   return __builtin_popcount(br_below_turns<1>(b, key, n));
 }
-template <bool ALL>  // of 64 lanes, else of the first 32
-__device__ __forceinline__ int br_wave_rank(int key) {
+__device__ __forceinline__ int br_wave_rank(int key, bool all) {  // of 64 lanes, else of the first 32
   key &= INT32_MAX;
   const auto a = __builtin_amdgcn_permlane16_swap((unsigned)key, (unsigned)key, false, false);
   int low = (int)a[0], high = (int)a[1];  // rows 0, 0, 2, 2 and 1, 1, 3, 3
   int rank = 0;
-  if constexpr (ALL) {
+  if (all) {
     const auto l = __builtin_amdgcn_permlane32_swap((unsigned)low, (unsigned)low, false, false);
     const auto h = __builtin_amdgcn_permlane32_swap((unsigned)high, (unsigned)high, false, false);
     rank = br_rows_below((int)l[1], (int)h[1], key);
