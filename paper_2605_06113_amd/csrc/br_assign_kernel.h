@@ -487,9 +487,9 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
         end = r + min(level - r, min(S_tot - p.S_greedy, n_alive));
         continue;
       }
-      const int left = LESS ? min(level - r, min(S_tot - p.S_greedy, n_alive)) : end - r;
-      if (none_below && tail_bulk_ok && left >= 3) {
-        const int done = tail_bulk(rank, r, left, -1);
+      if constexpr (LESS) end = r + min(level - r, min(S_tot - p.S_greedy, n_alive));
+      if (none_below && tail_bulk_ok && end - r >= 3) {
+        const int done = tail_bulk(rank, r, end - r, -1);
         if (done > 0) {
           r += done;
           continue;
