@@ -236,7 +236,8 @@ int32_t br_advance_decode(br_ctx *ctx, int32_t n_steps);
  * With candidate windows of up to 8 requests other launches of the call apply the decode steps where that pays.  BR-0: in
  * batches of 2048 clusters and more the wave that routes a cluster also applies them to that cluster's lists, so that some
  * clusters stream their lists while others are routing; in smaller batches with queues of up to 512 a second wave per
- * cluster does.  BR-H (H <= 8, queues of up to 512, at most 256 slots, supplied predictions): the projection's pass over the lists does.
+ * cluster does.  BR-H (H <= 8, queues of up to 512, at most 256 slots, supplied predictions): the projection's pass over the lists does,
+ * or, in batches of some thousand clusters with many steps, the wave that has routed the cluster.
  * Otherwise the decode kernel follows as a launch of its own on the same stream.
  * Arguments, ownership and errors as for br_route_step; n_steps >= 0 (0: identical to
  * br_route_step), BR_EINVAL otherwise.

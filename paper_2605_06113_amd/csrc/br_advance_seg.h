@@ -1,6 +1,7 @@
 // Decode steps on worker lists of up to 256 slots: LPL lanes hold a list of up to 4 * LPL slots, four consecutive slots each,
-// so a wave holds 64 / LPL lists side by side.  Used by the decode kernel (br_k_advance_seg) and by the waves that
-// apply the decode steps to the lists of the cluster they have routed (br_advance_lists).  PK as for br_adv_apply.
+// so a wave holds 64 / LPL lists side by side.  Used by the decode kernel (br_k_advance_seg), by the waves that
+// apply the decode steps to the lists of the cluster they have routed (br_advance_lists) and by the projection that applies them
+// (br_project_lists).  PK as for br_adv_apply.
 // A list is made dense again in LDS and goes back with 16-byte stores, whether or not it lost a request: one path without
 // branches.  Bound by memory traffic, and before that by what a wave issues: storing word by word what had moved took
 // eight masked stores of single words per list beside two of whole lines.  Kernel, us, before and now: 4096 clusters, G = 16,
@@ -252,7 +253,69 @@ __device__ __forceinline__ void br_with_row_unit(int P, F &&body) {
     body(float{}, std::integral_constant<int, 0>{});
 }
 
-// The decode steps of one cluster's lists without prediction rows (BR-0; 4096 clusters, G = 16, B = 144, overloaded, a step per call: whole pass 46.9 us
+// The decode steps of one cluster whose lists (of up to 4 * LPL slots, rows of UPR units V) are this wave's: lane g holds load
+// and length of worker g.  What a wave alone moves per unit of time is what it has in flight over the memory's latency, and a
+// wait for a load waits for the stores before it too, so RW groups of lists are loaded, decided and stored at a time, with as
+// few waits as that takes: one where the rows are requested together with the slots, which is done while every list
+// loses requests (`ahead`), else two.  Groups of lists that lose nothing have no rows to wait for (4096 clusters, G = 32, B = 96,
+// H = 4, one step, lightly loaded: whole pass 98.1 us with that wait, 96.0 so); not with one list to a group, where the
+// requests of two lists would no longer be on their way together (40 steps, B = 144: 221 us, 214 without).
+// lds: RW * BR_SEG_WORDS(1) words of the wave's.
+template <int LPL, int RW, int UPR, class V>
+__device__ __forceinline__ void br_advance_lists(const BrParams &p, int t, int inst, int lane, int Lcur, int nn, int *lds) {
+  constexpr int LPW = BR_WAVE / LPL;
+  constexpr bool SKIP = LPL < BR_WAVE;
+  const BrSegBase b = br_seg_base(p, (int64_t)br_uniform(inst) * p.G);
+  auto batch = [&](int g0, auto ahead) -> bool {
+    constexpr bool AHEAD = decltype(ahead)::value;
+    BrSegSlots<1> v[RW];
+    V q[RW][4];
+    BrSegPlan d[RW];
+    int n[RW], list[RW];
+    bool ok[RW], all = true;
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+      const int g = g0 + r * LPW + lane / LPL;
+      ok[r] = g < p.G;
+      list[r] = ok[r] ? g : 0;
+      n[r] = __builtin_amdgcn_ds_bpermute(list[r] << 2, nn);
+      n[r] = ok[r] ? n[r] : 0;
+      br_seg_load<LPL, 1>(b, p.Bs, list[r], n[r], lane, v[r]);
+    }
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int r = 0; r < RW; ++r) br_seg_rows_ask<LPL, UPR, V>(b.pred, p.Bs, p.P, list[r], 0, n[r], lane, q[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+      int *words = lds + r * BR_SEG_WORDS(1);
+      br_seg_decide<LPL, 1>(p, t, n[r], lane, v[r], words, reinterpret_cast<short *>(words + BR_SEG_LIST_WORDS), d[r]);
+      all = all && (d[r].kept < n[r] || n[r] == 0);
+      if constexpr (AHEAD)
+        d[r].from = 0;
+      else if (!SKIP || d[r].any)
+        br_seg_rows_ask<LPL, UPR, V>(b.pred, p.Bs, p.P, list[r], d[r].from, n[r], lane, q[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+      const int L = __builtin_amdgcn_ds_bpermute(list[r] << 2, Lcur);
+      br_seg_store<LPL, 1>(b, p.Bs, list[r], lane, v[r], d[r], lds + r * BR_SEG_WORDS(1));
+      br_seg_worker<LPL>(b, t, list[r], ok[r], L, lane, d[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < RW; ++r)
+      if (AHEAD || !SKIP || d[r].any)
+        br_seg_rows_place<LPL, UPR, V>(b.pred, p.Bs, p.P, list[r], d[r].from, n[r],
+                                       reinterpret_cast<const short *>(lds + r * BR_SEG_WORDS(1) + BR_SEG_LIST_WORDS), lane, q[r]);
+    br_wave_sync();  // the words are rewritten by the next lists
+    return br_ballot(!all) == 0ull;
+  };
+  bool ahead = false;
+  for (int g0 = 0; g0 < p.G; g0 += RW * LPW)
+    ahead = ahead ? batch(g0, std::true_type{}) : batch(g0, std::false_type{});
+}
+
+// The same for lists without prediction rows (BR-0; 4096 clusters, G = 16, B = 144, overloaded, a step per call: whole pass 46.9 us
 // with lists one by one through masked single-word stores, 41.5 so; 48 steps and 250 admissions 111.5 and 105.9), workers [g0, g1): `done` gets each list's worker, plan and the lane that
 // holds both whole.  lds: two turns of BR_SEG_WORDS(0) of the wave's.
 template <int LPL, int RW, class F>

@@ -334,10 +334,13 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
   BrParams p = ctx->p;
   // Decode steps in the call's other launches: BR-0 on the two waves per cluster of the split kernel where it serves, and on
   // the wave that has routed the cluster for batches that fill the chip (4096 clusters, G = 16, B = 144: a step 39 us
-  // against 47 as two launches, 48 steps 104 against 116); BR-H in the projection's pass over the lists (br_project_advances).
+  // against 47 as two launches, 48 steps 104 against 116); BR-H in the projection's pass over the lists (br_project_advances), or
+  // on the wave that has routed the cluster (br_route_h_advances).
   // Everywhere else they follow as a launch of their own.  BR-0 with queues of
   // 513..1024 and fewer clusters takes about the same either way (512 clusters 22.1 us, 21.0 in one launch; 8 steps 42.9 and 42.0).
   const bool fused_adv = p.H == 0 ? p.R_max <= 8 && (br_split_shape(p) || p.N >= BR_FULL_BATCH_N) : br_project_advances(p);
+  const bool tail = p.H > 0 && adv_t > 0 && fused_adv && br_route_h_advances(p, adv_t);  // BR-H: by the round's waves
+  const bool ahead = p.H > 0 && adv_t > 0 && fused_adv && !tail;                         // by the projection
   const bool split_adv = adv_t > 0 && !fused_adv;
   p.adv_t = split_adv ? 0 : adv_t;
   // The reductions ride along in the assignment launch where its waves can take them, since a launch of their own would wait
@@ -363,7 +366,7 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
   int32_t rc = br ? events_for(ctx, 4) : BR_OK;
   bool projected = resumed, routed = false;
   if (rc == BR_OK && p.H > 0 && !p.project && !resumed)
-    rc = enqueue(ctx, BR_K_PROJECT, [&] { p.adv_t > 0 ? br_launch_project_advance(p, ctx->st) : br_launch_project(p, ctx->st); }, br, &projected);
+    rc = enqueue(ctx, BR_K_PROJECT, [&] { ahead ? br_launch_project_advance(p, ctx->st) : br_launch_project(p, ctx->st); }, br, &projected);
   if (rc == BR_OK && score)
     rc = enqueue(ctx, BR_K_SCORE, [&] { br_launch_score(p, a, first, partials, ctx->st); }, br);
   if (p.H > BR_HP ? !long_helped : p.H > 0 && block) o.best_g = nullptr, o.best_i = nullptr;  // (done)
@@ -375,8 +378,8 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
         br_launch_route_h_helped(p, a, o, ctx->st);
       else if (helped)
         br_launch_route_helped(p, a, o, ctx->st);
-      else if (p.H > 0 && together)
-        br_launch_route_h(p, a, o, ctx->st);
+      else if (p.H > 0 && (together || tail))
+        br_launch_route_h(p, a, o, tail, ctx->st);
       else if (together)
         br_launch_route(p, a, o, ctx->st);
       else
@@ -384,7 +387,7 @@ static int32_t route(br_ctx *ctx, const br_arrivals *in, const br_step_out *out,
     }, br, &routed);
   }
   // the lists have had their decode steps but not the round that writes loads and lengths (a failed capture has run nothing)
-  if (projected && p.H > 0 && p.adv_t > 0) ctx->ahead = routed || (!resumed && capturing(ctx)) ? 0 : adv_t;
+  if (projected && ahead) ctx->ahead = routed || (!resumed && capturing(ctx)) ? 0 : adv_t;
   if (rc == BR_OK && split_adv) rc = enqueue(ctx, BR_K_ADVANCE, [&] { br_launch_advance(p, adv_t, ctx->st); }, br);
   return rc;
 }

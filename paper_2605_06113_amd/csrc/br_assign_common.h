@@ -529,6 +529,24 @@ __device__ __forceinline__ void br_advance_cluster(int inst, int lane, int Lcur,
   }
 }
 
+// Decode steps of a BR-H cluster by the wave that has just routed it (lists of up to 256 slots whose prediction rows move
+// along; a SIMD's waves end their rounds one after the other, so the memory works for some while others route): Lcur, nn: load and list length of worker `lane` after the round; lds: BR_TAIL_WORDS of the wave's.
+#define BR_TAIL_WORDS (2 * BR_SEG_WORDS(1))
+__device__ __forceinline__ void br_advance_cluster_rows(int inst, int lane, int Lcur, int nn, int *lds) {
+  const BrParams p = br_late_params();
+  br_wave_sync();  // the round's own writes into the lists are read back below
+  br_with_row_unit(p.P, [&](auto unit, auto upr) {
+    using V = decltype(unit);
+    constexpr int UPR = decltype(upr)::value;
+    if (p.Bs <= 64)
+      br_advance_lists<16, 2, UPR, V>(p, p.adv_t, inst, lane, Lcur, nn, lds);
+    else if (p.Bs <= 128)
+      br_advance_lists<32, 2, UPR, V>(p, p.adv_t, inst, lane, Lcur, nn, lds);
+    else
+      br_advance_lists<64, 2, UPR, V>(p, p.adv_t, inst, lane, Lcur, nn, lds);
+  });
+}
+
 // ---------------------------------------------------------------- split step: round and decode step on two waves
 // In the split kernels (BR-0, queues of up to 512) the decode steps of a cluster's lists as they stand at the
 // start of the step are applied by a second wave (the helper) while the first runs the round; the wave that ran

@@ -33,7 +33,7 @@
 // (most free slots, then largest horizon-min margin, then lowest index); equal request scores
 // resolve to the lowest sorted position; equal subset scores to the lowest mask.
 //
-// ADV (BR-0): the wave goes on to apply the decode steps to the lists of the cluster it has routed
+// ADV: the wave goes on to apply the decode steps to the lists of the cluster it has routed
 // (br_route_advance); a separate instantiation, so that the two kinds of launch carry distinct
 // kernel names in profiles.
 #pragma once
@@ -886,7 +886,7 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
 // more are waiting.  COOP (EM = 32): the block has four waves; all of them sort a long waiting set together
 // (br_sort_desc_block4) and share the epilogue and the decode step, wave 0 runs the round; the others compute the snapshot
 // reductions meanwhile (one cluster, G = 64, H = 8, a queue of 2048: whole pass 49.1 -> 43.0 us against a launch of tiles and one that folds them).
-// ADV: decode steps after the round (0: none; BR-0: that many long lists at a time, see br_advance_lists_any).
+// ADV: decode steps after the round, on its wave (0: none; BR-0: that many long lists at a time, see br_advance_lists_any).
 // SCORES: the snapshot reductions (best_g / best_i where asked for) are taken on the way (br_score_wave.h).
 // `split`: the cluster's BR_SPLIT_WORDS of LDS where the decode steps of the old list entries are applied apart (by
 // another wave meanwhile, or by this one before the round), or null.
@@ -906,7 +906,7 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
   static_assert(!COOP || EM == 32, "the four-wave sort covers 4 x 512 keys");
   constexpr bool BRH = HB > 0;
   constexpr int NH = HB + 1;
-  constexpr bool STEPS = BRH && EM <= 8 && !BIGR;  // decode steps may have been applied ahead of the round
+  constexpr bool STEPS = BRH && EM <= 8 && !BIGR && !ADV;  // decode steps may have been applied ahead of the round
   if (inst >= p.N) return;
   int *bound = lds;                              // [EM * 64] by arrival position: worker << 16 | slot, or -1
   int *lst = bound + EM * BR_WAVE;               // copy of the list
@@ -1061,7 +1061,10 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
         br_assign_epilogue_ahead<EM, HB>(inst, lane, q0, qn, cnt, bound, st.Lh[0], st.nn, rc, c0, ahead, lst);
       else
         br_assign_epilogue<EM, BRH>(inst, lane, q0, qn, cnt, bound, st.Lh[0], st.nn, rc, c0, AHEAD ? &words : nullptr);
-      if constexpr (ADV) br_advance_cluster<ADV>(inst, lane, st.Lh[0], st.nn, lds);
+      if constexpr (ADV && BRH)
+        br_advance_cluster_rows(inst, lane, st.Lh[0], st.nn, bound);
+      else if constexpr (ADV)
+        br_advance_cluster<ADV>(inst, lane, st.Lh[0], st.nn, lds);
     }
   }
 }

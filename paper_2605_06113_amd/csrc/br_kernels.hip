@@ -828,17 +828,14 @@ static void launch_project_advance(const BrParams &p, hipStream_t st) {
 }
 
 // BR-H, H <= 8: decode steps in the projection's pass over the lists, where the rows are supplied (maintained estimates query the
-// history), lists fit br_project_lists and the round's kernel has the epilogue for it (queues of up to 512, windows of up to 8).  Whole pass, us, with the
-// decode steps behind the round (a launch of their own; from 2048 clusters on in the round's, which streamed lists and rows a second time while other
-// clusters were routed) / so, reductions asked for, offered load 0.8 and 1.3 times what the workers serve (one figure: see there):
-//   one step       1 cluster, G = 16, B = 96, H = 4 (0.8) 14.5 / 10.1    H = 8 (1.3) 21.3 / 17.6    256: 18.0 / 13.8, 31.3 / 27.8    1500: 30.7 / 26.4, 63.1 / 57.6
-//                  2400, G = 48, H = 4 (0.7) 103 / 95    4096, G = 16, H = 4 (0.7) 59.0 / 57.9    4096, G = 32, H = 4, pairs (1.3) 121 / 112    4500 (0.9) 147 / 137
-//   8 steps        4096, G = 16, H = 4 (1.3) 118 / 114    G = 32 237 / 211    3000, G = 32, B = 144, H = 8 406 / 325
-//   16 to 40       1500, G = 32, H = 4 (0.8) 131 / 120    4096 (lookahead, 0.8) 236 / 216    2048, G = 64, H = 8 (0.9) 402 / 354
-//                  2048, G = 32, H = 8 (0.9) 316 / 306    2500, G = 32, B = 144, H = 4 (1.3) 286 / 280
-//   no gate        one step, 4096, G = 32, H = 4 (1.3) 175 / 167    8 steps, 1500 188 / 180; 4096, 70 % full (0.4) 139.9 / 139.1
-//                  8 steps, 4096, overloaded, in the round's launch / so: G = 32 306 / 312, G = 16 148 / 154 (a launch of their own 344, 169)
-// Rounds of hundreds of admissions without the gate differ most in length, and the short ones hid more of the second pass than the first one saves.
+// history), lists fit br_project_lists and the round's kernel has the epilogue for it (queues of up to 512, windows of up to 8); some batches have them
+// in the round's launch instead (br_route_h_advances).  Whole pass, us, the same round, a launch of their own behind it / so, B = 96, gate on, reductions asked for,
+// offered load in brackets:
+//   one step    1 cluster, G = 16, H = 4 (0.8) 15.1 / 10.1    H = 8 (1.3) 19.9 / 15.3    256: 17.2 / 13.4, 28.1 / 24.0    1500: 30.0 / 24.9, 57.6 / 50.1
+//               2400, G = 48, H = 4 (0.7) 101 / 94.6    4096, G = 16, H = 4 (0.7, 1.3) 62.3 / 57.8, 85.6 / 78.1    G = 32, H = 4, pairs (1.3) 132 / 120    4500 (0.9) 148 / 139
+//   8 steps     1500, G = 32, H = 4 (1.3) 120 / 112, no gate 191 / 183    4096, G = 32, H = 4 (0.7, 1.3) 141 / 129, 238 / 210    3000, G = 32, B = 144, H = 8 (1.3) 405 / 327
+//   20 to 40    1500, G = 32, H = 4 (0.8) 90.3 / 79.1    4096 (0.7) 211 / 187    2048, G = 64, H = 8 (0.9) 423 / 353    G = 32 (0.7, 1.3) 180 / 158, 203 / 179
+// (42 batches at loads of 0.7 and 1.3, gate on and off, 1, 8 and 40 steps: nowhere slower, 2 to 28 %.)
 bool br_project_advances(const BrParams &p) {
   return p.H > 0 && p.H <= BR_HP && p.pred_mode != 2 && p.Bs <= 256 && p.Q <= 512 && p.R_max <= 8;
 }

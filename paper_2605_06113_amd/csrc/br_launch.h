@@ -69,7 +69,8 @@ inline bool br_block_serves(const BrParams &p, bool matrix) {
 // BR-0, Q <= 1024: snapshot reductions and assignment in one launch
 void br_launch_route(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
 // BR-H (H <= BR_HP), Q <= 512: the same in one launch
-void br_launch_route_h(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);
+void br_launch_route_h(const BrParams &p, const BrArr &a, const BrOut &o, bool steps, hipStream_t st);  // steps: p.adv_t decode steps by its waves
+bool br_route_h_advances(const BrParams &p, int t);  // t decode steps there and not in the projection (br_project_advances)
 // batches below BR_FULL_BATCH_N without decode steps in the launch, queues of up to 512 (BR-0: 1024), windows of up to 8: the
 // round with the reductions (BR-0: and the matrix) on other waves of the cluster's block
 void br_launch_route_helped(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st);

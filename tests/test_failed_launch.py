@@ -88,7 +88,11 @@ class Library:
         self.fake.stand_in(launch, create, record, capture)
         rc = getattr(self.lib, name)(self.ctx, *args)
         self.fake.stand_in(0, 0, 0, 0)
-        return rc, re.findall(r"br_k_[a-z_0-9]*[a-z]", self.fake.stand_in_log().decode())
+        self.log = self.fake.stand_in_log().decode()
+        return rc, re.findall(r"br_k_[a-z_0-9]*[a-z]", self.log)
+
+    def free(self):
+        self.lib.br_free(self.ctx)
 
     def advance(self, steps, scores=False, **fail):
         out = self.binding.StepOut(best_g=1 << 30, best_i=1 << 30) if scores else self.binding.StepOut()

@@ -10,8 +10,10 @@ REPORT = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))
 WAVES = {
     "_Z11br_k_assignILi4ELi4ELi0ELb0ELb0E": 5, "_Z11br_k_assignILi8ELi4ELi0ELb0ELb0E": 4,   # no reductions
     "_Z11br_k_assignILi4ELi8ELi0ELb0ELb0E": 4, "_Z11br_k_assignILi8ELi8ELi0ELb0ELb0E": 4,
-    "_Z12br_k_route_hILi4ELi4E": 5, "_Z12br_k_route_hILi8ELi4E": 4,                         # with reductions
-    "_Z12br_k_route_hILi4ELi8E": 4, "_Z12br_k_route_hILi8ELi8E": 4,
+    "_Z12br_k_route_hILi4ELi4ELb0E": 5, "_Z12br_k_route_hILi8ELi4ELb0E": 4,                 # with reductions
+    "_Z12br_k_route_hILi4ELi8ELb0E": 4, "_Z12br_k_route_hILi8ELi8ELb0E": 4,
+    "_Z12br_k_route_hILi4ELi4ELb1E": 4, "_Z12br_k_route_hILi8ELi4ELb1E": 4,                 # and decode steps
+    "_Z12br_k_route_hILi4ELi8ELb1E": 4, "_Z12br_k_route_hILi8ELi8ELb1E": 4,
     "_Z17br_k_route_helpedILi4ELi4E": 5, "_Z17br_k_route_helpedILi8ELi4E": 5,               # below 2048 clusters
     "_Z17br_k_route_helpedILi4ELi8E": 4, "_Z17br_k_route_helpedILi8ELi8E": 4,
     "_Z16br_k_assign_longILi4ELi4ELi0E": 4, "_Z16br_k_assign_longILi4ELi2ELi0E": 4, "_Z16br_k_assign_longILi4ELi1ELi0E": 4,
