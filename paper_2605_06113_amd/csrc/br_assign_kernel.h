@@ -148,20 +148,6 @@ __device__ __forceinline__ void br_round(const BrParams &p, int inst, int lane, 
   };
   // rank of each member among the members by (load, index): lanes that are no members hold INT32_MAX
   auto rank_of = [&](int wkey) -> int {
-    if constexpr (E >= 16) {  // (one cluster of 64 workers, queue of 2048: the round 31.3 us, by row turns 31.9: nothing else runs beside it)
-      int rank = 0;
-#pragma unroll
-      for (int u = 0; u < 16; ++u) rank += (__builtin_amdgcn_readlane(wkey, u) < wkey) ? 1 : 0;
-      if (G > 16) {  // lanes beyond G hold INT32_MAX and never count
-#pragma unroll
-        for (int u = 16; u < 32; ++u) rank += (__builtin_amdgcn_readlane(wkey, u) < wkey) ? 1 : 0;
-      }
-      if (G > 32) {
-#pragma unroll
-        for (int u = 32; u < 64; ++u) rank += (__builtin_amdgcn_readlane(wkey, u) < wkey) ? 1 : 0;
-      }
-      return rank;
-    }
     if (small) return br_row_rank(wkey);
     return br_wave_rank(wkey, G > 32);
   };
