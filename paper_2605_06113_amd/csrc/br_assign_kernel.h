@@ -897,7 +897,7 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
   int *bound = lds;                              // [EM * 64] by arrival position: worker << 16 | slot, or -1
   int *lst = bound + EM * BR_WAVE;               // copy of the list
   int *slots = lst + BR_LIST_WORDS(EM);          // [64] requests of a bulk step in order of admission
-  int *ahead = slots + BR_WAVE;                  // EM <= 8, not BIGR: [BR_AHEAD_WORDS] (br_ahead_keep)
+  int *ahead = slots + BR_WAVE;                  // EM <= 8, not BIGR: [BR_AHEAD_WORDS] (br_ahead_store)
   int *win = ahead;                              // BIGR: [32] Stage-2 candidate window
   int *hitab = win + 32;                         // BIGR: [BR_SEARCH_WORDS] subset-sum tables
   int *svc = hitab + BR_SEARCH_WORDS;            // BIGR, shared: [32] mailbox
@@ -931,7 +931,7 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
   const int G = p.G;
   // two memory round trips for the cluster: these words, then the waiting set
   BrClusterIn<HB> in;
-  br_cluster_load<HB>(p, a, inst, lane, in);
+  br_cluster_load<HB, STEPS>(p, a, inst, lane, in);
   const int q0 = in.q0, cnt = in.cnt;
   const int qn = q0 + min(cnt, p.Q - q0);
 
@@ -953,7 +953,7 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
   const int nn_start = st.nn;
   if constexpr (BRH) {
     if (w == 0) {
-      if (STEPS && p.adv_t > 0) br_ahead_keep(p, inst, lane, st.nn, ahead);  // (before the margins replace it)
+      if (STEPS && p.adv_t > 0) ahead[lane] = in.lost, ahead[BR_WAVE + lane] = in.dL, ahead[2 * BR_WAVE + lane] = st.nn;  // (the margins replace it in memory)
       br_store_margins<HB>(p, inst, lane, st);
     }
   }

@@ -285,20 +285,14 @@ __device__ __forceinline__ void br_ahead_store(const BrParams &p, int64_t row, i
 // LDS of a cluster: [0..64) per worker: entries its list lost ahead of the round, [64..128) load change of the old entries,
 // [128..192) list length at the start of the step.
 #define BR_AHEAD_WORDS 192
-__device__ __forceinline__ void br_ahead_keep(const BrParams &p, int inst, int lane, int nn, int *ahead) {
-  const int64_t wrow = (int64_t)inst * p.G + (lane < p.G ? lane : 0);
-  ahead[lane] = p.mh[wrow * (p.H + 1)];
-  ahead[BR_WAVE + lane] = p.mh[wrow * (p.H + 1) + 1];
-  ahead[2 * BR_WAVE + lane] = nn;
-}
 
 // Loads of a cluster's worker words and queue lengths: everything that does not need the queue length, requested before
-// the first result is used (lanes without a worker read worker 0's words).
+// the first result is used (lanes without a worker read worker 0's words).  STEPS: with what br_ahead_store left, if it did.
 template <int HB>
 struct BrClusterIn {
-  int q0, cnt, n, L[HB + 1];
+  int q0, cnt, n, L[HB + 1], lost, dL;
 };
-template <int HB>
+template <int HB, bool STEPS = false>
 __device__ __forceinline__ void br_cluster_load(const BrParams &p, const BrArr &a, int inst, int lane, BrClusterIn<HB> &in) {
   const int64_t wrow = (int64_t)inst * p.G + (lane < p.G ? lane : 0);
   const int q0 = p.qlen[inst], cnt = a.count ? a.count[inst] : 0;
@@ -308,6 +302,10 @@ __device__ __forceinline__ void br_cluster_load(const BrParams &p, const BrArr &
   } else {
 #pragma unroll
     for (int h = 0; h <= HB; ++h) in.L[h] = p.Lh[wrow * (p.H + 1) + min(h, p.H)];
+  }
+  in.lost = 0, in.dL = 0;
+  if constexpr (STEPS) {
+    if (p.adv_t > 0) in.lost = p.mh[wrow * (p.H + 1)], in.dL = p.mh[wrow * (p.H + 1) + 1];
   }
   in.q0 = br_uniform(min(max(q0, 0), p.Q));
   in.cnt = br_uniform(min(max(cnt, 0), a.arr_cap));
