@@ -27,7 +27,7 @@ template <int E, int ADV>
 __global__ __launch_bounds__(256, ADV == 4 ? (E == 4 ? 6 : 5) : 1) void br_k_route(BrParams p, BrArr a, BrOut o) {
   extern __shared__ int lds_all[];
   constexpr bool MIX = ADV > 0 && E <= 8;
-  constexpr int ROUND = ADV ? BR_ROUND_ADV_WORDS(E) : BR_ROUND_WORDS(E, false), WORDS = ROUND + (MIX ? BR_SPLIT_WORDS : 0);
+  constexpr int ROUND = ADV ? BR_ROUND_ADV_WORDS(E) : BR_ROUND_WORDS(E, 0, false), WORDS = ROUND + (MIX ? BR_SPLIT_WORDS : 0);
   const int w = threadIdx.x >> 6, b = (int)blockIdx.x, inst = b * (int)(blockDim.x >> 6) + w;
   int *lds = lds_all + w * WORDS, *split = nullptr;
   if constexpr (MIX) {
@@ -44,7 +44,7 @@ template <int E>
 static void launch_route(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
   const int wpb = br_clusters_per_block(p.N, E);
   const bool adv = p.adv_t > 0;
-  const size_t lds = (size_t)wpb * (adv ? BR_ROUND_ADV_WORDS(E) + (E <= 8 ? BR_SPLIT_WORDS : 0) : BR_ROUND_WORDS(E, false)) * sizeof(int);
+  const size_t lds = (size_t)wpb * (adv ? BR_ROUND_ADV_WORDS(E) + (E <= 8 ? BR_SPLIT_WORDS : 0) : BR_ROUND_WORDS(E, 0, false)) * sizeof(int);
   const dim3 grid((unsigned)((p.N + wpb - 1) / wpb)), block(BR_WAVE * wpb);
   if (adv && E <= 8 && p.N > 4 * 1024 && p.N <= (E == 4 ? 6 : 5) * 1024)
     hipLaunchKernelGGL((br_k_route<E, E <= 8 ? 4 : 8>), grid, block, lds, st, p, a, o);

@@ -54,10 +54,10 @@
 // LDS of a cluster whose queue holds up to EM * 64 entries: bound [EM * 64], list copy, slots [64], what BR-H lists lost ahead of the round, Stage-2 window and
 // table (BIGR), then the mailbox of shared subset searches and the bit rows of br_subset_dp.h where they are used
 #define BR_SEARCH_WORDS 1344
-#define BR_ROUND_WORDS(EM, BIGR) ((EM) * BR_WAVE + BR_LIST_WORDS(EM) + BR_WAVE + ((EM) <= 8 && !(BIGR) ? BR_AHEAD_WORDS : 0) + ((BIGR) ? 32 + BR_SEARCH_WORDS : 0))
-// the same where the wave goes on to apply decode steps to its cluster's lists
-#define BR_ROUND_ADV_WORDS(EM) (BR_ROUND_WORDS(EM, false) > BR_PLAIN_WORDS ? BR_ROUND_WORDS(EM, false) : BR_PLAIN_WORDS)
-static_assert(BR_ROUND_WORDS(32, false) + BR_LIST_WORDS(32) >= 4 * BR_PLAIN_WORDS, "four waves share the lists' LDS");
+#define BR_ROUND_WORDS(EM, HB, BIGR) ((EM) * BR_WAVE + BR_LIST_WORDS(EM) + BR_WAVE + ((EM) <= 8 && (HB) > 0 && !(BIGR) ? BR_AHEAD_WORDS : 0) + ((BIGR) ? 32 + BR_SEARCH_WORDS : 0))
+// the same where the wave goes on to apply decode steps to its cluster's lists (BR-0)
+#define BR_ROUND_ADV_WORDS(EM) (BR_ROUND_WORDS(EM, 0, false) > BR_PLAIN_WORDS ? BR_ROUND_WORDS(EM, 0, false) : BR_PLAIN_WORDS)
+static_assert(BR_ROUND_WORDS(32, 0, false) + BR_LIST_WORDS(32) >= 4 * BR_PLAIN_WORDS, "four waves share the lists' LDS");
 static_assert(BR_SEARCH_WORDS >= BR_HALVES_WORDS && BR_SEARCH_WORDS >= BR_FEW_WORDS && BR_SEARCH_WORDS >= 1024, "LDS of a subset search");
 
 // Trips of 256 masks from which a block's four waves share a search: fewer are not worth two barriers.
@@ -893,17 +893,18 @@ __device__ __forceinline__ void br_assign_body(const BrParams &p, const BrArr &a
   constexpr bool BRH = HB > 0;
   constexpr int NH = HB + 1;
   constexpr bool STEPS = BRH && EM <= 8 && !BIGR && !ADV;  // decode steps may have been applied ahead of the round
+  static_assert(!STEPS || BR_DEAD_WORDS(EM) <= BR_LIST_WORDS(EM), "the epilogue's bit masks take the list's place");
   if (inst >= p.N) return;
   int *bound = lds;                              // [EM * 64] by arrival position: worker << 16 | slot, or -1
   int *lst = bound + EM * BR_WAVE;               // copy of the list
   int *slots = lst + BR_LIST_WORDS(EM);          // [64] requests of a bulk step in order of admission
-  int *ahead = slots + BR_WAVE;                  // EM <= 8, not BIGR: [BR_AHEAD_WORDS] (br_ahead_store)
+  int *ahead = slots + BR_WAVE;                  // STEPS: [BR_AHEAD_WORDS] (br_ahead_store)
   int *win = ahead;                              // BIGR: [32] Stage-2 candidate window
   int *hitab = win + 32;                         // BIGR: [BR_SEARCH_WORDS] subset-sum tables
   int *svc = hitab + BR_SEARCH_WORDS;            // BIGR, shared: [32] mailbox
   int *dprows = svc + (shared ? 32 : 0);         // BIGR, R_max > 16: bit rows of the subset search
   // COOP: [BR_LIST_WORDS(32)] the sorted list as it was at the start
-  int *lst2 = lds + BR_ROUND_WORDS(EM, BIGR) + (BIGR && p.R_max > 16 ? BR_DP_LDS_WORDS : 0);
+  int *lst2 = lds + BR_ROUND_WORDS(EM, HB, BIGR) + (BIGR && p.R_max > 16 ? BR_DP_LDS_WORDS : 0);
 
   const int lane = br_lane();
   if constexpr (BIGR && !COOP) {
@@ -1066,7 +1067,7 @@ template <int E, int HB, int ADV, bool BIGR = false, bool DP = false>
 // `share` (BIGR, queues of up to 1024; BR-0: reachable sums only): one cluster per block, its four waves share the searches
 __global__ __launch_bounds__(256, (HB > 0 && E == 8 && !BIGR) ? 4 : (HB > 0 && E == 4 && !BIGR) ? (HB == 4 ? 5 : 4) : ADV == 4 ? 6 : 1) void br_k_assign(BrParams p, BrArr a, BrOut o, int share) {
   extern __shared__ int lds_all[];
-  constexpr int WORDS = ADV ? BR_ROUND_ADV_WORDS(E) : BR_ROUND_WORDS(E, BIGR);
+  constexpr int WORDS = ADV ? BR_ROUND_ADV_WORDS(E) : BR_ROUND_WORDS(E, HB, BIGR);
   const int w = threadIdx.x >> 6;
   if constexpr (E == 32) {  // one cluster per block, four waves for the sort
     br_assign_body<E, HB, ADV, true, BIGR, false, false, false, DP>(p, a, o, lds_all, (int)blockIdx.x, w);
@@ -1097,7 +1098,7 @@ __global__ __launch_bounds__((1 + BR_HELPERS) * BR_WAVE) void br_k_route_helped(
     br_assign_body<E, HB, 0, false, false, false, true>(p, a, o, lds_all, inst);
   } else {
     br_snapshot_helper<E, HB>(p, a, o, inst, br_lane(), w - 1, BR_HELPERS, recip_g,
-                              lds_all + BR_ROUND_WORDS(E, false) + (w - 1) * (BR_LIST_WORDS(E) + 2 * BR_WAVE));
+                              lds_all + BR_ROUND_WORDS(E, HB, false) + (w - 1) * (BR_LIST_WORDS(E) + 2 * BR_WAVE));
     __builtin_amdgcn_s_waitcnt(0);  // every read has returned
     __syncthreads();
   }
@@ -1107,7 +1108,7 @@ static inline unsigned br_recip(int G) { return (unsigned)((0x100000000ull + (un
 
 template <int E, int HB>
 static void br_launch_helped_one(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
-  const size_t lds = (BR_ROUND_WORDS(E, false) + (size_t)BR_HELPERS * (BR_LIST_WORDS(E) + 2 * BR_WAVE)) * sizeof(int);
+  const size_t lds = (BR_ROUND_WORDS(E, HB, false) + (size_t)BR_HELPERS * (BR_LIST_WORDS(E) + 2 * BR_WAVE)) * sizeof(int);
   hipLaunchKernelGGL((br_k_route_helped<E, HB>), dim3((unsigned)p.N), dim3(BR_WAVE * (1 + BR_HELPERS)), lds, st, p, a, o,
                      br_recip(p.G));
 }
@@ -1120,7 +1121,7 @@ static void br_launch_assign_one(const BrParams &p, const BrArr &a, const BrOut 
   const bool dp = BIGR && p.R_max > 16;   // windows beyond 16 requests: one cluster per block, with LDS for the bit rows
   const int wpb = dp ? 1 : br_clusters_per_block(p.N, E);
   const bool adv = HB == 0 && !BIGR && p.adv_t > 0;
-  const size_t lds = ((size_t)wpb * (adv ? BR_ROUND_ADV_WORDS(E) : BR_ROUND_WORDS(E, BIGR)) + (dp ? BR_DP_LDS_WORDS : 0) +
+  const size_t lds = ((size_t)wpb * (adv ? BR_ROUND_ADV_WORDS(E) : BR_ROUND_WORDS(E, HB, BIGR)) + (dp ? BR_DP_LDS_WORDS : 0) +
                       (E == 32 ? BR_LIST_WORDS(32) : 0)) * sizeof(int);
   const dim3 grid((unsigned)((p.N + wpb - 1) / wpb)), block(E == 32 ? 4 * BR_WAVE : BR_WAVE * wpb);
   // (decode steps ride along for BR-0 with windows of up to 8 requests only; elsewhere the caller launches the decode kernel)
@@ -1135,7 +1136,7 @@ static void br_launch_assign_one(const BrParams &p, const BrArr &a, const BrOut 
     // The lines: 768 / 512 / 256 clusters for BR-H with queues of up to 256 / 512 / 1024, 1024 / 768 / 512 for reachable sums.
     const long long room = 1024ll * max(1, (E == 4 ? 4 : E == 8 ? 3 : 2) - (HB > 0 ? 1 : 0));
     if ((HB > 0 || dp) && E <= 16 && (long long)p.N * 4 <= room) {
-      const size_t lds1 = ((size_t)BR_ROUND_WORDS(E, true) + 32 + (dp ? BR_DP_LDS_WORDS : 0)) * sizeof(int);
+      const size_t lds1 = ((size_t)BR_ROUND_WORDS(E, HB, true) + 32 + (dp ? BR_DP_LDS_WORDS : 0)) * sizeof(int);
       if (HB == 0)  // (reachable sums)
         hipLaunchKernelGGL((br_k_assign<E, HB, 0, true, HB == 0>), dim3((unsigned)p.N), dim3(4 * BR_WAVE), lds1, st, p, a, o, 1);
       else

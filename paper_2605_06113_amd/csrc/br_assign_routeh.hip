@@ -6,7 +6,7 @@
 
 // LDS words of a cluster
 static constexpr int br_route_h_words(int E, bool adv) {
-  return adv && BR_TAIL_WORDS > BR_ROUND_WORDS(E, false) ? BR_TAIL_WORDS : BR_ROUND_WORDS(E, false);
+  return adv && BR_TAIL_WORDS > BR_ROUND_WORDS(E, BR_HP, false) ? BR_TAIL_WORDS : BR_ROUND_WORDS(E, BR_HP, false);
 }
 
 template <int E, int HB, bool ADV>

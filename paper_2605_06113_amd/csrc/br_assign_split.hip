@@ -18,7 +18,7 @@ template <int E, bool THIRD>
 __global__ __launch_bounds__(256, E == 4 ? 6 : 5) void br_k_route_split(BrParams p, BrArr a, BrOut o, unsigned recip_g) {
   extern __shared__ int lds_all[];
   const int w = threadIdx.x >> 6, lane = br_lane(), inst = (int)blockIdx.x;
-  int *split = lds_all + BR_ROUND_WORDS(E, false);
+  int *split = lds_all + BR_ROUND_WORDS(E, 0, false);
   // flags down before any wave looks: the lists, and what a third wave reads of the step-start state
   if (threadIdx.x == 0) split[0] = 0, split[1] = THIRD ? 0 : 1;
   __syncthreads();
@@ -37,7 +37,7 @@ __global__ __launch_bounds__(256, E == 4 ? 6 : 5) void br_k_route_split(BrParams
 
 template <int E, bool THIRD>
 static void launch_split_waves(const BrParams &p, const BrArr &a, const BrOut &o, hipStream_t st) {
-  const size_t lds = (BR_ROUND_WORDS(E, false) + BR_SPLIT_WORDS + BR_PLAIN_WORDS + (THIRD ? BR_LIST_WORDS(E) + 2 * BR_WAVE : 0)) * sizeof(int);
+  const size_t lds = (BR_ROUND_WORDS(E, 0, false) + BR_SPLIT_WORDS + BR_PLAIN_WORDS + (THIRD ? BR_LIST_WORDS(E) + 2 * BR_WAVE : 0)) * sizeof(int);
   hipLaunchKernelGGL((br_k_route_split<E, THIRD>), dim3((unsigned)p.N), dim3(BR_WAVE * (THIRD ? 3 : 2)), lds, st, p, a, o, br_recip(p.G));
 }
 

@@ -25,7 +25,6 @@ BY_THE_PROJECTION = [
     (4096, 4, 256, 40, 8, 0.3, 15), (3073, 3, 256, 40, 8, 0.3, 16), (4096, 7, 256, 40, 8, 0.3, 16), (3100, 17, 80, 128, 6, 0.3, 25),
 ]
 
-
 def places(lib):
     from paper_2605_06113_amd import workloads as wl
     for where, cases in (("round", BY_THE_ROUND), ("projection", BY_THE_PROJECTION)):
@@ -43,8 +42,19 @@ def places(lib):
             lib.free()
 
 
-def test_where_decode_steps_run(tmp_path):
-    run = subprocess.run([sys.executable, os.path.abspath(__file__), build(tmp_path, STAND_IN), "places"], cwd=ROOT, capture_output=True, text=True, timeout=300)
+def lds(lib):
+    """A BR-0 round has no room for what the projection of a BR-H call leaves to it."""
+    from paper_2605_06113_amd import workloads as wl
+    for H, more in ((0, 0), (4, 192)):
+        lib.context(wl.RouteConfig(name="lds", n_inst=4, G=8, B=20, max_wait=200, H=H))
+        assert lib.call("br_route_step", None, None)[0] == 0
+        assert int(re.search(r"br_k_assign\S* lds=(\d+)", lib.log).group(1)) == (4 * 64 + 4 * 64 + 64 + more) * 4
+        lib.free()
+
+
+@pytest.mark.parametrize("scenario", ["places", "lds"])
+def test_launches(tmp_path, scenario):
+    run = subprocess.run([sys.executable, os.path.abspath(__file__), build(tmp_path, STAND_IN), scenario], cwd=ROOT, capture_output=True, text=True, timeout=300)
     assert run.returncode == 0, run.stderr[-2000:]
 
 
@@ -76,4 +86,4 @@ def test_decode_steps_by_the_waves_of_the_round(N, G, B, Q, H, gate, steps):
 
 
 if __name__ == "__main__":
-    {"places": places}[sys.argv[2]](Library(sys.argv[1]))
+    {"places": places, "lds": lds}[sys.argv[2]](Library(sys.argv[1]))

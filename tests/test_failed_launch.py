@@ -28,9 +28,9 @@ void __hipRegisterFunction(void **, const void *f, char *, const char *n, unsign
 void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
 int __hipPushCallConfiguration(D3 gg, D3 bb, size_t s, void *st) { g = gg, b = bb, shm = s, str = st; return 0; }
 int __hipPopCallConfiguration(D3 *gg, D3 *bb, size_t *s, void **st) { *gg = g, *bb = b, *s = shm, *st = str; return 0; }
-int hipLaunchKernel(const void *f, D3, D3, void **, size_t, void *) {
+int hipLaunchKernel(const void *f, D3, D3, void **, size_t lds, void *) {
   if (hit(fail_launch)) return last = 2;
-  log_ += names[f] + "\n";
+  log_ += names[f] + " lds=" + std::to_string(lds) + "\n";
   return 0;
 }
 int hipGetLastError() { int e = last; last = 0; return e; }
@@ -79,7 +79,8 @@ class Library:
         self.binding, self.lib = binding, binding.load()
 
     def context(self, cfg):
-        c = self.binding.make_config(cfg, workspace=1 << 20, workspace_bytes=self.binding.workspace_bytes(cfg))
+        hist = dict(hist=1 << 30, hist_sum=1 << 30, hist_n=100) if cfg.H > 0 and cfg.pred_mode == 2 else {}
+        c = self.binding.make_config(cfg, workspace=1 << 20, workspace_bytes=1 << 40, **hist)
         self.ctx = C.c_void_p()
         assert self.lib.br_init(C.byref(c), None, C.byref(self.ctx)) == 0
         self.fake.stand_in_log()
