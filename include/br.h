@@ -76,7 +76,8 @@ enum {
 
 /* Kernel ids for br_profile_read(). */
 enum {
-  BR_K_PROJECT = 0, /* projected loads over the horizon (BR-H preparation; long horizons with short queues: in the assignment's launch) */
+  BR_K_PROJECT = 0, /* projected loads over the horizon (BR-H preparation), with the decode steps of br_route_advance where they ride in
+                       its pass over the lists (BR_K_ADVANCE counts no launch then); long horizons with short queues: in the assignment's launch */
   BR_K_SCORE = 1,   /* F-score matrix + stage-one reductions */
   BR_K_ASSIGN = 2,  /* sequential two-stage assignment */
   BR_K_ADVANCE = 3, /* decode step */

@@ -1,6 +1,6 @@
 // BR-H counterpart of br_k_route: for clusters with queues of up to 512 entries the wave that
 // owns a cluster first computes the snapshot reductions (K2 + K3, on the step-start margins of the projection
-// kernels), then runs the two-stage assignment (K4) and, ADV, applies the decode steps, in one launch.
+// kernels), then runs the two-stage assignment (K4) and, ADV, applies the decode steps (br_route_h_advances), in one launch.
 #include "br_assign_kernel.h"
 #include "br_score_wave.h"
 
@@ -34,6 +34,7 @@ static void launch_route_h(const BrParams &p, const BrArr &a, const BrOut &o, bo
 // keeps c_hat at H for most requests, makes rounds short: there only while lists and rows come from the last-level cache, and up to 16 lists a wave.
 // Whole pass, us, the same round, in the projection's pass / in the round's launch, B = 96 and 4096 clusters unless given, offered load 0.7 and 1.3 times what the workers serve:
 //   no gate    G = 16, H = 4 (144 MiB)           1 step 62.0 / 61.4, 84.7 / 83.6    8: 94.1 / 90.1, 154 / 144    40: 164 / 153, 273 / 256
+//                (0.4 times: 8 steps 63.6 / 66.9; the load is not known here)
 //              G = 32, queues of 512             1 step 112 / 116, 160 / 159        8: 174 / 171, 314 / 299      40: 309 / 290, 570 / 543
 //              G = 64, B = 64                    8: 236 / 227, 353 / 329            32: 422 / 392, 443 / 414
 //              G = 16, B = 200, queues of 512    8: 172 / 170, 306 / 298            32: 244 / 228, 405 / 378

@@ -43,14 +43,14 @@ __device__ __forceinline__ int br_last_offset(const BrParams &p, const float (&r
   return ch >= 1.0f ? (int)ch : -1;
 }
 
-// The projection and, in the same pass over the lists, the decode steps of their old entries (br_route_advance): neither
+// The projection and, in the same pass over the lists, the decode steps of their old entries (br_route_advance; br_project_advances): neither
 // needs the round, which reads the projections and appends its admissions to the lists as they are left here
 // (br_assign_epilogue_ahead).  LPL lanes hold a list as in br_k_advance_seg, four consecutive slots each; a request's row
 // is read, and stored again where it moves, by the lane whose number follows that of the slot (contiguous memory).
 // What a list lost and its load change go to the words of its margins (br_ahead_store); length and load stay until the
 // round has read them.
-// Bound by memory traffic (4096 clusters, G = 32, H = 4, lists of 96 slots, 40 steps: 432 MB in 106 us, 4.1 TB/s; the projection by itself 73 us
-// from cold memory).  Non-temporal stores, or two lists a lane group at a time, make no difference; non-temporal loads cost 7 us.
+// Bound by memory traffic (4096 clusters, G = 32, H = 4, lists of 96 slots, 40 steps: 448 MB in 107 us, 4.2 TB/s, both
+// over passes on three states in turn; the projection by itself 73 us from cold memory).  Non-temporal stores, or two lists a lane group at a time, make no difference; non-temporal loads cost 7 us.
 // row0: the first of `lists` lists (at most 64 / LPL); lds: BR_SEG_WORDS(1) of the wave's.
 template <int LPL, int HB, bool EXACT, int PK>
 __device__ __forceinline__ void br_project_lists(const BrParams &p, int64_t row0, int lists, int lane, int *lds) {
