@@ -97,9 +97,9 @@ def test_decode_steps_by_the_waves_of_the_round(N, G, B, Q, H, gate, steps):
         init.rem[i, g, :n], init.kv[i, g, :n] = rem, np.maximum(init.kv[i, g, :n], 1)
     print(f"[case] decode by the round N={N} G={G} B={B} Q={Q} H={H} gate={gate} steps={steps}", flush=True)
     oc, r = br_oracle.OracleCluster(cfg, init), binding.Router(cfg, init)
-    for rnd in range(2):
+    for rnd in range(3):
         ref = oc.route_step(arr)
-        out = r.route_step(arr, matrix=False, scores=rnd == 0, advance=steps)
+        out = r.route_step(arr, matrix=rnd == 1, scores=rnd < 2, advance=steps)
         compare_outputs({k: v for k, v in ref.items() if k in out}, out, cfg, f"decode by the round r{rnd}")
         oc.advance(steps)
         compare_state(oc, r.state(), cfg, f"decode by the round r{rnd}")
